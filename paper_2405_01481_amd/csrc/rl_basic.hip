@@ -52,30 +52,43 @@ void k_set_pages(int* block_table, int mpps, const int* triples_host, int n_trip
 }
 
 // ---------------------------------------------------------------- token bookkeeping
-// A finished sequence is parked: position -1, which every consumer reads as "no cache slot, no
-// attention, zeros" (the padding-row rule of the packed token lists), so it stops growing its cache.
-__global__ void step_begin_kernel(const int* tok_in, const int* last_tok, const int* seq_len, const int* finished,
-                                  int* cur_tok, int* tok_pos, int* tok_slot, int B) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    cur_tok[b] = tok_in ? tok_in[b] : last_tok[b];
-    tok_pos[b] = finished[b] ? -1 : seq_len[b];
-    tok_slot[b] = b;
+// Row descriptors of a chunk -- batch row, cache slot, first packed row, length of up to 240 rows -- reach the device as
+// kernel arguments: nothing is copied from host memory that would have to outlive the call, so the call need not wait.
+struct RowDescs { int v[4 * 240]; };
+__global__ void put_rows_kernel(RowDescs r, int n, int first, int* seq_first, int* row_slot, int* row_start, int* row_len) {
+    const int i = threadIdx.x;
+    if (i >= n) return;
+    seq_first[first + i] = r.v[4 * i];
+    row_slot[first + i] = r.v[4 * i + 1];
+    row_start[first + i] = r.v[4 * i + 2];
+    row_len[first + i] = r.v[4 * i + 3];
 }
-void k_step_begin(const int* tok_in, const int* last_tok, const int* seq_len, const int* finished, int* cur_tok,
-                  int* tok_pos, int* tok_slot, int B, hipStream_t s) {
-    step_begin_kernel<<<(B + 255) / 256, 256, 0, s>>>(tok_in, last_tok, seq_len, finished, cur_tok, tok_pos, tok_slot, B);
+void k_put_rows(const int* seq_first_h, const int* row_slot_h, const int* row_start_h, const int* row_len_h, int n,
+                int* seq_first, int* row_slot, int* row_start, int* row_len, hipStream_t s) {
+    for (int o = 0; o < n; o += 240) {
+        RowDescs r;
+        const int m = n - o < 240 ? n - o : 240;
+        for (int i = 0; i < m; ++i) {
+            r.v[4 * i] = seq_first_h[o + i];
+            r.v[4 * i + 1] = row_slot_h[o + i];
+            r.v[4 * i + 2] = row_start_h[o + i];
+            r.v[4 * i + 3] = row_len_h[o + i];
+        }
+        put_rows_kernel<<<1, 256, 0, s>>>(r, m, o, seq_first, row_slot, row_start, row_len);
+    }
 }
-
 // Pack rows of a padded [*, ld_ids] id matrix into a flat token list.
 // Row r of the chunk is batch row seq_first[r]; its row_len[r] tokens go to
 // [row_start[r], row_start[r] + row_len[r]).  tok_tgt (optional) = next token id of the
 // same row, or -1 when there is none inside full_len[r].
 // With align > 1 every row is padded to a multiple of align tokens; padding entries carry
 // token id 0, position -1 and no target.
+// blocks (optional): the prefill attention's work list, one entry (first row, length, query block) per 32-query block,
+// late (long) blocks first so that the tail of the grid is short work, rows in order within a block index: an entry's
+// place is the number of entries with a later block, plus the earlier rows that have this one.
 __global__ void pack_tokens_kernel(const int* ids, int ld_ids, const int* seq_first, const int* row_slot,
-                                   const int* row_start, const int* row_len, const int* full_len, int align,
-                                   int* tok_ids, int* tok_pos, int* tok_slot, int* tok_tgt) {
+                                   const int* row_start, const int* row_len, int align, int* tok_ids, int* tok_pos,
+                                   int* tok_slot, int* tok_tgt, int4* blocks) {
     int r = blockIdx.x;
     int b = seq_first[r], st = row_start[r], len = row_len[r];
     const int slot = row_slot[r];
@@ -86,15 +99,24 @@ __global__ void pack_tokens_kernel(const int* ids, int ld_ids, const int* seq_fi
         tok_ids[st + t] = real ? src[t] : 0;
         tok_pos[st + t] = real ? t : -1;
         tok_slot[st + t] = slot;
-        if (tok_tgt) tok_tgt[st + t] = (real && t + 1 < full_len[r]) ? src[t + 1] : -1;
+        if (tok_tgt) tok_tgt[st + t] = (real && t + 1 < len) ? src[t + 1] : -1;
+    }
+    if (!blocks) return;
+    for (int qb = threadIdx.x; qb < (len + 31) / 32; qb += blockDim.x) {
+        int at = 0;
+        for (int i = 0; i < (int)gridDim.x; ++i) {
+            const int nbi = (row_len[i] + 31) / 32;
+            at += max(0, nbi - (qb + 1)) + (i < r && nbi > qb ? 1 : 0);
+        }
+        blocks[at] = make_int4(st, len, qb, 0);
     }
 }
 void k_pack_tokens(const int* ids, int ld_ids, const int* seq_first, const int* row_slot, const int* row_start,
-                   const int* row_len, const int* full_len, int align, int* tok_ids, int* tok_pos, int* tok_slot,
-                   int* tok_tgt, int nrows, hipStream_t s) {
+                   const int* row_len, int align, int* tok_ids, int* tok_pos, int* tok_slot, int* tok_tgt, int4* blocks,
+                   int nrows, hipStream_t s) {
     if (nrows <= 0) return;
-    pack_tokens_kernel<<<nrows, 256, 0, s>>>(ids, ld_ids, seq_first, row_slot, row_start, row_len, full_len, align,
-                                             tok_ids, tok_pos, tok_slot, tok_tgt);
+    pack_tokens_kernel<<<nrows, 256, 0, s>>>(ids, ld_ids, seq_first, row_slot, row_start, row_len, align, tok_ids, tok_pos,
+                                             tok_slot, tok_tgt, blocks);
 }
 
 // After prefill of the first P-1 prompt tokens: remember the last prompt token, lengths, counters.
@@ -146,6 +168,15 @@ __global__ void out_len_kernel(const int* gen_count, int* out_len, int B) {
 }
 void k_out_len(const int* gen_count, int* out_len, int B, hipStream_t s) {
     out_len_kernel<<<(B + 255) / 256, 256, 0, s>>>(gen_count, out_len, B);
+}
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+// four consecutive values (4-element aligned) as floats
+template <typename T>
+__device__ __forceinline__ floatx4 load4(const T* p) {
+    typedef T T4 __attribute__((ext_vector_type(4)));
+    const T4 v = *reinterpret_cast<const T4*>(p);
+    return floatx4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
 }
 
 // ---------------------------------------------------------------- embedding gather
@@ -245,109 +276,228 @@ void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d
     else rmsnorm_kernel<f16_t, bf16_t><<<n, 256, 0, s>>>(x, (const bf16_t*)g, (f16_t*)out, d, eps, split);
 }
 
-// ---------------------------------------------------------------- plain tiled GEMM  C = A[M,K] * W[N,K]^T
-// 64x64 output tile, 16-wide k slab, 256 threads each 4x4, fp32 FMA accumulation.
-template <typename T, typename TW, int EPI>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(const T* __restrict__ A, int lda, const TW* __restrict__ W,
-                                                          const TW* __restrict__ W2, int M, int N, int K,
-                                                          float* outF, T* outT, int ldc) {
-    __shared__ float As[16][65];
-    __shared__ float Ws[16][65];
-    __shared__ float W2s[EPI == EPI_SWIGLU ? 16 : 1][65];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    float acc[4][4] = {}, acc2[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
+// ---------------------------------------------------------------- start of a decode step
+// One block per row: the row's position and cache slot, its embedding into the residual stream, and -- norm_gain given
+// -- the first layer's RMSNorm of it (split: as fp16 pairs).  One launch of about 5 us where there were three.
+// A finished sequence is parked: position -1, which every consumer reads as "no cache slot, no
+// attention, zeros" (the padding-row rule of the packed token lists), so it stops growing its cache.
+template <typename T, typename TW>
+__global__ __launch_bounds__(256) void step_start_kernel(const int* tok_in, const int* last_tok, const int* seq_len,
+                                                         const int* finished, int* tok_pos, int* tok_slot, const TW* E, int d,
+                                                         int V, float* x, int* errflag, const TW* norm_gain, T* h, float eps,
+                                                         int split) {
+    __shared__ float red[16];
+    const int b = blockIdx.x;
+    int id = tok_in ? tok_in[b] : last_tok[b];
+    if (threadIdx.x == 0) {
+        tok_pos[b] = finished[b] ? -1 : seq_len[b];
+        tok_slot[b] = b;
+        if (id < 0 || id >= V) atomicOr(errflag, 1);
+    }
+    id = min(max(id, 0), V - 1);
+    const TW* row = E + (int64_t)id * d;
+    float* xo = x + (int64_t)b * d;
+    // d is a multiple of 64
+    float ss = 0.f;
+    for (int j = threadIdx.x * 4; j < d; j += 1024) {
+        const floatx4 v = load4(row + j);
+        *reinterpret_cast<floatx4*>(xo + j) = v;
+        ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    }
+    if (!norm_gain) return;
+    ss = block_sum(ss, red);
+    const float rs = 1.0f / sqrtf(ss / (float)d + eps);
+    T* o = h + (int64_t)b * d * (split ? 2 : 1);
+    for (int j = threadIdx.x * 4; j < d; j += 1024) {
+        const floatx4 v = load4(row + j);
+        put_pair4(o + j, d, make_float4(v[0], v[1], v[2], v[3]), rs, norm_gain + j, split);
+    }
+}
+void k_step_start(int dtype, const int* tok_in, const int* last_tok, const int* seq_len, const int* finished, int* tok_pos,
+                  int* tok_slot, const void* E, int d, int V, float* x, int* errflag, const void* norm_gain, void* h,
+                  float eps, int split, int B, hipStream_t s) {
+    if (B <= 0) return;
+    if (dtype == 0)
+        step_start_kernel<float, float><<<B, 256, 0, s>>>(tok_in, last_tok, seq_len, finished, tok_pos, tok_slot, (const float*)E,
+                                                          d, V, x, errflag, (const float*)norm_gain, (float*)h, eps, split);
+    else
+        step_start_kernel<f16_t, bf16_t><<<B, 256, 0, s>>>(tok_in, last_tok, seq_len, finished, tok_pos, tok_slot,
+                                                           (const bf16_t*)E, d, V, x, errflag, (const bf16_t*)norm_gain,
+                                                           (f16_t*)h, eps, split);
+}
+
+// ---------------------------------------------------------------- plain GEMM  C = A[M,K] * W[N,K]^T
+// fp32 multiply-adds on the matrix cores (v_mfma_f32_16x16x4_f32), whatever the operand types.  A workgroup owns
+// MT x NT tiles of 16 x 16 outputs; its eight waves split K between them -- wave w takes the 16-wide k chunks
+// w, w + 8, ... -- and their sums are added in wave order through LDS.  The shapes this path serves are small (the fp32
+// configuration's matrices are 0.25 - 4 MB, decode has a handful of rows): what bounds them is the latency of the
+// loads and the number of waves in flight, not arithmetic, hence the K split inside the workgroup and tiles that
+// shrink with the grid (k_gemm_simple).  A lane fetches four consecutive k of its row at once: as A and W use the
+// same assignment of k to MFMA steps, any assignment gives the same contraction.  The order of the sums depends on K
+// alone, so a row's bits do not depend on how many rows run beside it.
+// Measured on the fp32 configuration (d 256, ffn 1024, vocab 4096; 4 rows, decode): 31 us (QKV, LM head), 39 us (gate /
+// up) and 75 us (O, down) per GEMM with 64 x 64 tiles on plain multiply-adds (4 - 64 workgroups of one k loop), 3.7, 4.5
+// and 4.8 us now, of which about 2 are the launch.
+// NORM: A is the fp32 residual stream and its RMSNorm is part of the GEMM: with r = 1 / rms of the row,
+// sum_k (x r g) W = r sum_k (x g) W, and the sum of squares comes from the values the lanes hold anyway.
+struct PlainGemmArgs {
+    const void *A, *W, *W2;
+    int lda, M, N, K;
+    float* outF;
+    void* outT;
+    int ldc;
+    const void* gain;   // NORM
+    float eps;
+};
+template <typename T, typename TW, int EPI, int MT, int NT, bool NORM>
+__global__ __launch_bounds__(512) void gemm_plain_kernel(PlainGemmArgs a) {
+    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;        // weight matrices
+    constexpr int U = MT * NT * NW <= 2 ? 4 : 1;         // chunks requested at a time
+    __shared__ float red[8][NW * NT * 256];
+    __shared__ float ssq[8][MT * 16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, q4 = lane >> 4;
+    const int m0 = blockIdx.y * (16 * MT), n0 = blockIdx.x * (16 * NT);
+    const T* Ap[MT];
+    const TW* Wp[NW][NT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int idx = tid + i * 256, r = idx >> 4, kk = idx & 15;
-            int k = k0 + kk;
-            As[kk][r] = (m0 + r < M && k < K) ? to_f(A[(int64_t)(m0 + r) * lda + k]) : 0.f;
-            Ws[kk][r] = (n0 + r < N && k < K) ? to_f(W[(int64_t)(n0 + r) * K + k]) : 0.f;
-            if (EPI == EPI_SWIGLU) W2s[kk][r] = (n0 + r < N && k < K) ? to_f(W2[(int64_t)(n0 + r) * K + k]) : 0.f;
+    for (int i = 0; i < MT; ++i) Ap[i] = (const T*)a.A + (int64_t)min(m0 + i * 16 + r16, a.M - 1) * a.lda + q4 * 4;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int64_t o = (int64_t)min(n0 + j * 16 + r16, a.N - 1) * a.K + q4 * 4;
+        Wp[0][j] = (const TW*)a.W + o;
+        if (NW == 2) Wp[NW - 1][j] = (const TW*)a.W2 + o;
+    }
+    floatx4 acc[NW][MT][NT];
+    float ss[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        ss[i] = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[w][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int nc = a.K / 16;                              // K is a multiple of 64
+    for (int c0 = wave; c0 < nc; c0 += 8 * U) {
+        floatx4 af[U][MT], wf[U][NW][NT], gf[NORM ? U : 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = min(c0 + 8 * u, nc - 1) * 16;   // past the end: the last chunk again, not used
+#pragma unroll
+            for (int i = 0; i < MT; ++i) af[u][i] = load4(Ap[i] + k);
+            if (NORM) gf[NORM ? u : 0] = load4((const TW*)a.gain + k + q4 * 4);
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) wf[u][w][j] = load4(Wp[w][j] + k);
         }
-        __syncthreads();
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4], b2[4];
+        for (int u = 0; u < U; ++u) {
+            if (c0 + 8 * u >= nc) break;                  // wave-uniform
+            if (NORM) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Ws[kk][tx * 4 + i]; }
-            if (EPI == EPI_SWIGLU) {
+                for (int i = 0; i < MT; ++i) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) b2[i] = W2s[kk][tx * 4 + i];
+                    for (int e = 0; e < 4; ++e) ss[i] += af[u][i][e] * af[u][i][e];
+                    af[u][i] *= gf[NORM ? u : 0];
+                }
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc[i][j] += a[i] * b[j];
-                    if (EPI == EPI_SWIGLU) acc2[i][j] += a[i] * b2[j];
-                }
+                for (int w = 0; w < NW; ++w)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+                            acc[w][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[u][i][e], wf[u][w][j][e], acc[w][i][j], 0, 0, 0);
         }
-        __syncthreads();
+    }
+    if (NORM) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            float s = ss[i];                              // this lane's share of row i * 16 + r16
+            s += __shfl_xor(s, 16, RL_WAVE);
+            s += __shfl_xor(s, 32, RL_WAVE);
+            if (q4 == 0) ssq[wave][i * 16 + r16] = s;
+        }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
+    for (int i = 0; i < MT; ++i) {
+        if (i > 0) __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            int64_t o = (int64_t)m * ldc + n;
-            float v = acc[i][j];
-            if (EPI == EPI_STORE_F32) outF[o] = v;
-            else if (EPI == EPI_STORE_T) outT[o] = from_f<T>(v);
-            else if (EPI == EPI_RESID) outF[o] += v;
-            else { float u = acc2[i][j]; outT[o] = from_f<T>(v / (1.0f + __expf(-v)) * u); }
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) *reinterpret_cast<floatx4*>(&red[wave][(w * NT + j) * 256 + lane * 4]) = acc[w][i][j];
+        __syncthreads();
+        for (int e = threadIdx.x; e < NT * 256; e += 512) {
+            const int l = (e & 255) >> 2, row = i * 16 + 4 * (l >> 4) + (e & 3), m = m0 + row, n = n0 + (e >> 8) * 16 + (l & 15);
+            if (m >= a.M || n >= a.N) continue;
+            float v = 0.f, u = 0.f, s = 0.f;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                v += red[w][e];
+                if (NW == 2) u += red[w][(NW - 1) * NT * 256 + e];
+                if (NORM) s += ssq[w][row];
+            }
+            if (NORM) {
+                const float rs = 1.0f / sqrtf(s / (float)a.K + a.eps);
+                v *= rs;
+                u *= rs;
+            }
+            const int64_t o = (int64_t)m * a.ldc + n;
+            if (EPI == EPI_STORE_F32) a.outF[o] = v;
+            else if (EPI == EPI_RESID) a.outF[o] += v;
+            else ((T*)a.outT)[o] = from_f<T>(v / (1.0f + __expf(-v)) * u);
         }
     }
 }
+template <typename T, typename TW, int EPI, bool NORM>
+static void gemm_plain_t(const PlainGemmArgs& a, hipStream_t s) {
+    // The largest tile that still gives the 256 compute units two workgroups each: a bigger tile reads its operands
+    // fewer times, but a grid that leaves units idle costs more than that.
+    auto wgs = [&](int mt, int nt) { return (int64_t)((a.M + 16 * mt - 1) / (16 * mt)) * ((a.N + 16 * nt - 1) / (16 * nt)); };
+    if (wgs(4, 4) >= 512) gemm_plain_kernel<T, TW, EPI, 4, 4, NORM><<<dim3((a.N + 63) / 64, (a.M + 63) / 64), 512, 0, s>>>(a);
+    else if (wgs(2, 2) >= 512) gemm_plain_kernel<T, TW, EPI, 2, 2, NORM><<<dim3((a.N + 31) / 32, (a.M + 31) / 32), 512, 0, s>>>(a);
+    else gemm_plain_kernel<T, TW, EPI, 1, 1, NORM><<<dim3((a.N + 15) / 16, (a.M + 15) / 16), 512, 0, s>>>(a);
+}
 template <typename T, typename TW>
-static void gemm_simple_t(int epi, const T* A, int lda, const TW* W, const TW* W2, int M, int N, int K, float* outF,
-                          T* outT, int ldc, hipStream_t s) {
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
+static void gemm_simple_t(int epi, const PlainGemmArgs& a, hipStream_t s) {
     switch (epi) {
-        case EPI_STORE_F32: gemm_simple_kernel<T, TW, EPI_STORE_F32><<<grid, 256, 0, s>>>(A, lda, W, W2, M, N, K, outF, outT, ldc); break;
-        case EPI_STORE_T: gemm_simple_kernel<T, TW, EPI_STORE_T><<<grid, 256, 0, s>>>(A, lda, W, W2, M, N, K, outF, outT, ldc); break;
-        case EPI_RESID: gemm_simple_kernel<T, TW, EPI_RESID><<<grid, 256, 0, s>>>(A, lda, W, W2, M, N, K, outF, outT, ldc); break;
-        default: gemm_simple_kernel<T, TW, EPI_SWIGLU><<<grid, 256, 0, s>>>(A, lda, W, W2, M, N, K, outF, outT, ldc); break;
+        case EPI_STORE_F32: gemm_plain_t<T, TW, EPI_STORE_F32, false>(a, s); break;
+        case EPI_RESID: gemm_plain_t<T, TW, EPI_RESID, false>(a, s); break;
+        default: gemm_plain_t<T, TW, EPI_SWIGLU, false>(a, s); break;
     }
 }
 void k_gemm_simple(int dtype, int epi, const void* A, int lda, const void* W, const void* W2, int M, int N, int K,
                    float* outF, void* outT, int ldc, hipStream_t s) {
     if (M <= 0 || N <= 0) return;
-    if (dtype == 0) gemm_simple_t<float, float>(epi, (const float*)A, lda, (const float*)W, (const float*)W2, M, N, K, outF, (float*)outT, ldc, s);
-    else gemm_simple_t<f16_t, bf16_t>(epi, (const f16_t*)A, lda, (const bf16_t*)W, (const bf16_t*)W2, M, N, K, outF, (f16_t*)outT, ldc, s);
+    const PlainGemmArgs a{A, W, W2, lda, M, N, K, outF, outT, ldc, nullptr, 0.f};
+    if (dtype == 0) gemm_simple_t<float, float>(epi, a, s);
+    else gemm_simple_t<f16_t, bf16_t>(epi, a, s);
+}
+void k_gemm_norm_f32(int epi, const float* x, const float* gain, float eps, const float* W, const float* W2, int M, int N,
+                     int K, float* out, int ldc, hipStream_t s) {
+    if (M <= 0 || N <= 0) return;
+    const PlainGemmArgs a{x, W, W2, K, M, N, K, out, out, ldc, gain, eps};
+    if (epi == EPI_SWIGLU) gemm_plain_t<float, float, EPI_SWIGLU, true>(a, s);
+    else gemm_plain_t<float, float, EPI_STORE_F32, true>(a, s);
 }
 
 // ---------------------------------------------------------------- RoPE + split + KV append
-// qkv fp32 [n, (Hq+2Hkv) hd] -> rotated q (T) [n, Hq hd]; rotated k and plain v to the
-// contiguous buffers (optional) and to the page slot of (slot, pos) (optional).
-// With nsplit > 1 the row is the sum, in split order, of nsplit partial rows split_stride apart.
+// Plain path, whole sequences: qkv fp32 [n, (Hq+2Hkv) hd] -> rotated q (T) [n, Hq hd]; rotated k and plain v to the
+// contiguous buffers and to the page slot of (slot, pos) (optional).
 template <typename T>
-__global__ __launch_bounds__(256) void rope_append_kernel(const float* qkv, int nsplit, int64_t split_stride,
-                                                          const int* tok_pos, const int* tok_slot,
+__global__ __launch_bounds__(256) void rope_append_kernel(const float* qkv, const int* tok_pos, const int* tok_slot,
                                                           const float2* rope, T* q_out, T* k_out, T* v_out, T* pool,
                                                           int layer, KvGeom geo, const int* bt, int mpps, int Hq) {
-    extern __shared__ float rowbuf[];
     const int n = blockIdx.x, hd = geo.hd, half = hd / 2, Hkv = geo.Hkv;
     const int pos = tok_pos[n];
-    const int width = (Hq + 2 * Hkv) * hd;
-    const float* row = qkv + (int64_t)n * width;
-    if (nsplit > 1) {
-        for (int i = threadIdx.x; i < width; i += 256) {
-            float v = row[i];
-            for (int sp = 1; sp < nsplit; ++sp) v += row[sp * split_stride + i];
-            rowbuf[i] = v;
-        }
-        __syncthreads();
-        row = rowbuf;
-    }
-    if (pos < 0) {   // parked / padding row: zero query, no key or value
+    const float* row = qkv + (int64_t)n * (Hq + 2 * Hkv) * hd;
+    if (pos < 0) {   // padding row: zero query, no key or value
         for (int i = threadIdx.x; i < Hq * hd; i += 256) q_out[(int64_t)n * Hq * hd + i] = from_f<T>(0.f);
-        if (k_out) for (int i = threadIdx.x; i < Hkv * hd; i += 256) k_out[(int64_t)n * Hkv * hd + i] = from_f<T>(0.f);
-        if (v_out) for (int i = threadIdx.x; i < Hkv * hd; i += 256) v_out[(int64_t)n * Hkv * hd + i] = from_f<T>(0.f);
+        for (int i = threadIdx.x; i < Hkv * hd; i += 256) k_out[(int64_t)n * Hkv * hd + i] = from_f<T>(0.f);
+        for (int i = threadIdx.x; i < Hkv * hd; i += 256) v_out[(int64_t)n * Hkv * hd + i] = from_f<T>(0.f);
         return;
     }
     const float2* rt = rope + (int64_t)pos * half;
@@ -373,10 +523,8 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float* qkv, int 
         float a = krow[g * hd + j], b = krow[g * hd + j + half];
         float2 cs = rt[j];
         T r0 = from_f<T>(a * cs.x - b * cs.y), r1 = from_f<T>(b * cs.x + a * cs.y);
-        if (k_out) {
-            T* o = k_out + (int64_t)n * Hkv * hd + g * hd;
-            o[j] = r0; o[j + half] = r1;
-        }
+        T* o = k_out + (int64_t)n * Hkv * hd + g * hd;
+        o[j] = r0; o[j + half] = r1;
         if (pool) {
             pool[geo.k_off(layer, page, g, slot_tok, j)] = r0;
             pool[geo.k_off(layer, page, g, slot_tok, j + half)] = r1;
@@ -387,23 +535,20 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float* qkv, int 
     for (int i = threadIdx.x; i < Hkv * hd; i += 256) {
         int g = i / hd, dd = i % hd;
         T v = from_f<T>(vrow[i]);
-        if (v_out) v_out[(int64_t)n * Hkv * hd + i] = v;
+        v_out[(int64_t)n * Hkv * hd + i] = v;
         if (pool) pool[geo.v_off(layer, page, g, slot_tok, dd)] = v;
     }
 }
-void k_rope_append(int dtype, const float* qkv, int nsplit, int64_t split_stride, int n, const int* tok_pos,
-                   const int* tok_slot, const float2* rope, void* q_out, void* k_out, void* v_out, void* pool,
-                   int layer, KvGeom geo, const int* block_table, int mpps, int Hq, hipStream_t s) {
+void k_rope_append(int dtype, const float* qkv, int n, const int* tok_pos, const int* tok_slot, const float2* rope,
+                   void* q_out, void* k_out, void* v_out, void* pool, int layer, KvGeom geo, const int* block_table,
+                   int mpps, int Hq, hipStream_t s) {
     if (n <= 0) return;
-    size_t lds = nsplit > 1 ? (size_t)(Hq + 2 * geo.Hkv) * geo.hd * sizeof(float) : 0;
     if (dtype == 0)
-        rope_append_kernel<float><<<n, 256, lds, s>>>(qkv, nsplit, split_stride, tok_pos, tok_slot, rope,
-                                                      (float*)q_out, (float*)k_out, (float*)v_out, (float*)pool,
-                                                      layer, geo, block_table, mpps, Hq);
+        rope_append_kernel<float><<<n, 256, 0, s>>>(qkv, tok_pos, tok_slot, rope, (float*)q_out, (float*)k_out, (float*)v_out,
+                                                    (float*)pool, layer, geo, block_table, mpps, Hq);
     else
-        rope_append_kernel<f16_t><<<n, 256, lds, s>>>(qkv, nsplit, split_stride, tok_pos, tok_slot, rope,
-                                                      (f16_t*)q_out, (f16_t*)k_out, (f16_t*)v_out, (f16_t*)pool,
-                                                      layer, geo, block_table, mpps, Hq);
+        rope_append_kernel<f16_t><<<n, 256, 0, s>>>(qkv, tok_pos, tok_slot, rope, (f16_t*)q_out, (f16_t*)k_out, (f16_t*)v_out,
+                                                    (f16_t*)pool, layer, geo, block_table, mpps, Hq);
 }
 
 #define RL_MAX_SPLITS 16
@@ -548,13 +693,17 @@ void k_resid_norm(int dtype, float* x, const float* part, int nsplit, int64_t sp
 // One block per (query token, query head).  Keys 0..pos of the query's own sequence,
 // read either from contiguous [tokens, Hkv, hd] buffers (the sequence's tokens are
 // consecutive, so key m sits at row n - pos + m) or from the paged pool.
-template <typename T>
-__global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const T* kc, const T* vc, const T* pool,
-                                                          int layer, KvGeom geo, const int* bt, int mpps,
-                                                          const int* tok_pos, const int* tok_slot, T* out, int Hq) {
-    extern __shared__ float sm[];
-    const int hd = geo.hd, Hkv = geo.Hkv;
-    const int n = blockIdx.x, h = blockIdx.y, g = h / (Hq / Hkv);
+// DEC (decode, paged, one row per cache slot): q, k and v of the new token come straight from the QKV projection's
+// fp32 row.  The block rotates its own query head and its kv head's new key, rounds all three to T, and uses the new
+// key and value from LDS; the group's first head appends them to the page.  One launch instead of two per layer: at
+// the sizes this path serves each of them is little more than its launch (4.7 + 8.5 us before, 7.4 us now; 4 rows, 48 keys).
+template <typename T, bool DEC>
+__global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const float* qkv, const float2* rope, const T* kc,
+                                                          const T* vc, T* pool, int layer, KvGeom geo, const int* bt,
+                                                          int mpps, const int* tok_pos, const int* tok_slot, T* out, int Hq) {
+    extern __shared__ __attribute__((aligned(16))) float sm[];
+    const int hd = geo.hd, Hkv = geo.Hkv, half = hd / 2, G = Hq / Hkv;
+    const int n = blockIdx.x, h = blockIdx.y, g = h / G;
     const int pos = tok_pos[n], ctx = pos + 1;
     if (ctx <= 0) {            // parked row (position -1): no keys, zeros
         if (threadIdx.x < hd) out[((int64_t)n * Hq + h) * hd + threadIdx.x] = from_f<T>(0.f);
@@ -563,23 +712,45 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const T* k
     float* qs = sm;            // [hd]
     float* red = sm + hd;      // [16]
     float* part = red + 16;    // [256]
-    float* sc = part + 256;    // [ctx]
-    const int* btr = pool ? bt + (int64_t)tok_slot[n] * mpps : nullptr;
-    for (int j = threadIdx.x; j < hd; j += 256) qs[j] = to_f(q[((int64_t)n * Hq + h) * hd + j]);
+    float* kn = part + 256;    // [hd] DEC: the new token's key and value, as the cache will hold them
+    float* vn = kn + hd;       // [hd]
+    float* sc = vn + hd;       // [ctx, rounded up to 4]
+    const int* btr = DEC ? bt + (int64_t)tok_slot[n] * mpps : nullptr;
+    if (DEC) {
+        const float* row = qkv + (int64_t)n * (Hq + 2 * Hkv) * hd;
+        if (threadIdx.x < 2 * half) {                       // first the query's pairs, then the key's
+            const int j = threadIdx.x % half;
+            const float* r = row + (threadIdx.x < half ? h : Hq + g) * hd;
+            float* o = threadIdx.x < half ? qs : kn;
+            const float2 cs = rope[(int64_t)pos * half + j];
+            o[j] = to_f(from_f<T>(r[j] * cs.x - r[j + half] * cs.y));
+            o[j + half] = to_f(from_f<T>(r[j + half] * cs.x + r[j] * cs.y));
+        }
+        if (threadIdx.x < hd) vn[threadIdx.x] = to_f(from_f<T>(row[(Hq + Hkv + g) * hd + threadIdx.x]));
+    } else {
+        for (int j = threadIdx.x; j < hd; j += 256) qs[j] = to_f(q[((int64_t)n * Hq + h) * hd + j]);
+    }
     __syncthreads();
     const float scale = 1.0f / sqrtf((float)hd);
     float lmax = -INFINITY;
-    for (int m = threadIdx.x; m < ctx; m += 256) {
+    // four threads per key: a context of a few dozen keys would otherwise leave most of the block idle behind one
+    // thread's chain of loads
+    const int sub = threadIdx.x & 3;
+    for (int m = threadIdx.x >> 2; m < ctx; m += 64) {
+        const T* kr = DEC ? pool + geo.k_off(layer, btr[m / geo.PT], g, m % geo.PT, 0)
+                          : kc + ((int64_t)(n - pos + m) * Hkv + g) * hd;
+        const bool fresh = DEC && m == pos;                 // its page slot may not be written yet: LDS holds it
         float dot = 0.f;
-        if (pool) {
-            int64_t base = geo.k_off(layer, btr[m / geo.PT], g, m % geo.PT, 0);
-            for (int j = 0; j < hd; ++j) dot += qs[j] * to_f(pool[base + j]);
-        } else {
-            const T* kr = kc + ((int64_t)(n - pos + m) * Hkv + g) * hd;
-            for (int j = 0; j < hd; ++j) dot += qs[j] * to_f(kr[j]);
+#pragma unroll 4
+        for (int j = sub * 4; j < hd; j += 16) {
+            const floatx4 kv = fresh ? *reinterpret_cast<const floatx4*>(kn + j) : load4(kr + j);
+            const floatx4 qv = *reinterpret_cast<const floatx4*>(qs + j);
+            dot += qv[0] * kv[0] + qv[1] * kv[1] + qv[2] * kv[2] + qv[3] * kv[3];
         }
+        dot += __shfl_xor(dot, 1, RL_WAVE);
+        dot += __shfl_xor(dot, 2, RL_WAVE);
         dot *= scale;
-        sc[m] = dot;
+        if (sub == 0) sc[m] = dot;
         lmax = fmaxf(lmax, dot);
     }
     float mx = block_max(lmax, red);
@@ -588,11 +759,20 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const T* k
     float tot = block_sum(ls, red);   // has barriers: sc[] visible afterwards
     const int dd = threadIdx.x % hd, grp = threadIdx.x / hd, ngrp = 256 / hd;
     float acc = 0.f;
-    for (int m = grp; m < ctx; m += ngrp) {
-        float v;
-        if (pool) v = to_f(pool[geo.v_off(layer, btr[m / geo.PT], g, m % geo.PT, dd)]);
-        else v = to_f(vc[((int64_t)(n - pos + m) * Hkv + g) * hd + dd]);
-        acc += sc[m] * v;
+    if (DEC) {
+        // V pages are dim-major: four tokens of a dimension are one load
+        for (int m = grp * 4; m < pos; m += ngrp * 4) {
+            const T* vp = pool + geo.v_off(layer, btr[m / geo.PT], g, m % geo.PT, dd);
+            if (m + 4 <= pos) {
+                const floatx4 v = load4(vp);
+                acc += sc[m] * v[0] + sc[m + 1] * v[1] + sc[m + 2] * v[2] + sc[m + 3] * v[3];
+            } else {
+                for (int i = 0; m + i < pos; ++i) acc += sc[m + i] * to_f(vp[i]);
+            }
+        }
+        if (grp == 0) acc += sc[pos] * vn[dd];
+    } else {
+        for (int m = grp; m < ctx; m += ngrp) acc += sc[m] * to_f(vc[((int64_t)(n - pos + m) * Hkv + g) * hd + dd]);
     }
     part[threadIdx.x] = acc;
     __syncthreads();
@@ -600,22 +780,40 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const T* k
         float o = 0.f;
         for (int i = 0; i < ngrp; ++i) o += part[i * hd + threadIdx.x];
         out[((int64_t)n * Hq + h) * hd + threadIdx.x] = from_f<T>(o / tot);
+        if (DEC && h == g * G) {
+            pool[geo.k_off(layer, btr[pos / geo.PT], g, pos % geo.PT, threadIdx.x)] = from_f<T>(kn[threadIdx.x]);
+            pool[geo.v_off(layer, btr[pos / geo.PT], g, pos % geo.PT, threadIdx.x)] = from_f<T>(vn[threadIdx.x]);
+        }
     }
 }
-void k_attn_simple(int dtype, const void* q, const void* kc, const void* vc, const void* pool, int layer, KvGeom geo,
-                   const int* block_table, int mpps, const int* tok_pos, const int* tok_slot, void* out, int n,
-                   int Hq, int max_ctx, hipStream_t s) {
+size_t k_attn_simple_lds(int hd, int max_ctx) { return (size_t)(3 * hd + 16 + 256 + (max_ctx + 3) / 4 * 4) * sizeof(float); }
+void k_attn_simple(int dtype, const void* q, const void* kc, const void* vc, const int* tok_pos, void* out, int n, int Hq,
+                   int Hkv, int hd, int max_ctx, hipStream_t s) {
     if (n <= 0) return;
-    size_t lds = (size_t)(geo.hd + 16 + 256 + max_ctx) * sizeof(float);
+    const size_t lds = k_attn_simple_lds(hd, max_ctx);
+    const KvGeom geo{Hkv, hd, 16, 0};
     dim3 grid(n, Hq);
     if (dtype == 0)
-        attn_simple_kernel<float><<<grid, 256, lds, s>>>((const float*)q, (const float*)kc, (const float*)vc,
-                                                         (const float*)pool, layer, geo, block_table, mpps, tok_pos,
-                                                         tok_slot, (float*)out, Hq);
+        attn_simple_kernel<float, false><<<grid, 256, lds, s>>>((const float*)q, nullptr, nullptr, (const float*)kc,
+                                                                (const float*)vc, nullptr, 0, geo, nullptr, 0, tok_pos,
+                                                                nullptr, (float*)out, Hq);
     else
-        attn_simple_kernel<f16_t><<<grid, 256, lds, s>>>((const f16_t*)q, (const f16_t*)kc, (const f16_t*)vc,
-                                                         (const f16_t*)pool, layer, geo, block_table, mpps, tok_pos,
-                                                         tok_slot, (f16_t*)out, Hq);
+        attn_simple_kernel<f16_t, false><<<grid, 256, lds, s>>>((const f16_t*)q, nullptr, nullptr, (const f16_t*)kc,
+                                                                (const f16_t*)vc, nullptr, 0, geo, nullptr, 0, tok_pos,
+                                                                nullptr, (f16_t*)out, Hq);
+}
+void k_attn_simple_decode(int dtype, const float* qkv, const float2* rope, void* pool, int layer, KvGeom geo,
+                          const int* block_table, int mpps, const int* tok_pos, const int* tok_slot, void* out, int n,
+                          int Hq, int max_ctx, hipStream_t s) {
+    if (n <= 0) return;
+    const size_t lds = k_attn_simple_lds(geo.hd, max_ctx);
+    dim3 grid(n, Hq);
+    if (dtype == 0)
+        attn_simple_kernel<float, true><<<grid, 256, lds, s>>>(nullptr, qkv, rope, nullptr, nullptr, (float*)pool, layer, geo,
+                                                               block_table, mpps, tok_pos, tok_slot, (float*)out, Hq);
+    else
+        attn_simple_kernel<f16_t, true><<<grid, 256, lds, s>>>(nullptr, qkv, rope, nullptr, nullptr, (f16_t*)pool, layer, geo,
+                                                               block_table, mpps, tok_pos, tok_slot, (f16_t*)out, Hq);
 }
 
 // ---------------------------------------------------------------- sampling

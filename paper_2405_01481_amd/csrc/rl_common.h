@@ -73,7 +73,7 @@ struct KvGeom {
 // fp16 KV cache (fp32 residual stream and accumulation in both).  bf16 -> fp16 is exact for
 // every weight of normal fp16 magnitude, so the weights lose nothing; activations keep an
 // 11-bit significand instead of bf16's 8.  All pointers device.  Nothing here synchronises.
-enum { EPI_STORE_F32 = 0, EPI_STORE_T = 1, EPI_RESID = 2, EPI_SWIGLU = 3 };
+enum { EPI_STORE_F32 = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
 
 struct SampleArgs {
     uint64_t seed;
@@ -92,11 +92,18 @@ void k_fill_i32(int* p, int v, int64_t n, hipStream_t s);
 void k_fill_f32(float* p, float v, int64_t n, hipStream_t s);
 void k_rope_table(float2* tab, int max_seq, int hd, float base, hipStream_t s);
 void k_set_pages(int* block_table, int mpps, const int* triples_host, int n_triples, hipStream_t s);
-void k_step_begin(const int* tok_in, const int* last_tok, const int* seq_len, const int* finished, int* cur_tok,
-                  int* tok_pos, int* tok_slot, int B, hipStream_t s);
+// Start of a decode step: position and cache slot of every row, its embedding into x and, with norm_gain, the first
+// layer's RMSNorm into h (fp16 pairs with split).
+void k_step_start(int dtype, const int* tok_in, const int* last_tok, const int* seq_len, const int* finished, int* tok_pos,
+                  int* tok_slot, const void* E, int d, int V, float* x, int* errflag, const void* norm_gain, void* h,
+                  float eps, int split, int B, hipStream_t s);
+// n row descriptors of a chunk from host arrays through kernel arguments (nothing is copied by the runtime, the host
+// arrays are free when the call returns)
+void k_put_rows(const int* seq_first_h, const int* row_slot_h, const int* row_start_h, const int* row_len_h, int n,
+                int* seq_first, int* row_slot, int* row_start, int* row_len, hipStream_t s);
 void k_pack_tokens(const int* ids, int ld_ids, const int* seq_first, const int* row_slot, const int* row_start,
-                   const int* row_len, const int* full_len, int align, int* tok_ids, int* tok_pos, int* tok_slot,
-                   int* tok_tgt, int nrows, hipStream_t s);
+                   const int* row_len, int align, int* tok_ids, int* tok_pos, int* tok_slot, int* tok_tgt, int4* blocks,
+                   int nrows, hipStream_t s);
 void k_prefill_state(const int* ids, int ld_ids, const int* row_len, int* last_tok, int* seq_len, int* gen_count,
                      int* finished, int* step_count, int B, hipStream_t s);
 // State of n freshly prefilled slots: slot row_slot[i] starts sequence seq_first[i] (row of ids, also its output
@@ -109,17 +116,25 @@ void k_embed(int dtype, const int* ids, int n, const void* E, int d, int V, floa
 void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split = 0);
 void k_gemm_simple(int dtype, int epi, const void* A, int lda, const void* W, const void* W2, int M, int N, int K,
                    float* outF, void* outT, int ldc, hipStream_t s);
-void k_rope_append(int dtype, const float* qkv, int nsplit, int64_t split_stride, int n, const int* tok_pos,
-                   const int* tok_slot, const float2* rope, void* q_out, void* k_out, void* v_out, void* pool,
-                   int layer, KvGeom geo, const int* block_table, int mpps, int Hq, hipStream_t s);
+// C = RMSNorm(x; gain) * W^T (EPI_STORE_F32) or SwiGLU of it (W gate, W2 up), all fp32: the norm is part of the GEMM.
+void k_gemm_norm_f32(int epi, const float* x, const float* gain, float eps, const float* W, const float* W2, int M, int N,
+                     int K, float* out, int ldc, hipStream_t s);
+void k_rope_append(int dtype, const float* qkv, int n, const int* tok_pos, const int* tok_slot, const float2* rope,
+                   void* q_out, void* k_out, void* v_out, void* pool, int layer, KvGeom geo, const int* block_table,
+                   int mpps, int Hq, hipStream_t s);
 void k_rope_append_split(int dtype, const float* part, int nsplit, int64_t split_stride, int n, const int* tok_pos,
                          const int* tok_slot, const float2* rope, void* q_out, void* pool, int layer, KvGeom geo,
                          const int* block_table, int mpps, int Hq, hipStream_t s, int split = 0, int layer_lo = 0);
 void k_resid_norm(int dtype, float* x, const float* part, int nsplit, int64_t split_stride, const void* g, void* out,
                   int n, int d, float eps, hipStream_t s, int split = 0);
-void k_attn_simple(int dtype, const void* q, const void* kc, const void* vc, const void* pool, int layer, KvGeom geo,
-                   const int* block_table, int mpps, const int* tok_pos, const int* tok_slot, void* out, int n,
-                   int Hq, int max_ctx, hipStream_t s);
+// Plain attention over whole sequences (contiguous k, v), and of one new token per cache slot (which also rotates and
+// appends).  LDS grows with the context: k_attn_simple_lds(hd, max_ctx) bytes per workgroup.
+size_t k_attn_simple_lds(int hd, int max_ctx);
+void k_attn_simple(int dtype, const void* q, const void* kc, const void* vc, const int* tok_pos, void* out, int n, int Hq,
+                   int Hkv, int hd, int max_ctx, hipStream_t s);
+void k_attn_simple_decode(int dtype, const float* qkv, const float2* rope, void* pool, int layer, KvGeom geo,
+                          const int* block_table, int mpps, const int* tok_pos, const int* tok_slot, void* out, int n,
+                          int Hq, int max_ctx, hipStream_t s);
 void k_sample(const float* logits, int ldz, int V, int B, SampleArgs a, int* last_tok, int* seq_len, int* gen_count,
               int* finished, int* step_count, int* tok_out, float* logp_out, int* out_ids, float* out_logp,
               int out_stride, hipStream_t s);

@@ -32,9 +32,9 @@ static int fail(int code, const char* fmt, ...) {
 // ---------------------------------------------------------------- workspace layout
 struct Layout {
     size_t x, h, h_keep, qkv, q, kbuf, vbuf, attn, ffn, logits, rope, block_table;
-    size_t last_tok, seq_len, gen_count, finished, cur_tok, step_count;
+    size_t last_tok, seq_len, gen_count, finished, step_count;
     size_t tok_ids, tok_pos, tok_slot, tok_tgt;
-    size_t seq_first, row_start, row_len, full_len, row_slot, d_seq_len, d_prompt_len, errflag;
+    size_t seq_first, row_start, row_len, row_slot, d_seq_len, d_prompt_len, errflag;
     size_t out_row, seq_id, gen_limit;   // queue mode: per-slot output row, sequence id, token limit
     size_t splitk, attn_part, attn_ml, lse_part, z_tgt, blocks;
     size_t total;
@@ -92,7 +92,6 @@ static Layout make_layout(const rl_model_cfg& c) {
     L.seq_len = take((size_t)c.max_batch * 4);
     L.gen_count = take((size_t)c.max_batch * 4);
     L.finished = take((size_t)c.max_batch * 4);
-    L.cur_tok = take((size_t)c.max_batch * 4);
     L.step_count = take((size_t)c.max_batch * 4);
     L.tok_ids = take((size_t)rows * 4);
     L.tok_pos = take((size_t)rows * 4);
@@ -101,7 +100,6 @@ static Layout make_layout(const rl_model_cfg& c) {
     L.seq_first = take((size_t)c.max_batch * 4);
     L.row_start = take((size_t)c.max_batch * 4);
     L.row_len = take((size_t)c.max_batch * 4);
-    L.full_len = take((size_t)c.max_batch * 4);
     L.row_slot = take((size_t)c.max_batch * 4);
     L.out_row = take((size_t)c.max_batch * 4);
     L.seq_id = take((size_t)c.max_batch * 4);
@@ -223,10 +221,11 @@ struct rl_ctx {
         float temp;
         hipStream_t s;
         const void* out_len = nullptr;   // non-null: queue mode (per-slot output rows, ids, limits)
+        int ctx_cap = 0;                 // plain kernels: longest context the captured attention launches have LDS for
         bool operator==(const GraphKey& o) const {
             return B == o.B && G == o.G && impl == o.impl && eos == o.eos && out_ids == o.out_ids &&
                    out_logp == o.out_logp && seed == o.seed && base == o.base && temp == o.temp && s == o.s &&
-                   out_len == o.out_len;
+                   out_len == o.out_len && ctx_cap == o.ctx_cap;
         }
     } gkey{};
     hipGraphExec_t gexec = nullptr;
@@ -354,9 +353,29 @@ static void attention(rl_ctx* c, int l, int n, bool paged, int max_ctx, int nblo
         k_attn_prefill(a, nblocks, s);
         return;
     }
-    k_attn_simple(m.dtype, c->at<char>(L.q), paged ? nullptr : c->at<char>(L.kbuf), paged ? nullptr : c->at<char>(L.vbuf),
-                  paged ? c->pool : nullptr, l, c->geo, c->at<int>(L.block_table), L.mpps, c->at<int>(L.tok_pos),
-                  c->at<int>(L.tok_slot), c->at<char>(L.attn), n, m.n_q_heads, max_ctx, s);
+    if (paged)
+        k_attn_simple_decode(m.dtype, c->at<float>(L.qkv), c->at<float2>(L.rope), c->pool, l, c->geo, c->at<int>(L.block_table),
+                             L.mpps, c->at<int>(L.tok_pos), c->at<int>(L.tok_slot), c->at<char>(L.attn), n, m.n_q_heads,
+                             max_ctx, s);
+    else
+        k_attn_simple(m.dtype, c->at<char>(L.q), c->at<char>(L.kbuf), c->at<char>(L.vbuf), c->at<int>(L.tok_pos),
+                      c->at<char>(L.attn), n, m.n_q_heads, m.n_kv_heads, m.head_dim, max_ctx, s);
+}
+
+// RMSNorm and the GEMM behind it, plain path: one kernel for fp32 (it computes the norm from the operand it reads
+// anyway: 4 us saved per launch), two for bf16, whose norm output is rounded to fp16 on the way.
+static void norm_gemm(rl_ctx* c, int cls, int epi, const float* x, const void* gain, const void* W, const void* W2, int n,
+                      int N, float* outF, void* outT, hipStream_t s) {
+    const rl_model_cfg& m = c->cfg;
+    if (m.dtype == RL_FP32) {
+        ProfScope ps(c, cls, s);
+        k_gemm_norm_f32(epi, x, (const float*)gain, m.rms_eps, (const float*)W, (const float*)W2, n, N, m.d_model,
+                        epi == EPI_SWIGLU ? (float*)outT : outF, N, s);
+        return;
+    }
+    void* h = c->at<char>(c->L.h);
+    k_rmsnorm(m.dtype, x, gain, h, n, m.d_model, m.rms_eps, s);
+    gemm(c, cls, epi, h, m.d_model, W, W2, n, N, m.d_model, outF, outT, N, s);
 }
 
 static bool run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
@@ -366,7 +385,6 @@ static bool run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged,
     const int dt = m.dtype;
     const size_t e = esz_of(dt);
     const int qd = m.n_q_heads * m.head_dim;
-    void* h = c->at<char>(L.h);
     float* qkv = c->at<float>(L.qkv);
     void* q = c->at<char>(L.q);
     void* kb = c->at<char>(L.kbuf);
@@ -379,16 +397,14 @@ static bool run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged,
     const float2* rope = c->at<float2>(L.rope);
     const int gcls = paged ? RL_K_GEMM_DECODE : RL_K_GEMM_PREFILL;
     for (int l = l0; l < l1; ++l) {
-        k_rmsnorm(dt, x, W.attn_norm[l], h, n, m.d_model, m.rms_eps, s);
-        gemm(c, gcls, EPI_STORE_F32, h, m.d_model, W.wqkv[l], nullptr, n, L.nqkv, m.d_model, qkv, nullptr, L.nqkv, s);
-        k_rope_append(dt, qkv, 1, 0, n, tpos, tslot, rope, q, paged ? nullptr : kb, paged ? nullptr : vb,
-                      write_pages ? c->pool : nullptr, l, c->geo, bt, L.mpps, m.n_q_heads, s);
+        norm_gemm(c, gcls, EPI_STORE_F32, x, W.attn_norm[l], W.wqkv[l], nullptr, n, L.nqkv, qkv, nullptr, s);
+        if (!paged)
+            k_rope_append(dt, qkv, n, tpos, tslot, rope, q, kb, vb, write_pages ? c->pool : nullptr, l, c->geo, bt, L.mpps,
+                          m.n_q_heads, s);
         attention(c, l, n, paged, max_ctx, nblocks, s);
         gemm(c, gcls, EPI_RESID, att, qd, W.wo[l], nullptr, n, m.d_model, qd, x, nullptr, m.d_model, s);
-        k_rmsnorm(dt, x, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s);
         const char* wg = (const char*)W.w_gate_up[l];
-        gemm(c, gcls, EPI_SWIGLU, h, m.d_model, wg, wg + (size_t)m.d_ffn * m.d_model * e, n, m.d_ffn, m.d_model,
-             nullptr, ffn, m.d_ffn, s);
+        norm_gemm(c, gcls, EPI_SWIGLU, x, W.ffn_norm[l], wg, wg + (size_t)m.d_ffn * m.d_model * e, n, m.d_ffn, nullptr, ffn, s);
         gemm(c, gcls, EPI_RESID, ffn, m.d_ffn, W.w_down[l], nullptr, n, m.d_model, m.d_ffn, x, nullptr, m.d_model, s);
     }
     return false;
@@ -425,7 +441,7 @@ static int decode_splits(int n, int N, int K) {
     return k_gemm_mfma_splits_used(K, want);
 }
 
-// bf16 weights / fp16 activations on the MFMA kernels.
+// bf16 weights / fp16 activations on the MFMA kernels.  paged: h holds the first layer's norm output (k_step_start).
 static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
                             int nblocks, hipStream_t s, float* x, int l0, int l1) {
     const rl_model_cfg& m = c->cfg;
@@ -452,7 +468,6 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
         g.K = g.lda;
         g.Kw = width;
     };
-    if (paged) k_rmsnorm(1, x, W.attn_norm[l0], h, n, m.d_model, m.rms_eps, s, l0 < c->precise);
     for (int l = l0; l < l1; ++l) {
         const int sp = l < c->precise, sp_next = l + 1 < c->precise && l + 1 < m.n_layers;
         GemmArgs g;
@@ -524,17 +539,17 @@ static bool run_layers(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool 
     return run_layers_plain(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
 }
 
-// LM head on rows [0, nr) of h: logits fp32 [nr, V]
-static void lm_head_logits(rl_ctx* c, int cls, const WeightsHost& W, const void* hrows, int nr, hipStream_t s) {
+// Logits fp32 [nr, V] of nr rows.  Tuned path: of the workspace's h, which holds the final norm's output; plain path: of
+// the residual stream x, final norm included.
+static void lm_head_logits(rl_ctx* c, int cls, const WeightsHost& W, const float* x, int nr, hipStream_t s) {
     const rl_model_cfg& m = c->cfg;
     if (c->impl == 1) {
         GemmArgs g;
-        g.M = nr; g.A = (const f16_t*)hrows; g.lda = m.d_model; g.W = (const bf16_t*)W.lm_head; g.N = m.vocab;
+        g.M = nr; g.A = c->at<f16_t>(c->L.h); g.lda = m.d_model; g.W = (const bf16_t*)W.lm_head; g.N = m.vocab;
         g.K = m.d_model; g.outF = c->at<float>(c->L.logits); g.ldc = m.vocab;
         mfma(c, cls, MG_STORE_F32, g, 1, s);
     } else {
-        gemm(c, cls, EPI_STORE_F32, hrows, m.d_model, W.lm_head, nullptr, nr, m.vocab, m.d_model,
-             c->at<float>(c->L.logits), nullptr, m.vocab, s);
+        norm_gemm(c, cls, EPI_STORE_F32, x, W.final_norm, W.lm_head, nullptr, nr, m.vocab, c->at<float>(c->L.logits), nullptr, s);
     }
 }
 
@@ -552,7 +567,7 @@ static bool fast_path_supported(const rl_model_cfg& m) {
 // starts at a multiple of 32 rows (the MFMA attention walks 32-key blocks) and the padding rows
 // are marked; the plain path packs densely.
 struct Chunk {
-    std::vector<int> rows_b, starts, lens, full;
+    std::vector<int> rows_b, starts, lens;
     std::vector<int> slots;   // cache slot of each row; empty = the row index itself
     int n = 0;          // rows in the list, padding included
     int max_ctx = 1;
@@ -570,7 +585,6 @@ static int chunk_take(const rl_ctx* c, const std::vector<int>& len_of, int b0, i
         ch.rows_b.push_back(b1);
         ch.starts.push_back(ch.n);
         ch.lens.push_back(len_of[b1]);
-        ch.full.push_back(len_of[b1]);
         ch.n += alen;
         ch.max_ctx = std::max(ch.max_ctx, len_of[b1]);
         ++b1;
@@ -578,35 +592,21 @@ static int chunk_take(const rl_ctx* c, const std::vector<int>& len_of, int b0, i
     return b1;
 }
 
-// Upload a chunk's row descriptors and build the packed token arrays on the device.
+// Hand a chunk's row descriptors to the device (as kernel arguments: nothing to wait for) and build the packed token
+// arrays and the attention work list there.
 static int pack_chunk(rl_ctx* c, const int* ids, int ld_ids, Chunk& ch, bool targets, hipStream_t s) {
     const Layout& L = c->L;
-    const size_t nb = ch.rows_b.size() * sizeof(int);
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.seq_first), ch.rows_b.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.row_start), ch.starts.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.row_len), ch.lens.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.full_len), ch.full.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.row_slot), (ch.slots.empty() ? ch.rows_b : ch.slots).data(), nb,
-                           hipMemcpyHostToDevice, s));
-    std::vector<int4> blocks;
+    const int nrows = (int)ch.rows_b.size();
     if (c->impl == 1) {
-        // one workgroup per 32-query block; long (late) blocks first so the tail of the grid is short work
-        int maxqb = 0;
-        for (int len : ch.lens) maxqb = std::max(maxqb, (len + 31) / 32);
-        for (int qb = maxqb - 1; qb >= 0; --qb)
-            for (size_t r = 0; r < ch.lens.size(); ++r)
-                if (qb < (ch.lens[r] + 31) / 32) blocks.push_back(make_int4(ch.starts[r], ch.lens[r], qb, 0));
-        ch.nblocks = (int)blocks.size();
+        ch.nblocks = 0;
+        for (int len : ch.lens) ch.nblocks += (len + 31) / 32;
         if (ch.nblocks > L.max_blocks) return fail(RL_EINVAL, "internal: attention block list overflow");
-        if (ch.nblocks)
-            HIP_TRY(hipMemcpyAsync(c->at<int4>(L.blocks), blocks.data(), blocks.size() * sizeof(int4),
-                                   hipMemcpyHostToDevice, s));
     }
-    // the host vectors may be reused by the caller right after this returns
-    HIP_TRY(hipStreamSynchronize(s));
+    k_put_rows(ch.rows_b.data(), (ch.slots.empty() ? ch.rows_b : ch.slots).data(), ch.starts.data(), ch.lens.data(), nrows,
+               c->at<int>(L.seq_first), c->at<int>(L.row_slot), c->at<int>(L.row_start), c->at<int>(L.row_len), s);
     k_pack_tokens(ids, ld_ids, c->at<int>(L.seq_first), c->at<int>(L.row_slot), c->at<int>(L.row_start),
-                  c->at<int>(L.row_len), c->at<int>(L.full_len), pack_align(c), c->at<int>(L.tok_ids), c->at<int>(L.tok_pos),
-                  c->at<int>(L.tok_slot), targets ? c->at<int>(L.tok_tgt) : nullptr, (int)ch.rows_b.size(), s);
+                  c->at<int>(L.row_len), pack_align(c), c->at<int>(L.tok_ids), c->at<int>(L.tok_pos), c->at<int>(L.tok_slot),
+                  targets ? c->at<int>(L.tok_tgt) : nullptr, c->impl == 1 ? c->at<int4>(L.blocks) : nullptr, nrows, s);
     return RL_OK;
 }
 
@@ -1007,8 +1007,7 @@ int rollout_prefill(rl_ctx* c, const int32_t* prompt_ids, const int32_t* prompt_
         }
     }
     // prompt lengths to the device for the state kernel
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.d_prompt_len), prompt_len, (size_t)B * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    k_put_i32(c->at<int>(L.d_prompt_len), prompt_len, B, s);
     k_prefill_state(prompt_ids, Pmax, c->at<int>(L.d_prompt_len), c->at<int>(L.last_tok), c->at<int>(L.seq_len),
                     c->at<int>(L.gen_count), c->at<int>(L.finished), c->at<int>(L.step_count), B, s);
     for (int b = 0; b < B; ++b) c->cached[b] = need[b];
@@ -1019,12 +1018,12 @@ int rollout_prefill(rl_ctx* c, const int32_t* prompt_ids, const int32_t* prompt_
 
 static int decode_step_impl(rl_ctx* c, const rl_sample_cfg* sample, const int32_t* tok_in, int32_t* tok_out,
                             float* logp_out, int32_t* out_ids, float* out_logp, int out_stride, hipStream_t s,
-                            int32_t* queue_out_len = nullptr) {
+                            int32_t* queue_out_len = nullptr, int ctx_cap = 0) {
     const rl_model_cfg& m = c->cfg;
     const Layout& L = c->L;
     const int B = c->B;
     std::vector<int> need(B);
-    int max_ctx = 1;
+    int max_ctx = std::max(1, ctx_cap);
     for (int b = 0; b < B; ++b) {
         if (c->parked[b]) { need[b] = c->cached[b]; continue; }
         if (c->cap[b] > 0) {
@@ -1038,12 +1037,11 @@ static int decode_step_impl(rl_ctx* c, const rl_sample_cfg* sample, const int32_
     }
     int rc = ensure_pages(c, need, s);
     if (rc) return rc;
-    k_step_begin(tok_in, c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.finished), c->at<int>(L.cur_tok),
-                 c->at<int>(L.tok_pos), c->at<int>(L.tok_slot), B, s);
-    k_embed(m.dtype, c->at<int>(L.cur_tok), B, c->policy.tok_embed, m.d_model, m.vocab, c->at<float>(L.x),
-            c->at<int>(L.errflag), s);
-    if (!run_layers(c, c->policy, B, true, true, max_ctx, 0, s))
-        k_rmsnorm(m.dtype, c->at<float>(L.x), c->policy.final_norm, c->at<char>(L.h), B, m.d_model, m.rms_eps, s);
+    const bool fast = c->impl == 1;
+    k_step_start(m.dtype, tok_in, c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.finished), c->at<int>(L.tok_pos),
+                 c->at<int>(L.tok_slot), c->policy.tok_embed, m.d_model, m.vocab, c->at<float>(L.x), c->at<int>(L.errflag),
+                 fast ? c->policy.attn_norm[0] : nullptr, c->at<char>(L.h), m.rms_eps, c->precise > 0, B, s);
+    run_layers(c, c->policy, B, true, true, max_ctx, 0, s);   // tuned: leaves h = RMSNorm(x; final_norm)
     SampleArgs a{sample->seed, sample->seq_id_base, sample->temperature, sample->eos_id};
     if (queue_out_len) {
         a.out_row = c->at<int>(L.out_row);
@@ -1067,13 +1065,23 @@ static int decode_step_impl(rl_ctx* c, const rl_sample_cfg* sample, const int32_
                         c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.gen_count), c->at<int>(L.finished),
                         c->at<int>(L.step_count), tok_out, logp_out, out_ids, out_logp, out_stride, s);
     } else {
-        lm_head_logits(c, RL_K_GEMM_DECODE, c->policy, c->at<char>(L.h), B, s);
+        lm_head_logits(c, RL_K_GEMM_DECODE, c->policy, c->at<float>(L.x), B, s);
         k_sample(c->at<float>(L.logits), m.vocab, m.vocab, B, a, c->at<int>(L.last_tok), c->at<int>(L.seq_len),
                  c->at<int>(L.gen_count), c->at<int>(L.finished), c->at<int>(L.step_count), tok_out, logp_out, out_ids,
                  out_logp, out_stride, s);
     }
     for (int b = 0; b < B; ++b) c->cached[b] = need[b];
     return RL_OK;
+}
+
+// Whether the decode step is captured and replayed: not on the null stream (it cannot be captured), not while launches
+// are timed one by one, and on the plain kernels only while the attention's LDS for the run's longest context fits
+// what a workgroup may have without asking (longer ones stay eager, their LDS grows with the context).
+static bool graph_usable(const rl_ctx* c, hipStream_t s, int ctx_cap) {
+    for (int k = 0; k < RL_K_COUNT; ++k)
+        if (c->prof_on[k] != 0) return false;
+    if (c->impl != 1 && k_attn_simple_lds(c->cfg.head_dim, ctx_cap) > 65536) return false;
+    return s != nullptr && c->use_graph;
 }
 
 static int check_sample(const rl_sample_cfg* sample) {
@@ -1116,18 +1124,17 @@ int rollout_generate(rl_ctx* c, const rl_sample_cfg* sample, const int32_t* prom
     for (int b = 0; b < B; ++b) need[b] = prompt_len[b] - 1 + G;
     rc = ensure_pages(c, need, s);
     if (rc) return rc;
-    bool profiling = false;
-    for (int k = 0; k < RL_K_COUNT; ++k) profiling = profiling || c->prof_on[k] != 0;
-    if (c->impl == 1 && s != nullptr && c->use_graph && !profiling) {
+    const int ctx_cap = *std::max_element(need.begin(), need.end());
+    if (graph_usable(c, s, ctx_cap)) {
         // The step is identical from one token to the next (positions, step counters and page
         // tables live on the device), so it is captured once and replayed G times.
         rl_ctx::GraphKey key{B, G, c->impl, sample->eos_id, out_ids, out_logp, sample->seed, sample->seq_id_base,
-                             sample->temperature, s};
+                             sample->temperature, s, nullptr, c->impl == 1 ? 0 : ctx_cap};
         if (!c->gexec || !(key == c->gkey)) {
             if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
             std::vector<int> saved = c->cached;
             HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, G, s);
+            rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, G, s, nullptr, ctx_cap);
             hipGraph_t graph = nullptr;
             hipError_t e = hipStreamEndCapture(s, &graph);
             c->cached = saved;
@@ -1179,7 +1186,6 @@ static int prefill_rows(rl_ctx* c, const int32_t* ids, int Pmax, const int32_t* 
             ch.slots.push_back(slots[i1]);
             ch.starts.push_back(ch.n);
             ch.lens.push_back(len);
-            ch.full.push_back(len);
             ch.n += alen;
             ch.max_ctx = std::max(ch.max_ctx, len);
             ++i1;
@@ -1194,14 +1200,11 @@ static int prefill_rows(rl_ctx* c, const int32_t* ids, int Pmax, const int32_t* 
     }
     std::vector<int> pl(n), lim(n);
     for (int i = 0; i < n; ++i) { pl[i] = plen[rows[i]]; lim[i] = limit[rows[i]]; }
-    const size_t nb = (size_t)n * sizeof(int);
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.seq_first), rows.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.row_slot), slots.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.row_len), pl.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.full_len), lim.data(), nb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));   // the host vectors go out of scope
+    // (the descriptors' first-row field carries the token limit here)
+    k_put_rows(rows.data(), slots.data(), lim.data(), pl.data(), n, c->at<int>(L.seq_first), c->at<int>(L.row_slot),
+               c->at<int>(L.row_start), c->at<int>(L.row_len), s);
     k_prefill_state_slots(ids, Pmax, n, c->at<int>(L.seq_first), c->at<int>(L.row_slot), c->at<int>(L.row_len),
-                          c->at<int>(L.full_len), c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.gen_count),
+                          c->at<int>(L.row_start), c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.gen_count),
                           c->at<int>(L.finished), c->at<int>(L.step_count), c->at<int>(L.out_row), c->at<int>(L.seq_id),
                           c->at<int>(L.gen_limit), s);
     for (int i = 0; i < n; ++i) {
@@ -1250,9 +1253,9 @@ int rollout_generate_queue(rl_ctx* c, const rl_sample_cfg* sample, const int32_t
     if ((rc = prefill_rows(c, prompt_ids, Pmax, prompt_len, gen_limit, rows, slots, s))) { rollout_reset(c); return rc; }
     live = nslots;
     c->B = nslots;
-    bool profiling = false;
-    for (int k = 0; k < RL_K_COUNT; ++k) profiling = profiling || c->prof_on[k] != 0;
-    const bool graph = c->impl == 1 && s != nullptr && c->use_graph && !profiling;
+    int ctx_cap = 1;
+    for (int q = 0; q < Q; ++q) ctx_cap = std::max(ctx_cap, prompt_len[q] - 1 + gen_limit[q]);
+    const bool graph = graph_usable(c, s, ctx_cap);
     std::vector<int> fin(nslots), slen(nslots), need(nslots);
     while (live > 0) {
         // reserve the burst's pages up front: nothing is allocated between two looks at the flags
@@ -1261,12 +1264,12 @@ int rollout_generate_queue(rl_ctx* c, const rl_sample_cfg* sample, const int32_t
         if ((rc = ensure_pages(c, need, s))) { rollout_reset(c); return rc; }
         if (graph) {
             rl_ctx::GraphKey key{nslots, Gmax, c->impl, sample->eos_id, out_ids, out_logp, sample->seed,
-                                 sample->seq_id_base, sample->temperature, s, out_len};
+                                 sample->seq_id_base, sample->temperature, s, out_len, c->impl == 1 ? 0 : ctx_cap};
             if (!c->gexec || !(key == c->gkey)) {
                 if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
                 std::vector<int> saved = c->cached;
                 HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-                rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, Gmax, s, out_len);
+                rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, Gmax, s, out_len, ctx_cap);
                 hipGraph_t g = nullptr;
                 hipError_t e = hipStreamEndCapture(s, &g);
                 c->cached = saved;
@@ -1326,8 +1329,8 @@ int rollout_generate_queue(rl_ctx* c, const rl_sample_cfg* sample, const int32_t
 static void score_head(rl_ctx* c, const WeightsHost& W, float* x, int n, float* logp_out, int Lmax, hipStream_t s) {
     const rl_model_cfg& m = c->cfg;
     const Layout& L = c->L;
-    k_rmsnorm(m.dtype, x, W.final_norm, c->at<char>(L.h), n, m.d_model, m.rms_eps, s);
     if (c->impl == 1) {
+        k_rmsnorm(m.dtype, x, W.final_norm, c->at<char>(L.h), n, m.d_model, m.rms_eps, s);
         // LM head with the log-sum-exp and the target gather in its epilogue: no logits in memory
         GemmArgs g;
         g.M = n; g.A = c->at<f16_t>(L.h); g.lda = m.d_model; g.W = (const bf16_t*)W.lm_head; g.N = m.vocab;
@@ -1339,10 +1342,9 @@ static void score_head(rl_ctx* c, const WeightsHost& W, float* x, int n, float* 
                      logp_out, Lmax, s);
         return;
     }
-    const size_t e = esz_of(m.dtype);
     for (int r0 = 0; r0 < n; r0 += L.logit_rows) {
         int nr = std::min(L.logit_rows, n - r0);
-        lm_head_logits(c, RL_K_LMHEAD_SCORE, W, c->at<char>(L.h) + (size_t)r0 * m.d_model * e, nr, s);
+        lm_head_logits(c, RL_K_LMHEAD_SCORE, W, x + (size_t)r0 * m.d_model, nr, s);
         k_lse_gather(c->at<float>(L.logits), m.vocab, m.vocab, nr, c->at<int>(L.tok_tgt) + r0,
                      c->at<int>(L.tok_slot) + r0, c->at<int>(L.tok_pos) + r0, logp_out, Lmax, s);
     }
@@ -1570,9 +1572,8 @@ int score_logprobs_kl(rl_ctx* c, const rl_weights* policy, const rl_weights* ref
     }
     if (kl || kl_penalty) {
         const Layout& L = c->L;
-        HIP_TRY(hipMemcpyAsync(c->at<int>(L.d_seq_len), seq_len, (size_t)B * 4, hipMemcpyHostToDevice, s));
-        HIP_TRY(hipMemcpyAsync(c->at<int>(L.d_prompt_len), prompt_len, (size_t)B * 4, hipMemcpyHostToDevice, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        k_put_i32(c->at<int>(L.d_seq_len), seq_len, B, s);
+        k_put_i32(c->at<int>(L.d_prompt_len), prompt_len, B, s);
         k_kl(logp_policy, logp_ref, c->at<int>(L.d_seq_len), c->at<int>(L.d_prompt_len), B, Lmax, kl_coef, kl,
              kl_penalty, s);
     }
@@ -1603,7 +1604,7 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
     const size_t e = esz_of(m.dtype);
     const bool fused = c->impl == 1 && k_gemm_mfma_supported(MG_KLFULL, m.vocab, m.d_model, m.head_dim);
     k_fill_f32(kl_out, 0.f, (int64_t)B * Lmax, s);
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.d_prompt_len), prompt_len, (size_t)B * 4, hipMemcpyHostToDevice, s));
+    k_put_i32(c->at<int>(L.d_prompt_len), prompt_len, B, s);
     std::vector<int> len_of(seq_len, seq_len + B);
     // rows per dual-head launch: the partials (5 floats per row and 64 columns) share the buffer of the
     // log-sum-exp partials (2 floats); the plain path holds two logit blocks in the logits buffer
@@ -1689,9 +1690,8 @@ int ppo_rewards(rl_ctx* c, const float* kl, const float* seq_reward, const int32
             return fail(RL_EINVAL, "row %d: need 1 <= seq_len <= Lmax and 0 <= prompt_len <= seq_len", b);
     hipStream_t s = (hipStream_t)stream;
     const Layout& L = c->L;
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.d_seq_len), seq_len, (size_t)B * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(c->at<int>(L.d_prompt_len), prompt_len, (size_t)B * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    k_put_i32(c->at<int>(L.d_seq_len), seq_len, B, s);
+    k_put_i32(c->at<int>(L.d_prompt_len), prompt_len, B, s);
     k_ppo_reward(kl, seq_reward, c->at<int>(L.d_seq_len), c->at<int>(L.d_prompt_len), B, Lmax, kl_coef, rewards, s);
     HIP_TRY(hipGetLastError());
     return RL_OK;
