@@ -58,8 +58,8 @@ struct GemmArgs {
     float* kl_part = nullptr;
     int vt_cap = 0;             // > 0: v_out is dim-major [Hkv][hd][vt_cap tokens]; 0: token-major [M][Hkv][hd]
     KvGeom geo{};
-    // 256 x 256 workgroup tiles (splits == 1 only): 0 never, 1 when the grid fills the chip at one workgroup
-    // per CU, 2 whenever the shape allows (N multiple of 256, K of 128)
+    // tiles of up to 256 x 256 (splits == 1 only): 0 never, 1 when 128 x 128 tiles are more than one per CU,
+    // 2 whenever the shape allows (N multiple of 256, K of 128)
     int big_mode = 1;
 };
 

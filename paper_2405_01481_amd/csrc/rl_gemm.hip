@@ -4,10 +4,10 @@
 // (exact for every weight of normal fp16 magnitude) -- or are read from an fp16 copy where a weight set
 // has one; the contraction runs on fp16 MFMAs (v_mfma_f32_16x16x32_f16 in the large-M kernel,
 // v_mfma_f32_32x32x16_f16 in the others) with fp32 accumulation.  Four kernels share one set of epilogues:
-//   * gemm_mfma_kernel: 128 x 128 tiles staged through registers, two workgroups per CU -- small and
-//     medium M, and split-K for decode batches above 128 rows;
-//   * gemm_dma8_kernel: 256 x 256 tiles, eight waves, operands staged by global -> LDS loads -- the
-//     large-M GEMMs of prefill and scoring once the grid fills the chip;
+//   * gemm_mfma_kernel: 128 x 128 tiles staged through registers -- small M, and split-K for decode
+//     batches above 128 rows;
+//   * gemm_dma8_kernel: tiles of 96 to 256 rows x 256 columns, eight waves, operands staged by global ->
+//     LDS loads -- the large-M GEMMs of prefill and scoring;
 //   * gemm_dma_kernel:  128 x 128 tiles staged the same way, two GEMMs on one tile -- the exact
 //     full-vocabulary KL, which needs the policy's and the reference's logits of a tile together;
 //   * gemm_ring_kernel: the weight-streaming GEMMs of a decode step (M <= 128 rows), split over K so
@@ -98,40 +98,42 @@ __device__ __forceinline__ float row32_max(float v) {
     v = fmaxf(v, dpp_move<0x140>(v));   // row_mirror
     return fmaxf(v, __shfl_xor(v, 16, RL_WAVE));
 }
-// The same two reductions for the 16 register rows of a band at once, level by level: the 16 chains are independent,
+// The same two reductions for all register rows of a band at once, level by level: the chains are independent,
 // so consecutive instructions never wait on one another (a data-parallel-primitive move needs two idle slots after
 // the instruction that wrote its source).  Same operations per row, in the same order, as row32_max / row32_sum.
-template <int CTRL>
-__device__ __forceinline__ void rows16_max_step(float (&v)[16]) {
-    float t[16];
+template <int CTRL, int N>
+__device__ __forceinline__ void rows_max_step(float (&v)[N]) {
+    float t[N];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) t[r] = dpp_move<CTRL>(v[r]);
+    for (int r = 0; r < N; ++r) t[r] = dpp_move<CTRL>(v[r]);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = fmaxf(v[r], t[r]);
+    for (int r = 0; r < N; ++r) v[r] = fmaxf(v[r], t[r]);
 }
-template <int CTRL>
-__device__ __forceinline__ void rows16_sum_step(float (&v)[16]) {
-    float t[16];
+template <int CTRL, int N>
+__device__ __forceinline__ void rows_sum_step(float (&v)[N]) {
+    float t[N];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) t[r] = dpp_move<CTRL>(v[r]);
+    for (int r = 0; r < N; ++r) t[r] = dpp_move<CTRL>(v[r]);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] += t[r];
+    for (int r = 0; r < N; ++r) v[r] += t[r];
 }
-__device__ __forceinline__ void rows16_max(float (&v)[16]) {
-    rows16_max_step<0xB1>(v); rows16_max_step<0x4E>(v); rows16_max_step<0x141>(v); rows16_max_step<0x140>(v);
-    float t[16];
+template <int N>
+__device__ __forceinline__ void rows_max(float (&v)[N]) {
+    rows_max_step<0xB1>(v); rows_max_step<0x4E>(v); rows_max_step<0x141>(v); rows_max_step<0x140>(v);
+    float t[N];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) t[r] = __shfl_xor(v[r], 16, RL_WAVE);
+    for (int r = 0; r < N; ++r) t[r] = __shfl_xor(v[r], 16, RL_WAVE);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = fmaxf(v[r], t[r]);
+    for (int r = 0; r < N; ++r) v[r] = fmaxf(v[r], t[r]);
 }
-__device__ __forceinline__ void rows16_sum(float (&v)[16]) {
-    rows16_sum_step<0xB1>(v); rows16_sum_step<0x4E>(v); rows16_sum_step<0x141>(v); rows16_sum_step<0x140>(v);
-    float t[16];
+template <int N>
+__device__ __forceinline__ void rows_sum(float (&v)[N]) {
+    rows_sum_step<0xB1>(v); rows_sum_step<0x4E>(v); rows_sum_step<0x141>(v); rows_sum_step<0x140>(v);
+    float t[N];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) t[r] = __shfl_xor(v[r], 16, RL_WAVE);
+    for (int r = 0; r < N; ++r) t[r] = __shfl_xor(v[r], 16, RL_WAVE);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] += t[r];
+    for (int r = 0; r < N; ++r) v[r] += t[r];
 }
 __device__ __forceinline__ float row32_sum(float v) {
     v += dpp_move<0xB1>(v);
@@ -150,6 +152,7 @@ __device__ __forceinline__ float swiglu_act(float g, float u) {
 // Epilogue shared by the tile kernels, for one 32-row band of a wave's accumulators: acc[j][r] of the
 // wave in tile-column position wn is C(row, col) with
 //   row = m_base + 8*(r/4) + 4*(lane/32) + r%4,   col(tile-local) = wn*TN*32 + j*32 + lane%32
+// NR = 8 takes the band's first 16 rows only (registers 0 .. 7).
 // Row metadata of the MG_QKV epilogue held across a wave: lane l keeps position and cache page of rows row0 + l and
 // row0 + 64 + l (fetched before the main loop, so that the epilogue starts without a chain of dependent loads).
 struct QkvRowMeta {
@@ -176,7 +179,7 @@ __device__ __forceinline__ QkvRowMeta qkv_row_meta(const GemmArgs& a, int row0, 
     return q;
 }
 
-template <int EPI, int BN, int TN, int WGN>
+template <int EPI, int BN, int TN, int WGN, int NR = 16>
 __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs& a, int m_base, int nb, int wn,
                                             int ks, int lane, const QkvRowMeta* pre = nullptr) {
     const int lg = lane >> 5, lrow = lane & 31;
@@ -185,7 +188,7 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
         // lowest column (the lowest lane that holds it), as the sampler's arg-max rule wants.
         const int nblk = a.N / 32;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < NR; ++r) {
             const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
@@ -203,9 +206,9 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
     if (EPI == MG_RESID) {
         // read-modify-write of the fp32 residual stream: all of the band's loads are issued before the
         // first add (rows past M read row M-1 instead of branching, so nothing separates the loads)
-        float old[TN][16];
+        float old[TN][NR];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < NR; ++r) {
             const int m = min(m_base + 8 * (r >> 2) + 4 * lg + (r & 3), a.M - 1);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
@@ -213,7 +216,7 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < NR; ++r) {
             const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
             if (m >= a.M) continue;
 #pragma unroll
@@ -238,13 +241,13 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
             return hd == 128 ? nb * BN + (c0 & ~127) + (((c0 & 127) >> 5) >> 1) * 32 + (c0 & 31) : nb * BN + c0;
         };
         const int head_hi = col_of(TN - 2) / hd;              // wave-uniform
-        int pos[16];                                           // < 0: padding row of the packed token list
-        int page[16];
+        int pos[NR];                                           // < 0: padding row of the packed token list
+        int page[NR];
         const bool to_pool = a.pool != nullptr && head_hi >= Hq;
         if (pre) {
             // the wave already holds these, one row per lane: pick them up with cross-lane reads
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < NR; ++r) {
                 const int rel = m_base - pre->row0 + 8 * (r >> 2) + 4 * lg + (r & 3);   // 0 .. 127
                 const int src = rel & 63;
                 const int p0 = __shfl(pre->pos[0], src, RL_WAVE), p1 = __shfl(pre->pos[1], src, RL_WAVE);
@@ -254,18 +257,18 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
             }
         } else {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < NR; ++r) {
                 const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
                 const int p_ = a.tok_pos[min(m, a.M - 1)];
                 pos[r] = m < a.M ? p_ : -1;
             }
         }
         if (to_pool && !pre) {
-            int slot[16];
+            int slot[NR];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) slot[r] = a.tok_slot[min(m_base + 8 * (r >> 2) + 4 * lg + (r & 3), a.M - 1)];
+            for (int r = 0; r < NR; ++r) slot[r] = a.tok_slot[min(m_base + 8 * (r >> 2) + 4 * lg + (r & 3), a.M - 1)];
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
+            for (int r = 0; r < NR; ++r)
                 page[r] = a.block_table[(int64_t)(pos[r] >= 0 ? slot[r] : 0) * a.mpps + max(pos[r], 0) / a.geo.PT];
         }
         const int S = a.split_out ? 2 : 1;                     // fp16 pairs: rows of q and k are [hi heads | lo heads]
@@ -274,13 +277,13 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
             const int j = 2 * jp, col0 = col_of(j);
             const int head = col0 / hd, jj = col0 % hd;        // jj < half; the partner column is jj + half
             if (head < Hq + Hkv) {
-                float2 cs[16];
+                float2 cs[NR];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) cs[r] = a.rope[(int64_t)max(pos[r], 0) * half + jj];
+                for (int r = 0; r < NR; ++r) cs[r] = a.rope[(int64_t)max(pos[r], 0) * half + jj];
                 __builtin_amdgcn_sched_barrier(0);
                 // q and k: rotate, round (and keep what the rounding left over), store token-major; k also to its page
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
+                for (int r = 0; r < NR; ++r) {
                     const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
                     if (m >= a.M) continue;
                     const bool pad = pos[r] < 0;               // padding rows get zeros: nothing non-finite is ever read back
@@ -318,7 +321,7 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
                 // token-major V
                 {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
+                    for (int r = 0; r < NR; ++r) {
                         const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
                         if (m >= a.M) continue;
                         const bool pad = pos[r] < 0;
@@ -336,7 +339,7 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
             // registers r = 4k .. 4k+3 of a lane are four consecutive tokens of one dimension, so they leave as one
             // 8-byte store instead of four 2-byte stores a cache line apart from their neighbours'.
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
+            for (int rq = 0; rq < NR / 4; ++rq) {
                 const int m4 = m_base + 8 * rq + 4 * lg;
                 if (m4 >= a.M) continue;
                 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
@@ -392,10 +395,10 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
         // per-element bounds checks or branches, one row pointer per register row.  Same values as the general path.
         constexpr int OUT_COLS = EPI == MG_SWIGLU ? TN * 16 : TN * 32;       // output columns of this wave
         const int n_first = (EPI == MG_SWIGLU ? nb * (BN / 2) : nb * BN) + wn * OUT_COLS;
-        if (m_base + 32 <= a.M && n_first + OUT_COLS <= a.N && !a.split_out) {   // wave-uniform
+        if (m_base + 2 * NR <= a.M && n_first + OUT_COLS <= a.N && !a.split_out) {   // wave-uniform
             f16_t* o = a.outH + (int64_t)(m_base + 4 * lg) * a.ldc + n_first + lrow;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < NR; ++r) {
                 f16_t* orow = o + (int64_t)(8 * (r >> 2) + (r & 3)) * a.ldc;
                 if constexpr (EPI == MG_SWIGLU) {
 #pragma unroll
@@ -411,31 +414,31 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
     if constexpr (EPI == MG_LSE) {
         // A band that lies wholly inside the matrix: the 16 rows' reductions run level by level, then the stores.  Same
         // values as the row-by-row form below.
-        if (m_base + 32 <= a.M) {                               // wave-uniform
-            int tg[16];
+        if (m_base + 2 * NR <= a.M) {                               // wave-uniform
+            int tg[NR];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) tg[r] = a.tgt[m_base + 8 * (r >> 2) + 4 * lg + (r & 3)];
-            float mx[16], se[16];
+            for (int r = 0; r < NR; ++r) tg[r] = a.tgt[m_base + 8 * (r >> 2) + 4 * lg + (r & 3)];
+            float mx[NR], se[NR];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < NR; ++r) {
                 mx[r] = acc[0][r];
 #pragma unroll
                 for (int j = 1; j < TN; ++j) mx[r] = fmaxf(mx[r], acc[j][r]);
             }
-            rows16_max(mx);
+            rows_max(mx);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < NR; ++r) {
                 se[r] = 0.f;
 #pragma unroll
                 for (int j = 0; j < TN; ++j) se[r] += __expf(acc[j][r] - mx[r]);
             }
-            rows16_sum(se);
+            rows_sum(se);
             const int nparts = (a.N / BN) * WGN;
             const int c_first = nb * BN + wn * TN * 32 + lrow;   // this lane's column of acc[0]
             float2* part = a.lse_part + (int64_t)(m_base + 4 * lg) * nparts + nb * WGN + wn;
             float* zt = a.z_tgt + m_base + 4 * lg;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < NR; ++r) {
                 const int ro = 8 * (r >> 2) + (r & 3);
                 if (lrow == 0) part[(int64_t)ro * nparts] = make_float2(mx[r], se[r]);
                 const int d = tg[r] - c_first;                  // 0, 32, ..: the target is this lane's column of acc[d / 32]
@@ -449,13 +452,13 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
     {
         // the targets of the lane's 16 rows, fetched before the first store (a load behind a store that may alias it
         // waits for the store)
-        int tgt[EPI == MG_LSE ? 16 : 1];
+        int tgt[EPI == MG_LSE ? NR : 1];
         if constexpr (EPI == MG_LSE) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) tgt[r] = a.tgt[min(m_base + 8 * (r >> 2) + 4 * lg + (r & 3), a.M - 1)];
+            for (int r = 0; r < NR; ++r) tgt[r] = a.tgt[min(m_base + 8 * (r >> 2) + 4 * lg + (r & 3), a.M - 1)];
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < NR; ++r) {
             const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
             if (m >= a.M) continue;
             if (EPI == MG_STORE_F32) {
@@ -844,7 +847,8 @@ __device__ __forceinline__ void dma_mainloop(const GemmArgs& a, const f16_t* Aop
 #undef DG_STEP
 }
 
-// Large-M GEMM, 256 x 256 tiles, eight waves (2 x 4; 128 x 64 of C per wave; two waves per SIMD, so a wave that waits
+// Large-M GEMM, tiles of 32 MI rows x 256 columns (MI = 3 .. 8, by the number of rows: big_row_blocks), eight waves
+// (2 x 4; 16 MI x 64 of C per wave; what follows says 128 x 64, MI = 8; two waves per SIMD, so a wave that waits
 // -- at a barrier, for its fragment reads, behind a queued staging load -- leaves the SIMD's matrix core to the other
 // one), operands staged global -> LDS through FIVE stages of 32 k with the loads of two consecutive k-tiles issued
 // together.  A stage row is 64 B, half a 128-byte cache line, and a request for half a line makes the L2 deliver the
@@ -871,11 +875,12 @@ __device__ __forceinline__ void dma_mainloop(const GemmArgs& a, const f16_t* Aop
 // epilogues, which are written for the 32 x 32 layout, each wave passes them through its own 17 KB of the then idle
 // LDS, 64 rows at a time.
 // Requires K % 64 == 0, no split over K, 5 * 512 * 64 bytes of LDS.
-template <int EPI, bool WF16>
+template <int EPI, bool WF16, int MI>
 __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
-    constexpr int BM = 256, BN = 256, WGN = 4, TM = 4, TN = 2;
+    constexpr int BM = 32 * MI, BN = 256, WGN = 4, TN = 2;
+    constexpr int MI0 = (MI + 1) / 2, MI1 = MI / 2;      // 16-row blocks of the wave in slice 0 and in slice 1
     constexpr int STAGE = (BM + BN) * 64;
-    constexpr int LPT = 4;
+    constexpr int LPA = (BM + 127) / 128, LPT = LPA + 2;  // staging loads per wave and k-tile: of A, in all
     typedef float floatx4_t __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [5 stages][A 256 x 64 B | W 256 x 64 B]
     const int tid = threadIdx.x, lane = tid & 63;
@@ -886,13 +891,18 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     if (!tile_of(blockIdx.x, MB, NB, mb, nb)) return;
     const int m0 = mb * BM;
     const int nk = a.K / 32, nkw = a.Kw / 32;
+    // 16-row block of its operand that load l of this wave stages; where A has fewer blocks than 8 LPA, the waves left
+    // over stage a block twice (same bytes to the same place), so that every wave counts the same loads
+#define X8_BLOCK(l)                                                                                             \
+    ((l) >= LPA ? ((l) - LPA) * 8 + wave                                                                        \
+                : (l) * 8 + wave < BM / 16 ? (l) * 8 + wave : (l) * 8 + wave - ((l) > 0 ? 8 : BM / 16))
     unsigned g_off[LPT];
     {
         const int lc = (lane & 3) ^ ((lane >> 4) & 3);
 #pragma unroll
         for (int l = 0; l < LPT; ++l) {
-            const int r = ((l & 1) * 8 + wave) * 16 + (lane >> 2);
-            g_off[l] = l < 2 ? ((unsigned)min(m0 + r, a.M - 1) * (unsigned)a.lda + lc * 8) * 2u   // rows >= M: clamped, never stored
+            const int r = X8_BLOCK(l) * 16 + (lane >> 2);
+            g_off[l] = l < LPA ? ((unsigned)min(m0 + r, a.M - 1) * (unsigned)a.lda + lc * 8) * 2u   // rows >= M: clamped, never stored
                              : ((unsigned)min(w_row_of<EPI, BN>(r, nb, a), a.Wrows - 1) * (unsigned)a.Kw + lc * 8) * 2u;
         }
     }
@@ -902,50 +912,59 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
 #define X8_LOAD(st, kt, l)                                                                                      \
     {                                                                                                           \
         const int kt_ = min((kt), nk - 1);                                                                      \
-        const unsigned sa_ = lds_base + (st) * STAGE + ((l) >= 2 ? BM * 64 : 0) + (((l) & 1) * 8 + wave) * 1024; \
-        const char* g_ = (l) < 2 ? Ag + (size_t)kt_ * 64 : Wg + (size_t)wrap_k(kt_, nkw) * 64;                  \
+        const unsigned sa_ = lds_base + (st) * STAGE + ((l) >= LPA ? BM * 64 : 0) + X8_BLOCK(l) * 1024;         \
+        const char* g_ = (l) < LPA ? Ag + (size_t)kt_ * 64 : Wg + (size_t)wrap_k(kt_, nkw) * 64;                \
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                            \
                      :: "s"(sa_), "v"(g_off[l]), "s"(g_) : "memory");                                           \
     }
     // fragment offsets inside a stage: row lane % 16 of a 16-row block, logical 16-byte chunk lane / 16, swizzled
     const int fr = lane & 15;
     const int fko = ((lane >> 4) ^ ((fr >> 2) & 3)) * 16;
-    const int fa = (wm * 128 + fr) * 64 + fko;                 // + i * 1024 for the i-th 16-row block of the wave
+    const int fa = (wm * MI * 16 + fr) * 64 + fko;                 // + i * 1024 for the i-th 16-row block of the wave
     const int fw = BM * 64 + (wn * 64 + fr) * 64 + fko;        // + j * 1024
-    floatx4_t acc[8][4];
+    floatx4_t acc[MI][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    half8 af[2][4];
+    half8 af[2][MI0];
     u32x4_t wf[2][4], bw[WF16 ? 1 : 4];   // W fragments as they go into the MFMAs; bf16 fragments waiting for their conversion
 #define X8_CVT2(w) __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(__uint_as_float((w) << 16), __uint_as_float((w) & 0xffff0000u)))
 #define X8_LDA(so, i) *reinterpret_cast<const half8*>(smem + (so) + fa + (i) * 1024)
 #define X8_LDW(so, j) *reinterpret_cast<const u32x4_t*>(smem + (so) + fw + (j) * 1024)
-    // One slice: 16 MFMAs on A set AS (rows AS * 64 ..) and W set WS.  NR fragment reads spread behind the first
-    // MFMAs (slice 0: the wave's rows 64-127 of stage NSO into A set 1; slice 1: W of stage NSO into W set 1 - WS, then
-    // rows 0-63 into A set 0); LOADS pairs of staging loads behind MFMAs 12, 14.
+    // One slice: NQ = 4 MI0 or 4 MI1 MFMAs on A set AS (slice 0: the wave's first MI0 row blocks, slice 1: the others) and
+    // W set WS.  The fragment reads are spread behind the first MFMAs (slice 0: the row blocks of slice 1, stage NSO,
+    // into A set 1; slice 1: W of stage NSO into W set 1 - WS, then the row blocks of slice 0 into A set 0), LOADS pairs
+    // of staging loads behind the last quarter.  With MI = 8: reads behind MFMAs 0, 2, 4, 6 / 0 - 3 and 4, 6, 8, 10,
+    // conversions behind 8 - 15, loads behind 12, 14.
 #define X8_SLICE(AS, WS, NSO, LOADS, LB, PT, PS0, PS1)                                                          \
-    _Pragma("unroll") for (int q = 0; q < 16; ++q) {                                                            \
-        const int j_ = q / 4, i_ = q % 4;                                                                       \
-        acc[(AS) * 4 + i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[AS][i_], __builtin_bit_cast(half8, wf[WS][j_]), acc[(AS) * 4 + i_][j_], 0, 0, 0); \
+    _Pragma("unroll") for (int q = 0; q < 4 * ((AS) ? MI1 : MI0); ++q) {                                        \
+        constexpr int NI_ = (AS) ? MI1 : MI0, NQ_ = 4 * NI_;                                                    \
+        const int j_ = q / NI_, i_ = q % NI_;                                                                   \
+        acc[(AS) * MI0 + i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[AS][i_], __builtin_bit_cast(half8, wf[WS][j_]), acc[(AS) * MI0 + i_][j_], 0, 0, 0); \
         if ((AS) == 0) {                                                                                        \
-            if (q < 8 && (q & 1) == 0) af[1][q / 2 < 4 ? q / 2 : 0] = X8_LDA(NSO, 4 + q / 2);                   \
+            _Pragma("unroll") for (int u_ = 0; u_ < MI1; ++u_)                                                  \
+                if (u_ * (NQ_ / 2) / MI1 == q) af[1][u_] = X8_LDA(NSO, MI0 + u_);                               \
         } else {                                                                                                \
-            if (q < 4) {                                                                                        \
-                if (WF16) wf[1 - (WS)][q < 4 ? q : 0] = X8_LDW(NSO, q);                                         \
-                else bw[!WF16 && q < 4 ? q : 0] = X8_LDW(NSO, q);                                               \
-            } else if (q < 12 && (q & 1) == 0) af[0][q >= 4 && q < 12 ? (q - 4) / 2 : 0] = X8_LDA(NSO, (q - 4) / 2); \
-            if (!WF16 && q >= 8) {           /* half a bf16 fragment -> fp16 per slot */                        \
-                const int c_ = q >= 8 ? q - 8 : 0, jj_ = c_ >> 1, h_ = (c_ & 1) * 2;                            \
-                wf[1 - (WS)][jj_][h_] = X8_CVT2(bw[WF16 ? 0 : jj_][h_]);                                        \
-                wf[1 - (WS)][jj_][h_ + 1] = X8_CVT2(bw[WF16 ? 0 : jj_][h_ + 1]);                                \
+            _Pragma("unroll") for (int u_ = 0; u_ < 4; ++u_)                                                    \
+                if (u_ * NQ_ / 16 == q) {                                                                       \
+                    if (WF16) wf[1 - (WS)][u_] = X8_LDW(NSO, u_);                                               \
+                    else bw[WF16 ? 0 : u_] = X8_LDW(NSO, u_);                                                   \
+                }                                                                                               \
+            _Pragma("unroll") for (int u_ = 0; u_ < MI0; ++u_)                                                  \
+                if (NQ_ / 4 + u_ * (NQ_ / 2) / MI0 == q) af[0][u_] = X8_LDA(NSO, u_);                           \
+            _Pragma("unroll") for (int c_ = 0; c_ < 8; ++c_)   /* half a bf16 fragment -> fp16 per unit */      \
+                if (!WF16 && NQ_ / 2 + c_ * (NQ_ / 2) / 8 == q) {                                               \
+                    const int jj_ = c_ >> 1, h_ = (c_ & 1) * 2;                                                 \
+                    wf[1 - (WS)][jj_][h_] = X8_CVT2(bw[WF16 ? 0 : jj_][h_]);                                    \
+                    wf[1 - (WS)][jj_][h_ + 1] = X8_CVT2(bw[WF16 ? 0 : jj_][h_ + 1]);                            \
+                }                                                                                               \
+        }                                                                                                       \
+        _Pragma("unroll") for (int u_ = 0; u_ < (LOADS); ++u_)                                                  \
+            if (NQ_ - NQ_ / 4 + u_ * (NQ_ / 8) == q) {                                                          \
+                X8_LOAD(PS0, PT, (LB) + u_)                                                                     \
+                X8_LOAD(PS1, (PT) + 1, (LB) + u_)                                                               \
             }                                                                                                   \
-        }                                                                                                       \
-        if (q >= 12 && (q & 1) == 0 && (q - 12) / 2 < (LOADS)) {                                                \
-            X8_LOAD(PS0, PT, (LB) + (q - 12) / 2)                                                               \
-            X8_LOAD(PS1, (PT) + 1, (LB) + (q - 12) / 2)                                                         \
-        }                                                                                                       \
         __builtin_amdgcn_sched_barrier(0);                                                                      \
     }
     int s0 = 0, s1 = 1, s2 = 2, s3 = 3, s4 = 4;
@@ -954,11 +973,11 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
 #pragma unroll
     for (int l = 0; l < LPT; ++l) { X8_LOAD(2, 2, l) X8_LOAD(3, 3, l) }
     QkvRowMeta meta;
-    if constexpr (EPI == MG_QKV) meta = qkv_row_meta(a, m0 + wm * 128, lane);
+    if constexpr (EPI == MG_QKV) meta = qkv_row_meta(a, m0 + wm * MI * 16, lane);
     __builtin_amdgcn_s_waitcnt(dma_waitcnt(EPI == MG_QKV ? 0 : 2 * LPT + 1, 15));
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) af[0][i] = X8_LDA(0, i);
+    for (int i = 0; i < MI0; ++i) af[0][i] = X8_LDA(0, i);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const u32x4_t w_ = X8_LDW(0, j);
@@ -967,24 +986,25 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     }
     for (int kt = 0; kt < nk; kt += 2) {
         const int o0 = s0 * STAGE, o1 = s1 * STAGE, o2 = s2 * STAGE;
-        // even k-tile kt (W set 0): rows 0-63, barrier (tile kt+1 complete, stage of tile kt released after this
-        // slice's reads), rows 64-127 with the first loads of pair (kt+4, kt+5)
+        // even k-tile kt (W set 0): slice 0, barrier (tile kt+1 complete, stage of tile kt released after this
+        // slice's reads), slice 1 with the first loads of pair (kt+4, kt+5)
         X8_SLICE(0, 0, o0, 0, 0, 0, 0, 0)
         __builtin_amdgcn_s_waitcnt(dma_waitcnt(2 * LPT, 0));
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
-        X8_SLICE(1, 0, o1, 2, 0, kt + 4, s4, s0)
+        X8_SLICE(1, 0, o1, LPT - 2, 0, kt + 4, s4, s0)
         // odd k-tile kt+1 (W set 1)
-        X8_SLICE(0, 1, o1, 1, 2, kt + 4, s4, s0)
-        __builtin_amdgcn_s_waitcnt(dma_waitcnt(6 + 1, 0));
+        X8_SLICE(0, 1, o1, 1, LPT - 2, kt + 4, s4, s0)
+        __builtin_amdgcn_s_waitcnt(dma_waitcnt(2 * (LPT - 1) + 1, 0));
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
-        X8_SLICE(1, 1, o2, 1, 3, kt + 4, s4, s0)
+        X8_SLICE(1, 1, o2, 1, LPT - 1, kt + 4, s4, s0)
         const int t0 = s0, t1 = s1;
         s0 = s2; s1 = s3; s2 = s4; s3 = t0; s4 = t1;
     }
     __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 15));   // nothing may land in LDS after this point
 #undef X8_LOAD
+#undef X8_BLOCK
 #undef X8_CVT2
 #undef X8_LDA
 #undef X8_LDW
@@ -996,26 +1016,36 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     float* patch = reinterpret_cast<float*>(smem) + wave * (64 * 68);
     const QkvRowMeta* pre = EPI == MG_QKV ? &meta : nullptr;
     const int lg = lane >> 5, lrow = lane & 31;
-    // written out per half: with the largest epilogue the unroller gives up on a loop over the halves, and the
-    // accumulators must stay statically indexed
+    // written out per half of 64 rows: with the largest epilogue the unroller gives up on a loop over the halves, and
+    // the accumulators must stay statically indexed.  A wave's last band has 16 rows where MI is odd.
+#define D8_READ(hf, b)                                                                                          \
+        floatx16 band##b[TN];                                                                                   \
+        _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                          \
+            _Pragma("unroll") for (int r = 0; r < 16; ++r)                                                      \
+                if ((hf) * 64 + (b) * 32 + 8 * (r >> 2) < MI * 16)                                              \
+                    band##b[j][r] = patch[((b) * 32 + 8 * (r >> 2) + 4 * lg + (r & 3)) * 68 + j * 32 + lrow];
+#define D8_BAND(hf, b)                                                                                          \
+        if constexpr ((hf) * 64 + (b) * 32 < MI * 16)                                                           \
+            mg_epilogue<EPI, BN, TN, WGN, (hf) * 64 + (b) * 32 + 32 <= MI * 16 ? 16 : 8>(                       \
+                band##b, a, m0 + wm * MI * 16 + (hf) * 64 + (b) * 32, nb, wn, 0, lane, pre);
 #define D8_HALF(hf)                                                                                             \
-    {                                                                                                           \
+    if constexpr ((hf) * 4 < MI) {                                                                              \
         _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                           \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                       \
-                _Pragma("unroll") for (int t = 0; t < 4; ++t)                                                   \
-                    patch[(i * 16 + 4 * (lane >> 4) + t) * 68 + j * 16 + (lane & 15)] = acc[(hf) * 4 + i][j][t]; \
+            if ((hf) * 4 + i < MI)                                                                              \
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                   \
+                    _Pragma("unroll") for (int t = 0; t < 4; ++t)                                               \
+                        patch[(i * 16 + 4 * (lane >> 4) + t) * 68 + j * 16 + (lane & 15)] = acc[(hf) * 4 + i < MI ? (hf) * 4 + i : 0][j][t]; \
         __builtin_amdgcn_wave_barrier();      /* LDS accesses of a wave complete in order */                    \
-        floatx16 band[2][TN];                                                                                   \
-        _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                           \
-            _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                      \
-                _Pragma("unroll") for (int r = 0; r < 16; ++r)                                                  \
-                    band[b][j][r] = patch[(b * 32 + 8 * (r >> 2) + 4 * lg + (r & 3)) * 68 + j * 32 + lrow];     \
+        D8_READ(hf, 0)                                                                                          \
+        D8_READ(hf, 1)                                                                                          \
         __builtin_amdgcn_wave_barrier();                                                                        \
-        mg_epilogue<EPI, BN, TN, WGN>(band[0], a, m0 + wm * 128 + (hf) * 64, nb, wn, 0, lane, pre);             \
-        mg_epilogue<EPI, BN, TN, WGN>(band[1], a, m0 + wm * 128 + (hf) * 64 + 32, nb, wn, 0, lane, pre);        \
+        D8_BAND(hf, 0)                                                                                          \
+        D8_BAND(hf, 1)                                                                                          \
     }
     D8_HALF(0)
     D8_HALF(1)
+#undef D8_READ
+#undef D8_BAND
 #undef D8_HALF
 }
 
@@ -1200,18 +1230,57 @@ static void launch_dma(const GemmArgs& a, int n_blocks_n, int splits, hipStream_
     dim3 grid(8 * ((n_blocks_n * ((a.M + BM - 1) / BM) + 7) / 8), 1, splits);
     gemm_dma_kernel<EPI, BM, BN, WGM, WGN, MINWG><<<grid, 256, lds, s>>>(b);
 }
-template <int EPI, bool WF16 = false>
-static void launch_dma8(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
-    constexpr int lds = 5 * 512 * 64;
+template <int EPI, bool WF16, int MI>
+static void launch_dma8_t(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
+    constexpr int BM = 32 * MI, stages = 5 * (BM + 256) * 64, patches = 8 * 64 * 68 * 4;
+    constexpr int lds = stages > patches ? stages : patches;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_dma8_kernel<EPI, WF16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        (void)hipFuncSetAttribute((const void*)gemm_dma8_kernel<EPI, WF16, MI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         attr_set = true;
     }
     GemmArgs b = a;
     b.n_blocks_n = n_blocks_n;
-    dim3 grid(8 * ((n_blocks_n * ((a.M + 255) / 256) + 7) / 8), 1, 1);
-    gemm_dma8_kernel<EPI, WF16><<<grid, 512, lds, s>>>(b);
+    dim3 grid(8 * ((n_blocks_n * ((a.M + BM - 1) / BM) + 7) / 8), 1, 1);
+    gemm_dma8_kernel<EPI, WF16, MI><<<grid, 512, lds, s>>>(b);
+}
+template <int EPI, bool WF16>
+static void launch_dma8(const GemmArgs& a, int n_blocks_n, int mi, hipStream_t s) {
+    switch (mi) {
+        case 3: launch_dma8_t<EPI, WF16, 3>(a, n_blocks_n, s); break;
+        case 4: launch_dma8_t<EPI, WF16, 4>(a, n_blocks_n, s); break;
+        case 5: launch_dma8_t<EPI, WF16, 5>(a, n_blocks_n, s); break;
+        case 6: launch_dma8_t<EPI, WF16, 6>(a, n_blocks_n, s); break;
+        case 7: launch_dma8_t<EPI, WF16, 7>(a, n_blocks_n, s); break;
+        default: launch_dma8_t<EPI, WF16, 8>(a, n_blocks_n, s); break;
+    }
+}
+// Tile height of the large-M kernel in units of 32 rows: the one whose rounds of 256 tiles (one workgroup per CU) cost
+// least.  A round costs its k loop -- relative to 256 rows 0.575 .. 1 below, measured: short tiles reread W more often
+// and feed fewer MFMAs per fragment -- plus an epilogue that goes with the rows (24 k-tiles' worth for the residual's
+// read-modify-write, 8 for the others); the last, incomplete round runs at a higher clock: 0.7 + 0.3 x its filling.
+// Over the layer shapes of the 1B, 8B and 70B models, 352 to 16384 rows, fp16 and bf16 weights, the height taken is
+// within 0.3 % of the best of the six on average (6 % at worst); against 256 rows throughout: O projection of the 8B
+// shape at 4928 rows 185 -> 150 us, 1B gate/up at 2240 rows 140 -> 124 us, 70B down projection at 12544 rows 5599 ->
+// 5361 us.  Every height gives the same bits: a row's sums run over k in the same order.
+#ifdef FORCE_MI
+static int g_force_mi = 8;
+#endif
+static int big_row_blocks(int epi, const GemmArgs& a, int n_blocks_n) {
+#ifdef FORCE_MI
+    return g_force_mi;
+#endif
+    static const float loop[9] = {0, 0, 0, 0.575f, 0.62f, 0.76f, 0.855f, 0.95f, 1.0f};
+    int best = 8;
+    float best_cost = 0.f;
+    for (int mi = 8; mi >= 3; --mi) {
+        const int64_t tiles = (int64_t)((a.M + 32 * mi - 1) / (32 * mi)) * n_blocks_n;
+        const float rem = (float)(tiles % 256) / 256.f;
+        const float rounds = (float)(tiles / 256) + (rem > 0.f ? 0.7f + 0.3f * rem : 0.f);
+        const float cost = rounds * (loop[mi] * (float)(a.K / 32) + (epi == MG_RESID ? 24.f : 8.f) * (float)mi / 8.f);
+        if (mi == 8 || cost < best_cost) { best = mi; best_cost = cost; }
+    }
+    return best;
 }
 static int g_big_reads_copy = 1;   // measurement switch: 0 = the large-M GEMMs convert bf16 weights even where an fp16 copy exists
 void k_gemm_big_reads_copy(int on) { g_big_reads_copy = on; }
@@ -1219,8 +1288,9 @@ template <int EPI>
 static void launch_big(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
     GemmArgs b = a;
     b.k_per_split = a.K;
-    if (a.w_f16) launch_dma8<EPI, true>(b, n_blocks_n, s);
-    else launch_dma8<EPI>(b, n_blocks_n, s);
+    const int mi = big_row_blocks(EPI, a, n_blocks_n);
+    if (a.w_f16) launch_dma8<EPI, true>(b, n_blocks_n, mi, s);
+    else launch_dma8<EPI, false>(b, n_blocks_n, mi, s);
 }
 
 bool k_gemm_mfma_supported(int epi, int N, int K, int hd) {
@@ -1231,18 +1301,21 @@ bool k_gemm_mfma_supported(int epi, int N, int K, int hd) {
     return N % 128 == 0;
 }
 
-// Whether the 256 x 256 kernel takes this GEMM (a.Wrows filled in).
+// Whether the large-M kernel takes this GEMM (a.Wrows filled in): where 128 x 128 tiles would be more than one per CU.
+// Up to there the 128 x 128 kernel is as fast on fp16 weights (8B O projection, 352 rows: 47 against 46 us) and faster
+// on bf16 (48 against 62); beyond it, two of its workgroups share a CU and lose (2240 rows: 119 against 74 and 85 us).
+// The rule does not look at the weights' type, so that a set with an fp16 copy and one without give the same bits.
 static bool use_big(int epi, const GemmArgs& a, int splits) {
     if (!a.big_mode || splits != 1) return false;
     const int out_cols = epi == MG_SWIGLU ? 2 * a.N : a.N;   // tile columns
     if (out_cols % 256 != 0 || a.K % 128 != 0) return false;
     if ((uint64_t)a.M * a.lda * 2 >= (1ull << 32) || (uint64_t)a.Wrows * a.Kw * 2 >= (1ull << 32)) return false;
-    const int64_t tiles = (int64_t)((a.M + 255) / 256) * (out_cols / 256);
-    return a.big_mode >= 2 || tiles >= 512;   // one workgroup per CU: at least two rounds of 256
+    const int64_t tiles = (int64_t)((a.M + 127) / 128) * (out_cols / 128);
+    return a.big_mode >= 2 || tiles > 256;
 }
 
 int k_gemm_mfma_lse_parts(int M, int N, int K, int big_mode) {
-    // column groups are as wide as a wave's share of the tile: 64 columns on the 256 x 256 and on the 128 x 128 kernel
+    // column groups are as wide as a wave's share of the tile: 64 columns on the 256-column and on the 128 x 128 kernel
     (void)M; (void)K; (void)big_mode;
     return N / 64;
 }

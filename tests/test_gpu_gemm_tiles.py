@@ -1,0 +1,45 @@
+"""The large-M GEMM's tile heights (96 to 256 rows, chosen from the number of rows): every height gives the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2405_01481_amd import rollout as R
+from paper_2405_01481_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+SHAPE = synth.ModelShape("tiles1024", 2, 1024, 8, 2, 128, 1024, 2048, 10000.0, "bf16", 0.02)
+
+
+# rows in one chunk -> heights / 32 of the QKV, residual, gate/up and LM-head GEMMs by the launcher's rule:
+# 3300: 3 3 4 4, 5500: 5 3 6 6, 7000: 6 4 7 7, 8000: 6 4 8 8, 9500: 8 5 5 5, 11000: 5 6 6 6, 13000: 5 7 7 7, 15000: 6 8 8 8
+@pytest.mark.parametrize("copy", [False, True], ids=["bf16", "fp16copy"])
+def test_tile_heights_give_the_same_bits(copy):
+    """One chunk of many rows (tall tiles) against chunks of at most 1024 rows (96-row tiles throughout, which the
+    oracle tests of the large-M kernel cover): scores equal bit for bit, last partial tile and ragged ends included."""
+    w = synth.make_weights(SHAPE, 1, DEV)
+    B, L = 32, 512
+    res = {}
+    totals = (3300, 5500, 7000, 8000, 9500, 11000, 13000, 15000)
+    rng = np.random.default_rng(5)
+    ids = rng.integers(0, SHAPE.vocab, size=(B, L)).astype(np.int32)
+    d = torch.tensor(ids, device=DEV)
+    for chunk in (16384, 1024):
+        cfg = R.make_cfg(SHAPE, B, L, max_chunk_tokens=chunk)
+        shadow = torch.empty(R.rollout_weight_shadow_bytes(cfg), dtype=torch.uint8, device=DEV) if copy else None
+        W = R.Weights(w, shadow=shadow)
+        ro = R.Rollout(cfg, W, DEV)
+        ro.rollout_set_impl(2)
+        for n in totals:
+            r = np.random.default_rng(n)
+            lens = np.full(B, n // B, np.int32) + r.integers(-20, 21, size=B).astype(np.int32)
+            plens = np.maximum(1, lens // 2).astype(np.int32)
+            lp = torch.full((B, L), 9.0, dtype=torch.float32, device=DEV)
+            ro.score_logprobs_kl(W, None, d, lens, plens, 0.0, lp)
+            ro.rollout_check()
+            res[chunk, n] = lp.cpu().numpy()
+        ro.close()
+    for n in totals:
+        assert np.isfinite(res[1024, n]).all()
+        assert np.array_equal(res[16384, n], res[1024, n]), n
