@@ -1411,15 +1411,22 @@ static void launch_ring(const GemmArgs& a, int n_blocks_n, int splits, hipStream
 
 
 // fp16 copy of a bf16 weight tensor, by the conversion the kernels themselves apply (so that a GEMM on the copy
-// gives the same bits); n multiple of 8
-__global__ void bf16_to_f16_kernel(const u32x4_t* src, half8* dst, int64_t n8) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n8) dst[i] = bf16x8_to_half8(src[i]);
+// gives the same bits); n multiple of 8.  Bound by memory: four 16-byte loads of a thread are in flight before its
+// first store.
+__global__ __launch_bounds__(256) void bf16_to_f16_kernel(const u32x4_t* src, half8* dst, int64_t n8) {
+    const int64_t i0 = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    u32x4_t v[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (i0 + t * 256 < n8) v[t] = __builtin_nontemporal_load(src + i0 + t * 256);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (i0 + t * 256 < n8) dst[i0 + t * 256] = bf16x8_to_half8(v[t]);
 }
 void k_bf16_to_f16(const void* src, void* dst, int64_t n, hipStream_t s) {
     const int64_t n8 = n / 8;
     if (n8 <= 0) return;
-    bf16_to_f16_kernel<<<(unsigned)((n8 + 255) / 256), 256, 0, s>>>((const u32x4_t*)src, (half8*)dst, n8);
+    bf16_to_f16_kernel<<<(unsigned)((n8 + 1023) / 1024), 256, 0, s>>>((const u32x4_t*)src, (half8*)dst, n8);
 }
 
 static int g_decode_tile_above = -1;   // rows above which k_gemm_decode takes the 128 x 128 tile kernel; < 0: never

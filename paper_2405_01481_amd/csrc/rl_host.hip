@@ -31,7 +31,7 @@ static int fail(int code, const char* fmt, ...) {
 
 // ---------------------------------------------------------------- workspace layout
 struct Layout {
-    size_t x, h, h_keep, qkv, q, kbuf, vbuf, attn, ffn, logits, rope, block_table;
+    size_t x, h, h_keep, qkv, q, kbuf, vbuf, attn, ffn, ffn_bytes, logits, rope, block_table;
     size_t last_tok, seq_len, gen_count, finished, step_count;
     size_t tok_ids, tok_pos, tok_slot, tok_tgt;
     size_t seq_first, row_start, row_len, row_slot, d_seq_len, d_prompt_len, errflag;
@@ -85,6 +85,7 @@ static Layout make_layout(const rl_model_cfg& c) {
     L.vbuf = take((size_t)rows * kd * e * pw);
     L.attn = take((size_t)rows * qd * e * pw);
     L.ffn = take((size_t)rows * c.d_ffn * e * pw);
+    L.ffn_bytes = (size_t)rows * c.d_ffn * e * pw;
     L.logits = take((size_t)L.logit_rows * c.vocab * 4);
     L.rope = take((size_t)c.max_seq * (c.head_dim / 2) * sizeof(float2));
     L.block_table = take((size_t)c.max_batch * L.mpps * 4);
@@ -410,7 +411,16 @@ static bool run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged,
     return false;
 }
 
-static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s) {
+// Idle workspace a large-M GEMM may put an fp16 copy of its bf16 weights in for the time of the launch.
+struct Scratch { char* p = nullptr; size_t bytes = 0; };
+
+// Rows from which a GEMM on bf16 weights without an fp16 copy is worth one, made just before it in idle workspace: the
+// copy moves 4 bytes per weight, the kernel then runs without conversions beside its MFMAs, which saves a tenth of its
+// time and therefore grows with the rows.  Same bits.  Measured on whole passes: 70B width, 12544 rows 245.0 -> 233.4 ms;
+// 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.
+static const int kConvertRows = 4096;
+
+static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s, Scratch idle = {}) {
     ProfScope ps(c, cls, s);
     GemmArgs a = a0;
     a.big_mode = c->big_mode;
@@ -425,8 +435,15 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
         if (const void* h = copy_of((const void*)a.W)) { a.W = (const bf16_t*)h; a.w_f16 = 1; }
         k_gemm_decode(epi, a, splits, s);
     } else {
-        if (k_gemm_mfma_reads_f16_copy(epi, a, splits))
-            if (const void* h = copy_of((const void*)a.W)) { a.W = (const bf16_t*)h; a.w_f16 = 1; }
+        if (k_gemm_mfma_reads_f16_copy(epi, a, splits)) {
+            const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * (a.Kw > 0 ? a.Kw : a.K);
+            if (const void* h = copy_of((const void*)a.W)) {
+                a.W = (const bf16_t*)h; a.w_f16 = 1;
+            } else if (a.M >= kConvertRows && idle.bytes >= 2 * elems) {
+                k_bf16_to_f16(a.W, idle.p, (int64_t)elems, s);
+                a.W = (const bf16_t*)idle.p; a.w_f16 = 1;
+            }
+        }
         k_gemm_mfma(epi, a, splits, s);
     }
 }
@@ -472,6 +489,11 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
         const int sp = l < c->precise, sp_next = l + 1 < c->precise && l + 1 < m.n_layers;
         GemmArgs g;
         g.M = n;
+        // the FFN activation's buffer is as wide as a pair layer needs it: in a plain layer its rows end half way (all
+        // widths are multiples of 64, so the copy's start is 16-byte aligned)
+        Scratch idle;
+        if (!paged && !sp && L.ffn_bytes > (size_t)n * m.d_ffn * 2)
+            idle = {c->at<char>(L.ffn) + (size_t)n * m.d_ffn * 2, L.ffn_bytes - (size_t)n * m.d_ffn * 2};
         if (paged) {
             // weight-streaming GEMMs, split over K; consumers reduce the partial sums
             g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.wqkv[l]; g.N = L.nqkv;
@@ -510,21 +532,21 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             g.pool = write_pages ? (f16_t*)c->pool : nullptr; g.block_table = bt; g.mpps = L.mpps; g.layer = l;
             g.Hq = m.n_q_heads; g.Hkv = m.n_kv_heads; g.hd = m.head_dim; g.geo = c->geo; g.vt_cap = L.vt_cap;
             g.split_out = sp; g.layer_lo = m.n_layers + l;
-            mfma(c, gcls, MG_QKV, g, 1, s);
+            mfma(c, gcls, MG_QKV, g, 1, s, idle);
             attention(c, l, n, false, max_ctx, nblocks, s);
             g = GemmArgs();
             g.M = n; g.A = att; pair_in(g, qd, sp); g.W = (const bf16_t*)W.wo[l]; g.N = m.d_model;
             g.outF = x; g.ldc = m.d_model;
-            mfma(c, gcls, MG_RESID, g, 1, s);
+            mfma(c, gcls, MG_RESID, g, 1, s, idle);
             k_rmsnorm(1, x, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
             g = GemmArgs();
             g.M = n; g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.w_gate_up[l]; g.N = m.d_ffn;
             g.up_offset = m.d_ffn; g.outH = ffn; g.ldc = sp ? 2 * m.d_ffn : m.d_ffn; g.split_out = sp;
-            mfma(c, gcls, MG_SWIGLU, g, 1, s);
+            mfma(c, gcls, MG_SWIGLU, g, 1, s, idle);
             g = GemmArgs();
             g.M = n; g.A = ffn; pair_in(g, m.d_ffn, sp); g.W = (const bf16_t*)W.w_down[l]; g.N = m.d_model;
             g.outF = x; g.ldc = m.d_model;
-            mfma(c, gcls, MG_RESID, g, 1, s);
+            mfma(c, gcls, MG_RESID, g, 1, s, idle);
         }
     }
     return paged;
@@ -1336,7 +1358,8 @@ static void score_head(rl_ctx* c, const WeightsHost& W, float* x, int n, float* 
         g.M = n; g.A = c->at<f16_t>(L.h); g.lda = m.d_model; g.W = (const bf16_t*)W.lm_head; g.N = m.vocab;
         g.K = m.d_model; g.tgt = c->at<int>(L.tok_tgt); g.lse_part = c->at<float2>(L.lse_part);
         g.z_tgt = c->at<float>(L.z_tgt);
-        mfma(c, RL_K_LMHEAD_SCORE, MG_LSE, g, 1, s);
+        // behind the last layer everything from the qkv to the FFN buffer is idle (they lie one behind the other)
+        mfma(c, RL_K_LMHEAD_SCORE, MG_LSE, g, 1, s, {c->at<char>(L.qkv), L.ffn + L.ffn_bytes - L.qkv});
         k_lse_reduce(c->at<float2>(L.lse_part), k_gemm_mfma_lse_parts(n, m.vocab, m.d_model, c->big_mode),
                      c->at<float>(L.z_tgt), n, c->at<int>(L.tok_tgt), c->at<int>(L.tok_slot), c->at<int>(L.tok_pos),
                      logp_out, Lmax, s);

@@ -17,7 +17,8 @@ SHAPE = synth.ModelShape("tiles1024", 2, 1024, 8, 2, 128, 1024, 2048, 10000.0, "
 @pytest.mark.parametrize("copy", [False, True], ids=["bf16", "fp16copy"])
 def test_tile_heights_give_the_same_bits(copy):
     """One chunk of many rows (tall tiles) against chunks of at most 1024 rows (96-row tiles throughout, which the
-    oracle tests of the large-M kernel cover): scores equal bit for bit, last partial tile and ragged ends included."""
+    oracle tests of the large-M kernel cover): scores equal bit for bit, last partial tile and ragged ends included.
+    Without copies, 4096 rows and more also take the fp16 copy made in idle workspace (plain layer and LM head)."""
     w = synth.make_weights(SHAPE, 1, DEV)
     B, L = 32, 512
     res = {}
