@@ -23,6 +23,7 @@ struct GemmArgs {
     int Wrows = 0;              // filled by the launcher
     int n_blocks_n = 0;         // filled by the launcher
     int k_per_split = 0;        // filled by the launcher
+    int rotate_k = 0;           // filled by the launcher (k_gemm_stream)
     int up_offset = 0;          // MG_SWIGLU: row of W where the up projection starts
     float* outF = nullptr;      // MG_STORE_F32 (+ split * split_stride) / MG_RESID
     f16_t* outH = nullptr;      // MG_STORE_F16 / MG_SWIGLU
@@ -76,6 +77,12 @@ int k_gemm_mfma_lse_parts(int M, int N, int K, int big_mode);
 bool k_gemm_decode_supported(int epi, int N, int K);   // K and tile columns multiples of 128
 int k_gemm_decode_splits_used(int K, int splits);
 void k_gemm_decode(int epi, GemmArgs a, int splits, hipStream_t s);
+// Decode GEMM of at most 64 rows on tiles of 16 .. 128 columns; the same epilogues and operands as k_gemm_decode, K and Kw
+// multiples of 128, W below 4 GiB.  k_gemm_stream_splits: the number of K splits (partial sums) that suits an MG_STORE_F32
+// GEMM; it depends on the shape alone.
+bool k_gemm_stream_supported(int epi, int N, int K, int Kw);
+int k_gemm_stream_splits(int N, int K);
+void k_gemm_stream(int epi, GemmArgs a, int splits, hipStream_t s);
 // Measurement switch: k_gemm_decode takes the 128 x 128 tile kernel above this many rows (default 64; < 0: never).
 void k_gemm_decode_tile_above(int rows);
 

@@ -10,39 +10,17 @@
 //     LDS loads -- the large-M GEMMs of prefill and scoring;
 //   * gemm_dma_kernel:  128 x 128 tiles staged the same way, two GEMMs on one tile -- the exact
 //     full-vocabulary KL, which needs the policy's and the reference's logits of a tile together;
-//   * gemm_ring_kernel: the weight-streaming GEMMs of a decode step (M <= 128 rows), split over K so
-//     that all 256 CUs stream a slice of W; partial sums go to a [split][M][N] fp32 buffer and are
+//   * gemm_ring_kernel: the weight-streaming GEMMs of a decode step (contexts of 65 to 128 rows; rl_gemm_stream.hip
+//     has those of fewer), split over K so that all 256 CUs stream a slice of W; partial sums go to a [split][M][N] fp32 buffer and are
 //     reduced, in a fixed order, by the consumer kernel.
 // Epilogues: fp32 store / split-K partial, fp16 store, residual add, SwiGLU, RoPE + q/k/v split for
 // the QKV projection, log-sum-exp + target gather for the scoring LM head, and per-block sampling
 // statistics for the decode LM head.
 #include "rl_common.h"
 #include "rl_gemm.h"
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+#include "rl_gemm_dev.h"
 
 #define BK 64
-
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ half8 bf16x8_to_half8(u32x4_t w) {
-    fp16x2 p0 = __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u));
-    fp16x2 p1 = __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w[1] << 16), __uint_as_float(w[1] & 0xffff0000u));
-    fp16x2 p2 = __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w[2] << 16), __uint_as_float(w[2] & 0xffff0000u));
-    fp16x2 p3 = __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w[3] << 16), __uint_as_float(w[3] & 0xffff0000u));
-    return half8{(f16_t)p0[0], (f16_t)p0[1], (f16_t)p1[0], (f16_t)p1[1], (f16_t)p2[0], (f16_t)p2[1], (f16_t)p3[0], (f16_t)p3[1]};
-}
-
-// k index into W for k index `k` of an A operand carried as fp16 pairs ([hi | lo] along K, K = 2 Kw): both
-// halves multiply the same W columns.  For a plain operand Kw = K and nothing wraps.
-__device__ __forceinline__ int wrap_k(int k, int Kw) { return k >= Kw ? k - Kw : k; }
-
-// fp16 pair of a float: hi = fp16(v), lo = fp16(v - hi); hi + lo carries about 22 significant bits.
-__device__ __forceinline__ void split_f16(float v, f16_t& hi, f16_t& lo) {
-    hi = (f16_t)v;
-    lo = (f16_t)(v - (float)hi);
-}
 
 // Which row of W feeds LDS row r of the B tile of column-block nb.
 //  EPI_SWIGLU: the tile holds BN/2 gate rows and the matching BN/2 up rows, interleaved in
@@ -87,10 +65,6 @@ __device__ __forceinline__ bool tile_of(int id, int MB, int NB, int& mb, int& nb
 // ends with the same bits.  Four steps inside each row of 16 lanes are data-parallel-primitive moves (swap lanes 1
 // apart, 2 apart, mirror 8, mirror 16: each lane always meets a partner that holds the complementary set, and both
 // form the same commutative combination), the step across the two rows is one cross-lane shuffle.
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
 __device__ __forceinline__ float row32_max(float v) {
     v = fmaxf(v, dpp_move<0xB1>(v));    // quad_perm [1,0,3,2]
     v = fmaxf(v, dpp_move<0x4E>(v));    // quad_perm [2,3,0,1]
@@ -141,12 +115,6 @@ __device__ __forceinline__ float row32_sum(float v) {
     v += dpp_move<0x141>(v);
     v += dpp_move<0x140>(v);
     return v + __shfl_xor(v, 16, RL_WAVE);
-}
-
-// SiLU(g) * u.  The quotient is g times a reciprocal (1 ulp) instead of a division (ten instructions): the result is
-// rounded to fp16 right after.  Very negative g: exp overflows to +inf, its reciprocal is 0, the product -0.
-__device__ __forceinline__ float swiglu_act(float g, float u) {
-    return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
 // Epilogue shared by the tile kernels, for one 32-row band of a wave's accumulators: acc[j][r] of the
@@ -670,7 +638,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a) {
 //  * One barrier per k-tile: after it, every wave has read its last fragments of the tile's stage, which
 //    can then be refilled, and the next tile is complete in LDS.
 // Requires (k extent per split) % 128 == 0 and operand byte offsets below 4 GiB (checked by the launcher).
-constexpr int dma_waitcnt(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (lgkm << 8); }
 
 // Exact-KL epilogue for one 32-row band: zp / zr are the policy's and the reference's logits of the same
 // (row, column) entries.  Per row and per wave (TN*32 columns) five numbers leave the kernel:
@@ -1263,13 +1230,7 @@ static void launch_dma8(const GemmArgs& a, int n_blocks_n, int mi, hipStream_t s
 // within 0.3 % of the best of the six on average (6 % at worst); against 256 rows throughout: O projection of the 8B
 // shape at 4928 rows 185 -> 150 us, 1B gate/up at 2240 rows 140 -> 124 us, 70B down projection at 12544 rows 5599 ->
 // 5361 us.  Every height gives the same bits: a row's sums run over k in the same order.
-#ifdef FORCE_MI
-static int g_force_mi = 8;
-#endif
 static int big_row_blocks(int epi, const GemmArgs& a, int n_blocks_n) {
-#ifdef FORCE_MI
-    return g_force_mi;
-#endif
     static const float loop[9] = {0, 0, 0, 0.575f, 0.62f, 0.76f, 0.855f, 0.95f, 1.0f};
     int best = 8;
     float best_cost = 0.f;

@@ -1,0 +1,278 @@
+// Weight-streaming GEMMs of a decode step of at most 64 rows:  C[M,N] = A[M,K] (fp16) * W[N,K]^T (bf16 or fp16 copy).
+//
+// Bound by reading W once.  What a plain read of these matrices reaches here, launch included, sets the floor: 12.6 MB
+// in 3.8 us, 33.5 MB in 6.5, 117 MB in 20, 235 MB in 38 (3.3, 5.2, 5.8, 6.2 TB/s).  Three things decide how close a
+// GEMM comes, all measured:
+//   * how rows are read.  64-byte pieces of 16 rows (operands straight into MFMA layout) reach 60 - 80 % of the plain
+//     read on the short matrices, 256-byte pieces 95 %.  So operands go global -> LDS in k-tiles of 128 (a 1 KB
+//     request = 4 rows x 256 B), 16-byte chunks XOR-swizzled with the row on the source side, so that the fragment
+//     reads (16 rows x 64 B, one 16-byte read per lane) meet no bank conflict.
+//   * where the workgroups stand in k.  Rows whose length is a power of two put the same k of all rows on the same
+//     memory channels, and workgroups start together: workgroup b therefore starts at k-tile b (mod its range) and
+//     wraps.  235 MB gate/up 47.5 -> 39.3 us, 1B gate/up 16.3 -> 13.7, 70B O projection 34.7 -> 28.4; where rows are
+//     not a power of two long it only costs (70B down projection 88 -> 98 us) and is not done.
+//   * the shape of the work.  One workgroup per CU with no remainder: the tile is CT x 16 columns, CT = 1 .. 8, and K is
+//     split over Z workgroups whose partial sums the consumer reduces (stream_plan).
+// Eight waves: four along the k-tile (32 k each), two along the columns, so that every W fragment is read, and on bf16
+// weights converted, by one wave only; each wave holds all MT x 16 rows.  The four partial accumulators meet in LDS after
+// the loop, in wave order.  Three stages, one barrier per k-tile; the loads are issued from inline assembly (the compiler
+// would wait for them at every barrier) and counted by hand: two tiles are in flight while one is consumed.
+// Against the 128-column ring kernel (which stays for batches above 64 rows: it reads A half as often), per launch,
+// ring -> here: 8B at 3 rows QKV 12.8 -> 11, O 9.8 -> 8, gate/up 52 -> 39, down 23 -> 21.5, LM head 222 -> 177 us; 1B at
+// 32 rows 8.2 -> 5.3, 7.0 -> 4.1, 21.7 -> 13.7, 11.3 -> 8.9; 70B (bf16) at 64 rows 38 -> 34, 38 -> 28.5, 171 -> 170, 84 -> 88.
+#include "rl_common.h"
+#include "rl_gemm.h"
+#include "rl_gemm_dev.h"
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+static constexpr int GS_KT = 128, GS_RB = 256, GS_NS = 3, GS_WK = 4;
+static constexpr int gs_lds(int MT, int CT) { return GS_NS * (CT + MT) * 16 * GS_RB; }   // also holds the MT x CT x 4 KB of the exchange
+
+// Row of W behind row rr of the 16-row tile t.  MG_SWIGLU: 8 gate rows and the 8 up rows of the same columns.
+template <int EPI>
+__device__ __forceinline__ int stream_w_row(int t, int rr, const GemmArgs& a) {
+    if (EPI == MG_SWIGLU) return (rr < 8 ? 0 : a.up_offset - 8) + t * 8 + rr;
+    return t * 16 + rr;
+}
+
+template <int EPI, int MT, int CT, bool WF16>
+__global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm_stream_kernel(GemmArgs a) {
+    constexpr int WN = 8 / GS_WK, CW = (CT + WN - 1) / WN;
+    constexpr int STAGE = (CT + MT) * 16 * GS_RB;
+    constexpr int NBLK = STAGE / 1024, NI = (NBLK + 7) / 8;   // 1 KB requests per k-tile; per wave (waves 4 .. 7 one fewer if odd)
+    constexpr bool ODD = NBLK % 8 != 0;
+    static_assert(NBLK % 4 == 0 && MT * CT * GS_WK * 1024 <= gs_lds(MT, CT), "stage and exchange");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, q = lane >> 4, wk = wave % GS_WK, wn = wave / GS_WK;
+    const int t0 = blockIdx.x * CT;                            // first 16-row tile of W
+    const int kbeg = blockIdx.z * a.k_per_split, kend = min(a.K, kbeg + a.k_per_split);
+    const int nk = (kend - kbeg) / GS_KT, kt0 = kbeg / GS_KT, nkw = a.Kw / GS_KT;
+    const int rot = a.rotate_k ? (int)(blockIdx.x % (unsigned)nk) : 0;
+    const bool all_blocks = !ODD || wave < 4;
+    // Staging: request t of a wave fills the 1 KB block t*8 + wave of a stage = 4 rows (W tiles first, then A); lane ->
+    // row + lane/16, physical chunk lane%16, which holds the row's logical chunk (lane%16) ^ (row%16).
+    unsigned g_off[NI];
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+        const int row = (t * 8 + wave) * 4 + (lane >> 4);
+        const unsigned ch = (unsigned)((lane & 15) ^ (row & 15)) * 16u;
+        const bool isW = t * 8 + wave < CT * 4;
+        const int src = isW ? min(stream_w_row<EPI>(t0 + (row >> 4), row & 15, a), a.Wrows - 1) : min(row - CT * 16, a.M - 1);
+        g_off[t] = (unsigned)src * (unsigned)(isW ? a.Kw : a.lda) * 2u + ch;   // rows past the end: clamped, never stored
+    }
+    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+    const char* const Ag = reinterpret_cast<const char*>(a.A);
+    const char* const Wg = reinterpret_cast<const char*>(a.W);
+#define GS_ISSUE(stage, kt)                                                                                     \
+    {                                                                                                           \
+        const int k_ = kt0 + ((kt) + rot >= nk ? (kt) + rot - nk : (kt) + rot);                                 \
+        const char* w_ = Wg + (size_t)wrap_k(k_, nkw) * GS_RB;                                                  \
+        const char* a_ = Ag + (size_t)k_ * GS_RB;                                                               \
+        _Pragma("unroll") for (int t = 0; t < NI; ++t) {                                                        \
+            if (t < NI - 1 || all_blocks) {                                                                     \
+                const char* g_ = t * 8 + wave < CT * 4 ? w_ : a_;                                               \
+                const unsigned sa_ = lds_base + (stage) * STAGE + t * 8192;                                     \
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                    \
+                             :: "s"(sa_), "v"(g_off[t]), "s"(g_) : "memory");                                   \
+            }                                                                                                   \
+        }                                                                                                       \
+    }
+    floatx4 acc[MT][CW];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < CW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int frag = r * GS_RB + (((wk * 4 + q) ^ r) * 16);    // this lane's 16 bytes of a 16-row tile
+#pragma unroll
+    for (int s = 0; s < GS_NS - 1; ++s) GS_ISSUE(s, min(s, nk - 1))
+    int st = 0, fill = GS_NS - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+        // tile kt landed (the GS_NS - 2 younger ones may be in flight), own fragment reads of tile kt - 1 done
+        if (all_blocks) __builtin_amdgcn_s_waitcnt(dma_waitcnt(NI * (GS_NS - 2), 0));
+        else __builtin_amdgcn_s_waitcnt(dma_waitcnt((NI - 1) * (GS_NS - 2), 0));
+        __syncthreads();
+        // every wave is done with tile kt - 1: its stage takes tile kt + 2 (the last trips re-request the final tile, so
+        // that the counts hold)
+        GS_ISSUE(fill, min(kt + GS_NS - 1, nk - 1))
+        fill = fill + 1 == GS_NS ? 0 : fill + 1;
+        const char* sp = smem + st * STAGE + frag;
+        st = st + 1 == GS_NS ? 0 : st + 1;
+        u32x4_t w[CW];
+        half8 af[MT];
+#pragma unroll
+        for (int j = 0; j < CW; ++j)
+            if (CT % WN == 0 || wn * CW + j < CT) w[j] = *reinterpret_cast<const u32x4_t*>(sp + (wn * CW + j) * 16 * GS_RB);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) af[i] = *reinterpret_cast<const half8*>(sp + (CT + i) * 16 * GS_RB);
+#pragma unroll
+        for (int j = 0; j < CW; ++j) {
+            if (CT % WN == 0 || wn * CW + j < CT) {
+                const half8 wf = WF16 ? __builtin_bit_cast(half8, w[j]) : bf16x8_to_half8(w[j]);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[i], wf, acc[i][j], 0, 0, 0);
+            }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));             // nothing may land in LDS from here on
+    __syncthreads();
+#undef GS_ISSUE
+    // the four waves along k meet in LDS; tile (i, j) of lane (r, q): column r, rows 4 q .. 4 q + 3
+    floatx4* const red = reinterpret_cast<floatx4*>(smem);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < CW; ++j)
+            if (CT % WN == 0 || wn * CW + j < CT) red[((i * CT + wn * CW + j) * GS_WK + wk) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    auto sum = [&](int i, int j) {
+        const floatx4* p = red + (i * CT + j) * GS_WK * 64 + lane;
+        floatx4 v = p[0];
+#pragma unroll
+        for (int w = 1; w < GS_WK; ++w) {
+            const floatx4 o = p[w * 64];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[x] += o[x];
+        }
+        return v;
+    };
+    if constexpr (EPI == MG_SAMPLE) {
+        // statistics of 32-column blocks = two tiles; ties of the maximum go to the lowest column
+        const int nblk = a.N / 32;
+        for (int t = wave; t < MT * CT / 2; t += 8) {
+            const int i = t / (CT / 2), jp = t % (CT / 2), blk = blockIdx.x * (CT / 2) + jp;
+            const floatx4 v0 = sum(i, 2 * jp), v1 = sum(i, 2 * jp + 1);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                float mx = fmaxf(v0[x], v1[x]);
+                mx = fmaxf(mx, dpp_move<0xB1>(mx));    // quad_perm [1,0,3,2]
+                mx = fmaxf(mx, dpp_move<0x4E>(mx));    // quad_perm [2,3,0,1]
+                mx = fmaxf(mx, dpp_move<0x141>(mx));   // row_half_mirror
+                mx = fmaxf(mx, dpp_move<0x140>(mx));   // row_mirror
+                const unsigned h0 = (unsigned)(__ballot(v0[x] == mx) >> (16 * q)) & 0xffffu;
+                const unsigned h1 = (unsigned)(__ballot(v1[x] == mx) >> (16 * q)) & 0xffffu;
+                const int mi = __ffs(h0 | h1 << 16) - 1;
+                float e1 = __expf(v0[x] - mx) + __expf(v1[x] - mx);
+                float eT = __expf((v0[x] - mx) * a.inv_temp) + __expf((v1[x] - mx) * a.inv_temp);
+                e1 += dpp_move<0xB1>(e1); eT += dpp_move<0xB1>(eT);
+                e1 += dpp_move<0x4E>(e1); eT += dpp_move<0x4E>(eT);
+                e1 += dpp_move<0x141>(e1); eT += dpp_move<0x141>(eT);
+                e1 += dpp_move<0x140>(e1); eT += dpp_move<0x140>(eT);
+                const int m = i * 16 + q * 4 + x;
+                if (r == 0 && m < a.M && blk < nblk) a.samp_part[(int64_t)m * nblk + blk] = make_float4(mx, eT, e1, __int_as_float(mi));
+            }
+        }
+    } else {
+        for (int t = wave; t < MT * CT; t += 8) {
+            const int i = t / CT, j = t % CT;
+            const floatx4 v = sum(i, j);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int m = i * 16 + q * 4 + x;
+                if constexpr (EPI == MG_SWIGLU) {
+                    const float up = __shfl_xor(v[x], 8, RL_WAVE);      // lanes r < 8 hold the gate, r + 8 the up column
+                    const int n = (t0 + j) * 8 + r;
+                    if (r < 8 && m < a.M && n < a.N) {
+                        const float act = swiglu_act(v[x], up);
+                        f16_t hi, lo;
+                        split_f16(act, hi, lo);
+                        f16_t* o = a.outH + (int64_t)m * a.ldc + n;
+                        o[0] = hi;
+                        if (a.split_out) o[a.N] = lo;
+                    }
+                } else {
+                    const int n = (t0 + j) * 16 + r;
+                    if (m < a.M && n < a.N) a.outF[(int64_t)blockIdx.z * a.split_stride + (int64_t)m * a.ldc + n] = v[x];
+                }
+            }
+        }
+    }
+}
+
+// Tiles per workgroup and splits over K.  A workgroup's time goes with its k-tiles x (CT + 1) -- W's tiles and, from L2,
+// the rows of A -- times the rounds of 256 workgroups; each split costs its consumer a pass over the partial sums.
+// Of the measured candidates the rule takes the fastest or one within 3 % (8B QKV 3 x 2 splits, O and down 4 x 4, gate/up
+// 7, 1B O 2 x 4, down 4 x 8, gate/up 4, 70B QKV 5 x 2, O and down 8 x 4, gate/up 7, LM heads 8).  The rule must not look
+// at the rows: a row's bits would depend on its batch-mates.  z: in, the number of splits, 0 for the best; out, theirs.
+static void stream_plan(int epi, int N, int K, int& ct, int& z) {
+    const int tiles = (epi == MG_SWIGLU ? 2 * N : N) / 16, units = K / GS_KT;
+    const int zmin = z > 0 ? z : 1, zmax = z > 0 ? z : (units < 8 ? units : 8);
+    float best = 0.f;
+    ct = 0;
+    for (int zz = zmin; zz <= zmax; ++zz) {
+        const int per = (units + zz - 1) / zz;
+        if ((units + per - 1) / per != zz) continue;
+        for (int c = 1; c <= 8; ++c) {
+            if (epi == MG_SAMPLE && c % 2 != 0) continue;
+            const int wgs = (tiles + c - 1) / c * zz;
+            const float cost = (float)((wgs + 255) / 256) * (float)per * (float)(c + 1) + 1.8f * (float)zz * (float)N / 2048.f;
+            if (ct == 0 || cost < best) { best = cost; ct = c; z = zz; }
+        }
+    }
+}
+
+bool k_gemm_stream_supported(int epi, int N, int K, int Kw) {
+    if (epi != MG_STORE_F32 && epi != MG_SWIGLU && epi != MG_SAMPLE) return false;
+    const int rows = epi == MG_SWIGLU ? 2 * N : N;
+    return K > 0 && K % GS_KT == 0 && Kw % GS_KT == 0 && rows % 32 == 0 && (uint64_t)rows * Kw * 2 < (1ull << 32);
+}
+
+int k_gemm_stream_splits(int N, int K) {
+    int ct, z = 0;
+    stream_plan(MG_STORE_F32, N, K, ct, z);
+    return z;
+}
+
+template <int EPI, int MT, int CT, bool WF16>
+static void launch_stream_t(const GemmArgs& a, int tiles, int z, hipStream_t s) {
+    constexpr int lds = gs_lds(MT, CT);
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void*)gemm_stream_kernel<EPI, MT, CT, WF16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_set = true;
+    }
+    gemm_stream_kernel<EPI, MT, CT, WF16><<<dim3((tiles + CT - 1) / CT, 1, z), 512, lds, s>>>(a);
+}
+template <int EPI, int CT>
+static void launch_stream_ct(const GemmArgs& a, int tiles, int z, hipStream_t s) {
+    if constexpr (EPI != MG_SAMPLE || CT % 2 == 0) {
+        if (a.w_f16) {
+            if (a.M <= 16) launch_stream_t<EPI, 1, CT, true>(a, tiles, z, s);
+            else if (a.M <= 32) launch_stream_t<EPI, 2, CT, true>(a, tiles, z, s);
+            else launch_stream_t<EPI, 4, CT, true>(a, tiles, z, s);
+        } else {
+            if (a.M <= 16) launch_stream_t<EPI, 1, CT, false>(a, tiles, z, s);
+            else if (a.M <= 32) launch_stream_t<EPI, 2, CT, false>(a, tiles, z, s);
+            else launch_stream_t<EPI, 4, CT, false>(a, tiles, z, s);
+        }
+    }
+}
+template <int EPI>
+static void launch_stream(const GemmArgs& a, int tiles, int ct, int z, hipStream_t s) {
+    switch (ct) {
+        case 1: launch_stream_ct<EPI, 1>(a, tiles, z, s); break;
+        case 2: launch_stream_ct<EPI, 2>(a, tiles, z, s); break;
+        case 3: launch_stream_ct<EPI, 3>(a, tiles, z, s); break;
+        case 4: launch_stream_ct<EPI, 4>(a, tiles, z, s); break;
+        case 5: launch_stream_ct<EPI, 5>(a, tiles, z, s); break;
+        case 6: launch_stream_ct<EPI, 6>(a, tiles, z, s); break;
+        case 7: launch_stream_ct<EPI, 7>(a, tiles, z, s); break;
+        default: launch_stream_ct<EPI, 8>(a, tiles, z, s); break;
+    }
+}
+
+void k_gemm_stream(int epi, GemmArgs a, int splits, hipStream_t s) {
+    if (a.Kw <= 0) a.Kw = a.K;
+    if (a.M <= 0 || a.M > 64 || !k_gemm_stream_supported(epi, a.N, a.K, a.Kw)) return;   // callers check first
+    int ct, z = epi == MG_STORE_F32 && splits > 1 ? splits : 1;
+    stream_plan(epi, a.N, a.K, ct, z);
+    if (ct == 0) return;                                       // a split count that is not one of this K's
+    a.k_per_split = (a.K / GS_KT + z - 1) / z * GS_KT;
+    a.Wrows = epi == MG_SWIGLU ? a.up_offset + a.N : a.N;
+    a.rotate_k = (a.Kw & (a.Kw - 1)) == 0;
+    const int tiles = (epi == MG_SWIGLU ? 2 * a.N : a.N) / 16;
+    if (epi == MG_STORE_F32) launch_stream<MG_STORE_F32>(a, tiles, ct, z, s);
+    else if (epi == MG_SWIGLU) launch_stream<MG_SWIGLU>(a, tiles, ct, z, s);
+    else launch_stream<MG_SAMPLE>(a, tiles, ct, z, s);
+}

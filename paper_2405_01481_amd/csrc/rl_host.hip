@@ -420,6 +420,12 @@ struct Scratch { char* p = nullptr; size_t bytes = 0; };
 // 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.
 static const int kConvertRows = 4096;
 
+// Decode GEMMs of contexts of at most 64 rows run on the streaming kernel, others on the ring kernel.  The rule looks at
+// the context's limit, not at the rows of a call: a row's bits do not depend on its batch-mates.
+static bool streams(const rl_ctx* c, int epi, int N, int K, int Kw) {
+    return c->cfg.max_batch <= 64 && k_gemm_stream_supported(epi, N, K, Kw);
+}
+
 static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s, Scratch idle = {}) {
     ProfScope ps(c, cls, s);
     GemmArgs a = a0;
@@ -433,7 +439,8 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
     if (cls == RL_K_GEMM_DECODE && a.M <= 128 && (epi == MG_STORE_F32 || epi == MG_SWIGLU || epi == MG_SAMPLE) &&
         k_gemm_decode_supported(epi, a.N, a.K)) {
         if (const void* h = copy_of((const void*)a.W)) { a.W = (const bf16_t*)h; a.w_f16 = 1; }
-        k_gemm_decode(epi, a, splits, s);
+        if (streams(c, epi, a.N, a.K, a.Kw > 0 ? a.Kw : a.K)) k_gemm_stream(epi, a, splits, s);
+        else k_gemm_decode(epi, a, splits, s);
     } else {
         if (k_gemm_mfma_reads_f16_copy(epi, a, splits)) {
             const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * (a.Kw > 0 ? a.Kw : a.K);
@@ -451,7 +458,8 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
 // Split count for a decode GEMM of n rows with N output columns: one 8-wave workgroup per CU and 128-column
 // tiles, so aim for as many workgroups as fit in one round of 256 CUs.  Returns the number of partial
 // buffers the kernel that mfma() picks for this shape will actually write.
-static int decode_splits(int n, int N, int K) {
+static int decode_splits(const rl_ctx* c, int n, int N, int K, int Kw) {
+    if (k_gemm_decode_supported(MG_STORE_F32, N, K) && streams(c, MG_STORE_F32, N, K, Kw)) return k_gemm_stream_splits(N, K);
     int want = std::max(1, 256 / std::max(1, N / 128));
     want = std::min(want, kMaxSplitK);
     if (n <= 128 && k_gemm_decode_supported(MG_STORE_F32, N, K)) return k_gemm_decode_splits_used(K, want);
@@ -498,7 +506,7 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             // weight-streaming GEMMs, split over K; consumers reduce the partial sums
             g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.wqkv[l]; g.N = L.nqkv;
             g.outF = part; g.ldc = L.nqkv; g.split_stride = (int64_t)n * L.nqkv;
-            int ks = decode_splits(n, L.nqkv, g.K);
+            int ks = decode_splits(c, n, L.nqkv, g.K, g.Kw);
             mfma(c, gcls, MG_STORE_F32, g, ks, s);
             // plain layers on the tuned kernels: attention is the consumer of the partial sums (a decode row's cache
             // slot is its row index, which is what that kernel assumes)
@@ -511,7 +519,7 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             g = GemmArgs();
             g.M = n; g.A = att; pair_in(g, qd, sp); g.W = (const bf16_t*)W.wo[l]; g.N = m.d_model;
             g.outF = part; g.ldc = m.d_model; g.split_stride = (int64_t)n * m.d_model;
-            ks = decode_splits(n, m.d_model, g.K);
+            ks = decode_splits(c, n, m.d_model, g.K, g.Kw);
             mfma(c, gcls, MG_STORE_F32, g, ks, s);
             k_resid_norm(1, x, part, ks, g.split_stride, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
             g = GemmArgs();
@@ -521,7 +529,7 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             g = GemmArgs();
             g.M = n; g.A = ffn; pair_in(g, m.d_ffn, sp); g.W = (const bf16_t*)W.w_down[l]; g.N = m.d_model;
             g.outF = part; g.ldc = m.d_model; g.split_stride = (int64_t)n * m.d_model;
-            ks = decode_splits(n, m.d_model, g.K);
+            ks = decode_splits(c, n, m.d_model, g.K, g.Kw);
             mfma(c, gcls, MG_STORE_F32, g, ks, s);
             const void* next = (l + 1 < m.n_layers) ? W.attn_norm[l + 1] : W.final_norm;
             k_resid_norm(1, x, part, ks, g.split_stride, next, h, n, m.d_model, m.rms_eps, s, sp_next);

@@ -1,0 +1,46 @@
+"""The decode step's weight-streaming GEMMs (contexts of at most 64 rows): one, two and four 16-row tiles of activations
+with remainders, every number of column tiles a workgroup may take, K split and not, rows of a power of two long (start
+rotated) and not, bf16 weights and an fp16 copy -- against the oracle, and row by row against smaller batches."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import rollout_oracle as O
+from paper_2405_01481_amd import rollout as R
+from paper_2405_01481_amd import synth
+from tests.helpers import verify_rollout
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+# column tiles of the gate/up GEMM and the LM head: 7 and 8; 3 and 4; 5 and 6; 4 (last one short) and 2; widths that
+# are no multiple of 128 (C's FFN: the pair layer's down projection wraps inside a k-tile and stays on the ring kernel)
+SHAPES = [
+    synth.ModelShape("stream_a", 2, 1024, 8, 2, 128, 14336, 32768, 10000.0, "bf16", 0.02),
+    synth.ModelShape("stream_b", 2, 384, 6, 3, 64, 6144, 12288, 10000.0, "bf16", 0.04),
+    synth.ModelShape("stream_c", 2, 256, 32, 8, 128, 10304, 24576, 10000.0, "bf16", 0.04),
+    synth.ModelShape("stream_d", 2, 640, 10, 5, 64, 8320, 8064, 10000.0, "bf16", 0.04),
+]
+
+
+@pytest.mark.parametrize("copy", [False, True], ids=["bf16", "fp16copy"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
+def test_stream_gemm_rows_and_widths(shape, copy):
+    P, G, most = 9, 4, 64
+    w = synth.make_weights(shape, 1, DEV)
+    cfg = R.make_cfg(shape, most, P + G)
+    shadow = torch.empty(R.rollout_weight_shadow_bytes(cfg), dtype=torch.uint8, device=DEV) if copy else None
+    ro = R.Rollout(cfg, R.Weights(w, shadow=shadow), DEV)
+    m = O.Model(shape, synth.weights_for_oracle(w))
+    ids, lens = synth.make_prompts(shape.vocab, most, P, 3, 3)
+    res = {}
+    for n in (1, 15, 16, 17, 33, 64):
+        out = torch.full((n, G), -1, dtype=torch.int32, device=DEV)
+        lp = torch.full((n, G), 9.0, dtype=torch.float32, device=DEV)
+        ro.rollout_generate(R.sample_cfg(4, 0.8), torch.tensor(ids[:n], device=DEV), lens[:n], G, out, None, lp)
+        ro.rollout_check()
+        res[n] = (out.cpu().numpy(), lp.cpu().numpy())
+    for n in (1, 15, 16, 17, 33):                      # a row's bits do not depend on its batch-mates
+        assert np.array_equal(res[n][0], res[64][0][:n]) and np.array_equal(res[n][1], res[64][1][:n]), n
+    verify_rollout(m, [ids[b, :lens[b]] for b in range(most)], *res[64], 0.8, 4, 0, 1e-3, 2e-2, rows=[0, 16, 63])
+    ro.close()
