@@ -28,7 +28,9 @@ struct DecodeAttnArgs {
 // Whether k_attn_decode can take the QKV partial sums itself (qkv_part) for these head counts; it launches nothing
 // if asked to for others, or for a pair layer.
 bool k_attn_decode_consumes_qkv(int Hq, int Hkv, int hd);
-void k_attn_decode(const DecodeAttnArgs& a, int B, int nsplit, hipStream_t s);
+// waves per workgroup (4 or 8) and splits of a sequence's keys that suit a context's limits
+void k_attn_decode_plan(int max_batch, int Hkv, int mpps, int max_splits, int* waves, int* nsplit);
+void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s);
 
 // Causal attention over a packed token list.  Sequences start at rows that are multiples of 32
 // and every row up to the next multiple of 32 past a sequence's end holds finite values.

@@ -10,6 +10,8 @@
 // lane for P^T.  K is read token-major, V dim-major (the paged pool stores V pages
 // as [kv head][dim][token] for this reason), both straight from global memory in
 // operand layout -- a (page, kv head) tile is one contiguous 4 KB block.
+#include <algorithm>
+
 #include "rl_common.h"
 #include "rl_attn.h"
 
@@ -24,7 +26,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // ------------------------------------------------------------------ decode: one new query per sequence
-// Workgroup = (sequence b, kv head g, split).  Its 4 waves take page pairs round-robin
+// Workgroup = (sequence b, kv head g, split).  Its NW waves take pages round-robin
 // from the split's page range; query heads g*G .. g*G+G-1 are the MFMA columns 0..G-1
 // (columns >= G are zero padding).  Per-wave results are merged through LDS; with more
 // than one split the workgroup writes an unnormalised partial (o, m, l) per head.
@@ -36,36 +38,41 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // way, the workgroup sums the partials of its own G query heads and of its kv head's new key and value (in split
 // order), rotates q and k, keeps them in LDS as fp16, and -- split 0 only, after its loop -- appends k and v to the
 // cache page.
+// A wave's page numbers are fetched once, one per lane (64 iterations' worth; without splits even before the position
+// is known), so that a page's loads wait for no index load; with up to 8 waves per workgroup short contexts need no
+// splits and no merge kernel.  32 rows, 8 kv heads, 200 keys, head_dim 64: 2 splits x 4 waves + merge 12.8 us, 8 waves
+// 7.0 us; 64 rows, 280 keys: 13.5 + 4.8 us, 11.2; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
 // Queries are then read from LDS, and the wave that holds the page of the new token takes that token's key row and
 // value column from LDS instead of from the page, so nothing depends on when the appended values become visible.
-template <int HD, int PT, bool SP, bool FU>
-__global__ __launch_bounds__(256, SP ? 2 : 4) void attn_decode_kernel(DecodeAttnArgs a) {
+template <int HD, int PT, bool SP, bool FU, int NW>
+__global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(DecodeAttnArgs a) {
     static_assert(!(SP && FU), "the pair layers keep the separate consumer kernel");
     static_assert(PT == 16, "page tile is one 16-row MFMA block");
     constexpr int KS = HD / 32;    // k-steps of the 16x16x32 S^T MFMAs
     constexpr int DB = HD / 16;    // 16-dim blocks of O^T
-    __shared__ float sm_m[4][16], sm_l[4][16];
-    __shared__ float sm_o[4][8][HD + 4];
+    constexpr int NT = NW * 64, PS = 512 / NT;   // threads; column pairs of q, k, v per thread (FU)
+    __shared__ float sm_m[NW][16], sm_l[NW][16];
+    __shared__ float sm_o[NW][8][HD + 4];
     __shared__ __attribute__((aligned(16))) f16_t sm_q[FU ? 8 : 1][HD], sm_k[HD], sm_v[HD];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, g4 = lane >> 4;
     const int b = blockIdx.x, g = blockIdx.y, split = blockIdx.z;
     const int G = a.Hq / a.Hkv;
-    // FU: the partial sums of this thread's (at most two) column pairs are requested before anything else -- they
+    // FU: the partial sums of this thread's (at most PS) column pairs are requested before anything else -- they
     // depend on nothing but the row -- so they travel together with the position, the page index and the first page.
     // Pair i = (head hh = i / (hd/2), j = i % (hd/2)) covers columns j and j + hd/2 of head hh; hh < G a query head,
     // hh == G the key, hh == G + 1 the value.
     constexpr int NE = 6;                           // splits requested up front (the rest, if any, later)
     constexpr int HALF = HD / 2;
-    float pe0[FU ? 2 : 1][NE], pe1[FU ? 2 : 1][NE];
-    const float* prow[2] = {nullptr, nullptr};
+    float pe0[FU ? PS : 1][NE], pe1[FU ? PS : 1][NE];
+    const float* prow[PS] = {};
     if (FU) {
         const int width = (a.Hq + 2 * a.Hkv) * HD;
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
+        for (int sl = 0; sl < PS; ++sl) {
             // no branches here (a thread without a second pair re-reads the last pair, a split past the last one
             // re-reads the last split): conditional loads would be waited for one by one
-            const int i = min((int)threadIdx.x + sl * 256, (G + 2) * HALF - 1);
+            const int i = min((int)threadIdx.x + sl * NT, (G + 2) * HALF - 1);
             const int hh = i / HALF, j = i % HALF;
             prow[sl] = a.qkv_part + (int64_t)b * width + (hh < G ? g * G + hh : hh == G ? a.Hq + g : a.Hq + a.Hkv + g) * HD + j;
 #pragma unroll
@@ -76,17 +83,24 @@ __global__ __launch_bounds__(256, SP ? 2 : 4) void attn_decode_kernel(DecodeAttn
             }
         }
     }
+    const int* bt = a.block_table + (int64_t)b * a.mpps;
+    // page numbers of the wave's pages pbeg + wave + NW * (0 .. 63): lane l keeps the l-th.  Without splits pbeg is 0 and the
+    // load goes out together with the position's; entries past the last page are never used.
+    int pages = 0;
+    if (gridDim.z == 1) pages = bt[min(wave + NW * lane, a.mpps - 1)];
     const int ctx = a.tok_pos[b] + 1;
-    float2 cs_new[FU ? 2 : 1];                      // (cos, sin) of the new token's position for this thread's pairs
+    float2 cs_new[FU ? PS : 1];                      // (cos, sin) of the new token's position for this thread's pairs
     if (FU) {
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl)
-            cs_new[sl] = a.rope[(int64_t)max(ctx - 1, 0) * HALF + min((int)threadIdx.x + sl * 256, (G + 2) * HALF - 1) % HALF];
+        for (int sl = 0; sl < PS; ++sl)
+            cs_new[sl] = a.rope[(int64_t)max(ctx - 1, 0) * HALF + min((int)threadIdx.x + sl * NT, (G + 2) * HALF - 1) % HALF];
     }
     const int npages = (ctx + PT - 1) / PT;
     const int chunk = (npages + (int)gridDim.z - 1) / (int)gridDim.z;
     const int pbeg = split * chunk, pend = min(npages, pbeg + chunk);
-    const int* bt = a.block_table + (int64_t)b * a.mpps;
+    if (gridDim.z != 1) pages = bt[min(pbeg + wave + NW * lane, a.mpps - 1)];
+    const int p_new = (ctx - 1) / PT, st_new = (ctx - 1) % PT;   // page and slot of the new token
+    const int64_t page_new = FU && ctx > 0 ? bt[p_new] : 0;
     const f16_t* kbase = a.pool + a.geo.k_off(a.layer, 0, g, 0, 0) + col * HD + g4 * 8;
     const f16_t* vbase = a.pool + a.geo.v_off(a.layer, 0, g, 0, 0) + col * PT + g4 * 4;
     const int64_t page_stride = a.geo.page_elems();
@@ -130,15 +144,14 @@ __global__ __launch_bounds__(256, SP ? 2 : 4) void attn_decode_kernel(DecodeAttn
         }                                                                                                        \
     }
     if (p < pend) {
-        const int64_t pg = bt[p];
+        const int64_t pg = __builtin_amdgcn_readlane(pages, 0);
         AD_FETCH(pg)
     }
-    const int p_new = (ctx - 1) / PT, st_new = (ctx - 1) % PT;   // page and slot of the new token
     if (FU) {
         if (ctx > 0) {   // uniform over the workgroup; a parked row has no keys and no query
 #pragma unroll
-            for (int sl = 0; sl < 2; ++sl) {
-                const int i = threadIdx.x + sl * 256;
+            for (int sl = 0; sl < PS; ++sl) {
+                const int i = threadIdx.x + sl * NT;
                 if (i < (G + 2) * HALF) {
                     const int hh = i / HALF, j = i % HALF;
                     const float2 cs = cs_new[sl];
@@ -174,7 +187,8 @@ __global__ __launch_bounds__(256, SP ? 2 : 4) void attn_decode_kernel(DecodeAttn
             else qf[s] = half8{0, 0, 0, 0, 0, 0, 0, 0};
         }
     }
-    for (; p < pend; p += 4) {
+    int it = 0;                                     // the wave's pages so far
+    for (; p < pend; p += NW) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) { kf[s] = kn[s]; if (SP) kfl[s] = knl[s]; }
 #pragma unroll
@@ -194,8 +208,11 @@ __global__ __launch_bounds__(256, SP ? 2 : 4) void attn_decode_kernel(DecodeAttn
             }
         }
         {
-            const int pn = min(p + 4, pend - 1);          // the last iteration re-reads a valid page, unused
-            const int64_t pg = bt[pn];
+            if (p + NW < pend) {                          // else: the last iteration re-reads its own page, unused
+                ++it;
+                if ((it & 63) == 0) pages = bt[min(p + NW + NW * lane, a.mpps - 1)];
+            }
+            const int64_t pg = __builtin_amdgcn_readlane(pages, it & 63);
             AD_FETCH(pg)
         }
         floatx4 s0 = {0.f, 0.f, 0.f, 0.f};
@@ -244,10 +261,9 @@ __global__ __launch_bounds__(256, SP ? 2 : 4) void attn_decode_kernel(DecodeAttn
     // FU: the new token's key and value go to the cache only now -- stores count towards the same in-order
     // completion counter as loads, so stores issued before the loop would hold back every page load behind them
     if (FU && split == 0 && ctx > 0) {
-        const int64_t page = bt[p_new];
-        for (int i = threadIdx.x; i < HD; i += 256) {
-            a.pool_w[a.geo.k_off(a.layer, page, g, st_new, i)] = sm_k[i];
-            a.pool_w[a.geo.v_off(a.layer, page, g, st_new, i)] = sm_v[i];
+        for (int i = threadIdx.x; i < HD; i += NT) {
+            a.pool_w[a.geo.k_off(a.layer, page_new, g, st_new, i)] = sm_k[i];
+            a.pool_w[a.geo.v_off(a.layer, page_new, g, st_new, i)] = sm_v[i];
         }
     }
     // wave totals: l over the four key groups
@@ -262,13 +278,15 @@ __global__ __launch_bounds__(256, SP ? 2 : 4) void attn_decode_kernel(DecodeAttn
     }
     __syncthreads();
     const int nsplit = gridDim.z;
-    for (int idx = threadIdx.x; idx < G * HD; idx += 256) {
+    for (int idx = threadIdx.x; idx < G * HD; idx += NT) {
         const int hh = idx / HD, d = idx % HD;
-        float mt = fmaxf(fmaxf(sm_m[0][hh], sm_m[1][hh]), fmaxf(sm_m[2][hh], sm_m[3][hh]));
+        float mt = sm_m[0][hh];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) mt = fmaxf(mt, sm_m[w][hh]);
         float o = 0.f, l = 0.f;
         if (mt > -INFINITY) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < NW; ++w) {
                 float wt = fast_exp2(sm_m[w][hh] - mt);
                 o += wt * sm_o[w][hh][d];
                 l += wt * sm_l[w][hh];
@@ -315,31 +333,42 @@ __global__ __launch_bounds__(HD) void attn_merge_kernel(const float* part_o, con
     if (split) op[Hq * HD] = (f16_t)(r - (float)hi);
 }
 
-// The consumer form of the kernel gives each of its 256 threads at most two (column, column + hd/2) pairs of the
-// group's G query heads, key and value, and keeps the queries of at most 8 heads in LDS.
+// The consumer form of the kernel gives its threads at most 512 (column, column + hd/2) pairs of the group's G query
+// heads, key and value, and keeps the queries of at most 8 heads in LDS.
 bool k_attn_decode_consumes_qkv(int Hq, int Hkv, int hd) {
     const int G = Hq / Hkv;
     return (hd == 64 || hd == 128) && G <= 8 && (G + 2) * (hd / 2) <= 512;
 }
 
-void k_attn_decode(const DecodeAttnArgs& a, int B, int nsplit, hipStream_t s) {
+// Waves for the keys of one (sequence, kv head), from the context's limits: as many as make 4096 in all, each with at
+// least two pages of the longest sequence.  Up to 8 share a workgroup; beyond that the keys are split over workgroups and
+// merged by a kernel of their own, which costs as much as a short context's attention (4.6 us), so not for less.
+void k_attn_decode_plan(int max_batch, int Hkv, int mpps, int max_splits, int* waves, int* nsplit) {
+    const int want = std::min((4096 + max_batch * Hkv - 1) / (max_batch * Hkv), mpps / 2);
+    *waves = want >= 6 ? 8 : 4;
+    *nsplit = std::max(1, std::min(want / 8, max_splits));
+}
+
+template <int HD, bool SP, bool FU>
+static void launch_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s) {
+    const dim3 grid(B, a.Hkv, nsplit);
+    if (waves == 8) attn_decode_kernel<HD, 16, SP, FU, 8><<<grid, 512, 0, s>>>(a);
+    else attn_decode_kernel<HD, 16, SP, FU, 4><<<grid, 256, 0, s>>>(a);
+}
+template <int HD>
+static void launch_attn_decode_hd(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s) {
+    if (a.split) launch_attn_decode<HD, true, false>(a, B, waves, nsplit, s);
+    else if (a.qkv_part) launch_attn_decode<HD, false, true>(a, B, waves, nsplit, s);
+    else launch_attn_decode<HD, false, false>(a, B, waves, nsplit, s);
+    if (nsplit > 1)
+        attn_merge_kernel<HD><<<B * a.Hq, HD, 0, s>>>(a.part_o, a.part_ml, a.out, nsplit, a.Hq, a.split);
+}
+
+void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s) {
     if (B <= 0) return;
     if (a.qkv_part && (a.split || !k_attn_decode_consumes_qkv(a.Hq, a.Hkv, a.geo.hd))) return;   // callers check first
-    dim3 grid(B, a.Hkv, nsplit);
-    if (a.split) {
-        if (a.geo.hd == 128) attn_decode_kernel<128, 16, true, false><<<grid, 256, 0, s>>>(a);
-        else attn_decode_kernel<64, 16, true, false><<<grid, 256, 0, s>>>(a);
-    } else if (a.qkv_part) {
-        if (a.geo.hd == 128) attn_decode_kernel<128, 16, false, true><<<grid, 256, 0, s>>>(a);
-        else attn_decode_kernel<64, 16, false, true><<<grid, 256, 0, s>>>(a);
-    } else {
-        if (a.geo.hd == 128) attn_decode_kernel<128, 16, false, false><<<grid, 256, 0, s>>>(a);
-        else attn_decode_kernel<64, 16, false, false><<<grid, 256, 0, s>>>(a);
-    }
-    if (nsplit > 1) {
-        if (a.geo.hd == 128) attn_merge_kernel<128><<<B * a.Hq, 128, 0, s>>>(a.part_o, a.part_ml, a.out, nsplit, a.Hq, a.split);
-        else attn_merge_kernel<64><<<B * a.Hq, 64, 0, s>>>(a.part_o, a.part_ml, a.out, nsplit, a.Hq, a.split);
-    }
+    if (a.geo.hd == 128) launch_attn_decode_hd<128>(a, B, waves, nsplit, s);
+    else launch_attn_decode_hd<64>(a, B, waves, nsplit, s);
 }
 
 // ------------------------------------------------------------------ prefill / scoring: causal attention over packed sequences

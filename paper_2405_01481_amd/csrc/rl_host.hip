@@ -340,9 +340,9 @@ static void attention(rl_ctx* c, int l, int n, bool paged, int max_ctx, int nblo
         }
         // the split count is a property of the context (most sequences, longest sequence), never of the live batch:
         // a row's reduction order, and with it its bits, must not depend on its batch-mates
-        int nsplit = (1024 + m.max_batch * m.n_kv_heads - 1) / (m.max_batch * m.n_kv_heads);
-        nsplit = std::max(1, std::min(std::min(nsplit, kMaxAttnSplits), std::max(1, L.mpps / 8)));
-        k_attn_decode(a, n, nsplit, s);
+        int waves, nsplit;
+        k_attn_decode_plan(m.max_batch, m.n_kv_heads, L.mpps, kMaxAttnSplits, &waves, &nsplit);
+        k_attn_decode(a, n, waves, nsplit, s);
         return;
     }
     if (!paged && c->impl == 1) {

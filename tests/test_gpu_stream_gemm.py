@@ -44,3 +44,21 @@ def test_stream_gemm_rows_and_widths(shape, copy):
         assert np.array_equal(res[n][0], res[64][0][:n]) and np.array_equal(res[n][1], res[64][1][:n]), n
     verify_rollout(m, [ids[b, :lens[b]] for b in range(most)], *res[64], 0.8, 4, 0, 1e-3, 2e-2, rows=[0, 16, 63])
     ro.close()
+
+
+@pytest.mark.parametrize("most,max_seq,plen", [(64, 336, 300), (512, 4320, 4290)], ids=["8-waves", "4-waves-300-pages"])
+def test_decode_attention_waves_and_page_blocks(most, max_seq, plen):
+    """Eight waves on one (sequence, kv head) without splits, with remainders of pages per wave; and four waves over more
+    pages than the 64 per wave whose numbers are fetched at once (a context for many sequences, one of them long)."""
+    shape = synth.ModelShape("waves", 1, 256, 4, 2, 64, 256, 512, 10000.0, "bf16", 0.08)
+    G, lens = 5, np.array([plen, 1, 17, 130], np.int32)
+    w = synth.make_weights(shape, 1, DEV)
+    ro = R.Rollout(R.make_cfg(shape, most, max_seq, n_pages=400, max_chunk_tokens=max(max_seq, 512)), R.Weights(w), DEV)
+    ids = np.random.default_rng(3).integers(0, shape.vocab, size=(4, plen)).astype(np.int32)
+    out = torch.full((4, G), -1, dtype=torch.int32, device=DEV)
+    lp = torch.full((4, G), 9.0, dtype=torch.float32, device=DEV)
+    ro.rollout_generate(R.sample_cfg(4, 0.8), torch.tensor(ids, device=DEV), lens, G, out, None, lp)
+    ro.rollout_check()
+    m = O.Model(shape, synth.weights_for_oracle(w))
+    verify_rollout(m, [ids[b, :lens[b]] for b in range(4)], out.cpu().numpy(), lp.cpu().numpy(), 0.8, 4, 0, 1e-3, 2e-2)
+    ro.close()
