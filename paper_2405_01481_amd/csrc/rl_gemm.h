@@ -23,7 +23,7 @@ struct GemmArgs {
     int Wrows = 0;              // filled by the launcher
     int n_blocks_n = 0;         // filled by the launcher
     int k_per_split = 0;        // filled by the launcher
-    int rotate_k = 0;           // filled by the launcher (k_gemm_stream)
+    int rotate_k = 0;           // filled by the launcher (k_gemm_decode)
     int up_offset = 0;          // MG_SWIGLU: row of W where the up projection starts
     float* outF = nullptr;      // MG_STORE_F32 (+ split * split_stride) / MG_RESID
     f16_t* outH = nullptr;      // MG_STORE_F16 / MG_SWIGLU
@@ -72,18 +72,16 @@ void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s);
 int k_gemm_mfma_splits_used(int K, int splits);
 // Number of column groups per row that an MG_LSE launch of this shape writes (at most N / 64).
 int k_gemm_mfma_lse_parts(int M, int N, int K, int big_mode);
-// Decode GEMM (M <= 128, lda * 2 * 128 below 4 GiB) on 128-column tiles with LDS operand rings: epi MG_STORE_F32 (split-K partials to
-// outF + split * split_stride; plain store when one split) or MG_SWIGLU (never split).
-bool k_gemm_decode_supported(int epi, int N, int K);   // K and tile columns multiples of 128
-int k_gemm_decode_splits_used(int K, int splits);
-void k_gemm_decode(int epi, GemmArgs a, int splits, hipStream_t s);
-// Decode GEMM of at most 64 rows on tiles of 16 .. 128 columns; the same epilogues and operands as k_gemm_decode, K and Kw
-// multiples of 128, W below 4 GiB.  k_gemm_stream_splits: the number of K splits (partial sums) that suits an MG_STORE_F32
-// GEMM; it depends on the shape alone.
-bool k_gemm_stream_supported(int epi, int N, int K, int Kw);
-int k_gemm_stream_splits(int N, int K);
-void k_gemm_stream(int epi, GemmArgs a, int splits, hipStream_t s);
-// Measurement switch: k_gemm_decode takes the 128 x 128 tile kernel above this many rows (default 64; < 0: never).
+// Decode GEMM of at most 128 rows (rl_gemm_stream.hip): epi MG_STORE_F32 (partial sums of the K splits to outF + split *
+// split_stride; plain store when one split), MG_SWIGLU or MG_SAMPLE (never split).  K and Kw multiples of 128, W below
+// 4 GiB.  max_rows: the most rows the context will ever pass; tiles and k_gemm_decode_splits, the number of splits that suits an
+// MG_STORE_F32 GEMM, follow from it and the shape, never from the rows of a call.
+bool k_gemm_decode_supported(int epi, int N, int K, int Kw);
+int k_gemm_decode_splits(int N, int K, int max_rows);
+void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s);
+// The same GEMM (MG_STORE_F32, MG_SWIGLU) on the 128 x 128 tile kernel, a.k_per_split and a.Wrows filled in.
+void k_gemm_tile_decode(int epi, const GemmArgs& a, int splits, hipStream_t s);
+// Measurement switch: k_gemm_decode takes the 128 x 128 tile kernel above this many rows (default < 0: never).
 void k_gemm_decode_tile_above(int rows);
 
 // dst[i] = fp16(src[i]) for n bf16 values (n multiple of 8, both 16-byte aligned), bit for bit what the GEMM

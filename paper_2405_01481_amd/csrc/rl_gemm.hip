@@ -3,19 +3,16 @@
 // Weights stay bf16 in HBM and are converted to fp16 on their way to the MFMA operand registers
 // (exact for every weight of normal fp16 magnitude) -- or are read from an fp16 copy where a weight set
 // has one; the contraction runs on fp16 MFMAs (v_mfma_f32_16x16x32_f16 in the large-M kernel,
-// v_mfma_f32_32x32x16_f16 in the others) with fp32 accumulation.  Four kernels share one set of epilogues:
+// v_mfma_f32_32x32x16_f16 in the others) with fp32 accumulation.  Three kernels share one set of epilogues (the decode
+// step's weight-streaming GEMMs are in rl_gemm_stream.hip):
 //   * gemm_mfma_kernel: 128 x 128 tiles staged through registers -- small M, and split-K for decode
 //     batches above 128 rows;
 //   * gemm_dma8_kernel: tiles of 96 to 256 rows x 256 columns, eight waves, operands staged by global ->
 //     LDS loads -- the large-M GEMMs of prefill and scoring;
 //   * gemm_dma_kernel:  128 x 128 tiles staged the same way, two GEMMs on one tile -- the exact
 //     full-vocabulary KL, which needs the policy's and the reference's logits of a tile together;
-//   * gemm_ring_kernel: the weight-streaming GEMMs of a decode step (contexts of 65 to 128 rows; rl_gemm_stream.hip
-//     has those of fewer), split over K so that all 256 CUs stream a slice of W; partial sums go to a [split][M][N] fp32 buffer and are
-//     reduced, in a fixed order, by the consumer kernel.
 // Epilogues: fp32 store / split-K partial, fp16 store, residual add, SwiGLU, RoPE + q/k/v split for
-// the QKV projection, log-sum-exp + target gather for the scoring LM head, and per-block sampling
-// statistics for the decode LM head.
+// the QKV projection, log-sum-exp + target gather for the scoring LM head.
 #include "rl_common.h"
 #include "rl_gemm.h"
 #include "rl_gemm_dev.h"
@@ -151,26 +148,6 @@ template <int EPI, int BN, int TN, int WGN, int NR = 16>
 __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs& a, int m_base, int nb, int wn,
                                             int ks, int lane, const QkvRowMeta* pre = nullptr) {
     const int lg = lane >> 5, lrow = lane & 31;
-    if constexpr (EPI == MG_SAMPLE) {
-        // Reductions over the 32 lanes that hold one row of a 32-column MFMA tile.  Ties of the maximum go to the
-        // lowest column (the lowest lane that holds it), as the sampler's arg-max rule wants.
-        const int nblk = a.N / 32;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const float v = acc[j][r];
-                const float mx = row32_max(v);
-                const unsigned holders = (unsigned)(__ballot(v == mx) >> (32 * lg));
-                const int mi = __ffs(holders) - 1;
-                const float e1 = row32_sum(__expf(v - mx)), eT = row32_sum(__expf((v - mx) * a.inv_temp));
-                if (lrow == 0 && m < a.M)
-                    a.samp_part[(int64_t)m * nblk + nb * (BN / 32) + wn * TN + j] = make_float4(mx, eT, e1, __int_as_float(mi));
-            }
-        }
-        return;
-    }
     if (EPI == MG_RESID) {
         // read-modify-write of the fp32 residual stream: all of the band's loads are issued before the
         // first add (rows past M read row M-1 instead of branching, so nothing separates the loads)
@@ -1049,125 +1026,6 @@ __global__ __launch_bounds__(256, MINWG) void gemm_dma_kernel(GemmArgs a) {
     if (TM > 3) mg_epilogue<EPI, BN, TN, WGN>(acc[TM > 3 ? 3 : 0], a, m0 + wm * TM * 32 + 96, nb, wn, ks, lane);
 }
 
-// ------------------------------------------------------------------ decode GEMM (M <= 128), LDS rings
-// HBM-bound: C[128, 128 columns] per workgroup over one K slice (blockIdx.z; partial sums go to
-// outF + split * split_stride and are reduced by the consumer).  What counts is how many bytes of W a CU
-// keeps in flight, so the operands are staged by global -> LDS loads into two rings of 16 KB stages
-// (k-tile 64: rows of 128 B, whole cache lines per row and request): five stages of W, which comes from
-// HBM, and three of A, which every workgroup re-reads from L2.  Loads complete in issue order per wave,
-// so the two depths need separate issuers: waves 0-3 request only W (four tiles ahead), waves 4-7 only A
-// (two tiles ahead); each waits on its own vmcnt (by hand: the loads are issued from inline assembly so
-// that the compiler does not force them to complete at every barrier), and the barrier that follows
-// publishes the tile to all eight waves, which share the MFMA work (WGM x WGN waves of 32x32x16 tiles).
-// The same number of loads is issued on every trip (the last trips re-request the final tile), so the
-// wait counts hold to the end; vmcnt(0) before the epilogue keeps loads from landing in LDS after the
-// workgroup has ended.  16-byte chunks of a row are XOR-swizzled with (row >> 1) & 7 on the source side
-// of the loads: fragment reads are bank-conflict free without padding.
-template <int EPI, int WGM, int WGN, bool WF16>
-__global__ __launch_bounds__(512, 1) void gemm_ring_kernel(GemmArgs a) {
-    constexpr int BN = 128, DW = 5, DA = 3, ST = 16384;
-    constexpr int TM = 128 / WGM / 32, TN = BN / WGN / 32;
-    static_assert(WGM * WGN == 8, "eight waves");
-    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [DW][W 128 x 128 B] [DA][A 128 x 128 B]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool isW = wave < 4;
-    const int w4 = wave & 3, wm = wave / WGN, wn = wave % WGN;
-    const int ks = blockIdx.z;
-    int nb, mb;
-    if (!tile_of(blockIdx.x, 1, a.n_blocks_n, mb, nb)) return;
-    const int kbeg = ks * a.k_per_split, kend = min(a.K, kbeg + a.k_per_split);
-    const int nk = (kend - kbeg) / 64;
-    // Staging: instruction t of issuer wave w4 fills the 1 KB block t*4 + w4 of a stage = rows (t*4+w4)*8 .. +8;
-    // lane -> row + lane/8, physical chunk lane%8, which holds the row's logical chunk (lane%8) ^ ((row>>1)&7).
-    unsigned g_off[4];
-    {
-        const int lc = (lane & 7) ^ (((w4 & 1) * 4 + (lane >> 4)) & 7);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int r = (t * 4 + w4) * 8 + (lane >> 3);
-            g_off[t] = isW ? ((unsigned)min(w_row_of<EPI, BN>(r, nb, a), a.Wrows - 1) * (unsigned)a.Kw + lc * 8) * 2u
-                           : ((unsigned)min(r, a.M - 1) * (unsigned)a.lda + lc * 8) * 2u;   // rows >= M: clamped, never stored
-        }
-    }
-    const char* gbase = isW ? reinterpret_cast<const char*>(a.W) : reinterpret_cast<const char*>(a.A + kbeg);
-    const int kw0 = kbeg / 64, nkw = a.Kw / 64;   // W k-tile of A k-tile kt: kw0 + kt, wrapping at nkw
-    const int depth = isW ? DW : DA;
-    const unsigned ring = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + (isW ? 0 : DW * ST) + w4 * 1024;
-#define RG_ISSUE(stage, kt)                                                                                     \
-    {                                                                                                           \
-        const char* g_ = gbase + (size_t)(isW ? wrap_k(kw0 + (kt), nkw) : (kt)) * 128;                          \
-        _Pragma("unroll") for (int t = 0; t < 4; ++t) {                                                         \
-            const unsigned sa_ = ring + (stage) * ST + t * 4096;                                                \
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                        \
-                         :: "s"(sa_), "v"(g_off[t]), "s"(g_) : "memory");                                       \
-        }                                                                                                       \
-    }
-    // fragment addresses (stage 0): row lane%32 of a 32-row block, logical chunk slice*2 + lane/32, swizzled
-    int fa[4], fw[4];
-#pragma unroll
-    for (int sl = 0; sl < 4; ++sl) {
-        const int ko = ((sl * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 16;
-        fa[sl] = DW * ST + (wm * TM * 32 + (lane & 31)) * 128 + ko;
-        fw[sl] = (wn * TN * 32 + (lane & 31)) * 128 + ko;
-    }
-    floatx16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    // 32-row bands of this wave that hold real rows (batches below 128 rows leave the upper bands idle)
-    const int nact = min(TM, max(0, (a.M - wm * TM * 32 + 31) / 32));
-    for (int st = 0; st < depth - 1; ++st) RG_ISSUE(st, min(st, nk - 1))
-    int fill = depth - 1, a_st = 0, w_st = 0;   // stage to refill next; stages holding tile kt
-    for (int kt = 0; kt < nk; ++kt) {
-        // tile kt landed: a W issuer may still have tiles kt+1 .. kt+3 in flight, an A issuer tile kt+1
-        if (isW) __builtin_amdgcn_s_waitcnt(dma_waitcnt(4 * (DW - 2), 0));
-        else __builtin_amdgcn_s_waitcnt(dma_waitcnt(4 * (DA - 2), 0));
-        __syncthreads();
-        // every wave is done with tile kt-1: its stage takes tile kt + depth - 1
-        RG_ISSUE(fill, min(kt + depth - 1, nk - 1))
-        fill = fill + 1 == depth ? 0 : fill + 1;
-        // k-slices of 16: the fragments of slice sl+1 are requested before slice sl is converted and multiplied
-        half8 af[2][TM];
-        u32x4_t bw[2][TN];
-        const int ao = a_st * ST, wo = w_st * ST;
-#define RG_READ(set, sl)                                                                                        \
-        {                                                                                                       \
-            _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                      \
-                bw[set][j] = *reinterpret_cast<const u32x4_t*>(smem + fw[sl] + wo + j * 4096);                  \
-            _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                      \
-                if (i < nact) af[set][i] = *reinterpret_cast<const half8*>(smem + fa[sl] + ao + i * 4096);      \
-        }
-        if (nact > 0) RG_READ(0, 0)
-#pragma unroll
-        for (int sl = 0; sl < 4; ++sl) {
-            if (nact == 0) break;   // every row of this wave is past M: it only stages and keeps the barriers
-            if (sl < 3) RG_READ((sl + 1) & 1, sl + 1)
-            __builtin_amdgcn_sched_barrier(0);
-            half8 bf[TN];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bf[j] = WF16 ? __builtin_bit_cast(half8, bw[sl & 1][j]) : bf16x8_to_half8(bw[sl & 1][j]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    if (i < nact) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[sl & 1][i], bf[j], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#undef RG_READ
-        a_st = a_st + 1 == DA ? 0 : a_st + 1;
-        w_st = w_st + 1 == DW ? 0 : w_st + 1;
-    }
-    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 15));   // nothing may land in LDS after the workgroup ends
-#undef RG_ISSUE
-    mg_epilogue<EPI, BN, TN, WGN>(acc[0], a, wm * TM * 32, nb, wn, ks, lane);
-    if (TM > 1) mg_epilogue<EPI, BN, TN, WGN>(acc[TM > 1 ? 1 : 0], a, wm * TM * 32 + 32, nb, wn, ks, lane);
-}
-
 template <int BM, int BN, int WGM, int WGN, int EPI, int BKT = 64, bool WF16 = false>
 static void launch(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s) {
     constexpr size_t lds = (size_t)2 * (BM + BN) * (BKT + 8) * sizeof(f16_t);
@@ -1336,41 +1194,6 @@ void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s) {
     }
 }
 
-// ---- decode (M <= 128): ring kernel on 128-column tiles, split over K in units of 128
-bool k_gemm_decode_supported(int epi, int N, int K) {
-    if (epi != MG_STORE_F32 && epi != MG_SWIGLU && epi != MG_SAMPLE) return false;
-    const int cols = epi == MG_SWIGLU ? 2 * N : N;
-    return K % 128 == 0 && cols % 128 == 0 && (uint64_t)cols * K * 2 < (1ull << 32);
-}
-
-int k_gemm_decode_splits_used(int K, int splits) {
-    const int units = K / 128;
-    if (splits < 1) splits = 1;
-    const int per = (units + splits - 1) / splits;
-    return (units + per - 1) / per;
-}
-
-template <int EPI, int WGM, int WGN, bool WF16>
-static void launch_ring_t(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s) {
-    constexpr int lds = 8 * 16384;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_ring_kernel<EPI, WGM, WGN, WF16>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        attr_set = true;
-    }
-    GemmArgs b = a;
-    b.n_blocks_n = n_blocks_n;
-    dim3 grid(8 * ((n_blocks_n + 7) / 8), 1, splits);
-    gemm_ring_kernel<EPI, WGM, WGN, WF16><<<grid, 512, lds, s>>>(b);
-}
-template <int EPI, int WGM, int WGN>
-static void launch_ring(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s) {
-    if (a.w_f16) launch_ring_t<EPI, WGM, WGN, true>(a, n_blocks_n, splits, s);
-    else launch_ring_t<EPI, WGM, WGN, false>(a, n_blocks_n, splits, s);
-}
-
-
 // fp16 copy of a bf16 weight tensor, by the conversion the kernels themselves apply (so that a GEMM on the copy
 // gives the same bits); n multiple of 8.  Bound by memory: four 16-byte loads of a thread are in flight before its
 // first store.
@@ -1390,37 +1213,14 @@ void k_bf16_to_f16(const void* src, void* dst, int64_t n, hipStream_t s) {
     bf16_to_f16_kernel<<<(unsigned)((n8 + 1023) / 1024), 256, 0, s>>>((const u32x4_t*)src, (half8*)dst, n8);
 }
 
-static int g_decode_tile_above = -1;   // rows above which k_gemm_decode takes the 128 x 128 tile kernel; < 0: never
-void k_gemm_decode_tile_above(int rows) { g_decode_tile_above = rows; }
-
-void k_gemm_decode(int epi, GemmArgs a, int splits, hipStream_t s) {
-    if (a.M <= 0 || a.N <= 0 || a.M > 128) return;
-    if (a.Kw <= 0) a.Kw = a.K;
-    if (epi == MG_SWIGLU || epi == MG_SAMPLE) splits = 1;
-    const int units = a.K / 128;
-    if (splits < 1) splits = 1;
-    const int per = (units + splits - 1) / splits;
-    a.k_per_split = per * 128;
-    splits = (units + per - 1) / per;
-    a.Wrows = epi == MG_SWIGLU ? a.up_offset + a.N : a.N;
-    // Measurement switch: the register-staged 128 x 128 tile kernel (two workgroups per CU) in place of the ring
-    // kernel.  Back to back on 128 rows it streams W 4-9 % faster; inside the decode step the ring kernel on the
-    // policy's fp16 copy wins by 3 %, so it stays the default.  Both split K the same way (units of 128), so the
-    // partial buffers are the same.
-    if (g_decode_tile_above >= 0 && a.M > g_decode_tile_above && epi != MG_SAMPLE) {
-        a.k_per_split = per * 128;
-        if (epi == MG_SWIGLU) {
-            if (a.w_f16) launch<128, 128, 2, 2, MG_SWIGLU, 64, true>(a, a.N / 64, 1, s);
-            else launch<128, 128, 2, 2, MG_SWIGLU>(a, a.N / 64, 1, s);
-        } else {
-            if (a.w_f16) launch<128, 128, 2, 2, MG_STORE_F32, 64, true>(a, a.N / 128, splits, s);
-            else launch<128, 128, 2, 2, MG_STORE_F32>(a, a.N / 128, splits, s);
-        }
-        return;
+void k_gemm_tile_decode(int epi, const GemmArgs& a, int splits, hipStream_t s) {
+    if (epi == MG_SWIGLU) {
+        if (a.w_f16) launch<128, 128, 2, 2, MG_SWIGLU, 64, true>(a, a.N / 64, 1, s);
+        else launch<128, 128, 2, 2, MG_SWIGLU>(a, a.N / 64, 1, s);
+    } else {
+        if (a.w_f16) launch<128, 128, 2, 2, MG_STORE_F32, 64, true>(a, a.N / 128, splits, s);
+        else launch<128, 128, 2, 2, MG_STORE_F32>(a, a.N / 128, splits, s);
     }
-    if (epi == MG_SWIGLU) launch_ring<MG_SWIGLU, 4, 2>(a, a.N / 64, 1, s);   // gate / up pairs: two column tiles per wave
-    else if (epi == MG_SAMPLE) launch_ring<MG_SAMPLE, 2, 4>(a, a.N / 128, 1, s);
-    else launch_ring<MG_STORE_F32, 2, 4>(a, a.N / 128, splits, s);
 }
 
 int k_gemm_mfma_splits_used(int K, int splits) {

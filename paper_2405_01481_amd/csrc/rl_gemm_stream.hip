@@ -1,8 +1,9 @@
-// Weight-streaming GEMMs of a decode step of at most 64 rows:  C[M,N] = A[M,K] (fp16) * W[N,K]^T (bf16 or fp16 copy).
+// Weight-streaming GEMMs of a decode step of at most 128 rows:  C[M,N] = A[M,K] (fp16) * W[N,K]^T (bf16 or fp16 copy).
 //
 // Bound by reading W once.  What a plain read of these matrices reaches here, launch included, sets the floor: 12.6 MB
-// in 3.8 us, 33.5 MB in 6.5, 117 MB in 20, 235 MB in 38 (3.3, 5.2, 5.8, 6.2 TB/s).  Three things decide how close a
-// GEMM comes, all measured:
+// in 3.8 us, 33.5 MB in 6.5, 117 MB in 20, 235 MB in 38 (3.3, 5.2, 5.8, 6.2 TB/s).  A comes on top, from L2 and at about
+// 17 TB/s over all workgroups, each of which reads its rows once (gate/up of the 8B shape: 39.3, 40.7, 43.7, 54 us at 3, 32,
+// 64, 128 rows).  Three things decide how close a GEMM comes, all measured:
 //   * how rows are read.  64-byte pieces of 16 rows (operands straight into MFMA layout) reach 60 - 80 % of the plain
 //     read on the short matrices, 256-byte pieces 95 %.  So operands go global -> LDS in k-tiles of 128 (a 1 KB
 //     request = 4 rows x 256 B), 16-byte chunks XOR-swizzled with the row on the source side, so that the fragment
@@ -15,19 +16,21 @@
 //     split over Z workgroups whose partial sums the consumer reduces (stream_plan).
 // Eight waves: four along the k-tile (32 k each), two along the columns, so that every W fragment is read, and on bf16
 // weights converted, by one wave only; each wave holds all MT x 16 rows.  The four partial accumulators meet in LDS after
-// the loop, in wave order.  Three stages, one barrier per k-tile; the loads are issued from inline assembly (the compiler
-// would wait for them at every barrier) and counted by hand: two tiles are in flight while one is consumed.
-// Against the 128-column ring kernel (which stays for batches above 64 rows: it reads A half as often), per launch,
-// ring -> here: 8B at 3 rows QKV 12.8 -> 11, O 9.8 -> 8, gate/up 52 -> 39, down 23 -> 21.5, LM head 222 -> 177 us; 1B at
-// 32 rows 8.2 -> 5.3, 7.0 -> 4.1, 21.7 -> 13.7, 11.3 -> 8.9; 70B (bf16) at 64 rows 38 -> 34, 38 -> 28.5, 171 -> 170, 84 -> 88.
+// the loop, in wave order.  Three stages (above 64 rows two of A: LDS is full), one barrier per k-tile; the loads are issued
+// from inline assembly (the compiler would wait for them at every barrier) and counted by hand: two k-tiles of W are in
+// flight while one is consumed.
+// Against a kernel on 128 x 128 tiles with k-tiles of 64 (which it replaced), per launch: 8B at 3 rows QKV 12.8 -> 10.4 us, O 9.8
+// -> 8, gate/up 52 -> 40, down 23 -> 21, LM head 222 -> 177; at 128 rows 18.1 -> 17.3, 15.3 -> 14, 58 -> 54.5, 33.5 -> 33.5, 227 ->
+// 230; 1B at 32 rows 8.2 -> 5.3, 7.0 -> 4.2, 21.7 -> 13.9, 11.3 -> 9.3; 70B (bf16) at 64 rows 38 -> 33, 38 -> 29.5, 171 -> 170, 84 -> 82.
 #include "rl_common.h"
 #include "rl_gemm.h"
 #include "rl_gemm_dev.h"
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-static constexpr int GS_KT = 128, GS_RB = 256, GS_NS = 3, GS_WK = 4;
-static constexpr int gs_lds(int MT, int CT) { return GS_NS * (CT + MT) * 16 * GS_RB; }   // also holds the MT x CT x 4 KB of the exchange
+static constexpr int GS_KT = 128, GS_RB = 256, GS_WK = 4, GS_NW = 3;      // k-tile, its bytes per row, waves along k, stages of W
+static constexpr int gs_na(int MT) { return MT == 8 ? 2 : 3; }             // stages of A
+static constexpr int gs_lds(int MT, int CT) { return (GS_NW * CT + gs_na(MT) * MT) * 16 * GS_RB; }
 
 // Row of W behind row rr of the 16-row tile t.  MG_SWIGLU: 8 gate rows and the 8 up rows of the same columns.
 template <int EPI>
@@ -38,46 +41,58 @@ __device__ __forceinline__ int stream_w_row(int t, int rr, const GemmArgs& a) {
 
 template <int EPI, int MT, int CT, bool WF16>
 __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm_stream_kernel(GemmArgs a) {
-    constexpr int WN = 8 / GS_WK, CW = (CT + WN - 1) / WN;
-    constexpr int STAGE = (CT + MT) * 16 * GS_RB;
-    constexpr int NBLK = STAGE / 1024, NI = (NBLK + 7) / 8;   // 1 KB requests per k-tile; per wave (waves 4 .. 7 one fewer if odd)
-    constexpr bool ODD = NBLK % 8 != 0;
-    static_assert(NBLK % 4 == 0 && MT * CT * GS_WK * 1024 <= gs_lds(MT, CT), "stage and exchange");
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    constexpr int WN = 8 / GS_WK, CW = (CT + WN - 1) / WN, NA = gs_na(MT);
+    constexpr int WST = CT * 16 * GS_RB, AST = MT * 16 * GS_RB;               // bytes of a stage
+    constexpr int NBW = CT * 4, NBA = MT * 4;                                 // its 1 KB requests: 4 rows x 256 B each
+    constexpr int NIW = (NBW + 7) / 8, NIA = (NBA + 7) / 8;                   // per wave; odd tile counts: half of the waves one fewer
+    // what may be in flight when a k-tile is read: its younger siblings, W of GS_NW - 2 k-tiles and A of NA - 2
+    constexpr int FLY_W = GS_NW - 2, FLY_A = NA - 2, FLY = NIW * FLY_W + NIA * FLY_A;
+    constexpr int FEWER = (CT % 2 != 0 && MT % 2 != 0) ? FLY_W : CT % 2 != 0 ? FLY_W : MT % 2 != 0 ? FLY_A : 0;
+    constexpr int IB = MT * CT * GS_WK * 1024 <= gs_lds(MT, CT) ? MT : MT / 2;   // row tiles per exchange at the end
+    static_assert(IB * CT * GS_WK * 1024 <= gs_lds(MT, CT), "the exchange reuses the stages");
+    static_assert(MT % 2 == 0 || (MT == 1 && FLY_A == FLY_W), "one odd A tile, in flight as long as W's");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];            // [GS_NW][W tiles] [NA][A tiles]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, q = lane >> 4, wk = wave % GS_WK, wn = wave / GS_WK;
     const int t0 = blockIdx.x * CT;                            // first 16-row tile of W
     const int kbeg = blockIdx.z * a.k_per_split, kend = min(a.K, kbeg + a.k_per_split);
     const int nk = (kend - kbeg) / GS_KT, kt0 = kbeg / GS_KT, nkw = a.Kw / GS_KT;
     const int rot = a.rotate_k ? (int)(blockIdx.x % (unsigned)nk) : 0;
-    const bool all_blocks = !ODD || wave < 4;
-    // Staging: request t of a wave fills the 1 KB block t*8 + wave of a stage = 4 rows (W tiles first, then A); lane ->
-    // row + lane/16, physical chunk lane%16, which holds the row's logical chunk (lane%16) ^ (row%16).
-    unsigned g_off[NI];
+    // Staging: request t of a wave fills the 1 KB block t*8 + wave = 4 rows of a W stage, or (counted from wave 4 on if W's
+    // tiles are odd) of an A stage; lane -> row + lane/16, physical chunk lane%16, which holds the row's logical chunk
+    // (lane%16) ^ (row%16).
+    const int wa = (wave + 4 * (CT & 1)) & 7;
+    const bool has_w = CT % 2 == 0 || wave < 4, has_a = MT % 2 == 0 || wa < 4;     // the last request of the wave
+    unsigned w_off[NIW], a_off[NIA];
 #pragma unroll
-    for (int t = 0; t < NI; ++t) {
-        const int row = (t * 8 + wave) * 4 + (lane >> 4);
-        const unsigned ch = (unsigned)((lane & 15) ^ (row & 15)) * 16u;
-        const bool isW = t * 8 + wave < CT * 4;
-        const int src = isW ? min(stream_w_row<EPI>(t0 + (row >> 4), row & 15, a), a.Wrows - 1) : min(row - CT * 16, a.M - 1);
-        g_off[t] = (unsigned)src * (unsigned)(isW ? a.Kw : a.lda) * 2u + ch;   // rows past the end: clamped, never stored
+    for (int t = 0; t < NIW; ++t) {
+        const int row = (t * 8 + wave) * 4 + (lane >> 4);      // rows past the end: clamped, never stored
+        w_off[t] = (unsigned)min(stream_w_row<EPI>(t0 + (row >> 4), row & 15, a), a.Wrows - 1) * (unsigned)a.Kw * 2u +
+                   (unsigned)((lane & 15) ^ (row & 15)) * 16u;
     }
-    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+#pragma unroll
+    for (int t = 0; t < NIA; ++t) {
+        const int row = (t * 8 + wa) * 4 + (lane >> 4);
+        a_off[t] = (unsigned)min(row, a.M - 1) * (unsigned)a.lda * 2u + (unsigned)((lane & 15) ^ (row & 15)) * 16u;
+    }
+    const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+    const unsigned lds_a = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + GS_NW * WST + wa * 1024;
     const char* const Ag = reinterpret_cast<const char*>(a.A);
     const char* const Wg = reinterpret_cast<const char*>(a.W);
-#define GS_ISSUE(stage, kt)                                                                                     \
+#define GS_TILE(kt) (kt0 + ((kt) + rot >= nk ? (kt) + rot - nk : (kt) + rot))
+#define GS_REQ(lds, off, g)                                                                                     \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(off), "s"(g) : "memory")
+#define GS_ISSUE_W(stage, kt)                                                                                   \
     {                                                                                                           \
-        const int k_ = kt0 + ((kt) + rot >= nk ? (kt) + rot - nk : (kt) + rot);                                 \
-        const char* w_ = Wg + (size_t)wrap_k(k_, nkw) * GS_RB;                                                  \
-        const char* a_ = Ag + (size_t)k_ * GS_RB;                                                               \
-        _Pragma("unroll") for (int t = 0; t < NI; ++t) {                                                        \
-            if (t < NI - 1 || all_blocks) {                                                                     \
-                const char* g_ = t * 8 + wave < CT * 4 ? w_ : a_;                                               \
-                const unsigned sa_ = lds_base + (stage) * STAGE + t * 8192;                                     \
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                    \
-                             :: "s"(sa_), "v"(g_off[t]), "s"(g_) : "memory");                                   \
-            }                                                                                                   \
-        }                                                                                                       \
+        const char* g_ = Wg + (size_t)wrap_k(GS_TILE(kt), nkw) * GS_RB;                                         \
+        _Pragma("unroll") for (int t = 0; t < NIW; ++t)                                                         \
+            if (t < NIW - 1 || has_w) { const unsigned l_ = lds_w + (stage) * WST + t * 8192; GS_REQ(l_, w_off[t], g_); } \
+    }
+#define GS_ISSUE_A(stage, kt)                                                                                   \
+    {                                                                                                           \
+        const char* g_ = Ag + (size_t)GS_TILE(kt) * GS_RB;                                                      \
+        _Pragma("unroll") for (int t = 0; t < NIA; ++t)                                                         \
+            if (t < NIA - 1 || has_a) { const unsigned l_ = lds_a + (stage) * AST + t * 8192; GS_REQ(l_, a_off[t], g_); } \
     }
     floatx4 acc[MT][CW];
 #pragma unroll
@@ -85,27 +100,36 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
 #pragma unroll
         for (int j = 0; j < CW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int frag = r * GS_RB + (((wk * 4 + q) ^ r) * 16);    // this lane's 16 bytes of a 16-row tile
+    // in the order of the loop's requests, so that its counts hold from the first k-tile on
 #pragma unroll
-    for (int s = 0; s < GS_NS - 1; ++s) GS_ISSUE(s, min(s, nk - 1))
-    int st = 0, fill = GS_NS - 1;
+    for (int s = 0; s < GS_NW - 1; ++s) {
+        if (s >= GS_NW - NA) GS_ISSUE_A(s - (GS_NW - NA), min(s - (GS_NW - NA), nk - 1))
+        GS_ISSUE_W(s, min(s, nk - 1))
+    }
+    int w_st = 0, a_st = 0, w_fill = GS_NW - 1, a_fill = NA - 1;
     for (int kt = 0; kt < nk; ++kt) {
-        // tile kt landed (the GS_NS - 2 younger ones may be in flight), own fragment reads of tile kt - 1 done
-        if (all_blocks) __builtin_amdgcn_s_waitcnt(dma_waitcnt(NI * (GS_NS - 2), 0));
-        else __builtin_amdgcn_s_waitcnt(dma_waitcnt((NI - 1) * (GS_NS - 2), 0));
+        // k-tile kt landed, own fragment reads of k-tile kt - 1 done
+        if (CT % 2 != 0 && MT % 2 != 0) __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY - FEWER, 0));   // every wave lacks one
+        else if (FEWER == 0 || (has_w && has_a)) __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY, 0));
+        else __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY - FEWER, 0));
         __syncthreads();
-        // every wave is done with tile kt - 1: its stage takes tile kt + 2 (the last trips re-request the final tile, so
-        // that the counts hold)
-        GS_ISSUE(fill, min(kt + GS_NS - 1, nk - 1))
-        fill = fill + 1 == GS_NS ? 0 : fill + 1;
-        const char* sp = smem + st * STAGE + frag;
-        st = st + 1 == GS_NS ? 0 : st + 1;
+        // every wave is done with k-tile kt - 1: its stages are filled again (the last trips re-request the final k-tile,
+        // so that the counts hold)
+        GS_ISSUE_A(a_fill, min(kt + NA - 1, nk - 1))
+        GS_ISSUE_W(w_fill, min(kt + GS_NW - 1, nk - 1))
+        w_fill = w_fill + 1 == GS_NW ? 0 : w_fill + 1;
+        a_fill = a_fill + 1 == NA ? 0 : a_fill + 1;
+        const char* sw = smem + w_st * WST + frag;
+        const char* sa = smem + GS_NW * WST + a_st * AST + frag;
+        w_st = w_st + 1 == GS_NW ? 0 : w_st + 1;
+        a_st = a_st + 1 == NA ? 0 : a_st + 1;
         u32x4_t w[CW];
         half8 af[MT];
 #pragma unroll
         for (int j = 0; j < CW; ++j)
-            if (CT % WN == 0 || wn * CW + j < CT) w[j] = *reinterpret_cast<const u32x4_t*>(sp + (wn * CW + j) * 16 * GS_RB);
+            if (CT % WN == 0 || wn * CW + j < CT) w[j] = *reinterpret_cast<const u32x4_t*>(sw + (wn * CW + j) * 16 * GS_RB);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) af[i] = *reinterpret_cast<const half8*>(sp + (CT + i) * 16 * GS_RB);
+        for (int i = 0; i < MT; ++i) af[i] = *reinterpret_cast<const half8*>(sa + i * 16 * GS_RB);
 #pragma unroll
         for (int j = 0; j < CW; ++j) {
             if (CT % WN == 0 || wn * CW + j < CT) {
@@ -116,88 +140,97 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
         }
     }
     __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));             // nothing may land in LDS from here on
-    __syncthreads();
-#undef GS_ISSUE
-    // the four waves along k meet in LDS; tile (i, j) of lane (r, q): column r, rows 4 q .. 4 q + 3
+#undef GS_ISSUE_A
+#undef GS_ISSUE_W
+#undef GS_REQ
+#undef GS_TILE
+    // the four waves along k meet in LDS, IB row tiles at a time; tile (i, j) of lane (r, q): column r, rows 4 q .. 4 q + 3
     floatx4* const red = reinterpret_cast<floatx4*>(smem);
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int i0 = 0; i0 < MT; i0 += IB) {
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < CW; ++j)
-            if (CT % WN == 0 || wn * CW + j < CT) red[((i * CT + wn * CW + j) * GS_WK + wk) * 64 + lane] = acc[i][j];
-    __syncthreads();
-    auto sum = [&](int i, int j) {
-        const floatx4* p = red + (i * CT + j) * GS_WK * 64 + lane;
-        floatx4 v = p[0];
+        for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int w = 1; w < GS_WK; ++w) {
-            const floatx4 o = p[w * 64];
+            for (int j = 0; j < CW; ++j)
+                if (CT % WN == 0 || wn * CW + j < CT) red[((i * CT + wn * CW + j) * GS_WK + wk) * 64 + lane] = acc[i0 + i][j];
+        __syncthreads();
+        auto sum = [&](int i, int j) {
+            const floatx4* p = red + (i * CT + j) * GS_WK * 64 + lane;
+            floatx4 v = p[0];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] += o[x];
-        }
-        return v;
-    };
-    if constexpr (EPI == MG_SAMPLE) {
-        // statistics of 32-column blocks = two tiles; ties of the maximum go to the lowest column
-        const int nblk = a.N / 32;
-        for (int t = wave; t < MT * CT / 2; t += 8) {
-            const int i = t / (CT / 2), jp = t % (CT / 2), blk = blockIdx.x * (CT / 2) + jp;
-            const floatx4 v0 = sum(i, 2 * jp), v1 = sum(i, 2 * jp + 1);
+            for (int w = 1; w < GS_WK; ++w) {
+                const floatx4 o = p[w * 64];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                float mx = fmaxf(v0[x], v1[x]);
-                mx = fmaxf(mx, dpp_move<0xB1>(mx));    // quad_perm [1,0,3,2]
-                mx = fmaxf(mx, dpp_move<0x4E>(mx));    // quad_perm [2,3,0,1]
-                mx = fmaxf(mx, dpp_move<0x141>(mx));   // row_half_mirror
-                mx = fmaxf(mx, dpp_move<0x140>(mx));   // row_mirror
-                const unsigned h0 = (unsigned)(__ballot(v0[x] == mx) >> (16 * q)) & 0xffffu;
-                const unsigned h1 = (unsigned)(__ballot(v1[x] == mx) >> (16 * q)) & 0xffffu;
-                const int mi = __ffs(h0 | h1 << 16) - 1;
-                float e1 = __expf(v0[x] - mx) + __expf(v1[x] - mx);
-                float eT = __expf((v0[x] - mx) * a.inv_temp) + __expf((v1[x] - mx) * a.inv_temp);
-                e1 += dpp_move<0xB1>(e1); eT += dpp_move<0xB1>(eT);
-                e1 += dpp_move<0x4E>(e1); eT += dpp_move<0x4E>(eT);
-                e1 += dpp_move<0x141>(e1); eT += dpp_move<0x141>(eT);
-                e1 += dpp_move<0x140>(e1); eT += dpp_move<0x140>(eT);
-                const int m = i * 16 + q * 4 + x;
-                if (r == 0 && m < a.M && blk < nblk) a.samp_part[(int64_t)m * nblk + blk] = make_float4(mx, eT, e1, __int_as_float(mi));
+                for (int x = 0; x < 4; ++x) v[x] += o[x];
             }
-        }
-    } else {
-        for (int t = wave; t < MT * CT; t += 8) {
-            const int i = t / CT, j = t % CT;
-            const floatx4 v = sum(i, j);
+            return v;
+        };
+        if constexpr (EPI == MG_SAMPLE) {
+            // statistics of 32-column blocks = two tiles; ties of the maximum go to the lowest column
+            const int nblk = a.N / 32;
+            for (int t = wave; t < IB * CT / 2; t += 8) {
+                const int i = t / (CT / 2), jp = t % (CT / 2), blk = blockIdx.x * (CT / 2) + jp;
+                const floatx4 v0 = sum(i, 2 * jp), v1 = sum(i, 2 * jp + 1);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const int m = i * 16 + q * 4 + x;
-                if constexpr (EPI == MG_SWIGLU) {
-                    const float up = __shfl_xor(v[x], 8, RL_WAVE);      // lanes r < 8 hold the gate, r + 8 the up column
-                    const int n = (t0 + j) * 8 + r;
-                    if (r < 8 && m < a.M && n < a.N) {
-                        const float act = swiglu_act(v[x], up);
-                        f16_t hi, lo;
-                        split_f16(act, hi, lo);
-                        f16_t* o = a.outH + (int64_t)m * a.ldc + n;
-                        o[0] = hi;
-                        if (a.split_out) o[a.N] = lo;
+                for (int x = 0; x < 4; ++x) {
+                    float mx = fmaxf(v0[x], v1[x]);
+                    mx = fmaxf(mx, dpp_move<0xB1>(mx));    // quad_perm [1,0,3,2]
+                    mx = fmaxf(mx, dpp_move<0x4E>(mx));    // quad_perm [2,3,0,1]
+                    mx = fmaxf(mx, dpp_move<0x141>(mx));   // row_half_mirror
+                    mx = fmaxf(mx, dpp_move<0x140>(mx));   // row_mirror
+                    const unsigned h0 = (unsigned)(__ballot(v0[x] == mx) >> (16 * q)) & 0xffffu;
+                    const unsigned h1 = (unsigned)(__ballot(v1[x] == mx) >> (16 * q)) & 0xffffu;
+                    const int mi = __ffs(h0 | h1 << 16) - 1;
+                    float e1 = __expf(v0[x] - mx) + __expf(v1[x] - mx);
+                    float eT = __expf((v0[x] - mx) * a.inv_temp) + __expf((v1[x] - mx) * a.inv_temp);
+                    e1 += dpp_move<0xB1>(e1); eT += dpp_move<0xB1>(eT);
+                    e1 += dpp_move<0x4E>(e1); eT += dpp_move<0x4E>(eT);
+                    e1 += dpp_move<0x141>(e1); eT += dpp_move<0x141>(eT);
+                    e1 += dpp_move<0x140>(e1); eT += dpp_move<0x140>(eT);
+                    const int m = (i0 + i) * 16 + q * 4 + x;
+                    if (r == 0 && m < a.M && blk < nblk) a.samp_part[(int64_t)m * nblk + blk] = make_float4(mx, eT, e1, __int_as_float(mi));
+                }
+            }
+        } else {
+            for (int t = wave; t < IB * CT; t += 8) {
+                const int i = t / CT, j = t % CT;
+                const floatx4 v = sum(i, j);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const int m = (i0 + i) * 16 + q * 4 + x;
+                    if constexpr (EPI == MG_SWIGLU) {
+                        const float up = __shfl_xor(v[x], 8, RL_WAVE);      // lanes r < 8 hold the gate, r + 8 the up column
+                        const int n = (t0 + j) * 8 + r;
+                        if (r < 8 && m < a.M && n < a.N) {
+                            const float act = swiglu_act(v[x], up);
+                            f16_t hi, lo;
+                            split_f16(act, hi, lo);
+                            f16_t* o = a.outH + (int64_t)m * a.ldc + n;
+                            o[0] = hi;
+                            if (a.split_out) o[a.N] = lo;
+                        }
+                    } else {
+                        const int n = (t0 + j) * 16 + r;
+                        if (m < a.M && n < a.N) a.outF[(int64_t)blockIdx.z * a.split_stride + (int64_t)m * a.ldc + n] = v[x];
                     }
-                } else {
-                    const int n = (t0 + j) * 16 + r;
-                    if (m < a.M && n < a.N) a.outF[(int64_t)blockIdx.z * a.split_stride + (int64_t)m * a.ldc + n] = v[x];
                 }
             }
         }
     }
 }
 
-// Tiles per workgroup and splits over K.  A workgroup's time goes with its k-tiles x (CT + 1) -- W's tiles and, from L2,
-// the rows of A -- times the rounds of 256 workgroups; each split costs its consumer a pass over the partial sums.
-// Of the measured candidates the rule takes the fastest or one within 3 % (8B QKV 3 x 2 splits, O and down 4 x 4, gate/up
-// 7, 1B O 2 x 4, down 4 x 8, gate/up 4, 70B QKV 5 x 2, O and down 8 x 4, gate/up 7, LM heads 8).  The rule must not look
-// at the rows: a row's bits would depend on its batch-mates.  z: in, the number of splits, 0 for the best; out, theirs.
-static void stream_plan(int epi, int N, int K, int& ct, int& z) {
+// Tiles per workgroup and splits over K.  A workgroup's time goes with its k-tiles x (CT + what its rows of A cost), times
+// the rounds of 256 workgroups; each split costs its consumer a pass over the partial sums.  Both costs are those of the
+// context's limit (64 rows or 128).  Of the measured candidates the rule takes the fastest or one within 3 %: up to 64 rows 8B QKV
+// 3 x 2 splits, O and down 4 x 4, gate/up 7, 1B O 2 x 4, down 4 x 8, gate/up 4, 70B QKV 5 x 2, O and down 8 x 4, gate/up 7, LM
+// heads 8; up to 128 rows 8B QKV 6 x 4 (17.2 us; 3 x 2: 20), O 4 x 4 (13.2; 8 x 8: 15.2), down 8 x 8 (31.6; 4 x 4: 35), gate/up 7.
+// The rule must not look at the rows of a call: a row's bits would depend on its batch-mates.  z: in, the number of splits, 0
+// for the best; out, theirs.
+static void stream_plan(int epi, int N, int K, int max_rows, int& ct, int& z) {
     const int tiles = (epi == MG_SWIGLU ? 2 * N : N) / 16, units = K / GS_KT;
     const int zmin = z > 0 ? z : 1, zmax = z > 0 ? z : (units < 8 ? units : 8);
+    const float rows = max_rows <= 64 ? 1.f : 4.f, split = max_rows <= 64 ? 1.8f : 5.f;
     float best = 0.f;
     ct = 0;
     for (int zz = zmin; zz <= zmax; ++zz) {
@@ -206,21 +239,21 @@ static void stream_plan(int epi, int N, int K, int& ct, int& z) {
         for (int c = 1; c <= 8; ++c) {
             if (epi == MG_SAMPLE && c % 2 != 0) continue;
             const int wgs = (tiles + c - 1) / c * zz;
-            const float cost = (float)((wgs + 255) / 256) * (float)per * (float)(c + 1) + 1.8f * (float)zz * (float)N / 2048.f;
+            const float cost = (float)((wgs + 255) / 256) * (float)per * ((float)c + rows) + split * (float)zz * (float)N / 2048.f;
             if (ct == 0 || cost < best) { best = cost; ct = c; z = zz; }
         }
     }
 }
 
-bool k_gemm_stream_supported(int epi, int N, int K, int Kw) {
+bool k_gemm_decode_supported(int epi, int N, int K, int Kw) {
     if (epi != MG_STORE_F32 && epi != MG_SWIGLU && epi != MG_SAMPLE) return false;
     const int rows = epi == MG_SWIGLU ? 2 * N : N;
     return K > 0 && K % GS_KT == 0 && Kw % GS_KT == 0 && rows % 32 == 0 && (uint64_t)rows * Kw * 2 < (1ull << 32);
 }
 
-int k_gemm_stream_splits(int N, int K) {
+int k_gemm_decode_splits(int N, int K, int max_rows) {
     int ct, z = 0;
-    stream_plan(MG_STORE_F32, N, K, ct, z);
+    stream_plan(MG_STORE_F32, N, K, max_rows, ct, z);
     return z;
 }
 
@@ -240,11 +273,13 @@ static void launch_stream_ct(const GemmArgs& a, int tiles, int z, hipStream_t s)
         if (a.w_f16) {
             if (a.M <= 16) launch_stream_t<EPI, 1, CT, true>(a, tiles, z, s);
             else if (a.M <= 32) launch_stream_t<EPI, 2, CT, true>(a, tiles, z, s);
-            else launch_stream_t<EPI, 4, CT, true>(a, tiles, z, s);
+            else if (a.M <= 64) launch_stream_t<EPI, 4, CT, true>(a, tiles, z, s);
+            else launch_stream_t<EPI, 8, CT, true>(a, tiles, z, s);
         } else {
             if (a.M <= 16) launch_stream_t<EPI, 1, CT, false>(a, tiles, z, s);
             else if (a.M <= 32) launch_stream_t<EPI, 2, CT, false>(a, tiles, z, s);
-            else launch_stream_t<EPI, 4, CT, false>(a, tiles, z, s);
+            else if (a.M <= 64) launch_stream_t<EPI, 4, CT, false>(a, tiles, z, s);
+            else launch_stream_t<EPI, 8, CT, false>(a, tiles, z, s);
         }
     }
 }
@@ -262,14 +297,21 @@ static void launch_stream(const GemmArgs& a, int tiles, int ct, int z, hipStream
     }
 }
 
-void k_gemm_stream(int epi, GemmArgs a, int splits, hipStream_t s) {
+static int g_decode_tile_above = -1;   // measurement switch: rows above which the 128 x 128 tile kernel runs; < 0: never
+void k_gemm_decode_tile_above(int rows) { g_decode_tile_above = rows; }
+
+void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s) {
     if (a.Kw <= 0) a.Kw = a.K;
-    if (a.M <= 0 || a.M > 64 || !k_gemm_stream_supported(epi, a.N, a.K, a.Kw)) return;   // callers check first
+    if (a.M <= 0 || a.M > 128 || !k_gemm_decode_supported(epi, a.N, a.K, a.Kw)) return;   // callers check first
     int ct, z = epi == MG_STORE_F32 && splits > 1 ? splits : 1;
-    stream_plan(epi, a.N, a.K, ct, z);
+    stream_plan(epi, a.N, a.K, max_rows, ct, z);
     if (ct == 0) return;                                       // a split count that is not one of this K's
     a.k_per_split = (a.K / GS_KT + z - 1) / z * GS_KT;
     a.Wrows = epi == MG_SWIGLU ? a.up_offset + a.N : a.N;
+    if (g_decode_tile_above >= 0 && a.M > g_decode_tile_above && epi != MG_SAMPLE && (epi == MG_SWIGLU ? 2 * a.N : a.N) % 128 == 0) {
+        k_gemm_tile_decode(epi, a, z, s);                      // splits K the same way
+        return;
+    }
     a.rotate_k = (a.Kw & (a.Kw - 1)) == 0;
     const int tiles = (epi == MG_SWIGLU ? 2 * a.N : a.N) / 16;
     if (epi == MG_STORE_F32) launch_stream<MG_STORE_F32>(a, tiles, ct, z, s);

@@ -420,12 +420,6 @@ struct Scratch { char* p = nullptr; size_t bytes = 0; };
 // 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.
 static const int kConvertRows = 4096;
 
-// Decode GEMMs of contexts of at most 64 rows run on the streaming kernel, others on the ring kernel.  The rule looks at
-// the context's limit, not at the rows of a call: a row's bits do not depend on its batch-mates.
-static bool streams(const rl_ctx* c, int epi, int N, int K, int Kw) {
-    return c->cfg.max_batch <= 64 && k_gemm_stream_supported(epi, N, K, Kw);
-}
-
 static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s, Scratch idle = {}) {
     ProfScope ps(c, cls, s);
     GemmArgs a = a0;
@@ -437,10 +431,9 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
         return it != c->other_shadow_of.end() ? it->second : nullptr;
     };
     if (cls == RL_K_GEMM_DECODE && a.M <= 128 && (epi == MG_STORE_F32 || epi == MG_SWIGLU || epi == MG_SAMPLE) &&
-        k_gemm_decode_supported(epi, a.N, a.K)) {
+        k_gemm_decode_supported(epi, a.N, a.K, a.Kw > 0 ? a.Kw : a.K)) {
         if (const void* h = copy_of((const void*)a.W)) { a.W = (const bf16_t*)h; a.w_f16 = 1; }
-        if (streams(c, epi, a.N, a.K, a.Kw > 0 ? a.Kw : a.K)) k_gemm_stream(epi, a, splits, s);
-        else k_gemm_decode(epi, a, splits, s);
+        k_gemm_decode(epi, a, splits, c->cfg.max_batch, s);
     } else {
         if (k_gemm_mfma_reads_f16_copy(epi, a, splits)) {
             const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * (a.Kw > 0 ? a.Kw : a.K);
@@ -455,15 +448,11 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
     }
 }
 
-// Split count for a decode GEMM of n rows with N output columns: one 8-wave workgroup per CU and 128-column
-// tiles, so aim for as many workgroups as fit in one round of 256 CUs.  Returns the number of partial
-// buffers the kernel that mfma() picks for this shape will actually write.
+// Split count for a decode GEMM of n rows with N output columns: the number of partial buffers that the kernel which
+// mfma() picks for this shape will write.
 static int decode_splits(const rl_ctx* c, int n, int N, int K, int Kw) {
-    if (k_gemm_decode_supported(MG_STORE_F32, N, K) && streams(c, MG_STORE_F32, N, K, Kw)) return k_gemm_stream_splits(N, K);
-    int want = std::max(1, 256 / std::max(1, N / 128));
-    want = std::min(want, kMaxSplitK);
-    if (n <= 128 && k_gemm_decode_supported(MG_STORE_F32, N, K)) return k_gemm_decode_splits_used(K, want);
-    return k_gemm_mfma_splits_used(K, want);
+    if (n <= 128 && k_gemm_decode_supported(MG_STORE_F32, N, K, Kw)) return k_gemm_decode_splits(N, K, c->cfg.max_batch);
+    return k_gemm_mfma_splits_used(K, std::min(std::max(1, 256 / std::max(1, N / 128)), kMaxSplitK));
 }
 
 // bf16 weights / fp16 activations on the MFMA kernels.  paged: h holds the first layer's norm output (k_step_start).
@@ -1083,7 +1072,7 @@ static int decode_step_impl(rl_ctx* c, const rl_sample_cfg* sample, const int32_
     // only per-block statistics (16 bytes per row and 32 columns, in the same buffer), from which the sampler draws
     // and re-derives the 32 logits of the one block it lands in: the step's logits never reach memory.
     const bool fused = c->impl == 1 && c->fused_sample && B <= 128 && m.vocab % 128 == 0 && m.d_model % 8 == 0 &&
-                       k_gemm_decode_supported(MG_SAMPLE, m.vocab, m.d_model) &&
+                       k_gemm_decode_supported(MG_SAMPLE, m.vocab, m.d_model, m.d_model) &&
                        (size_t)B * (m.vocab / 32) * sizeof(float4) <= (size_t)L.logit_rows * m.vocab * 4;
     if (fused) {
         GemmArgs g;

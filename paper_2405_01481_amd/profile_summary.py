@@ -22,7 +22,7 @@ import subprocess
 import sys
 
 # kernel name pattern -> class of bench.py's roofline entries (the LM-head GEMM is the tile kernel with epilogue 5)
-CLASSES = {r"gemm_ring_kernel": "gemm_decode", r"attn_decode_kernel": "attn_decode",
+CLASSES = {r"gemm_(stream|ring)_kernel": "gemm_decode", r"attn_decode_kernel": "attn_decode",
            r"gemm_dma8?_kernel<[0-4][,>]": "gemm_prefill", r"gemm_dma8?_kernel<5[,>]": "lmhead_score",
            r"attn_prefill_kernel": "attn_prefill"}
 

@@ -1,4 +1,4 @@
-"""The decode step's weight-streaming GEMMs (contexts of at most 64 rows): one, two and four 16-row tiles of activations
+"""The decode step's weight-streaming GEMMs (contexts of at most 64 and 128 rows): one to eight 16-row tiles of activations
 with remainders, every number of column tiles a workgroup may take, K split and not, rows of a power of two long (start
 rotated) and not, bf16 weights and an fp16 copy -- against the oracle, and row by row against smaller batches."""
 import numpy as np
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 # column tiles of the gate/up GEMM and the LM head: 7 and 8; 3 and 4; 5 and 6; 4 (last one short) and 2; widths that
-# are no multiple of 128 (C's FFN: the pair layer's down projection wraps inside a k-tile and stays on the ring kernel)
+# are no multiple of 128 (C's FFN: the pair layer's down projection wraps inside a k-tile and stays on the 128 x 128 tile kernel)
 SHAPES = [
     synth.ModelShape("stream_a", 2, 1024, 8, 2, 128, 14336, 32768, 10000.0, "bf16", 0.02),
     synth.ModelShape("stream_b", 2, 384, 6, 3, 64, 6144, 12288, 10000.0, "bf16", 0.04),
@@ -23,10 +23,11 @@ SHAPES = [
 ]
 
 
+@pytest.mark.parametrize("most", [64, 128])
 @pytest.mark.parametrize("copy", [False, True], ids=["bf16", "fp16copy"])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
-def test_stream_gemm_rows_and_widths(shape, copy):
-    P, G, most = 9, 4, 64
+def test_stream_gemm_rows_and_widths(shape, copy, most):
+    P, G = 9, 4
     w = synth.make_weights(shape, 1, DEV)
     cfg = R.make_cfg(shape, most, P + G)
     shadow = torch.empty(R.rollout_weight_shadow_bytes(cfg), dtype=torch.uint8, device=DEV) if copy else None
@@ -34,15 +35,16 @@ def test_stream_gemm_rows_and_widths(shape, copy):
     m = O.Model(shape, synth.weights_for_oracle(w))
     ids, lens = synth.make_prompts(shape.vocab, most, P, 3, 3)
     res = {}
-    for n in (1, 15, 16, 17, 33, 64):
+    few = (1, 15, 16, 17, 33) if most == 64 else (1, 17, 33, 64, 65, 113)
+    for n in few + (most,):
         out = torch.full((n, G), -1, dtype=torch.int32, device=DEV)
         lp = torch.full((n, G), 9.0, dtype=torch.float32, device=DEV)
         ro.rollout_generate(R.sample_cfg(4, 0.8), torch.tensor(ids[:n], device=DEV), lens[:n], G, out, None, lp)
         ro.rollout_check()
         res[n] = (out.cpu().numpy(), lp.cpu().numpy())
-    for n in (1, 15, 16, 17, 33):                      # a row's bits do not depend on its batch-mates
-        assert np.array_equal(res[n][0], res[64][0][:n]) and np.array_equal(res[n][1], res[64][1][:n]), n
-    verify_rollout(m, [ids[b, :lens[b]] for b in range(most)], *res[64], 0.8, 4, 0, 1e-3, 2e-2, rows=[0, 16, 63])
+    for n in few:                                      # a row's bits do not depend on its batch-mates
+        assert np.array_equal(res[n][0], res[most][0][:n]) and np.array_equal(res[n][1], res[most][1][:n]), n
+    verify_rollout(m, [ids[b, :lens[b]] for b in range(most)], *res[most], 0.8, 4, 0, 1e-3, 2e-2, rows=[0, 16, most - 1])
     ro.close()
 
 
