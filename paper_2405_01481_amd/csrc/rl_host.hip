@@ -416,7 +416,7 @@ struct Scratch { char* p = nullptr; size_t bytes = 0; };
 
 // Rows from which a GEMM on bf16 weights without an fp16 copy is worth one, made just before it in idle workspace: the
 // copy moves 4 bytes per weight, the kernel then runs without conversions beside its MFMAs, which saves a tenth of its
-// time and therefore grows with the rows.  Same bits.  Measured on whole passes: 70B width, 12544 rows 245.0 -> 233.4 ms;
+// time and therefore grows with the rows (a pair layer's count twice: it multiplies every weight twice).  Same bits.  Measured on whole passes: 70B width, 12544 rows 245.0 -> 233.4 ms;
 // 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.
 static const int kConvertRows = 4096;
 
@@ -436,10 +436,11 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
         k_gemm_decode(epi, a, splits, c->cfg.max_batch, s);
     } else {
         if (k_gemm_mfma_reads_f16_copy(epi, a, splits)) {
-            const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * (a.Kw > 0 ? a.Kw : a.K);
+            const int kw = a.Kw > 0 ? a.Kw : a.K;
+            const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * kw;
             if (const void* h = copy_of((const void*)a.W)) {
                 a.W = (const bf16_t*)h; a.w_f16 = 1;
-            } else if (a.M >= kConvertRows && idle.bytes >= 2 * elems) {
+            } else if ((int64_t)a.M * (a.K / kw) >= kConvertRows && idle.bytes >= 2 * elems) {
                 k_bf16_to_f16(a.W, idle.p, (int64_t)elems, s);
                 a.W = (const bf16_t*)idle.p; a.w_f16 = 1;
             }
@@ -486,11 +487,9 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
         const int sp = l < c->precise, sp_next = l + 1 < c->precise && l + 1 < m.n_layers;
         GemmArgs g;
         g.M = n;
-        // the FFN activation's buffer is as wide as a pair layer needs it: in a plain layer its rows end half way (all
-        // widths are multiples of 64, so the copy's start is 16-byte aligned)
-        Scratch idle;
-        if (!paged && !sp && L.ffn_bytes > (size_t)n * m.d_ffn * 2)
-            idle = {c->at<char>(L.ffn) + (size_t)n * m.d_ffn * 2, L.ffn_bytes - (size_t)n * m.d_ffn * 2};
+        // idle workspace (all offsets are multiples of 256): the FFN activation's buffer up to the gate/up GEMM, the buffers
+        // of the attention block from there on
+        const Scratch idle_ffn = {c->at<char>(L.ffn), L.ffn_bytes}, idle_attn = {c->at<char>(L.qkv), L.ffn - L.qkv};
         if (paged) {
             // weight-streaming GEMMs, split over K; consumers reduce the partial sums
             g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.wqkv[l]; g.N = L.nqkv;
@@ -529,21 +528,21 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             g.pool = write_pages ? (f16_t*)c->pool : nullptr; g.block_table = bt; g.mpps = L.mpps; g.layer = l;
             g.Hq = m.n_q_heads; g.Hkv = m.n_kv_heads; g.hd = m.head_dim; g.geo = c->geo; g.vt_cap = L.vt_cap;
             g.split_out = sp; g.layer_lo = m.n_layers + l;
-            mfma(c, gcls, MG_QKV, g, 1, s, idle);
+            mfma(c, gcls, MG_QKV, g, 1, s, idle_ffn);
             attention(c, l, n, false, max_ctx, nblocks, s);
             g = GemmArgs();
             g.M = n; g.A = att; pair_in(g, qd, sp); g.W = (const bf16_t*)W.wo[l]; g.N = m.d_model;
             g.outF = x; g.ldc = m.d_model;
-            mfma(c, gcls, MG_RESID, g, 1, s, idle);
+            mfma(c, gcls, MG_RESID, g, 1, s, idle_ffn);
             k_rmsnorm(1, x, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
             g = GemmArgs();
             g.M = n; g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.w_gate_up[l]; g.N = m.d_ffn;
             g.up_offset = m.d_ffn; g.outH = ffn; g.ldc = sp ? 2 * m.d_ffn : m.d_ffn; g.split_out = sp;
-            mfma(c, gcls, MG_SWIGLU, g, 1, s, idle);
+            mfma(c, gcls, MG_SWIGLU, g, 1, s, idle_attn);
             g = GemmArgs();
             g.M = n; g.A = ffn; pair_in(g, m.d_ffn, sp); g.W = (const bf16_t*)W.w_down[l]; g.N = m.d_model;
             g.outF = x; g.ldc = m.d_model;
-            mfma(c, gcls, MG_RESID, g, 1, s, idle);
+            mfma(c, gcls, MG_RESID, g, 1, s, idle_attn);
         }
     }
     return paged;
