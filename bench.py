@@ -497,14 +497,17 @@ def main():
 
     n_tok_scored = 2 * float(seq_len.sum()) if not args.no_score else 0.0
     n_tok_prefill = float(np.sum(plen - 1))
-    attn_pairs = sum(int(L_) * (int(L_) + 1) / 2.0 for L_ in seq_len) * (2 if not args.no_score else 0) + \
-        sum(int(p_ - 1) * int(p_) / 2.0 for p_ in plen)
+    # prompt prefill ends with the last layer's keys and values: no attention, output projection or FFN there
+    prefill_layers = shape.n_layers - 1
+    prefill_params = shape.body_params() * prefill_layers / shape.n_layers + 2.0 * shape.n_kv_heads * shape.head_dim * shape.d_model
+    attn_pairs = shape.n_layers * sum(int(L_) * (int(L_) + 1) / 2.0 for L_ in seq_len) * (2 if not args.no_score else 0) + \
+        prefill_layers * sum(int(p_ - 1) * int(p_) / 2.0 for p_ in plen)
     work = {
-        "gemm_prefill": ("mfma", 2.0 * shape.body_params() * (n_tok_scored + n_tok_prefill) / 1e12, "TFLOP",
+        "gemm_prefill": ("mfma", 2.0 * (shape.body_params() * n_tok_scored + prefill_params * n_tok_prefill) / 1e12, "TFLOP",
                          "large-M MFMA GEMMs of prefill and scoring (gemm_dma8_kernel 256x256 / gemm_mfma_kernel 128x128)"),
         "lmhead_score": ("mfma", 2.0 * shape.head_params() * max(n_tok_scored - 2 * B, 0) / 1e12, "TFLOP",
                          "LM head + log-sum-exp + target gather (MG_LSE epilogue)"),
-        "attn_prefill": ("mfma", shape.n_layers * 4.0 * shape.n_q_heads * shape.head_dim * attn_pairs / 1e12, "TFLOP",
+        "attn_prefill": ("mfma", 4.0 * shape.n_q_heads * shape.head_dim * attn_pairs / 1e12, "TFLOP",
                          "causal prefill attention (attn_prefill_kernel)"),
         "gemm_decode": ("hbm", G * gemm_decode_bytes_per_step(shape, B) / 1e9, "GB",
                         "weight-streaming decode GEMMs (gemm_stream_kernel)"),

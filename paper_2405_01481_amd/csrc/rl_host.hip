@@ -317,7 +317,8 @@ static void gemm(rl_ctx* c, int cls, int epi, const void* A, int lda, const void
 // ---------------------------------------------------------------- decoder layers on n packed tokens
 // Inputs: x (fp32 residual stream) filled by the embedding, tok_pos / tok_slot descriptors.
 // paged = attention reads the paged cache (decode); else the chunk's own contiguous K/V.
-// write_pages = append K/V of these tokens to the paged cache.
+// write_pages = append K/V of these tokens to the paged cache; unpaged, that is all the pass is for (prompt prefill), and
+// the residual stream it leaves is undefined.
 // Returns true when h already holds RMSNorm(x; final_norm) (the tuned decode path fuses it).
 // qkv_part (decode, tuned kernels, plain layers): the QKV projection's split-K partial rows, which the attention
 // kernel then consumes itself instead of reading rotated queries and an already appended cache.
@@ -402,6 +403,7 @@ static bool run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged,
         if (!paged)
             k_rope_append(dt, qkv, n, tpos, tslot, rope, q, kb, vb, write_pages ? c->pool : nullptr, l, c->geo, bt, L.mpps,
                           m.n_q_heads, s);
+        if (!paged && write_pages && l + 1 == m.n_layers) break;   // prefill: nothing reads what lies behind the last keys and values
         attention(c, l, n, paged, max_ctx, nblocks, s);
         gemm(c, gcls, EPI_RESID, att, qd, W.wo[l], nullptr, n, m.d_model, qd, x, nullptr, m.d_model, s);
         const char* wg = (const char*)W.w_gate_up[l];
@@ -420,7 +422,8 @@ struct Scratch { char* p = nullptr; size_t bytes = 0; };
 // 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.
 static const int kConvertRows = 4096;
 
-static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s, Scratch idle = {}) {
+// w_skip: elements of a0.W that lie before the rows this GEMM uses (a0.W itself is what a weight set's copy is found by).
+static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s, Scratch idle = {}, size_t w_skip = 0) {
     ProfScope ps(c, cls, s);
     GemmArgs a = a0;
     a.big_mode = c->big_mode;
@@ -441,10 +444,12 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
             if (const void* h = copy_of((const void*)a.W)) {
                 a.W = (const bf16_t*)h; a.w_f16 = 1;
             } else if ((int64_t)a.M * (a.K / kw) >= kConvertRows && idle.bytes >= 2 * elems) {
-                k_bf16_to_f16(a.W, idle.p, (int64_t)elems, s);
+                k_bf16_to_f16(a.W + w_skip, idle.p, (int64_t)elems, s);
                 a.W = (const bf16_t*)idle.p; a.w_f16 = 1;
+                w_skip = 0;
             }
         }
+        a.W += w_skip;
         k_gemm_mfma(epi, a, splits, s);
     }
 }
@@ -528,6 +533,13 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             g.pool = write_pages ? (f16_t*)c->pool : nullptr; g.block_table = bt; g.mpps = L.mpps; g.layer = l;
             g.Hq = m.n_q_heads; g.Hkv = m.n_kv_heads; g.hd = m.head_dim; g.geo = c->geo; g.vt_cap = L.vt_cap;
             g.split_out = sp; g.layer_lo = m.n_layers + l;
+            // Prompt prefill ends with the last layer's keys and values: nothing reads the residual stream behind them, so
+            // that layer runs the key and value columns of its QKV projection and no more.
+            if (write_pages && l + 1 == m.n_layers) {
+                g.N = 2 * m.n_kv_heads * m.head_dim; g.Hq = 0; g.q_out = g.k_out = g.v_out = nullptr;
+                mfma(c, gcls, MG_QKV, g, 1, s, idle_ffn, (size_t)qd * m.d_model);
+                continue;
+            }
             mfma(c, gcls, MG_QKV, g, 1, s, idle_ffn);
             attention(c, l, n, false, max_ctx, nblocks, s);
             g = GemmArgs();
