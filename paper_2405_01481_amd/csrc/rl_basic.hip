@@ -77,6 +77,14 @@ void k_put_rows(const int* seq_first_h, const int* row_slot_h, const int* row_st
         put_rows_kernel<<<1, 256, 0, s>>>(r, m, o, seq_first, row_slot, row_start, row_len);
     }
 }
+// List of the rows first[i] .. first[i] + count[i] - 1 of every sequence i, from at[i] on.
+__global__ void list_rows_kernel(const int* at, const int* first, const int* count, int* rows) {
+    const int i = blockIdx.x;
+    for (int j = threadIdx.x; j < count[i]; j += blockDim.x) rows[at[i] + j] = first[i] + j;
+}
+void k_list_rows(const int* at, const int* first, const int* count, int n, int* rows, hipStream_t s) {
+    if (n > 0) list_rows_kernel<<<n, 256, 0, s>>>(at, first, count, rows);
+}
 // Pack rows of a padded [*, ld_ids] id matrix into a flat token list.
 // Row r of the chunk is batch row seq_first[r]; its row_len[r] tokens go to
 // [row_start[r], row_start[r] + row_len[r]).  tok_tgt (optional) = next token id of the
@@ -237,11 +245,13 @@ __device__ __forceinline__ void put_pair4(T* o, int64_t lo_off, float4 v, float 
 
 // ---------------------------------------------------------------- RMSNorm: out = x * rsqrt(mean(x^2) + eps) * g
 // split: the output row is twice as wide, [d values rounded to T | d remainders] (fp16 pairs).
+// rows (optional): output row n is the norm of row rows[n].
 template <typename T, typename TW>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const TW* g, T* out, int d, float eps, int split) {
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const TW* g, T* out, int d, float eps, int split,
+                                                      const int* rows) {
     __shared__ float red[16];
     int n = blockIdx.x;
-    const float* xr = x + (int64_t)n * d;
+    const float* xr = x + (int64_t)(rows ? rows[n] : n) * d;
     T* o = out + (int64_t)n * d * (split ? 2 : 1);
     if (d % 4 == 0 && d <= 8192) {
         // the row is read once, 16 bytes per lane, and kept in registers between the two passes
@@ -270,10 +280,11 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const TW* 
     float rs = 1.0f / sqrtf(ss / (float)d + eps);
     for (int j = threadIdx.x; j < d; j += 256) put_pair(o + j, d, xr[j] * rs * to_f(g[j]), split);
 }
-void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split) {
+void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split,
+               const int* rows) {
     if (n <= 0) return;
-    if (dtype == 0) rmsnorm_kernel<float, float><<<n, 256, 0, s>>>(x, (const float*)g, (float*)out, d, eps, 0);
-    else rmsnorm_kernel<f16_t, bf16_t><<<n, 256, 0, s>>>(x, (const bf16_t*)g, (f16_t*)out, d, eps, split);
+    if (dtype == 0) rmsnorm_kernel<float, float><<<n, 256, 0, s>>>(x, (const float*)g, (float*)out, d, eps, 0, rows);
+    else rmsnorm_kernel<f16_t, bf16_t><<<n, 256, 0, s>>>(x, (const bf16_t*)g, (f16_t*)out, d, eps, split, rows);
 }
 
 // ---------------------------------------------------------------- start of a decode step
@@ -1291,12 +1302,12 @@ void k_ppo_reward(const float* kl, const float* seq_reward, const int* seq_len, 
 // positions (pos + 1 >= max(prompt_len, 1)); rows without a next token inside their sequence are skipped.
 __global__ __launch_bounds__(64) void kl_full_reduce_kernel(const float* part, int nparts, const int* tok_tgt,
                                                             const int* tok_slot, const int* tok_pos,
-                                                            const int* prompt_len, float* out, int ld_out) {
-    const int r = blockIdx.x;
+                                                            const int* prompt_len, const int* rows, float* out, int ld_out) {
+    const int r = rows[blockIdx.x];                 // row of the packed token list behind the compacted row blockIdx.x
     if (tok_tgt[r] < 0) return;
     const int slot = tok_slot[r], t = tok_pos[r] + 1;
     if (t < max(prompt_len[slot], 1)) return;
-    const float* p = part + (int64_t)r * nparts * 5;
+    const float* p = part + (int64_t)blockIdx.x * nparts * 5;
     float mp = -INFINITY, sp = 0.f, tt = 0.f, mr = -INFINITY, sr = 0.f;
     for (int i = threadIdx.x; i < nparts; i += 64) {
         const float m1 = p[i * 5], s1 = p[i * 5 + 1], t1 = p[i * 5 + 2], m2 = p[i * 5 + 3], s2 = p[i * 5 + 4];
@@ -1316,23 +1327,23 @@ __global__ __launch_bounds__(64) void kl_full_reduce_kernel(const float* part, i
     if (threadIdx.x == 0) out[(int64_t)slot * ld_out + t] = tt / sp - (Mp + logf(sp)) + (Mr + logf(sr));
 }
 void k_kl_full_reduce(const float* part, int nparts, int nrows, const int* tok_tgt, const int* tok_slot,
-                      const int* tok_pos, const int* prompt_len, float* out, int ld_out, hipStream_t s) {
+                      const int* tok_pos, const int* prompt_len, const int* rows, float* out, int ld_out, hipStream_t s) {
     if (nrows <= 0) return;
-    kl_full_reduce_kernel<<<nrows, 64, 0, s>>>(part, nparts, tok_tgt, tok_slot, tok_pos, prompt_len, out, ld_out);
+    kl_full_reduce_kernel<<<nrows, 64, 0, s>>>(part, nparts, tok_tgt, tok_slot, tok_pos, prompt_len, rows, out, ld_out);
 }
 
 // The same from two materialised logit rows (plain path): one block per row.
 __global__ __launch_bounds__(1024) void kl_full_rows_kernel(const float* zp, const float* zr, int ldz, int V,
                                                             const int* tok_tgt, const int* tok_slot,
-                                                            const int* tok_pos, const int* prompt_len, float* out,
+                                                            const int* tok_pos, const int* prompt_len, const int* rows, float* out,
                                                             int ld_out) {
     __shared__ float red[16];
-    const int r = blockIdx.x;
+    const int r = rows[blockIdx.x];
     if (tok_tgt[r] < 0) return;
     const int slot = tok_slot[r], t = tok_pos[r] + 1;
     if (t < max(prompt_len[slot], 1)) return;
-    const float* a = zp + (int64_t)r * ldz;
-    const float* b = zr + (int64_t)r * ldz;
+    const float* a = zp + (int64_t)blockIdx.x * ldz;
+    const float* b = zr + (int64_t)blockIdx.x * ldz;
     float mp = -INFINITY, mr = -INFINITY;
     for (int i = threadIdx.x; i < V; i += 1024) { mp = fmaxf(mp, a[i]); mr = fmaxf(mr, b[i]); }
     mp = block_max(mp, red);
@@ -1350,10 +1361,10 @@ __global__ __launch_bounds__(1024) void kl_full_rows_kernel(const float* zp, con
     if (threadIdx.x == 0) out[(int64_t)slot * ld_out + t] = tt / sp - (mp + logf(sp)) + (mr + logf(sr));
 }
 void k_kl_full_rows(const float* zp, const float* zr, int ldz, int V, int nrows, const int* tok_tgt,
-                    const int* tok_slot, const int* tok_pos, const int* prompt_len, float* out, int ld_out,
+                    const int* tok_slot, const int* tok_pos, const int* prompt_len, const int* rows, float* out, int ld_out,
                     hipStream_t s) {
     if (nrows <= 0) return;
-    kl_full_rows_kernel<<<nrows, 1024, 0, s>>>(zp, zr, ldz, V, tok_tgt, tok_slot, tok_pos, prompt_len, out, ld_out);
+    kl_full_rows_kernel<<<nrows, 1024, 0, s>>>(zp, zr, ldz, V, tok_tgt, tok_slot, tok_pos, prompt_len, rows, out, ld_out);
 }
 
 // ---------------------------------------------------------------- log-prob from per-group (max, sum-exp) partials

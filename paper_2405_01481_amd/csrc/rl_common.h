@@ -113,7 +113,11 @@ void k_prefill_state_slots(const int* ids, int ld_ids, int n, const int* seq_fir
                            int* finished, int* step_count, int* out_row, int* seq_id, int* gen_limit, hipStream_t s);
 void k_embed(int dtype, const int* ids, int n, const void* E, int d, int V, float* x, int* errflag, hipStream_t s);
 // split = 1 (bf16 configurations only): the output row is a row of fp16 pairs, [d hi | d lo], value = hi + lo
-void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split = 0);
+// rows: output row i is the norm of row rows[i]
+void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split = 0,
+               const int* rows = nullptr);
+// rows[at[i] + j] = first[i] + j for j < count[i], i < n (all dev)
+void k_list_rows(const int* at, const int* first, const int* count, int n, int* rows, hipStream_t s);
 void k_gemm_simple(int dtype, int epi, const void* A, int lda, const void* W, const void* W2, int M, int N, int K,
                    float* outF, void* outT, int ldc, hipStream_t s);
 // C = RMSNorm(x; gain) * W^T (EPI_STORE_F32) or SwiGLU of it (W gate, W2 up), all fp32: the norm is part of the GEMM.
@@ -149,10 +153,11 @@ void k_lse_gather(const float* logits, int ldz, int V, int nrows, const int* tok
 void k_kl(const float* lp, const float* lr, const int* seq_len, const int* prompt_len, int B, int Lmax, float coef,
           float* kl, float* pen, hipStream_t s);
 void k_out_len(const int* gen_count, int* out_len, int B, hipStream_t s);
+// rows: the packed token list's row behind each of the nrows compacted ones
 void k_kl_full_reduce(const float* part, int nparts, int nrows, const int* tok_tgt, const int* tok_slot,
-                      const int* tok_pos, const int* prompt_len, float* out, int ld_out, hipStream_t s);
+                      const int* tok_pos, const int* prompt_len, const int* rows, float* out, int ld_out, hipStream_t s);
 void k_kl_full_rows(const float* zp, const float* zr, int ldz, int V, int nrows, const int* tok_tgt,
-                    const int* tok_slot, const int* tok_pos, const int* prompt_len, float* out, int ld_out,
+                    const int* tok_slot, const int* tok_pos, const int* prompt_len, const int* rows, float* out, int ld_out,
                     hipStream_t s);
 void k_value_head(int dtype, const float* x, const void* g, const void* head, int n, int d, float eps,
                   const int* tok_slot, const int* tok_pos, float* out, int ld_out, hipStream_t s);

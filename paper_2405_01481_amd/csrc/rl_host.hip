@@ -1648,17 +1648,34 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
         b0 = chunk_take(c, len_of, b0, B, ch);
         const int n = ch.n;
         if ((rc = pack_chunk(c, ids, Lmax, ch, true, s))) return rc;
+        // The LM heads run on the rows that predict a response token and no others (prompt rows, last tokens and padding are
+        // left out: half of the rows where prompts are half of the tokens).  Their list is kept where the log-sum-exp
+        // path keeps its targets' logits.
+        std::vector<int> at, first, count;
+        int nh = 0;
+        for (size_t i = 0; i < ch.rows_b.size(); ++i) {
+            const int p = std::max(prompt_len[ch.rows_b[i]], 1);
+            at.push_back(nh);
+            first.push_back(ch.starts[i] + p - 1);
+            count.push_back(std::max(0, ch.lens[i] - p));
+            nh += count.back();
+        }
+        int* const rows = c->at<int>(L.z_tgt);
+        k_put_rows(at.data(), ch.rows_b.data(), first.data(), count.data(), (int)at.size(), c->at<int>(L.seq_first),
+                   c->at<int>(L.row_slot), c->at<int>(L.row_start), c->at<int>(L.row_len), s);
+        k_list_rows(c->at<int>(L.seq_first), c->at<int>(L.row_start), c->at<int>(L.row_len), (int)at.size(), rows, s);
         // policy body, final norm; keep its hidden states while the reference body runs on the same rows
         k_embed(m.dtype, c->at<int>(L.tok_ids), n, wp.tok_embed, m.d_model, m.vocab, c->at<float>(L.x),
                 c->at<int>(L.errflag), s);
+        if (nh == 0) continue;                                   // nothing to score; the ids have been looked at
         run_layers(c, wp, n, false, false, ch.max_ctx, ch.nblocks, s);
-        k_rmsnorm(m.dtype, c->at<float>(L.x), wp.final_norm, c->at<char>(L.h_keep), n, m.d_model, m.rms_eps, s);
+        k_rmsnorm(m.dtype, c->at<float>(L.x), wp.final_norm, c->at<char>(L.h_keep), nh, m.d_model, m.rms_eps, s, 0, rows);
         k_embed(m.dtype, c->at<int>(L.tok_ids), n, wr.tok_embed, m.d_model, m.vocab, c->at<float>(L.x),
                 c->at<int>(L.errflag), s);
         run_layers(c, wr, n, false, false, ch.max_ctx, ch.nblocks, s);
-        k_rmsnorm(m.dtype, c->at<float>(L.x), wr.final_norm, c->at<char>(L.h), n, m.d_model, m.rms_eps, s);
-        for (int r0 = 0; r0 < n; r0 += kl_rows) {
-            const int nr = std::min(kl_rows, n - r0);
+        k_rmsnorm(m.dtype, c->at<float>(L.x), wr.final_norm, c->at<char>(L.h), nh, m.d_model, m.rms_eps, s, 0, rows);
+        for (int r0 = 0; r0 < nh; r0 += kl_rows) {
+            const int nr = std::min(kl_rows, nh - r0);
             const char* hp = c->at<char>(L.h_keep) + (size_t)r0 * m.d_model * e;
             const char* hr = c->at<char>(L.h) + (size_t)r0 * m.d_model * e;
             if (fused) {
@@ -1669,9 +1686,8 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
                 g.A2 = (const f16_t*)hr; g.lda2 = m.d_model; g.W2 = (const bf16_t*)wr.lm_head;
                 g.kl_part = c->at<float>(L.lse_part);
                 mfma(c, RL_K_LMHEAD_SCORE, MG_KLFULL, g, 1, s);
-                k_kl_full_reduce(c->at<float>(L.lse_part), nparts, nr, c->at<int>(L.tok_tgt) + r0,
-                                 c->at<int>(L.tok_slot) + r0, c->at<int>(L.tok_pos) + r0, c->at<int>(L.d_prompt_len),
-                                 kl_out, Lmax, s);
+                k_kl_full_reduce(c->at<float>(L.lse_part), nparts, nr, c->at<int>(L.tok_tgt), c->at<int>(L.tok_slot),
+                                 c->at<int>(L.tok_pos), c->at<int>(L.d_prompt_len), rows + r0, kl_out, Lmax, s);
             } else {
                 float* zp = c->at<float>(L.logits);
                 float* zr = zp + (size_t)kl_rows * m.vocab;
@@ -1679,8 +1695,8 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
                      nullptr, m.vocab, s);
                 gemm(c, RL_K_LMHEAD_SCORE, EPI_STORE_F32, hr, m.d_model, wr.lm_head, nullptr, nr, m.vocab, m.d_model, zr,
                      nullptr, m.vocab, s);
-                k_kl_full_rows(zp, zr, m.vocab, m.vocab, nr, c->at<int>(L.tok_tgt) + r0, c->at<int>(L.tok_slot) + r0,
-                               c->at<int>(L.tok_pos) + r0, c->at<int>(L.d_prompt_len), kl_out, Lmax, s);
+                k_kl_full_rows(zp, zr, m.vocab, m.vocab, nr, c->at<int>(L.tok_tgt), c->at<int>(L.tok_slot),
+                               c->at<int>(L.tok_pos), c->at<int>(L.d_prompt_len), rows + r0, kl_out, Lmax, s);
             }
         }
     }
