@@ -9,8 +9,8 @@
 //     batches above 128 rows;
 //   * gemm_dma8_kernel: tiles of 96 to 256 rows x 256 columns, eight waves, operands staged by global ->
 //     LDS loads -- the large-M GEMMs of prefill and scoring;
-//   * gemm_dma_kernel:  128 x 128 tiles staged the same way, two GEMMs on one tile -- the exact
-//     full-vocabulary KL, which needs the policy's and the reference's logits of a tile together;
+//   * gemm_kl8_kernel:  the same loop run twice on tiles of 128 rows -- the exact full-vocabulary KL, which needs the
+//     policy's and the reference's logits of a tile together.
 // Epilogues: fp32 store / split-K partial, fp16 store, residual add, SwiGLU, RoPE + q/k/v split for
 // the QKV projection, log-sum-exp + target gather for the scoring LM head.
 #include "rl_common.h"
@@ -593,204 +593,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------ tile GEMM with global -> LDS staging
-// Four waves (WGM x WGN) per workgroup, tile BM x BN, k-tile 32, four LDS stages.
-// Used as 256 x 256 (2 x 2 waves of 128 x 128, one workgroup per CU) for the large-M GEMMs: 16
-// accumulator tiles per wave, so one k-slice of 16 costs 8 LDS fragment reads for 16 MFMAs -- half the
-// LDS traffic per flop of the 128 x 128 register-staged kernel above, which is bound by it.  (Split over
-// K works too -- blockIdx.z, partial sums to outF + split * split_stride -- but is not used.)
-//  * Operands are staged by global -> LDS loads (no registers in between); rows are 64 B and the 16-byte
-//    chunks of a row are XOR-swizzled with (row >> 2) & 3 -- on the source side of the load -- so that
-//    the fragment reads are bank-conflict free without padding.  W stays bf16 in LDS and is converted
-//    to fp16 in registers after the fragment read.
-//  * The staging loads are issued from inline assembly: the compiler's wait-count pass would otherwise
-//    force every one of them to complete at each barrier.  vmcnt is therefore managed by hand -- a
-//    tile's loads are issued three k-tiles ahead, and every step waits until at most the two youngest
-//    tiles are in flight.  The loop issues the same number of loads on every trip (the last trips
-//    re-request the final tile), so the counts hold to the end; vmcnt(0) before the epilogue makes
-//    sure no load can land in LDS after the workgroup has ended.  Loads the compiler adds (none in the
-//    loop) could only make these waits stricter: completion is in order.
-//  * The instruction order inside a k-slice is fixed with scheduling fences: one MFMA, then a unit of
-//    the next slice's preparation (fragment reads and staging loads in the first half of the slice, the
-//    conversion of the W fragments in the second).
-//  * One barrier per k-tile: after it, every wave has read its last fragments of the tile's stage, which
-//    can then be refilled, and the next tile is complete in LDS.
-// Requires (k extent per split) % 128 == 0 and operand byte offsets below 4 GiB (checked by the launcher).
-
-// Exact-KL epilogue for one 32-row band: zp / zr are the policy's and the reference's logits of the same
-// (row, column) entries.  Per row and per wave (TN*32 columns) five numbers leave the kernel:
-//   m_p = max z_p, S_p = sum exp(z_p - m_p), T = sum exp(z_p - m_p) (z_p - z_r), m_r = max z_r, S_r = sum exp(z_r - m_r)
-// from which  KL(pi_p || pi_r) = T/S_p - (m_p + log S_p) + (m_r + log S_r)  once all column groups are combined.
-template <int BN, int TN, int WGN>
-__device__ __forceinline__ void kl_epilogue(floatx16 (&zp)[TN], floatx16 (&zr)[TN], const GemmArgs& a, int m_base,
-                                            int nb, int wn, int lane) {
-    const int lg = lane >> 5, lrow = lane & 31;
-    const int nparts = (a.N / BN) * WGN;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
-        float mp = zp[0][r], mr = zr[0][r];
-#pragma unroll
-        for (int j = 1; j < TN; ++j) { mp = fmaxf(mp, zp[j][r]); mr = fmaxf(mr, zr[j][r]); }
-#pragma unroll
-        for (int o = 1; o < 32; o <<= 1) {
-            mp = fmaxf(mp, __shfl_xor(mp, o, RL_WAVE));
-            mr = fmaxf(mr, __shfl_xor(mr, o, RL_WAVE));
-        }
-        float sp = 0.f, t = 0.f, sr = 0.f;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const float e = __expf(zp[j][r] - mp);
-            sp += e;
-            t += e * (zp[j][r] - zr[j][r]);
-            sr += __expf(zr[j][r] - mr);
-        }
-#pragma unroll
-        for (int o = 1; o < 32; o <<= 1) {
-            sp += __shfl_xor(sp, o, RL_WAVE);
-            t += __shfl_xor(t, o, RL_WAVE);
-            sr += __shfl_xor(sr, o, RL_WAVE);
-        }
-        if (lrow == 0 && m < a.M) {
-            float* o = a.kl_part + ((int64_t)m * nparts + nb * WGN + wn) * 5;
-            o[0] = mp; o[1] = sp; o[2] = t; o[3] = mr; o[4] = sr;
-        }
-    }
-}
-
-// The k loop of gemm_dma_kernel for one tile: acc = A[m0.., kbeg..] * W[tile nb]^T over nk k-tiles of 32.
-// Aop / Wop are the operands (row strides lda / a.Kw); ends with every staging load landed (vmcnt(0)).
-template <int EPI, int BM, int BN, int WGM, int WGN>
-__device__ __forceinline__ void dma_mainloop(const GemmArgs& a, const f16_t* Aop, int lda, const bf16_t* Wop, int m0,
-                                             int nb, int kbeg, int nk, int wave, int lane, char* smem,
-                                             floatx16 (&acc)[BM / WGM / 32][BN / WGN / 32]) {
-    constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
-    constexpr int SLOTS = TM * TN, HS = SLOTS / 2;   // MFMAs per k-slice; slots of its first half
-    constexpr int STAGE = (BM + BN) * 64;            // bytes per stage: A rows then W rows, 64 B each
-    constexpr int LPT = (BM + BN) / 64;              // staging loads per wave per k-tile
-    constexpr int L1 = LPT / 2;                      // loads [0, L1) go out one step later than [L1, LPT)
-    constexpr int RPS = (TN + TM) / HS, CPS = 2 * TN / HS;   // fragment reads / conversion halves per slot
-    static_assert(WGM * WGN == 4 && SLOTS % 2 == 0 && (TN + TM) % HS == 0 && (2 * TN) % HS == 0, "tile shape");
-    static_assert(BM % 64 == 0 && BN % 64 == 0, "whole 16-row blocks per wave and operand");
-    const int wm = wave / WGN, wn = wave % WGN;
-    // Staging: load l of wave w fills the 1 KB block l*4 + w of a stage = 16 rows of A (l < BM/64) or W;
-    // lane -> row + lane/4, physical chunk lane%4, which holds the row's logical chunk (lane%4) ^ ((row>>2)&3).
-    unsigned g_off[LPT];
-    {
-        const int lc = (lane & 3) ^ ((lane >> 4) & 3);
-#pragma unroll
-        for (int l = 0; l < LPT; ++l) {
-            if (l < BM / 64) {
-                const int r = (l * 4 + wave) * 16 + (lane >> 2);
-                g_off[l] = ((unsigned)min(m0 + r, a.M - 1) * (unsigned)lda + lc * 8) * 2u;   // rows >= M: clamped, never stored
-            } else {
-                const int r = ((l - BM / 64) * 4 + wave) * 16 + (lane >> 2);
-                g_off[l] = ((unsigned)min(w_row_of<EPI, BN>(r, nb, a), a.Wrows - 1) * (unsigned)a.Kw + lc * 8) * 2u;
-            }
-        }
-    }
-    const char* Ag = reinterpret_cast<const char*>(Aop + kbeg);
-    const char* Wg = reinterpret_cast<const char*>(Wop);
-    const int kw0 = kbeg / 32, nkw = a.Kw / 32;   // W k-tile of A k-tile kt: kw0 + kt, wrapping at nkw
-    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-#define DG_LOAD(stage, kt, l)                                                                                   \
-    {                                                                                                           \
-        const unsigned sa_ = lds_base + (stage) * STAGE + ((l) * 4 + wave) * 1024;                              \
-        const char* g_ = (l) < BM / 64 ? Ag + (size_t)(kt) * 64 : Wg + (size_t)wrap_k(kw0 + (kt), nkw) * 64;    \
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                            \
-                     :: "s"(sa_), "v"(g_off[l]), "s"(g_) : "memory");                                           \
-    }
-    // fragment addresses: row lane%32 of a 32-row block, logical chunk ks*2 + lane/32, swizzled
-    int fa[2][2], fw[2][2];   // [stage pair][k-slice]
-#pragma unroll
-    for (int hp = 0; hp < 2; ++hp)
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            const int ko = ((sl * 2 + (lane >> 5)) ^ ((lane >> 2) & 3)) * 16;
-            fa[hp][sl] = hp * 2 * STAGE + (wm * TM * 32 + (lane & 31)) * 64 + ko;
-            fw[hp][sl] = hp * 2 * STAGE + BM * 64 + (wn * TN * 32 + (lane & 31)) * 64 + ko;
-        }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    half8 af[2][TM];
-    u32x4_t bf[2][TN], bw[TN];
-#define DG_CVT2(w) __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(__uint_as_float((w) << 16), __uint_as_float((w) & 0xffff0000u)))
-#define DG_LDA(stage, sl, i) *reinterpret_cast<const half8*>(smem + fa[(stage) >> 1][sl] + ((stage) & 1) * STAGE + (i) * 2048)
-#define DG_LDW(stage, sl, j) *reinterpret_cast<const u32x4_t*>(smem + fw[(stage) >> 1][sl] + ((stage) & 1) * STAGE + (j) * 2048)
-    // One k-slice: SLOTS MFMAs on fragment set CUR.  After each MFMA of the first half: RPS fragment reads
-    // of slice (NSTAGE, NSL) into the other set (W fragments first) and the staging loads [LB, LE) of
-    // tile DKT into stage DSTAGE (spread over the slots); after each MFMA of the second half: CPS
-    // half-fragment conversions of those W fragments.
-#define DG_SLICE(CUR, NSTAGE, NSL, LB, LE, DSTAGE, DKT)                                                         \
-    _Pragma("unroll") for (int q = 0; q < SLOTS; ++q) {                                                         \
-        const int j_ = q / TM, i_ = q % TM;                                                                     \
-        acc[i_][j_] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[CUR][i_], __builtin_bit_cast(half8, bf[CUR][j_]), acc[i_][j_], 0, 0, 0); \
-        if (q < HS) {                                                                                           \
-            _Pragma("unroll") for (int u_ = 0; u_ < RPS; ++u_) {                                                \
-                const int f_ = q * RPS + u_;                                                                    \
-                if (f_ < TN) bw[f_ < TN ? f_ : 0] = DG_LDW(NSTAGE, NSL, f_);                                    \
-                else af[1 - (CUR)][f_ >= TN ? f_ - TN : 0] = DG_LDA(NSTAGE, NSL, f_ - TN);                      \
-            }                                                                                                   \
-            _Pragma("unroll") for (int l_ = (LB); l_ < (LE); ++l_) {                                            \
-                const int slot_ = HS >= 2 * ((LE) - (LB)) ? 2 * (l_ - (LB)) + 1 : (l_ - (LB)) % HS;             \
-                if (slot_ == q) DG_LOAD(DSTAGE, DKT, l_)                                                        \
-            }                                                                                                   \
-        } else {                                                                                                \
-            _Pragma("unroll") for (int u_ = 0; u_ < CPS; ++u_) {                                                \
-                const int c_ = (q - HS) * CPS + u_, jj_ = c_ >> 1, h_ = (c_ & 1) * 2;                           \
-                bf[1 - (CUR)][jj_][h_] = DG_CVT2(bw[jj_][h_]);                                                  \
-                bf[1 - (CUR)][jj_][h_ + 1] = DG_CVT2(bw[jj_][h_ + 1]);                                          \
-            }                                                                                                   \
-        }                                                                                                       \
-        __builtin_amdgcn_sched_barrier(0);                                                                      \
-    }
-    // k-tile kt sits in stage S = kt % 4.  Its first slice also issues the later part of the requests
-    // for tile kt+3; after the barrier its stage is free and takes the first part of tile kt+4.
-#define DG_STEP(S, KT)                                                                                          \
-    {                                                                                                           \
-        { const int dkt_ = min((KT) + 3, nk - 1);                                                               \
-          DG_SLICE(0, S, 1, L1, LPT, ((S) + 3) & 3, dkt_) }                                                     \
-        __builtin_amdgcn_s_waitcnt(dma_waitcnt(2 * LPT, 0));   /* own part of tile kt+1 landed, own reads done */ \
-        __syncthreads();                                                                                        \
-        __builtin_amdgcn_sched_barrier(0);                                                                      \
-        { const int dkt_ = min((KT) + 4, nk - 1);                                                               \
-          DG_SLICE(1, ((S) + 1) & 3, 0, 0, L1, S, dkt_) }                                                       \
-    }
-    // prologue: tiles 0..2 and the first part of tile 3
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-        const int kt_ = min(st, nk - 1);
-#pragma unroll
-        for (int l = 0; l < (st < 3 ? LPT : L1); ++l) DG_LOAD(st, kt_, l)
-    }
-    __builtin_amdgcn_s_waitcnt(dma_waitcnt(2 * LPT + L1, 15));   // tile 0 landed
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[0][i] = DG_LDA(0, 0, i);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        bw[j] = DG_LDW(0, 0, j);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) bf[0][j][c] = DG_CVT2(bw[j][c]);
-    }
-    for (int kt = 0; kt < nk; kt += 4) {   // nk % 4 == 0
-        DG_STEP(0, kt)
-        DG_STEP(1, kt + 1)
-        DG_STEP(2, kt + 2)
-        DG_STEP(3, kt + 3)
-    }
-    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 15));   // nothing may land in LDS after the workgroup ends
-#undef DG_LOAD
-#undef DG_CVT2
-#undef DG_LDA
-#undef DG_LDW
-#undef DG_SLICE
-#undef DG_STEP
-}
-
 // Large-M GEMM, tiles of 32 MI rows x 256 columns (MI = 3 .. 8, by the number of rows: big_row_blocks), eight waves
 // (2 x 4; 16 MI x 64 of C per wave; what follows says 128 x 64, MI = 8; two waves per SIMD, so a wave that waits
 // -- at a barrier, for its fragment reads, behind a queued staging load -- leaves the SIMD's matrix core to the other
@@ -819,21 +621,15 @@ __device__ __forceinline__ void dma_mainloop(const GemmArgs& a, const f16_t* Aop
 // epilogues, which are written for the 32 x 32 layout, each wave passes them through its own 17 KB of the then idle
 // LDS, 64 rows at a time.
 // Requires K % 64 == 0, no split over K, 5 * 512 * 64 bytes of LDS.
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
 template <int EPI, bool WF16, int MI>
-__global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
-    constexpr int BM = 32 * MI, BN = 256, WGN = 4, TN = 2;
+__device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, int lda, const bf16_t* Wop, int m0, int nb, int wave,
+                                          int lane, char* smem, floatx4_t (&acc)[MI][4], QkvRowMeta& meta) {
+    constexpr int BM = 32 * MI, BN = 256, WGN = 4;
     constexpr int MI0 = (MI + 1) / 2, MI1 = MI / 2;      // 16-row blocks of the wave in slice 0 and in slice 1
     constexpr int STAGE = (BM + BN) * 64;
     constexpr int LPA = (BM + 127) / 128, LPT = LPA + 2;  // staging loads per wave and k-tile: of A, in all
-    typedef float floatx4_t __attribute__((ext_vector_type(4)));
-    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [5 stages][A 256 x 64 B | W 256 x 64 B]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
-    const int NB = a.n_blocks_n, MB = (a.M + BM - 1) / BM;
-    int nb, mb;
-    if (!tile_of(blockIdx.x, MB, NB, mb, nb)) return;
-    const int m0 = mb * BM;
     const int nk = a.K / 32, nkw = a.Kw / 32;
     // 16-row block of its operand that load l of this wave stages; where A has fewer blocks than 8 LPA, the waves left
     // over stage a block twice (same bytes to the same place), so that every wave counts the same loads
@@ -846,12 +642,12 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
 #pragma unroll
         for (int l = 0; l < LPT; ++l) {
             const int r = X8_BLOCK(l) * 16 + (lane >> 2);
-            g_off[l] = l < LPA ? ((unsigned)min(m0 + r, a.M - 1) * (unsigned)a.lda + lc * 8) * 2u   // rows >= M: clamped, never stored
+            g_off[l] = l < LPA ? ((unsigned)min(m0 + r, a.M - 1) * (unsigned)lda + lc * 8) * 2u   // rows >= M: clamped, never stored
                              : ((unsigned)min(w_row_of<EPI, BN>(r, nb, a), a.Wrows - 1) * (unsigned)a.Kw + lc * 8) * 2u;
         }
     }
-    const char* Ag = reinterpret_cast<const char*>(a.A);
-    const char* Wg = reinterpret_cast<const char*>(a.W);
+    const char* Ag = reinterpret_cast<const char*>(Aop);
+    const char* Wg = reinterpret_cast<const char*>(Wop);
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
 #define X8_LOAD(st, kt, l)                                                                                      \
     {                                                                                                           \
@@ -866,7 +662,6 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     const int fko = ((lane >> 4) ^ ((fr >> 2) & 3)) * 16;
     const int fa = (wm * MI * 16 + fr) * 64 + fko;                 // + i * 1024 for the i-th 16-row block of the wave
     const int fw = BM * 64 + (wn * 64 + fr) * 64 + fko;        // + j * 1024
-    floatx4_t acc[MI][4];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -916,7 +711,6 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     for (int l = 0; l < LPT; ++l) { X8_LOAD(0, 0, l) X8_LOAD(1, 1, l) }
 #pragma unroll
     for (int l = 0; l < LPT; ++l) { X8_LOAD(2, 2, l) X8_LOAD(3, 3, l) }
-    QkvRowMeta meta;
     if constexpr (EPI == MG_QKV) meta = qkv_row_meta(a, m0 + wm * MI * 16, lane);
     __builtin_amdgcn_s_waitcnt(dma_waitcnt(EPI == MG_QKV ? 0 : 2 * LPT + 1, 15));
     __syncthreads();
@@ -953,6 +747,21 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
 #undef X8_LDA
 #undef X8_LDW
 #undef X8_SLICE
+}
+
+template <int EPI, bool WF16, int MI>
+__global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
+    constexpr int BM = 32 * MI, BN = 256, WGN = 4, TN = 2;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [5 stages][A 256 x 64 B | W 256 x 64 B]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    int nb, mb;
+    if (!tile_of(blockIdx.x, (a.M + BM - 1) / BM, a.n_blocks_n, mb, nb)) return;
+    const int m0 = mb * BM;
+    floatx4_t acc[MI][4];
+    QkvRowMeta meta;
+    dma8_loop<EPI, WF16, MI>(a, a.A, a.lda, a.W, m0, nb, wave, lane, smem, acc, meta);
     __syncthreads();                                   // every wave is done with the stages: LDS is free
     // 16 x 16 layout -> 32 x 32 layout through this wave's own [64 rows][64 columns] fp32 patch; row stride 68 floats:
     // four rows further on is 16 banks further on, so neither the writes (lanes 16 apart: 4 rows apart) nor the reads
@@ -993,37 +802,85 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
 #undef D8_HALF
 }
 
-template <int EPI, int BM, int BN, int WGM, int WGN, int MINWG>
-__global__ __launch_bounds__(256, MINWG) void gemm_dma_kernel(GemmArgs a) {
-    constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
-    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [4 stages][A BM x 64 B | W BN x 64 B]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int NB = a.n_blocks_n, MB = (a.M + BM - 1) / BM, ks = blockIdx.z;
-    int nb, mb;
-    if (!tile_of(blockIdx.x, MB, NB, mb, nb)) return;
-    const int m0 = mb * BM;
-    const int kbeg = ks * a.k_per_split, kend = min(a.K, kbeg + a.k_per_split);
-    const int nk = (kend - kbeg) / 32;               // multiple of 4
-    floatx16 acc[TM][TN];
-    if (EPI == MG_KLFULL) {
-        // two GEMMs on the same tile, one after the other through the same LDS stages: reference logits
-        // first (kept in registers), then the policy's; the epilogue needs both for every (row, column)
-        floatx16 acc_r[TM][TN];
-        dma_mainloop<EPI, BM, BN, WGM, WGN>(a, a.A2, a.lda2, a.W2, m0, nb, kbeg, nk, wave, lane, smem, acc_r);
-        __syncthreads();   // every wave is done reading the stages before they are refilled
-        dma_mainloop<EPI, BM, BN, WGM, WGN>(a, a.A, a.lda, a.W, m0, nb, kbeg, nk, wave, lane, smem, acc);
-        kl_epilogue<BN, TN, WGN>(acc[0], acc_r[0], a, m0 + wm * TM * 32, nb, wn, lane);
-        if (TM > 1) kl_epilogue<BN, TN, WGN>(acc[TM > 1 ? 1 : 0], acc_r[TM > 1 ? 1 : 0], a, m0 + wm * TM * 32 + 32, nb, wn, lane);
-        return;
+// Exact-KL epilogue for one 32-row band: zp / zr are the policy's and the reference's logits of the same
+// (row, column) entries.  Per row and per wave (64 columns) five numbers leave the kernel:
+//   m_p = max z_p, S_p = sum exp(z_p - m_p), T = sum exp(z_p - m_p) (z_p - z_r), m_r = max z_r, S_r = sum exp(z_r - m_r)
+// from which  KL(pi_p || pi_r) = T/S_p - (m_p + log S_p) + (m_r + log S_r)  once all column groups are combined.  The 16
+// rows' reductions run level by level (independent chains).
+__device__ __forceinline__ void kl_epilogue(floatx16 (&zp)[2], floatx16 (&zr)[2], const GemmArgs& a, int m_base, int group,
+                                            int lane) {
+    const int lg = lane >> 5, lrow = lane & 31;
+    float mp[16], mr[16], sp[16], st[16], sr[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { mp[r] = fmaxf(zp[0][r], zp[1][r]); mr[r] = fmaxf(zr[0][r], zr[1][r]); }
+    rows_max(mp);
+    rows_max(mr);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float e0 = __expf(zp[0][r] - mp[r]), e1 = __expf(zp[1][r] - mp[r]);
+        sp[r] = e0 + e1;
+        st[r] = e0 * (zp[0][r] - zr[0][r]) + e1 * (zp[1][r] - zr[1][r]);
+        sr[r] = __expf(zr[0][r] - mr[r]) + __expf(zr[1][r] - mr[r]);
     }
-    dma_mainloop<EPI, BM, BN, WGM, WGN>(a, a.A, a.lda, a.W, m0, nb, kbeg, nk, wave, lane, smem, acc);
-    // written out: with the largest epilogue the unroller gives up on a loop over the bands
-    mg_epilogue<EPI, BN, TN, WGN>(acc[0], a, m0 + wm * TM * 32, nb, wn, ks, lane);
-    if (TM > 1) mg_epilogue<EPI, BN, TN, WGN>(acc[TM > 1 ? 1 : 0], a, m0 + wm * TM * 32 + 32, nb, wn, ks, lane);
-    if (TM > 2) mg_epilogue<EPI, BN, TN, WGN>(acc[TM > 2 ? 2 : 0], a, m0 + wm * TM * 32 + 64, nb, wn, ks, lane);
-    if (TM > 3) mg_epilogue<EPI, BN, TN, WGN>(acc[TM > 3 ? 3 : 0], a, m0 + wm * TM * 32 + 96, nb, wn, ks, lane);
+    rows_sum(sp);
+    rows_sum(st);
+    rows_sum(sr);
+    const int nparts = a.N / 64;
+    if (lrow != 0) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
+        if (m >= a.M) continue;
+        float* o = a.kl_part + ((int64_t)m * nparts + group) * 5;
+        o[0] = mp[r]; o[1] = sp[r]; o[2] = st[r]; o[3] = mr[r]; o[4] = sr[r];
+    }
+}
+
+// Both LM heads of the exact KL on one tile: the reference's logits first (kept in the accumulators), then the policy's, by
+// the loop above on tiles of 128 x 256 -- two sets of 64 accumulator registers per lane; taller tiles would spill.  Bound by
+// the matrix cores.  2942 rows, d = 4096, V = 128256, fp16 copies: 6.2 ms (1.0 PFLOP/s); four waves on 128 x 128 tiles with bf16 weights, which
+// this replaced, 8.4 ms.  N a multiple of 64: column groups past it are left out.
+template <bool WF16>
+__global__ __launch_bounds__(512, 1) void gemm_kl8_kernel(GemmArgs a) {
+    constexpr int MI = 4, BM = 32 * MI, WGN = 4, TN = 2;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    int nb, mb;
+    if (!tile_of(blockIdx.x, (a.M + BM - 1) / BM, a.n_blocks_n, mb, nb)) return;
+    const int m0 = mb * BM;
+    floatx4_t acc_r[MI][4], acc_p[MI][4];
+    QkvRowMeta meta;
+    dma8_loop<MG_KLFULL, WF16, MI>(a, a.A2, a.lda2, a.W2, m0, nb, wave, lane, smem, acc_r, meta);
+    __syncthreads();                                   // the stages are filled again
+    dma8_loop<MG_KLFULL, WF16, MI>(a, a.A, a.lda, a.W, m0, nb, wave, lane, smem, acc_p, meta);
+    __syncthreads();
+    // 16 x 16 -> 32 x 32 layout through the wave's own LDS patch, as in the kernel above: 64 rows x 64 columns, one set
+    // after the other
+    float* patch = reinterpret_cast<float*>(smem) + wave * (64 * 68);
+    const int lg = lane >> 5, lrow = lane & 31;
+    floatx16 zr[2][TN], zp[2][TN];
+#define KL_RELAYOUT(acc, z)                                                                                     \
+    {                                                                                                           \
+        _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                          \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                       \
+                _Pragma("unroll") for (int t = 0; t < 4; ++t)                                                   \
+                    patch[(i * 16 + 4 * (lane >> 4) + t) * 68 + j * 16 + (lane & 15)] = acc[i][j][t];           \
+        __builtin_amdgcn_wave_barrier();      /* LDS accesses of a wave complete in order */                    \
+        _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                           \
+            _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                      \
+                _Pragma("unroll") for (int r = 0; r < 16; ++r)                                                  \
+                    z[b][j][r] = patch[(b * 32 + 8 * (r >> 2) + 4 * lg + (r & 3)) * 68 + j * 32 + lrow];        \
+        __builtin_amdgcn_wave_barrier();                                                                        \
+    }
+    KL_RELAYOUT(acc_r, zr)
+    KL_RELAYOUT(acc_p, zp)
+#undef KL_RELAYOUT
+    const int group = nb * WGN + wn;
+    if (group * 64 >= a.N) return;
+    kl_epilogue(zp[0], zr[0], a, m0 + wm * 64, group, lane);
+    kl_epilogue(zp[1], zr[1], a, m0 + wm * 64 + 32, group, lane);
 }
 
 template <int BM, int BN, int WGM, int WGN, int EPI, int BKT = 64, bool WF16 = false>
@@ -1041,19 +898,18 @@ static void launch(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s)
     gemm_mfma_kernel<BM, BN, WGM, WGN, EPI, BKT, WF16><<<grid, 256, lds, s>>>(b);
 }
 
-template <int EPI, int BM, int BN, int WGM, int WGN, int MINWG>
-static void launch_dma(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s) {
-    constexpr int lds = 4 * (BM + BN) * 64;
+template <bool WF16>
+static void launch_kl8(const GemmArgs& a, hipStream_t s) {
+    constexpr int BM = 128, stages = 5 * (BM + 256) * 64, patches = 8 * 64 * 68 * 4, lds = stages > patches ? stages : patches;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void*)gemm_dma_kernel<EPI, BM, BN, WGM, WGN, MINWG>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        (void)hipFuncSetAttribute((const void*)gemm_kl8_kernel<WF16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         attr_set = true;
     }
     GemmArgs b = a;
-    b.n_blocks_n = n_blocks_n;
-    dim3 grid(8 * ((n_blocks_n * ((a.M + BM - 1) / BM) + 7) / 8), 1, splits);
-    gemm_dma_kernel<EPI, BM, BN, WGM, WGN, MINWG><<<grid, 256, lds, s>>>(b);
+    b.n_blocks_n = (a.N + 255) / 256;
+    dim3 grid(8 * ((b.n_blocks_n * ((a.M + BM - 1) / BM) + 7) / 8), 1, 1);
+    gemm_kl8_kernel<WF16><<<grid, 512, lds, s>>>(b);
 }
 template <int EPI, bool WF16, int MI>
 static void launch_dma8_t(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
@@ -1141,7 +997,8 @@ int k_gemm_mfma_lse_parts(int M, int N, int K, int big_mode) {
 
 // Whether k_gemm_mfma will run this GEMM on the kernel that can read an fp16 copy of W (GemmArgs.w_f16).
 bool k_gemm_mfma_reads_f16_copy(int epi, GemmArgs a, int splits) {
-    if (a.M <= 0 || a.N <= 0 || epi == MG_KLFULL || !g_big_reads_copy) return false;
+    if (a.M <= 0 || a.N <= 0 || !g_big_reads_copy) return false;
+    if (epi == MG_KLFULL) return true;
     if (a.Kw <= 0) a.Kw = a.K;
     if (splits < 1) splits = 1;
     const int kt = a.K / BK, per = (kt + splits - 1) / splits;
@@ -1160,7 +1017,7 @@ void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s) {
     splits = (kt + per - 1) / per;
     a.Wrows = epi == MG_SWIGLU ? a.up_offset + a.N : a.N;
     const bool big = use_big(epi, a, splits);
-    if (a.w_f16 && !(big && epi != MG_KLFULL)) return;   // callers check k_gemm_mfma_reads_f16_copy first
+    if (a.w_f16 && !big && epi != MG_KLFULL) return;     // callers check k_gemm_mfma_reads_f16_copy first
     switch (epi) {
         case MG_STORE_F32:
             if (big) launch_big<MG_STORE_F32>(a, a.N / 256, s);
@@ -1186,9 +1043,9 @@ void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s) {
             if (big) launch_big<MG_QKV>(a, a.N / 256, s);
             else launch<128, 128, 2, 2, MG_QKV>(a, a.N / 128, 1, s);
             break;
-        case MG_KLFULL:   // two accumulator sets per tile: 128 x 128 tiles on the LDS-staged kernel
-            a.k_per_split = a.K;
-            launch_dma<MG_KLFULL, 128, 128, 2, 2, 2>(a, a.N / 128, 1, s);
+        case MG_KLFULL:
+            if (a.w_f16) launch_kl8<true>(a, s);
+            else launch_kl8<false>(a, s);
             break;
         default: break;
     }

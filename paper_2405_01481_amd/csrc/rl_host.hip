@@ -441,7 +441,11 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
         if (k_gemm_mfma_reads_f16_copy(epi, a, splits)) {
             const int kw = a.Kw > 0 ? a.Kw : a.K;
             const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * kw;
-            if (const void* h = copy_of((const void*)a.W)) {
+            const void* const h = copy_of((const void*)a.W);
+            if (epi == MG_KLFULL) {                            // both models' copies or neither's
+                const void* const h2 = copy_of((const void*)a.W2);
+                if (h && h2) { a.W = (const bf16_t*)h; a.W2 = (const bf16_t*)h2; a.w_f16 = 1; }
+            } else if (h) {
                 a.W = (const bf16_t*)h; a.w_f16 = 1;
             } else if ((int64_t)a.M * (a.K / kw) >= kConvertRows && idle.bytes >= 2 * elems) {
                 k_bf16_to_f16(a.W + w_skip, idle.p, (int64_t)elems, s);
