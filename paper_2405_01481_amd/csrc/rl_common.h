@@ -129,8 +129,9 @@ void k_rope_append(int dtype, const float* qkv, int n, const int* tok_pos, const
 void k_rope_append_split(int dtype, const float* part, int nsplit, int64_t split_stride, int n, const int* tok_pos,
                          const int* tok_slot, const float2* rope, void* q_out, void* pool, int layer, KvGeom geo,
                          const int* block_table, int mpps, int Hq, hipStream_t s, int split = 0, int layer_lo = 0);
-void k_resid_norm(int dtype, float* x, const float* part, int nsplit, int64_t split_stride, const void* g, void* out,
-                  int n, int d, float eps, hipStream_t s, int split = 0);
+// bf16 gains, fp16 output
+void k_resid_norm(float* x, const float* part, int nsplit, int64_t split_stride, const void* g, void* out, int n, int d,
+                  float eps, hipStream_t s, int split = 0);
 // Plain attention over whole sequences (contiguous k, v), and of one new token per cache slot (which also rotates and
 // appends).  LDS grows with the context: k_attn_simple_lds(hd, max_ctx) bytes per workgroup.
 size_t k_attn_simple_lds(int hd, int max_ctx);

@@ -10,8 +10,9 @@
 //     reads (16 rows x 64 B, one 16-byte read per lane) meet no bank conflict.
 //   * where the workgroups stand in k.  Rows whose length is a power of two put the same k of all rows on the same
 //     memory channels, and workgroups start together: workgroup b therefore starts at k-tile b (mod its range) and
-//     wraps.  235 MB gate/up 47.5 -> 39.3 us, 1B gate/up 16.3 -> 13.7, 70B O projection 34.7 -> 28.4; where rows are
-//     not a power of two long it only costs (70B down projection 88 -> 98 us) and is not done.
+//     wraps.  235 MB gate/up 47.5 -> 39.3 us, 1B gate/up 16.3 -> 13.7, 70B O projection 34.7 -> 28.4.  Where rows are
+//     not a power of two long it only costs (70B down projection 88 -> 98 us), and where a split has fewer than 16 k-tiles the
+//     splits stand apart anyway (1B down, 8 splits of 8: 9.4 us rotated, 8.9 not): not done there.
 //   * the shape of the work.  One workgroup per CU with no remainder: the tile is CT x 16 columns, CT = 1 .. 8, and K is
 //     split over Z workgroups whose partial sums the consumer reduces (stream_plan).
 // Eight waves: four along the k-tile (32 k each), two along the columns, so that every W fragment is read, and on bf16
@@ -312,7 +313,7 @@ void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s)
         k_gemm_tile_decode(epi, a, z, s);                      // splits K the same way
         return;
     }
-    a.rotate_k = (a.Kw & (a.Kw - 1)) == 0;
+    a.rotate_k = (a.Kw & (a.Kw - 1)) == 0 && a.k_per_split >= 16 * GS_KT;
     const int tiles = (epi == MG_SWIGLU ? 2 * a.N : a.N) / 16;
     if (epi == MG_STORE_F32) launch_stream<MG_STORE_F32>(a, tiles, ct, z, s);
     else if (epi == MG_SWIGLU) launch_stream<MG_SWIGLU>(a, tiles, ct, z, s);

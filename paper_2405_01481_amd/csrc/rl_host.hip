@@ -518,7 +518,7 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             g.outF = part; g.ldc = m.d_model; g.split_stride = (int64_t)n * m.d_model;
             ks = decode_splits(c, n, m.d_model, g.K, g.Kw);
             mfma(c, gcls, MG_STORE_F32, g, ks, s);
-            k_resid_norm(1, x, part, ks, g.split_stride, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
+            k_resid_norm(x, part, ks, g.split_stride, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
             g = GemmArgs();
             g.M = n; g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.w_gate_up[l]; g.N = m.d_ffn;
             g.up_offset = m.d_ffn; g.outH = ffn; g.ldc = sp ? 2 * m.d_ffn : m.d_ffn; g.split_out = sp;
@@ -529,7 +529,7 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             ks = decode_splits(c, n, m.d_model, g.K, g.Kw);
             mfma(c, gcls, MG_STORE_F32, g, ks, s);
             const void* next = (l + 1 < m.n_layers) ? W.attn_norm[l + 1] : W.final_norm;
-            k_resid_norm(1, x, part, ks, g.split_stride, next, h, n, m.d_model, m.rms_eps, s, sp_next);
+            k_resid_norm(x, part, ks, g.split_stride, next, h, n, m.d_model, m.rms_eps, s, sp_next);
         } else {
             k_rmsnorm(1, x, W.attn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
             g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.wqkv[l]; g.N = L.nqkv;
