@@ -340,13 +340,16 @@ bool k_attn_decode_consumes_qkv(int Hq, int Hkv, int hd) {
     return (hd == 64 || hd == 128) && G <= 8 && (G + 2) * (hd / 2) <= 512;
 }
 
-// Waves for the keys of one (sequence, kv head), from the context's limits: as many as make 4096 in all, each with at
-// least two pages of the longest sequence.  Up to 8 share a workgroup; beyond that the keys are split over workgroups and
-// merged by a kernel of their own, which costs as much as a short context's attention (4.6 us), so not for less.
+// From the context's limits: a workgroup draws up to 38 KB/us, four waves of it as much as eight, so 256 workgroups are
+// enough to read the cache at memory speed, and a split costs a merge kernel and the query's preparation once more.  Hence
+// splits only up to 256 workgroups, of at least 16 pages of the longest sequence each; eight waves where fewer than 512
+// workgroups leave room (short contexts: 32 rows x 200 keys 6.0 -> 5.3 us, but 64 rows x 300 keys at head_dim 128 16.0 ->
+// 17.6).  8 kv heads, head_dim 128, merge included, splits 1 / 2 / 4 / 8: 32 rows x 1600 keys 40.6 / 42.4 / 45 / 50 us,
+// 16 x 4000 59 / 51 / 50 / 54, 8 x 1600 21.8 / 16.5 / 15.8 / 16.9, 1 x 4000 46 / 28 / 18.6 / 14.9, 8 x 300 8.0 / 9.0 / 8.7 / 10.3.
 void k_attn_decode_plan(int max_batch, int Hkv, int mpps, int max_splits, int* waves, int* nsplit) {
-    const int want = std::min((4096 + max_batch * Hkv - 1) / (max_batch * Hkv), mpps / 2);
-    *waves = want >= 6 ? 8 : 4;
-    *nsplit = std::max(1, std::min(want / 8, max_splits));
+    const int wgs = max_batch * Hkv;
+    *waves = wgs < 512 ? 8 : 4;
+    *nsplit = std::max(1, std::min(std::min((256 + wgs - 1) / wgs, mpps / 16), max_splits));
 }
 
 template <int HD, bool SP, bool FU>
