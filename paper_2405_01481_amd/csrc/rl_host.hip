@@ -230,11 +230,12 @@ struct rl_ctx {
         }
     } gkey{};
     hipGraphExec_t gexec = nullptr;
+    hipEvent_t gdone = nullptr;      // behind the last replay of gexec
     bool use_graph = true;
     bool fused_sample = true;        // decode LM head emits block statistics instead of logits (tuned path)
     bool fused_qkv = true;           // decode attention sums, rotates and appends the QKV projection's partial rows itself
-    // captured steps that may still be running when the policy is swapped without waiting: destroyed once the
-    // event recorded behind their last launch has completed
+    // captured steps that another one has replaced while their replays may still be queued (no call waits for its
+    // work): destroyed once the event recorded behind their last replay has completed
     struct Retired { hipGraphExec_t g; hipEvent_t ev; };
     std::vector<Retired> retired;
     // profiling
@@ -721,24 +722,14 @@ static int ensure_other_shadow(rl_ctx* c, const WeightsHost& W, hipStream_t s) {
 
 static int ensure_copy_stream(rl_ctx* c);
 
-// Put the captured decode step aside (its launches may still be in flight on the stream it was captured on).
-static void retire_graph(rl_ctx* c) {
-    if (!c->gexec) return;
-    hipEvent_t ev = nullptr;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess && hipEventRecord(ev, c->gkey.s) == hipSuccess) {
-        c->retired.push_back({c->gexec, ev});
-    } else {
-        if (ev) (void)hipEventDestroy(ev);
-        (void)hipStreamSynchronize(c->gkey.s);
-        (void)hipGraphExecDestroy(c->gexec);
-    }
-    c->gexec = nullptr;
-}
-// Destroy the retired steps whose work has completed (all of them, after waiting, with force).
+// Destroy the replaced steps whose replays have completed; with force all of them, after waiting.
+static const size_t kMaxRetired = 8;   // replaced steps kept at most: a caller that queues more of them waits for the oldest
 static void reap_graphs(rl_ctx* c, bool force) {
     for (size_t i = 0; i < c->retired.size();) {
-        if (force) (void)hipEventSynchronize(c->retired[i].ev);
-        if (force || hipEventQuery(c->retired[i].ev) == hipSuccess) {
+        const bool wait = force || c->retired.size() > kMaxRetired;   // i is then the oldest one left
+        if (!wait && hipPeekAtLastError() != hipSuccess) return;      // an error the call has yet to report: leave it in place
+        if (wait) (void)hipEventSynchronize(c->retired[i].ev);
+        if (wait || hipEventQuery(c->retired[i].ev) == hipSuccess) {
             (void)hipGraphExecDestroy(c->retired[i].g);
             (void)hipEventDestroy(c->retired[i].ev);
             c->retired.erase(c->retired.begin() + i);
@@ -747,6 +738,13 @@ static void reap_graphs(rl_ctx* c, bool force) {
             ++i;
         }
     }
+}
+// Put the captured decode step aside: its replays may still be queued on the stream it ran on.
+static void retire_graph(rl_ctx* c) {
+    if (c->gexec) c->retired.push_back({c->gexec, c->gdone});
+    c->gexec = nullptr;
+    c->gdone = nullptr;
+    reap_graphs(c, false);
 }
 
 // Bytes of a device-resident copy of a whole weight set (every tensor 256-byte aligned).
@@ -848,8 +846,8 @@ int rollout_init(const rl_model_cfg* cfg, const rl_weights* policy, void* worksp
 
 void rollout_destroy(rl_ctx* c) {
     if (!c) return;
+    retire_graph(c);
     reap_graphs(c, true);
-    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
     if (c->copy_stream) {
         (void)hipStreamSynchronize(c->copy_stream);
         (void)hipStreamDestroy(c->copy_stream);
@@ -913,7 +911,6 @@ int rollout_set_policy(rl_ctx* c, const rl_weights* policy) {
         w.staging = nullptr;
         w.staging_bytes = 0;
         c->policy = w;
-        reap_graphs(c, false);
         retire_graph(c);   // the old policy's captured step may still be replaying on the caller's stream
         rc = build_shadow(c, cs);
         if (rc) return rc;
@@ -924,7 +921,7 @@ int rollout_set_policy(rl_ctx* c, const rl_weights* policy) {
     if (c->policy_pending) { HIP_TRY(hipEventSynchronize(c->ev_policy)); c->policy_pending = false; }
     c->policy = w;
     // the captured decode step holds the old pointers; caches built with the old weights are void
-    if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
+    retire_graph(c);
     rc = build_shadow(c, nullptr);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(nullptr));
@@ -949,7 +946,7 @@ int rollout_set_impl(rl_ctx* c, int32_t impl) {
     c->impl = impl >= 1 ? 1 : 0;
     c->big_mode = impl == 2 ? 2 : 1;
     c->precise = c->impl == 1 ? std::min(kDefaultPreciseLayers, precise_cap(c->cfg)) : 0;
-    if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
+    retire_graph(c);
     return rollout_reset(c);
 }
 
@@ -969,21 +966,21 @@ int rollout_set_precise_layers(rl_ctx* c, int32_t n) {
         return fail(RL_EINVAL, "precise layers: %d outside [0, %d] for this configuration", n, precise_cap(c->cfg));
     if (n > 0 && c->impl != 1) return fail(RL_EINVAL, "precise layers need the tuned kernels (impl 1 or 2)");
     c->precise = n;
-    if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
+    retire_graph(c);
     return rollout_reset(c);
 }
 
 int rollout_set_fused_sampling(rl_ctx* c, int32_t on) {
     if (!c) return fail(RL_EINVAL, "ctx is NULL");
     c->fused_sample = on != 0;
-    if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
+    retire_graph(c);
     return RL_OK;
 }
 
 int rollout_set_fused_qkv_consumer(rl_ctx* c, int32_t on) {
     if (!c) return fail(RL_EINVAL, "ctx is NULL");
     c->fused_qkv = on != 0;
-    if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
+    retire_graph(c);
     return RL_OK;
 }
 
@@ -1118,6 +1115,49 @@ static bool graph_usable(const rl_ctx* c, hipStream_t s, int ctx_cap) {
     return s != nullptr && c->use_graph;
 }
 
+// The decode step is identical from one token to the next (positions, step counters and page tables live on the
+// device), so it is captured once and replayed.  Makes c->gexec the step of `key`; one that it replaces is put aside.
+static int capture_step(rl_ctx* c, const rl_ctx::GraphKey& key, const rl_sample_cfg* sample, int32_t* out_ids, float* out_logp,
+                        int32_t* queue_out_len, int ctx_cap) {
+    if (c->gexec && key == c->gkey) return RL_OK;
+    retire_graph(c);
+    hipEvent_t done = nullptr;
+    HIP_TRY(hipEventCreateWithFlags(&done, hipEventDisableTiming));
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    int rc = RL_OK;
+    hipError_t e = hipStreamBeginCapture(key.s, hipStreamCaptureModeThreadLocal);
+    const char* what = "hipStreamBeginCapture";
+    if (e == hipSuccess) {
+        const std::vector<int> saved = c->cached;
+        rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, key.G, key.s, queue_out_len, ctx_cap);
+        c->cached = saved;
+        e = hipStreamEndCapture(key.s, &graph);
+        what = "hipStreamEndCapture";
+    }
+    if (rc == RL_OK && e == hipSuccess) {
+        e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+        what = "hipGraphInstantiate";
+    }
+    if (graph) (void)hipGraphDestroy(graph);
+    if (rc != RL_OK || e != hipSuccess) {
+        (void)hipEventDestroy(done);
+        return rc != RL_OK ? rc : fail(RL_EHIP, "%s: %s", what, hipGetErrorString(e));
+    }
+    c->gexec = exec;
+    c->gdone = done;
+    c->gkey = key;
+    return RL_OK;
+}
+static int replay_step(rl_ctx* c, int n) {
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n && e == hipSuccess; ++i) e = hipGraphLaunch(c->gexec, c->gkey.s);
+    const hipError_t r = hipEventRecord(c->gdone, c->gkey.s);   // also behind the launches before one that failed
+    if (e != hipSuccess) return fail(RL_EHIP, "hipGraphLaunch: %s", hipGetErrorString(e));
+    HIP_TRY(r);
+    return RL_OK;
+}
+
 static int check_sample(const rl_sample_cfg* sample) {
     if (!sample) return fail(RL_EINVAL, "sample cfg is NULL");
     if (!(sample->temperature >= 0.0f)) return fail(RL_EINVAL, "temperature must be >= 0");
@@ -1160,26 +1200,10 @@ int rollout_generate(rl_ctx* c, const rl_sample_cfg* sample, const int32_t* prom
     if (rc) return rc;
     const int ctx_cap = *std::max_element(need.begin(), need.end());
     if (graph_usable(c, s, ctx_cap)) {
-        // The step is identical from one token to the next (positions, step counters and page
-        // tables live on the device), so it is captured once and replayed G times.
-        rl_ctx::GraphKey key{B, G, c->impl, sample->eos_id, out_ids, out_logp, sample->seed, sample->seq_id_base,
-                             sample->temperature, s, nullptr, c->impl == 1 ? 0 : ctx_cap};
-        if (!c->gexec || !(key == c->gkey)) {
-            if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
-            std::vector<int> saved = c->cached;
-            HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, G, s, nullptr, ctx_cap);
-            hipGraph_t graph = nullptr;
-            hipError_t e = hipStreamEndCapture(s, &graph);
-            c->cached = saved;
-            if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
-            if (e != hipSuccess) return fail(RL_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-            e = hipGraphInstantiate(&c->gexec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (e != hipSuccess) { c->gexec = nullptr; return fail(RL_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e)); }
-            c->gkey = key;
-        }
-        for (int n = 0; n < G; ++n) HIP_TRY(hipGraphLaunch(c->gexec, s));
+        const rl_ctx::GraphKey key{B, G, c->impl, sample->eos_id, out_ids, out_logp, sample->seed, sample->seq_id_base,
+                                   sample->temperature, s, nullptr, c->impl == 1 ? 0 : ctx_cap};
+        if ((rc = capture_step(c, key, sample, out_ids, out_logp, nullptr, ctx_cap))) return rc;
+        if ((rc = replay_step(c, G))) return rc;
         for (int b = 0; b < B; ++b) c->cached[b] += G;
     } else {
         for (int n = 0; n < G; ++n) {
@@ -1297,24 +1321,11 @@ int rollout_generate_queue(rl_ctx* c, const rl_sample_cfg* sample, const int32_t
             need[b] = c->parked[b] ? c->cached[b] : std::min(c->cached[b] + kQueueBurst, c->cap[b]);
         if ((rc = ensure_pages(c, need, s))) { rollout_reset(c); return rc; }
         if (graph) {
-            rl_ctx::GraphKey key{nslots, Gmax, c->impl, sample->eos_id, out_ids, out_logp, sample->seed,
-                                 sample->seq_id_base, sample->temperature, s, out_len, c->impl == 1 ? 0 : ctx_cap};
-            if (!c->gexec || !(key == c->gkey)) {
-                if (c->gexec) { (void)hipGraphExecDestroy(c->gexec); c->gexec = nullptr; }
-                std::vector<int> saved = c->cached;
-                HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-                rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, Gmax, s, out_len, ctx_cap);
-                hipGraph_t g = nullptr;
-                hipError_t e = hipStreamEndCapture(s, &g);
-                c->cached = saved;
-                if (rc) { if (g) (void)hipGraphDestroy(g); rollout_reset(c); return rc; }
-                if (e != hipSuccess) { rollout_reset(c); return fail(RL_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e)); }
-                e = hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0);
-                (void)hipGraphDestroy(g);
-                if (e != hipSuccess) { c->gexec = nullptr; rollout_reset(c); return fail(RL_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e)); }
-                c->gkey = key;
-            }
-            for (int n = 0; n < kQueueBurst; ++n) HIP_TRY(hipGraphLaunch(c->gexec, s));
+            const rl_ctx::GraphKey key{nslots, Gmax, c->impl, sample->eos_id, out_ids, out_logp, sample->seed,
+                                       sample->seq_id_base, sample->temperature, s, out_len, c->impl == 1 ? 0 : ctx_cap};
+            rc = capture_step(c, key, sample, out_ids, out_logp, out_len, ctx_cap);
+            if (rc == RL_OK) rc = replay_step(c, kQueueBurst);
+            if (rc) { rollout_reset(c); return rc; }
             for (int b = 0; b < nslots; ++b) c->cached[b] = need[b];
         } else {
             for (int n = 0; n < kQueueBurst; ++n)
