@@ -765,9 +765,9 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const floa
     float* qs = sm;            // [hd]
     float* red = sm + hd;      // [16]
     float* part = red + 16;    // [256]
-    float* kn = part + 256;    // [hd] DEC: the new token's key and value, as the cache will hold them
-    float* vn = kn + hd;       // [hd]
-    float* sc = vn + hd;       // [ctx, rounded up to 4]
+    float* sc = part + 256;    // [ctx]
+    float* kn = part;          // [hd] DEC: the new token's key and value, as the cache will hold them (2 hd <= 256; the
+    float* vn = part + hd;     // [hd] partial sums come after their last use)
     const int* btr = DEC ? bt + (int64_t)tok_slot[n] * mpps : nullptr;
     if (DEC) {
         const float* row = qkv + (int64_t)n * (Hq + 2 * Hkv) * hd;
@@ -784,6 +784,8 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const floa
         for (int j = threadIdx.x; j < hd; j += 256) qs[j] = to_f(q[((int64_t)n * Hq + h) * hd + j]);
     }
     __syncthreads();
+    const int dd = threadIdx.x % hd, grp = threadIdx.x / hd, ngrp = 256 / hd;
+    const float k_new = DEC ? kn[dd] : 0.f, v_new = DEC ? vn[dd] : 0.f;
     const float scale = 1.0f / sqrtf((float)hd);
     float lmax = -INFINITY;
     // four threads per key: a context of a few dozen keys would otherwise leave most of the block idle behind one
@@ -810,7 +812,6 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const floa
     float ls = 0.f;
     for (int m = threadIdx.x; m < ctx; m += 256) { float e = __expf(sc[m] - mx); sc[m] = e; ls += e; }
     float tot = block_sum(ls, red);   // has barriers: sc[] visible afterwards
-    const int dd = threadIdx.x % hd, grp = threadIdx.x / hd, ngrp = 256 / hd;
     float acc = 0.f;
     if (DEC) {
         // V pages are dim-major: four tokens of a dimension are one load
@@ -823,7 +824,7 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const floa
                 for (int i = 0; m + i < pos; ++i) acc += sc[m + i] * to_f(vp[i]);
             }
         }
-        if (grp == 0) acc += sc[pos] * vn[dd];
+        if (grp == 0) acc += sc[pos] * v_new;
     } else {
         for (int m = grp; m < ctx; m += ngrp) acc += sc[m] * to_f(vc[((int64_t)(n - pos + m) * Hkv + g) * hd + dd]);
     }
@@ -834,12 +835,12 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T* q, const floa
         for (int i = 0; i < ngrp; ++i) o += part[i * hd + threadIdx.x];
         out[((int64_t)n * Hq + h) * hd + threadIdx.x] = from_f<T>(o / tot);
         if (DEC && h == g * G) {
-            pool[geo.k_off(layer, btr[pos / geo.PT], g, pos % geo.PT, threadIdx.x)] = from_f<T>(kn[threadIdx.x]);
-            pool[geo.v_off(layer, btr[pos / geo.PT], g, pos % geo.PT, threadIdx.x)] = from_f<T>(vn[threadIdx.x]);
+            pool[geo.k_off(layer, btr[pos / geo.PT], g, pos % geo.PT, threadIdx.x)] = from_f<T>(k_new);
+            pool[geo.v_off(layer, btr[pos / geo.PT], g, pos % geo.PT, threadIdx.x)] = from_f<T>(v_new);
         }
     }
 }
-size_t k_attn_simple_lds(int hd, int max_ctx) { return (size_t)(3 * hd + 16 + 256 + (max_ctx + 3) / 4 * 4) * sizeof(float); }
+size_t k_attn_simple_lds(int hd, int max_ctx) { return (size_t)(hd + 16 + 256 + max_ctx) * sizeof(float); }
 void k_attn_simple(int dtype, const void* q, const void* kc, const void* vc, const int* tok_pos, void* out, int n, int Hq,
                    int Hkv, int hd, int max_ctx, hipStream_t s) {
     if (n <= 0) return;

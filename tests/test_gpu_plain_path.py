@@ -62,3 +62,46 @@ def test_plain_decode_captured_and_eager(shape):
             assert np.array_equal(o, got[0][0]) and np.array_equal(l, got[0][1])
         verify_rollout(m, [ids[b, :lens[b]] for b in range(B)], got[0][0], got[0][1], 0.7, 4, 0, 1e-5, 1e-4)
     ro.close()
+
+
+def test_plain_attention_longest_context():
+    """The longest context whose scores a workgroup's LDS holds (head_dim + 16 + 256 floats of its 160 KB are taken by
+    everything else): prefill, decode and scoring take it.  One layer, so the last positions' keys and values come
+    straight from the embeddings and the oracle's formulas need one query at a time."""
+    shape = synth.ModelShape("long32f", 1, 64, 1, 1, 64, 64, 97, 10000.0, "fp32", 0.3)
+    most, G = 163840 // 4 - (64 + 16 + 256), 6
+    w = synth.make_weights(shape, 1, DEV)
+    W = R.Weights(w)
+    ro = R.Rollout(R.make_cfg(shape, 1, most), W, DEV)
+    P = most - G + 1                                        # the last decode step attends to `most` keys
+    ids = np.random.default_rng(5).integers(0, shape.vocab, size=(1, P)).astype(np.int32)
+    out = torch.zeros(1, G, dtype=torch.int32, device=DEV)
+    lp = torch.zeros(1, G, device=DEV)
+    ro.rollout_generate(R.sample_cfg(4, 0.0), torch.tensor(ids, device=DEV), [P], G, out, None, lp)
+    ro.rollout_check()
+    full = np.concatenate([ids, out.cpu().numpy()], axis=1)[:, :most]
+    scored = torch.zeros(1, most, device=DEV)
+    ro.score_logprobs_kl(W, None, torch.tensor(full, device=DEV), [most], [P], 0.003, scored)
+    ro.rollout_check()
+    o = synth.weights_for_oracle(w)
+    l = {k: np.asarray(v, np.float64) for k, v in o["layers"][0].items()}
+    x = np.asarray(o["tok_embed"], np.float64)[full[0]]
+    qkv = O.rmsnorm(x, l["attn_norm"], shape.rms_eps) @ l["wqkv"].T
+    pos = np.arange(most)
+    q, k = (O.rope(qkv[:, None, i * 64:i * 64 + 64], pos, shape.rope_base)[:, 0] for i in (0, 1))
+    v = qkv[:, 128:]
+    for t in range(P - 1, most):                            # the state after token t draws token t + 1
+        s = k[:t + 1] @ q[t] / 8.0
+        p = np.exp(s - s.max())
+        h = x[t] + (p @ v[:t + 1] / p.sum()) @ l["wo"].T
+        n = O.rmsnorm(h[None], l["ffn_norm"], shape.rms_eps)[0]
+        g, u = l["w_gate_up"][:64] @ n, l["w_gate_up"][64:] @ n
+        h = h + l["w_down"] @ (g / (1 + np.exp(-g)) * u)
+        z = np.asarray(o["lm_head"], np.float64) @ O.rmsnorm(h[None], np.asarray(o["final_norm"], np.float64), shape.rms_eps)[0]
+        lse = z.max() + np.log(np.exp(z - z.max()).sum())
+        tok = int(out[0, t - P + 1])
+        assert z[tok] > z.max() - 1e-3
+        assert abs(float(lp[0, t - P + 1]) - (z[tok] - lse)) < 1e-4
+        if t + 1 < most:
+            assert abs(float(scored[0, t + 1]) - (z[tok] - lse)) < 1e-4
+    ro.close()
