@@ -20,7 +20,9 @@
  *    but a small host-side state object.  It never allocates device memory.
  *  - `stream` is a hipStream_t passed as void* (NULL = the null stream).  All
  *    GPU work of a call is queued on it; calls return without waiting and the
- *    caller synchronises.  Calls on one context must not overlap.
+ *    caller synchronises.  Calls on one context must not overlap.  Work on a
+ *    stream that is being captured is refused (RL_EHIP) by every call except
+ *    rollout_decode_step, rollout_refresh_policy and ppo_rewards_noalloc.
  *  - Model: Llama-style decoder (pre-norm RMSNorm, rotary embedding with
  *    half-split pairing (j, j + head_dim/2), grouped-query attention, SwiGLU
  *    FFN, untied embedding / LM head, no biases).  Weight matrices are row-major

@@ -757,6 +757,16 @@ static size_t resident_bytes_of(const rl_model_cfg& c) {
     return 2 * al((size_t)c.vocab * d * e) + al(d * e) + layer * c.n_layers;
 }
 
+// Calls that move host state on (pages, sequence lengths, "the reference's copy is built") with the work they queue must
+// not be recorded: a graph under construction runs none of it, and a replay would run it without its host half.
+static int refuse_capture(hipStream_t s) {
+    if (s == nullptr) return RL_OK;   // the null stream cannot be captured
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &st));
+    if (st != hipStreamCaptureStatusNone) return fail(RL_EHIP, "operation not permitted when stream is capturing");
+    return RL_OK;
+}
+
 // Make stream s wait for a policy upload that may still be running on the copy stream.
 static int wait_policy(rl_ctx* c, hipStream_t s) {
     if (!c->policy_pending) return RL_OK;
@@ -1016,10 +1026,11 @@ int rollout_prefill(rl_ctx* c, const int32_t* prompt_ids, const int32_t* prompt_
             return fail(RL_EINVAL, "prompt_len[%d]=%d outside [1, min(Pmax, max_seq)]", b, prompt_len[b]);
     hipStream_t s = (hipStream_t)stream;
     const Layout& L = c->L;
+    int rcw = refuse_capture(s);
+    if (rcw) return rcw;
     c->B = 0;
     release_all_pages(c);
-    int rcw = wait_policy(c, s);
-    if (rcw) return rcw;
+    if ((rcw = wait_policy(c, s))) return rcw;
     std::vector<int> need(B);
     for (int b = 0; b < B; ++b) need[b] = prompt_len[b] - 1;
     int rc = ensure_pages(c, need, s);
@@ -1297,7 +1308,7 @@ int rollout_generate_queue(rl_ctx* c, const rl_sample_cfg* sample, const int32_t
     }
     hipStream_t s = (hipStream_t)stream;
     const Layout& L = c->L;
-    if ((rc = wait_policy(c, s))) return rc;
+    if ((rc = refuse_capture(s)) || (rc = wait_policy(c, s))) return rc;
     // entries past a row's length read eos_id (-1 when there is none) / log-prob 0
     k_fill_i32(out_ids, sample->eos_id, (int64_t)Q * Gmax, s);
     k_fill_i32(out_len, 0, Q, s);
@@ -1597,7 +1608,8 @@ int score_logprobs_kl(rl_ctx* c, const rl_weights* policy, const rl_weights* ref
         return fail(RL_EINVAL, "kl outputs need logp_policy and logp_ref buffers");
     hipStream_t s = (hipStream_t)stream;
     WeightsHost wp, wr;
-    int rc = RL_OK;
+    int rc = refuse_capture(s);
+    if (rc) return rc;
     if (policy) rc = copy_weights(m, policy, wp, "policy", true);
     else { wp = c->policy; rc = wait_policy(c, s); }   // the set the context generates with
     if (rc) return rc;
@@ -1642,7 +1654,7 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
     }
     WeightsHost wp, wr;
     int rc = copy_weights(m, policy, wp, "policy");
-    if (rc) return rc;
+    if (rc || (rc = refuse_capture((hipStream_t)stream))) return rc;
     if ((rc = copy_weights(m, reference, wr, "reference"))) return rc;
     if ((rc = ensure_other_shadow(c, wr, (hipStream_t)stream))) return rc;
     hipStream_t s = (hipStream_t)stream;
@@ -1733,8 +1745,8 @@ int score_values(rl_ctx* c, const rl_weights* model, const void* value_head, con
     if (!w.lm_head) w.lm_head = w.tok_embed;
     WeightsHost wh;
     int rc = copy_weights(m, &w, wh, "critic / reward model", true);
-    if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
+    if (rc || (rc = refuse_capture(s))) return rc;
     rc = wh.location == 1 ? score_pass_streamed(c, wh, ids, seq_len, B, Lmax, values, s, value_head)
                           : score_pass(c, wh, ids, seq_len, B, Lmax, values, s, value_head);
     if (rc) return rc;
@@ -1751,6 +1763,7 @@ int ppo_rewards(rl_ctx* c, const float* kl, const float* seq_reward, const int32
         if (seq_len[b] < 1 || seq_len[b] > Lmax || prompt_len[b] < 0 || prompt_len[b] > seq_len[b])
             return fail(RL_EINVAL, "row %d: need 1 <= seq_len <= Lmax and 0 <= prompt_len <= seq_len", b);
     hipStream_t s = (hipStream_t)stream;
+    if (int rc = refuse_capture(s)) return rc;
     const Layout& L = c->L;
     k_put_i32(c->at<int>(L.d_seq_len), seq_len, B, s);
     k_put_i32(c->at<int>(L.d_prompt_len), prompt_len, B, s);
