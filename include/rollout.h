@@ -335,8 +335,9 @@ int rollout_forget_fp16_copies(rl_ctx* ctx);
 /* Measurement switch (process-wide): decode-step GEMMs of more than `rows` rows run on the 128 x 128 tile kernel
  * instead of the LDS-ring weight streamer (default: a negative value = ring kernel for every batch). */
 int rollout_set_decode_tile_rows(int32_t rows);
-/* Measurement switch, process-wide: on = 0 makes the large-M GEMMs convert the bf16 weights even where an fp16 copy
- * (rl_weights.fp16_copy) exists; on != 0 (default) lets them read the copy.  Results are the same bit for bit. */
+/* Measurement switch, process-wide: on = 0 makes the large-M GEMMs leave the fp16 copies (rl_weights.fp16_copy) alone and
+ * treat every weight set as one that has none (converted on the fly, or ahead of a GEMM of many rows into workspace that
+ * is idle then); on != 0 (default) lets them read the copy.  Results are the same bit for bit. */
 int rollout_set_large_gemm_copy(int32_t on);
 
 /* Kernel classes for timing. */

@@ -66,7 +66,6 @@ struct GemmArgs {
 
 bool k_gemm_mfma_supported(int epi, int N, int K, int hd);
 bool k_gemm_mfma_reads_f16_copy(int epi, GemmArgs a, int splits);
-void k_gemm_big_reads_copy(int on);
 // splits > 1 only with MG_STORE_F32: partial sums of split s go to outF + s * split_stride.
 void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s);
 int k_gemm_mfma_splits_used(int K, int splits);

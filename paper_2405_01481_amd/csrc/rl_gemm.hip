@@ -957,8 +957,6 @@ static int big_row_blocks(int epi, const GemmArgs& a, int n_blocks_n) {
     }
     return best;
 }
-static int g_big_reads_copy = 1;   // measurement switch: 0 = the large-M GEMMs convert bf16 weights even where an fp16 copy exists
-void k_gemm_big_reads_copy(int on) { g_big_reads_copy = on; }
 template <int EPI>
 static void launch_big(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
     GemmArgs b = a;
@@ -997,7 +995,7 @@ int k_gemm_mfma_lse_parts(int M, int N, int K, int big_mode) {
 
 // Whether k_gemm_mfma will run this GEMM on the kernel that can read an fp16 copy of W (GemmArgs.w_f16).
 bool k_gemm_mfma_reads_f16_copy(int epi, GemmArgs a, int splits) {
-    if (a.M <= 0 || a.N <= 0 || !g_big_reads_copy) return false;
+    if (a.M <= 0 || a.N <= 0) return false;
     if (epi == MG_KLFULL) return true;
     if (a.Kw <= 0) a.Kw = a.K;
     if (splits < 1) splits = 1;

@@ -423,6 +423,8 @@ struct Scratch { char* p = nullptr; size_t bytes = 0; };
 // 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.
 static const int kConvertRows = 4096;
 
+static bool g_large_gemm_copy = true;   // rollout_set_large_gemm_copy: off = as if no weight set had a copy
+
 // w_skip: elements of a0.W that lie before the rows this GEMM uses (a0.W itself is what a weight set's copy is found by).
 static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s, Scratch idle = {}, size_t w_skip = 0) {
     ProfScope ps(c, cls, s);
@@ -442,7 +444,7 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
         if (k_gemm_mfma_reads_f16_copy(epi, a, splits)) {
             const int kw = a.Kw > 0 ? a.Kw : a.K;
             const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * kw;
-            const void* const h = copy_of((const void*)a.W);
+            const void* const h = g_large_gemm_copy ? copy_of((const void*)a.W) : nullptr;
             if (epi == MG_KLFULL) {                            // both models' copies or neither's
                 const void* const h2 = copy_of((const void*)a.W2);
                 if (h && h2) { a.W = (const bf16_t*)h; a.W2 = (const bf16_t*)h2; a.w_f16 = 1; }
@@ -966,7 +968,7 @@ int rollout_set_decode_tile_rows(int32_t rows) {
 }
 
 int rollout_set_large_gemm_copy(int32_t on) {
-    k_gemm_big_reads_copy(on != 0);
+    g_large_gemm_copy = on != 0;
     return RL_OK;
 }
 

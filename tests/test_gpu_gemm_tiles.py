@@ -44,3 +44,36 @@ def test_tile_heights_give_the_same_bits(copy):
     for n in totals:
         assert np.isfinite(res[1024, n]).all()
         assert np.array_equal(res[16384, n], res[1024, n]), n
+
+
+@pytest.mark.parametrize("on", [True, False], ids=["on", "off"])
+def test_copy_switch_leaves_sets_without_a_copy_alone(on):
+    """rollout_set_large_gemm_copy only decides whether existing copies are read: with the switch off, a set that has none
+    still has its LM head converted into idle workspace ahead of a GEMM of 4096 rows (the converted rows are still there
+    after the call), as does a set that has one, and nobody reads the copy (which is overwritten here)."""
+    w = synth.make_weights(SHAPE, 77 + on, DEV)
+    B, L = 8, 512
+    ids = torch.tensor(np.random.default_rng(5).integers(0, SHAPE.vocab, size=(B, L)).astype(np.int32), device=DEV)
+    lens = np.full(B, L, np.int32)
+    cfg = R.make_cfg(SHAPE, B, L)
+    first = w["lm_head"][0, :128].half().view(torch.int64)                  # 256 bytes
+    got = []
+    R.rollout_set_large_gemm_copy(on)
+    try:
+        for copy in (False, True) if not on else (False,):
+            shadow = torch.empty(R.rollout_weight_shadow_bytes(cfg), dtype=torch.uint8, device=DEV) if copy else None
+            W = R.Weights(w, shadow=shadow)
+            ro = R.Rollout(cfg, W, DEV)
+            ro.rollout_set_impl(2)
+            if copy:
+                shadow.fill_(0xff)
+            lp = torch.zeros(B, L, device=DEV)
+            ro.score_logprobs_kl(W, None, ids, lens, lens // 2, 0.0, lp)
+            ro.rollout_check()
+            ws = ro.workspace[:ro.workspace.numel() // 256 * 256].view(torch.int64).view(-1, 32)
+            assert (ws == first).all(dim=1).any()
+            got.append(lp.cpu().numpy())
+            ro.close()
+    finally:
+        R.rollout_set_large_gemm_copy(True)
+    assert all(np.isfinite(g).all() and np.array_equal(g, got[0]) for g in got)
