@@ -23,6 +23,7 @@ sys.path.insert(0, ROOT)
 
 from paper_2405_01481_amd import rollout as R   # noqa: E402
 from paper_2405_01481_amd import synth          # noqa: E402
+from paper_2405_01481_amd.profile_summary import traffic_entry   # noqa: E402
 
 HBM_PEAK_GBPS = 8000.0        # MI355X HBM3E
 MFMA_PEAK_TFLOPS = 2500.0     # dense bf16 / fp16 MFMA
@@ -199,7 +200,7 @@ def main():
     ap.add_argument("--precise-layers", type=int, default=None,
                     help="measurement switch: layers carried as fp16 pairs (library default 1)")
     ap.add_argument("--no-large-gemm-copy", action="store_true",
-                    help="measurement: the large-M GEMMs convert bf16 weights in the loop even where an fp16 copy exists")
+                    help="measurement: the large-M GEMMs leave existing fp16 copies alone, as for a set without copies")
     ap.add_argument("--separate-qkv-consumer", action="store_true",
                     help="measurement: a separate kernel sums, rotates and appends the decode QKV partial sums (default: decode attention does)")
     ap.add_argument("--vendor-gemm", action="store_true",
@@ -474,7 +475,7 @@ def main():
         ro2.close()
         del ro2
         if not args.no_score and not args.no_large_gemm_copy:
-            # and the scoring pass with the large-M GEMMs converting the bf16 weights themselves
+            # and the scoring pass with the large-M GEMMs on the bf16 weights, as for a set without copies
             R.rollout_set_large_gemm_copy(False)
             assemble()
             torch.cuda.synchronize()
@@ -504,7 +505,7 @@ def main():
         prefill_layers * sum(int(p_ - 1) * int(p_) / 2.0 for p_ in plen)
     work = {
         "gemm_prefill": ("mfma", 2.0 * (shape.body_params() * n_tok_scored + prefill_params * n_tok_prefill) / 1e12, "TFLOP",
-                         "large-M MFMA GEMMs of prefill and scoring (gemm_dma8_kernel 256x256 / gemm_mfma_kernel 128x128)"),
+                         "large-M MFMA GEMMs of prefill and scoring (gemm_dma8_kernel, tiles of up to 256x256 / gemm_mfma_kernel 128x128)"),
         "lmhead_score": ("mfma", 2.0 * shape.head_params() * max(n_tok_scored - 2 * B, 0) / 1e12, "TFLOP",
                          "LM head + log-sum-exp + target gather (MG_LSE epilogue)"),
         "attn_prefill": ("mfma", 4.0 * shape.n_q_heads * shape.head_dim * attn_pairs / 1e12, "TFLOP",
@@ -533,12 +534,13 @@ def main():
                "algorithmic_per_launch": amount / n, "algorithmic_unit": unit, "traffic": None}
         if bound == "mfma":
             ent["frac_of_sustained_mfma"] = achieved / mfma_sustained["random_operands"]
-        t = traffic_db.get(args.workload, {}).get(name)
+        t = traffic_entry(traffic_db, args.workload, name)
         if t and not reduced and args.impl in (-1, 1) and not t.get("context_dependent"):
             # HBM-side bytes per launch from rocprofv3 counters (FETCH_SIZE + WRITE_SIZE, scaled by a copy of known
-            # size), taken by the profile step that wrote profiles/hbm_traffic.json at the commit it names
+            # size), taken by the profile step that wrote profiles/hbm_traffic.json at the commit it names; none where
+            # what was counted is no kernel of the class any more
             ent["traffic"] = t["bytes_per_launch"]
-            ent["traffic_measured_at"] = traffic_db.get("commit")
+            ent["traffic_measured_at"] = t["commit"]
         rl.append(ent)
     rl.sort(key=lambda e: -e["ms_per_step"])
     roofline = rl[0] if rl else None

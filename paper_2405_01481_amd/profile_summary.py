@@ -7,7 +7,9 @@
         HBM-side bytes per launch of the kernel classes from two --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB per
         dispatch), each scaled by what the same counter reads for the 1 GiB device copies that
         `bench.py --calib-copy` runs first; merged into <out.json> under the workload's name together with the
-        current commit, which is where bench.py takes `roofline.traffic` from.
+        kernels that were counted and the current commit (run this where the repository's history is).  bench.py takes
+        `roofline.traffic` from there (traffic_entry): figures that name no commit, or a kernel that is none of the
+        class's any more, count as unmeasured.
 
 Reads files only; runs nothing on the GPU.
 """
@@ -22,9 +24,19 @@ import subprocess
 import sys
 
 # kernel name pattern -> class of bench.py's roofline entries (the LM-head GEMM is the tile kernel with epilogue 5)
-CLASSES = {r"gemm_(stream|ring)_kernel": "gemm_decode", r"attn_decode_kernel": "attn_decode",
-           r"gemm_dma8?_kernel<[0-4][,>]": "gemm_prefill", r"gemm_dma8?_kernel<5[,>]": "lmhead_score",
+CLASSES = {r"gemm_stream_kernel": "gemm_decode", r"attn_decode_kernel": "attn_decode",
+           r"gemm_dma8_kernel<[0-4][,>]": "gemm_prefill", r"gemm_dma8_kernel<5[,>]": "lmhead_score",
            r"attn_prefill_kernel": "attn_prefill"}
+
+
+def traffic_entry(db, workload, cls):
+    """The counted bytes of a class (the dict `traffic` wrote), or None where they are of no kernel bench.py runs now."""
+    ent = db.get(workload, {}).get(cls)
+    if not ent or not ent.get("commit") or not ent.get("kernels"):
+        return None
+    if any([c for pat, c in CLASSES.items() if re.match(pat, k)] != [cls] for k in ent["kernels"]):
+        return None
+    return ent
 
 
 def trace_table(path, top=24):
@@ -60,13 +72,20 @@ def traffic(fetch_csv, write_csv, workload, out_json):
         first = copies[0][:3]          # --calib-copy runs its three 1 GiB copies before anything else
         return gib_kib / (sum(first) / len(first))
     sf, sw = scale(fetch, "FETCH_SIZE"), scale(write, "WRITE_SIZE")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    try:
+        commit = subprocess.run(["git", "-C", root, "rev-parse", "--short", "HEAD"], capture_output=True, text=True).stdout.strip()
+    except Exception:
+        commit = ""
     res = {}
     for pattern, cls in CLASSES.items():
+        names = sorted(k for k in fetch if re.match(pattern, k))
         f = [x for k, v in fetch.items() if re.match(pattern, k) for x in v]
         w = [x for k, v in write.items() if re.match(pattern, k) for x in v]
         if not f or not w:
             continue
-        res[cls] = {"context_dependent": cls.startswith("attn_"),   # per-launch bytes grow with the sequences: only
+        res[cls] = {"kernels": names, "commit": commit,
+                    "context_dependent": cls.startswith("attn_"),   # per-launch bytes grow with the sequences: only
                     # comparable with a run of the same prompt and generation lengths
                     "bytes_per_launch": (sum(f) / len(f) * sf + sum(w) / len(w) * sw) * 1024.0,
                     "fetch_bytes_per_launch": sum(f) / len(f) * sf * 1024.0,
@@ -75,12 +94,6 @@ def traffic(fetch_csv, write_csv, workload, out_json):
         out = json.load(open(out_json))
     except Exception:
         out = {}
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    try:
-        commit = subprocess.run(["git", "-C", root, "rev-parse", "--short", "HEAD"], capture_output=True, text=True).stdout.strip()
-    except Exception:
-        commit = ""
-    out["commit"] = commit or out.get("commit", "")
     out["scale_factors"] = {"FETCH_SIZE": sf, "WRITE_SIZE": sw}
     out[workload] = res
     json.dump(out, open(out_json, "w"), indent=1, sort_keys=True)
