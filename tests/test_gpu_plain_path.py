@@ -1,5 +1,6 @@
-"""The plain (fp32) path's kernels at the sizes where they can go wrong, against the oracle: the GEMM's three tile sizes
-with remainders in rows and columns, and the captured decode step against the eager one."""
+"""The plain path's kernels at the sizes where they can go wrong, against the oracle: the GEMM's three tile sizes with
+remainders in rows and columns under every epilogue, the captured decode step against the eager one, and the longest
+context."""
 import numpy as np
 import pytest
 import torch
@@ -12,19 +13,50 @@ from tests.helpers import check_scores, verify_rollout
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
-# vocabularies that are no multiple of any tile width; 517 rows of 6001 columns reach the 64 x 64 tiles, 70 rows of
-# 3001 the 32 x 32 ones, 3 rows the 16 x 16 ones
+# widths that are no multiple of any tile; the rows of a scoring pass are one chunk, of which the LM head takes 512 at a time
 WIDE = synth.ModelShape("wide32f", 1, 128, 2, 1, 64, 192, 6001, 10000.0, "fp32", 0.08)
 MID = synth.ModelShape("mid32f", 2, 192, 3, 3, 64, 320, 3001, 10000.0, "fp32", 0.08)
 HD128 = synth.ModelShape("hd128f", 2, 256, 2, 1, 128, 128, 333, 10000.0, "fp32", 0.08)
+# layer GEMMs on taller tiles: the O and down projections (residual) and gate/up (SwiGLU) with few k and many columns
+LAYER32 = synth.ModelShape("layer32", 1, 1536, 2, 1, 64, 1600, 130, 10000.0, "fp32", 0.03)
+LAYER64 = synth.ModelShape("layer64", 1, 2048, 2, 1, 64, 2112, 130, 10000.0, "fp32", 0.03)
 
 
-@pytest.mark.parametrize("shape,lens", [(WIDE, [200, 317]), (MID, [1, 33, 36]), (HD128, [17, 3])], ids=["64", "32", "16"])
-def test_plain_gemm_tiles_against_oracle(shape, lens):
-    B, Lmax = len(lens), max(lens)
+def _tile(rows, cols):
+    """The launcher's rule: the largest tile that gives the 256 compute units two workgroups each."""
+    for t in (64, 32):
+        if -(-rows // t) * -(-cols // t) >= 512:
+            return t
+    return 16
+
+
+# tile of the QKV, O, gate/up and down GEMMs, and of the LM head's blocks of rows; each taller tile meets a remainder of rows
+# and, in the LM head, of columns (the layers' widths are multiples of 64)
+CASES = {
+    "head64": (WIDE, [200, 250], (16, 16, 16, 16), {64}),
+    "head32": (MID, [100, 33, 67], (16, 16, 16, 16), {32}),
+    "16": (HD128, [17, 3], (16, 16, 16, 16), {16}),
+    "layer32": (LAYER32, [200, 133], (16, 32, 32, 32), {16}),
+    "layer64": (LAYER64, [600, 425], (16, 64, 64, 64), {16}),
+}
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("name", CASES)
+def test_plain_gemm_tiles_against_oracle(name, dtype):
+    """fp32 has the norm inside the GEMM; bf16 weights (plain kernels asked for) have it in a kernel of its own."""
+    shape, lens, layer_tiles, head_tiles = CASES[name]
+    shape = synth.scaled_shape(shape, shape.name, dtype=dtype)
+    B, Lmax, n = len(lens), max(lens), sum(lens)
+    qd = shape.n_q_heads * shape.head_dim
+    assert tuple(_tile(n, w) for w in (qd + 2 * shape.n_kv_heads * shape.head_dim, shape.d_model, shape.d_ffn,
+                                       shape.d_model)) == layer_tiles
+    assert {_tile(min(512, n - r), shape.vocab) for r in range(0, n, 512)} == head_tiles
     wp, wr = synth.make_weights(shape, 1, DEV), synth.make_weights(shape, 2, DEV)
     Wp, Wr = R.Weights(wp), R.Weights(wr)
     ro = R.Rollout(R.make_cfg(shape, B, Lmax), Wp, DEV)
+    if dtype == "bf16":
+        ro.rollout_set_impl(0)
     rng = np.random.default_rng(7)
     ids = rng.integers(0, shape.vocab, size=(B, Lmax)).astype(np.int32)
     L = np.array(lens, np.int32)
@@ -33,7 +65,8 @@ def test_plain_gemm_tiles_against_oracle(shape, lens):
     ro.score_logprobs_kl(Wp, Wr, torch.tensor(ids, device=DEV), L, P, 0.003, *outs)
     ro.rollout_check()
     mp, mr = (O.Model(shape, synth.weights_for_oracle(w)) for w in (wp, wr))
-    check_scores(*[o.cpu().numpy() for o in outs], O.score_batch(mp, mr, ids, L, P, 0.003), 1e-4, 0.003)
+    check_scores(*[o.cpu().numpy() for o in outs], O.score_batch(mp, mr, ids, L, P, 0.003),
+                 1e-4 if dtype == "fp32" else 2e-2, 0.003)
     ro.close()
 
 
