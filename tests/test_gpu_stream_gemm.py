@@ -1,5 +1,5 @@
 """The decode step's weight-streaming GEMMs (contexts of at most 64 and 128 rows): one to eight 16-row tiles of activations
-with remainders, every number of column tiles a workgroup may take, K split and not, rows of a power of two long (start
+with remainders, every number of tiles of W a gate/up or LM-head workgroup may take, K split and not, rows of a power of two long (start
 rotated) and not, bf16 weights and an fp16 copy -- against the oracle, and row by row against smaller batches."""
 import numpy as np
 import pytest
@@ -13,20 +13,33 @@ from tests.helpers import verify_rollout
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
-# column tiles of the gate/up GEMM and the LM head: 7 and 8; 3 and 4; 5 and 6; 4 (last one short) and 2; widths that
-# are no multiple of 128 (C's FFN: the pair layer's down projection wraps inside a k-tile and stays on the 128 x 128 tile kernel)
-SHAPES = [
-    synth.ModelShape("stream_a", 2, 1024, 8, 2, 128, 14336, 32768, 10000.0, "bf16", 0.02),
-    synth.ModelShape("stream_b", 2, 384, 6, 3, 64, 6144, 12288, 10000.0, "bf16", 0.04),
-    synth.ModelShape("stream_c", 2, 256, 32, 8, 128, 10304, 24576, 10000.0, "bf16", 0.04),
-    synth.ModelShape("stream_d", 2, 640, 10, 5, 64, 8320, 8064, 10000.0, "bf16", 0.04),
-]
+# 16-row tiles of W that a workgroup of the gate/up GEMM and of the LM head takes (the LM head: even numbers only).  C's
+# last gate/up workgroup is short, and its FFN width is no multiple of 128: the pair layer's down projection wraps inside
+# a k-tile and runs on the 128 x 128 tile kernel.  (QKV, O and down projections take more than two tiles only at model
+# widths, which the tests of the five configurations cover.)
+SHAPES = {
+    synth.ModelShape("stream_a", 2, 1024, 8, 2, 128, 14336, 32768, 10000.0, "bf16", 0.02): (7, 8),
+    synth.ModelShape("stream_b", 2, 384, 6, 3, 64, 6144, 12288, 10000.0, "bf16", 0.04): (3, 4),
+    synth.ModelShape("stream_c", 2, 256, 32, 8, 128, 10304, 24576, 10000.0, "bf16", 0.04): (6, 6),
+    synth.ModelShape("stream_d", 2, 640, 10, 5, 64, 8320, 8064, 10000.0, "bf16", 0.04): (5, 2),
+    synth.ModelShape("stream_e", 2, 256, 4, 2, 64, 2048, 4096, 10000.0, "bf16", 0.06): (1, 2),
+    synth.ModelShape("stream_f", 2, 256, 4, 2, 64, 4096, 4096, 10000.0, "bf16", 0.06): (2, 2),
+    synth.ModelShape("stream_g", 2, 256, 4, 2, 64, 8192, 4096, 10000.0, "bf16", 0.06): (4, 2),
+    synth.ModelShape("stream_h", 2, 256, 4, 2, 64, 16384, 4096, 10000.0, "bf16", 0.06): (8, 2),
+}
+
+
+def _tiles(n_tiles, most, step):
+    """The launcher's rule for a GEMM that is not split over K: fewest rounds of 256 workgroups, weighed by their size."""
+    rows = 1 if most <= 64 else 4
+    return min(range(step, 9, step), key=lambda c: -(-(-(-n_tiles // c)) // 256) * (c + rows))
 
 
 @pytest.mark.parametrize("most", [64, 128])
 @pytest.mark.parametrize("copy", [False, True], ids=["bf16", "fp16copy"])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
 def test_stream_gemm_rows_and_widths(shape, copy, most):
+    assert (_tiles(shape.d_ffn // 8, most, 1), _tiles(shape.vocab // 16, most, 2)) == SHAPES[shape]
     P, G = 9, 4
     w = synth.make_weights(shape, 1, DEV)
     cfg = R.make_cfg(shape, most, P + G)
