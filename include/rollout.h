@@ -94,7 +94,8 @@ typedef struct rl_weights {
     void* fp16_copy;                /* optional (NULL = none), device-resident bf16 sets on the tuned path only: a dev
                                        buffer of rollout_weight_shadow_bytes(cfg) bytes, 256-byte aligned, in which the
                                        library keeps an fp16 copy of the bf16 matrices; the GEMMs that can, read the
-                                       copy and skip the conversion (same results bit for bit; 3-10 % faster).
+                                       copy and skip the conversion (same results bit for bit; scoring and prefill
+                                       passes 2-9 % faster, decode up to 2 %).
                                        POLICY given to rollout_init / rollout_set_policy: owned by the context until it
                                        is destroyed or given another policy; rebuilt by those calls and by
                                        rollout_refresh_policy.
@@ -332,8 +333,8 @@ int rollout_set_fused_qkv_consumer(rl_ctx* ctx, int32_t on);
  * brings one rebuilds it.  For callers that overwrite a reference set's values in place. */
 int rollout_forget_fp16_copies(rl_ctx* ctx);
 
-/* Measurement switch (process-wide): decode-step GEMMs of more than `rows` rows run on the 128 x 128 tile kernel
- * instead of the LDS-ring weight streamer (default: a negative value = ring kernel for every batch). */
+/* Measurement switch (process-wide): decode-step GEMMs of more than `rows` (and at most 128) rows run on the 128 x 128
+ * tile kernel instead of the weight-streaming kernel (default: a negative value = never). */
 int rollout_set_decode_tile_rows(int32_t rows);
 /* Measurement switch, process-wide: on = 0 makes the large-M GEMMs leave the fp16 copies (rl_weights.fp16_copy) alone and
  * treat every weight set as one that has none (converted on the fly, or ahead of a GEMM of many rows into workspace that

@@ -41,7 +41,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // A wave's page numbers are fetched once, one per lane (64 iterations' worth; without splits even before the position
 // is known), so that a page's loads wait for no index load; with up to 8 waves per workgroup short contexts need no
 // splits and no merge kernel.  32 rows, 8 kv heads, 200 keys, head_dim 64: 2 splits x 4 waves + merge 12.8 us, 8 waves
-// 7.0 us; 64 rows, 280 keys: 13.5 + 4.8 us, 11.2; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
+// 7.0 us; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
 // Queries are then read from LDS, and the wave that holds the page of the new token takes that token's key row and
 // value column from LDS instead of from the page, so nothing depends on when the appended values become visible.
 template <int HD, int PT, bool SP, bool FU, int NW>
@@ -342,7 +342,8 @@ bool k_attn_decode_consumes_qkv(int Hq, int Hkv, int hd) {
 
 // From the context's limits: a workgroup draws up to 38 KB/us, four waves of it as much as eight, so 256 workgroups are
 // enough to read the cache at memory speed, and a split costs a merge kernel and the query's preparation once more.  Hence
-// splits only up to 256 workgroups, of at least 16 pages of the longest sequence each; eight waves where fewer than 512
+// only as many splits as it takes to reach 256 workgroups, rounded up (25 rows of 8 kv heads: 2 splits, 400 workgroups), of
+// at least 16 pages of the longest sequence each; eight waves where fewer than 512
 // workgroups leave room (short contexts: 32 rows x 200 keys 6.0 -> 5.3 us, but 64 rows x 300 keys at head_dim 128 16.0 ->
 // 17.6).  8 kv heads, head_dim 128, merge included, splits 1 / 2 / 4 / 8: 32 rows x 1600 keys 40.6 / 42.4 / 45 / 50 us,
 // 16 x 4000 59 / 51 / 50 / 54, 8 x 1600 21.8 / 16.5 / 15.8 / 16.9, 1 x 4000 46 / 28 / 18.6 / 14.9, 8 x 300 8.0 / 9.0 / 8.7 / 10.3.

@@ -90,7 +90,7 @@ void k_list_rows(const int* at, const int* first, const int* count, int n, int* 
 // Pack rows of a padded [*, ld_ids] id matrix into a flat token list.
 // Row r of the chunk is batch row seq_first[r]; its row_len[r] tokens go to
 // [row_start[r], row_start[r] + row_len[r]).  tok_tgt (optional) = next token id of the
-// same row, or -1 when there is none inside full_len[r].
+// same row, or -1 when there is none.
 // With align > 1 every row is padded to a multiple of align tokens; padding entries carry
 // token id 0, position -1 and no target.
 // blocks (optional): the prefill attention's work list, one entry (first row, length, query block) per 32-query block,

@@ -2,7 +2,7 @@
 #pragma once
 #include "rl_common.h"
 
-enum { MG_STORE_F32 = 0, MG_STORE_F16 = 1, MG_RESID = 2, MG_SWIGLU = 3, MG_QKV = 4, MG_LSE = 5, MG_KLFULL = 6, MG_SAMPLE = 7 };
+enum { MG_STORE_F32 = 0, MG_RESID = 2, MG_SWIGLU = 3, MG_QKV = 4, MG_LSE = 5, MG_KLFULL = 6, MG_SAMPLE = 7 };
 
 struct GemmArgs {
     const f16_t* A = nullptr;   // [M, K] row-major, leading dimension lda
@@ -15,7 +15,7 @@ struct GemmArgs {
     // halves of a row in columns [0, Kw) and the lo halves in [Kw, 2 Kw), K = 2 Kw, and the k index into W wraps
     // at Kw, i.e. C = A_hi W^T + A_lo W^T in one pass.  Kw = 0: plain operand, W has K columns.
     int Kw = 0;
-    // Epilogues that emit fp16 activations (MG_SWIGLU, MG_QKV, MG_STORE_F16) write such pairs: hi where the
+    // Epilogues that emit fp16 activations (MG_SWIGLU, MG_QKV) write such pairs: hi where the
     // plain value would go, lo one plane further (next to it in the row for row-major outputs, whose leading
     // dimensions are then twice as wide; the cache's lo planes live in layer `layer_lo`).
     int split_out = 0;
@@ -26,7 +26,7 @@ struct GemmArgs {
     int rotate_k = 0;           // filled by the launcher (k_gemm_decode)
     int up_offset = 0;          // MG_SWIGLU: row of W where the up projection starts
     float* outF = nullptr;      // MG_STORE_F32 (+ split * split_stride) / MG_RESID
-    f16_t* outH = nullptr;      // MG_STORE_F16 / MG_SWIGLU
+    f16_t* outH = nullptr;      // MG_SWIGLU
     int ldc = 0;
     int64_t split_stride = 0;
     // MG_QKV

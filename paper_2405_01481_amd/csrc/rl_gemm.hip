@@ -11,7 +11,7 @@
 //     LDS loads -- the large-M GEMMs of prefill and scoring;
 //   * gemm_kl8_kernel:  the same loop run twice on tiles of 128 rows -- the exact full-vocabulary KL, which needs the
 //     policy's and the reference's logits of a tile together.
-// Epilogues: fp32 store / split-K partial, fp16 store, residual add, SwiGLU, RoPE + q/k/v split for
+// Epilogues: fp32 store / split-K partial, residual add, SwiGLU, RoPE + q/k/v split for
 // the QKV projection, log-sum-exp + target gather for the scoring LM head.
 #include "rl_common.h"
 #include "rl_gemm.h"
@@ -335,23 +335,17 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
         }
         return;
     }
-    if constexpr (EPI == MG_SWIGLU || EPI == MG_STORE_F16) {
+    if constexpr (EPI == MG_SWIGLU) {
         // A band that lies wholly inside the matrix (the rule on the large-M path) and leaves as plain fp16: no
         // per-element bounds checks or branches, one row pointer per register row.  Same values as the general path.
-        constexpr int OUT_COLS = EPI == MG_SWIGLU ? TN * 16 : TN * 32;       // output columns of this wave
-        const int n_first = (EPI == MG_SWIGLU ? nb * (BN / 2) : nb * BN) + wn * OUT_COLS;
-        if (m_base + 2 * NR <= a.M && n_first + OUT_COLS <= a.N && !a.split_out) {   // wave-uniform
+        const int n_first = nb * (BN / 2) + wn * TN * 16;      // of this wave's TN * 16 output columns
+        if (m_base + 2 * NR <= a.M && n_first + TN * 16 <= a.N && !a.split_out) {   // wave-uniform
             f16_t* o = a.outH + (int64_t)(m_base + 4 * lg) * a.ldc + n_first + lrow;
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
                 f16_t* orow = o + (int64_t)(8 * (r >> 2) + (r & 3)) * a.ldc;
-                if constexpr (EPI == MG_SWIGLU) {
 #pragma unroll
-                    for (int j = 0; j < TN; j += 2) orow[(j / 2) * 32] = (f16_t)swiglu_act(acc[j][r], acc[j + 1][r]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) orow[j * 32] = (f16_t)acc[j][r];
-                }
+                for (int j = 0; j < TN; j += 2) orow[(j / 2) * 32] = (f16_t)swiglu_act(acc[j][r], acc[j + 1][r]);
             }
             return;
         }
@@ -411,12 +405,6 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
                 for (int j = 0; j < TN; ++j) {
                     int n = nb * BN + wn * TN * 32 + j * 32 + lrow;
                     if (n < a.N) a.outF[(int64_t)ks * a.split_stride + (int64_t)m * a.ldc + n] = acc[j][r];
-                }
-            } else if (EPI == MG_STORE_F16) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    int n = nb * BN + wn * TN * 32 + j * 32 + lrow;
-                    if (n < a.N) a.outH[(int64_t)m * a.ldc + n] = (f16_t)acc[j][r];
                 }
             } else if (EPI == MG_SWIGLU) {
 #pragma unroll
@@ -752,7 +740,7 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
 template <int EPI, bool WF16, int MI>
 __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     constexpr int BM = 32 * MI, BN = 256, WGN = 4, TN = 2;
-    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [5 stages][A 256 x 64 B | W 256 x 64 B]
+    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [5 stages][A BM x 64 B | W 256 x 64 B]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
@@ -1020,10 +1008,6 @@ void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s) {
         case MG_STORE_F32:
             if (big) launch_big<MG_STORE_F32>(a, a.N / 256, s);
             else launch<128, 128, 2, 2, MG_STORE_F32>(a, a.N / 128, splits, s);
-            break;
-        case MG_STORE_F16:
-            if (big) launch_big<MG_STORE_F16>(a, a.N / 256, s);
-            else launch<128, 128, 2, 2, MG_STORE_F16>(a, a.N / 128, 1, s);
             break;
         case MG_RESID:
             if (big) launch_big<MG_RESID>(a, a.N / 256, s);

@@ -191,7 +191,7 @@ struct rl_ctx {
     int impl = 0;
     int precise = 0;                 // layers [0, precise) carry fp16-pair activations (tuned path only)
     int big_mode = 1;                // GemmArgs::big_mode of every tuned GEMM
-    // optional fp16 copy of the policy's matrices for the decode GEMMs (caller's buffer): bf16 pointer -> copy
+    // optional fp16 copy of the policy's matrices (caller's buffer): bf16 pointer -> copy
     std::unordered_map<const void*, const void*> shadow_of;
     // fp16 copy of one more weight set (the frozen reference): built when a set with rl_weights.fp16_copy is first
     // scored, kept while the same set (its first matrix) and the same buffer come back
@@ -320,7 +320,7 @@ static void gemm(rl_ctx* c, int cls, int epi, const void* A, int lda, const void
 // paged = attention reads the paged cache (decode); else the chunk's own contiguous K/V.
 // write_pages = append K/V of these tokens to the paged cache; unpaged, that is all the pass is for (prompt prefill), and
 // the residual stream it leaves is undefined.
-// Returns true when h already holds RMSNorm(x; final_norm) (the tuned decode path fuses it).
+// The tuned decode path leaves h = RMSNorm(x; final_norm).
 // qkv_part (decode, tuned kernels, plain layers): the QKV projection's split-K partial rows, which the attention
 // kernel then consumes itself instead of reading rotated queries and an already appended cache.
 static void attention(rl_ctx* c, int l, int n, bool paged, int max_ctx, int nblocks, hipStream_t s,
@@ -381,7 +381,7 @@ static void norm_gemm(rl_ctx* c, int cls, int epi, const float* x, const void* g
     gemm(c, cls, epi, h, m.d_model, W, W2, n, N, m.d_model, outF, outT, N, s);
 }
 
-static bool run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
+static void run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
                              int nblocks, hipStream_t s, float* x, int l0, int l1) {
     const rl_model_cfg& m = c->cfg;
     const Layout& L = c->L;
@@ -411,7 +411,6 @@ static bool run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged,
         norm_gemm(c, gcls, EPI_SWIGLU, x, W.ffn_norm[l], wg, wg + (size_t)m.d_ffn * m.d_model * e, n, m.d_ffn, nullptr, ffn, s);
         gemm(c, gcls, EPI_RESID, ffn, m.d_ffn, W.w_down[l], nullptr, n, m.d_model, m.d_ffn, x, nullptr, m.d_model, s);
     }
-    return false;
 }
 
 // Idle workspace a large-M GEMM may put an fp16 copy of its bf16 weights in for the time of the launch.
@@ -469,7 +468,7 @@ static int decode_splits(const rl_ctx* c, int n, int N, int K, int Kw) {
 }
 
 // bf16 weights / fp16 activations on the MFMA kernels.  paged: h holds the first layer's norm output (k_step_start).
-static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
+static void run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
                             int nblocks, hipStream_t s, float* x, int l0, int l1) {
     const rl_model_cfg& m = c->cfg;
     const Layout& L = c->L;
@@ -564,16 +563,15 @@ static bool run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             mfma(c, gcls, MG_RESID, g, 1, s, idle_attn);
         }
     }
-    return paged;
 }
 
 // Layers [l0, l1) (default: all) on the n packed rows whose residual stream is x (default: the workspace's).
-static bool run_layers(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
+static void run_layers(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
                        int nblocks, hipStream_t s, float* x = nullptr, int l0 = 0, int l1 = -1) {
     if (!x) x = c->at<float>(c->L.x);
     if (l1 < 0) l1 = c->cfg.n_layers;
-    if (c->impl == 1) return run_layers_fast(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
-    return run_layers_plain(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
+    if (c->impl == 1) run_layers_fast(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
+    else run_layers_plain(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
 }
 
 // Logits fp32 [nr, V] of nr rows.  Tuned path: of the workspace's h, which holds the final norm's output; plain path: of
@@ -647,10 +645,11 @@ static int pack_chunk(rl_ctx* c, const int* ids, int ld_ids, Chunk& ch, bool tar
     return RL_OK;
 }
 
-// ---------------------------------------------------------------- fp16 copy of the policy for the decode GEMMs
-// The decode GEMMs are bound by how fast a CU can pull weights, and the bf16 -> fp16 conversion they do next
-// to the MFMAs costs them about a tenth of that rate (30 % on the LM head).  With a caller-provided buffer of
-// the policy's size the conversion is done once per weight update instead of once per token.
+// ---------------------------------------------------------------- fp16 copy of the policy
+// With a caller-provided buffer of the policy's size the bf16 -> fp16 conversion that the GEMMs do next to their MFMAs is
+// done once per weight update.  Whole passes with a copy against none: scoring 9 % faster (70B width, 2220 rows), 6 - 7
+// (8B width, 1000 and 4000 rows), 2 (16384 rows, where a set without a copy gets one in idle workspace); decode steps 0
+// to 2 % (8B width, 1 to 128 rows: gemm_stream_kernel converts every fragment once).
 static size_t shadow_bytes_of(const rl_model_cfg& c) {
     if (c.dtype != RL_BF16) return 0;
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
@@ -1085,7 +1084,7 @@ static int decode_step_impl(rl_ctx* c, const rl_sample_cfg* sample, const int32_
     k_step_start(m.dtype, tok_in, c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.finished), c->at<int>(L.tok_pos),
                  c->at<int>(L.tok_slot), c->policy.tok_embed, m.d_model, m.vocab, c->at<float>(L.x), c->at<int>(L.errflag),
                  fast ? c->policy.attn_norm[0] : nullptr, c->at<char>(L.h), m.rms_eps, c->precise > 0, B, s);
-    run_layers(c, c->policy, B, true, true, max_ctx, 0, s);   // tuned: leaves h = RMSNorm(x; final_norm)
+    run_layers(c, c->policy, B, true, true, max_ctx, 0, s);
     SampleArgs a{sample->seed, sample->seq_id_base, sample->temperature, sample->eos_id};
     if (queue_out_len) {
         a.out_row = c->at<int>(L.out_row);
@@ -1775,9 +1774,8 @@ int ppo_rewards(rl_ctx* c, const float* kl, const float* seq_reward, const int32
 }
 
 // ---- ppo_rewards for callers that cannot allocate.  The per-sequence lengths have to be device arrays for the
-// kernel; ppo_rewards keeps them in the context's workspace and copies them there with the runtime.  Here they
-// live in a fixed array of the library's own and are written by kernels that take them as arguments, so the call
-// needs no context, no workspace and no copy: nothing in it allocates, and it can be recorded into a graph.
+// kernel, written by kernels that take them as arguments; ppo_rewards keeps them in the context's workspace, here they
+// live in a fixed array of the library's own, so the call needs no context: it can be recorded into a graph.
 static const int kNoAllocMaxB = 4096;                                    // sequences per call
 static __device__ __align__(256) int scratch[2 * kNoAllocMaxB];          // [seq_len | prompt_len], 32 KB per GPU
 static const int kMaxDevices = 64;
