@@ -203,7 +203,9 @@ int rollout_generate_queue(rl_ctx* ctx, const rl_sample_cfg* sample,
  * rollout_set_policy, also when that was uploaded from host memory).
  * Either weight set may be host-resident (location 1: "reference weights streamed layer by layer"): its
  * layers are copied into the set's staging buffer on a stream of the library's own, two layers deep,
- * while the previous layer runs on `stream` for all tokens; results are identical to the resident case.
+ * while the previous layer runs on `stream` for all tokens; results are identical to the resident case. The call
+ * then returns when the host tensors have been read (they may be changed or freed from there on, while the last
+ * layers are still running on `stream`); score_values does the same.
  * Errors: RL_EINVAL, RL_ENOSPACE (staging buffer too small). */
 int score_logprobs_kl(rl_ctx* ctx, const rl_weights* policy, const rl_weights* reference,
                       const int32_t* ids, const int32_t* seq_len, const int32_t* prompt_len,

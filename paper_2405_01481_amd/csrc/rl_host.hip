@@ -1582,6 +1582,9 @@ static int score_pass_streamed(rl_ctx* c, const WeightsHost& W, const int32_t* i
         if ((rc = pack_chunk(c, ids, Lmax, chunks[k], true, s))) return rc;
         apply_head(c, D, value_head, x_all + first[k] * m.d_model, chunks[k].n, logp_out, Lmax, s);
     }
+    // the caller's host tensors have been read when the call returns: they are on no stream that a caller could wait for
+    // or an allocator of pinned memory knows.  The last two layers' compute is still queued on s.
+    HIP_TRY(hipStreamSynchronize(cs));
     return RL_OK;
 }
 

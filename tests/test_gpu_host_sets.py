@@ -1,0 +1,55 @@
+"""Host-resident weight sets: a scoring call that returns has read them."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2405_01481_amd import rollout as R
+from paper_2405_01481_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+SHAPE = synth.ModelShape("hostset", 10, 1024, 8, 2, 128, 4096, 16384, 10000.0, "bf16", 0.02)
+
+
+def _tensors(w):
+    return [w["tok_embed"], w["final_norm"], w["lm_head"]] + [t for lay in w["layers"] for t in lay.values()]
+
+
+@pytest.mark.parametrize("call", ["logprobs", "values"])
+def test_host_tensors_may_change_when_the_call_returns(call):
+    """Every host tensor is overwritten right behind the call, without a wait for the stream; the scores are those of the
+    same set device-resident.  The uploads take milliseconds and wait for layers of 4096 rows."""
+    B, L = 16, 256
+    w = synth.make_weights(SHAPE, 1, DEV)
+    cfg = R.make_cfg(SHAPE, B, L)
+    W = R.Weights(w)
+    ro = R.Rollout(cfg, W, DEV)
+    staging = torch.empty(R.rollout_weight_staging_bytes(cfg), dtype=torch.uint8, device=DEV)
+    ids = torch.tensor(np.random.default_rng(3).integers(0, SHAPE.vocab, size=(B, L)).astype(np.int32), device=DEV)
+    lens, head = np.full(B, L, np.int32), torch.ones(SHAPE.d_model, dtype=SHAPE.torch_dtype, device=DEV)
+    host = [torch.empty(t.shape, dtype=t.dtype, pin_memory=True) for t in _tensors(w)]
+    it = iter(host)
+    named = {k: next(it) for k in ("tok_embed", "final_norm", "lm_head")}
+    named["layers"] = [{k: next(it) for k in lay} for lay in w["layers"]]
+
+    def score(model):
+        out = torch.zeros(B, L, device=DEV)
+        if call == "values":
+            ro.score_values(model, head, ids, lens, out)
+        else:
+            ro.score_logprobs_kl(model, None, ids, lens, lens // 2, 0.0, out)
+        return out
+
+    want = score(W).cpu().numpy()
+    streamed = R.Weights(named, staging=staging)
+    for _ in range(2):
+        for h, t in zip(host, _tensors(w)):
+            h.copy_(t)
+        torch.cuda.synchronize()
+        got = score(streamed)
+        for h in host:
+            h.zero_()
+        assert np.array_equal(got.cpu().numpy(), want) and np.abs(want).max() > 0
+    ro.rollout_check()
+    ro.close()
