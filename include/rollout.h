@@ -274,8 +274,8 @@ int rollout_check(rl_ctx* ctx, void* stream);
  *  - location 1 (host-resident set, pinned for the copies to be asynchronous): every tensor is copied into
  *    policy->staging (rollout_weight_resident_bytes) on a stream of the library's own and the call returns at once;
  *    work already queued with the old policy keeps running while the upload proceeds (the old set's memory is not
- *    touched, so with two device buffers the next set loads while the current one generates), and every later call
- *    that reads the policy makes its stream wait for the upload.  The host tensors must stay valid until then.
+ *    touched, so with two device buffers the next set loads while the current one generates), and the next call
+ *    that reads the policy waits for the upload.  The host tensors must stay valid until that call returns.
  * Errors: RL_EINVAL, RL_ENOSPACE, RL_EHIP. */
 int rollout_set_policy(rl_ctx* ctx, const rl_weights* policy);
 

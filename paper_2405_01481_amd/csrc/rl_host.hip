@@ -203,7 +203,7 @@ struct rl_ctx {
     hipEvent_t ev_begin = nullptr, ev_glob_copied = nullptr, ev_glob_free = nullptr;
     hipEvent_t ev_copied[2] = {nullptr, nullptr}, ev_free[2] = {nullptr, nullptr};
     // a policy uploaded from host memory by rollout_set_policy: its copies (and the rebuild of the fp16 copy) run on
-    // copy_stream; every call that reads the policy first makes its stream wait for ev_policy
+    // copy_stream; the first call that reads the policy waits for ev_policy
     hipEvent_t ev_policy = nullptr;
     bool policy_pending = false;
     // sequences
@@ -768,12 +768,21 @@ static int refuse_capture(hipStream_t s) {
     return RL_OK;
 }
 
-// Make stream s wait for a policy upload that may still be running on the copy stream.
+// Before work that reads the policy goes to stream s: wait for a policy upload that may still be running on the copy
+// stream.  The host waits, so that the host tensors have been read when the call returns (work queued on s runs on
+// meanwhile).  A stream under capture (rollout_refresh_policy) can only be made to wait itself.
 static int wait_policy(rl_ctx* c, hipStream_t s) {
     if (!c->policy_pending) return RL_OK;
-    if (hipEventQuery(c->ev_policy) == hipSuccess) { c->policy_pending = false; return RL_OK; }
-    (void)hipGetLastError();   // hipErrorNotReady is not an error
-    HIP_TRY(hipStreamWaitEvent(s, c->ev_policy, 0));
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s) HIP_TRY(hipStreamIsCapturing(s, &st));
+    if (st != hipStreamCaptureStatusNone) {
+        if (hipEventQuery(c->ev_policy) == hipSuccess) return RL_OK;
+        (void)hipGetLastError();   // hipErrorNotReady is not an error
+        HIP_TRY(hipStreamWaitEvent(s, c->ev_policy, 0));
+        return RL_OK;
+    }
+    HIP_TRY(hipEventSynchronize(c->ev_policy));
+    c->policy_pending = false;
     return RL_OK;
 }
 

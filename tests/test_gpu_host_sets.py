@@ -1,4 +1,4 @@
-"""Host-resident weight sets: a scoring call that returns has read them."""
+"""Host-resident weight sets: what may be changed or used again when a call returns."""
 import numpy as np
 import pytest
 import torch
@@ -51,5 +51,48 @@ def test_host_tensors_may_change_when_the_call_returns(call):
         for h in host:
             h.zero_()
         assert np.array_equal(got.cpu().numpy(), want) and np.abs(want).max() > 0
+    ro.rollout_check()
+    ro.close()
+
+
+def _pinned(w):
+    pin = lambda t: t.cpu().pin_memory()   # noqa: E731
+    out = {k: pin(w[k]) for k in ("tok_embed", "final_norm", "lm_head")}
+    out["layers"] = [{k: pin(v) for k, v in lay.items()} for lay in w["layers"]]
+    return out
+
+
+@pytest.mark.parametrize("overwrite", [True], ids=["host-tensors-change"])
+def test_policies_swapped_in_without_waits(overwrite):
+    """Policies uploaded in turn into two device buffers, each generating, with no wait anywhere.  With `overwrite`
+    every set's host tensors are overwritten (the last to be uploaded first) when the first call under it has returned."""
+    shape = synth.ModelShape("swaps", 3, 1024, 8, 2, 128, 2048, 32768, 10000.0, "bf16", 0.02)
+    B, P, runs = 8, 8, (400, 3, 5)
+    cfg = R.make_cfg(shape, B, P + max(runs))
+    ids, lens = synth.make_prompts(shape.vocab, B, P, 3, 3)
+    ids = torch.tensor(ids, device=DEV)
+    sets = [synth.make_weights(shape, i, DEV) for i in (1, 2, 3)]
+    ro = R.Rollout(cfg, R.Weights(sets[2]), DEV)
+    bufs = [torch.empty(R.rollout_weight_resident_bytes(cfg), dtype=torch.uint8, device=DEV) for _ in range(2)]
+    side = torch.cuda.Stream()
+
+    def swap_all(wait):
+        host = [_pinned(w) for w in sets]
+        outs = [(torch.zeros(B, g, dtype=torch.int32, device=DEV), torch.zeros(B, g, device=DEV)) for g in runs]
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for i, (out, lp) in enumerate(outs):
+                ro.rollout_set_policy(R.Weights(host[i], staging=bufs[i % 2]))
+                ro.rollout_generate(R.sample_cfg(4, 1.0), ids, lens, runs[i], out, None, lp)
+                if overwrite and not wait:
+                    for t in reversed(_tensors(host[i])):
+                        t.zero_()
+                if wait:
+                    torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        return [(o.cpu().numpy(), l.cpu().numpy()) for o, l in outs]
+
+    for want, got in zip(swap_all(True), swap_all(False)):
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
     ro.rollout_check()
     ro.close()
