@@ -275,7 +275,9 @@ int rollout_check(rl_ctx* ctx, void* stream);
  *    policy->staging (rollout_weight_resident_bytes) on a stream of the library's own and the call returns at once;
  *    work already queued with the old policy keeps running while the upload proceeds (the old set's memory is not
  *    touched, so with two device buffers the next set loads while the current one generates), and the next call
- *    that reads the policy waits for the upload.  The host tensors must stay valid until that call returns.
+ *    that reads the policy waits for the upload.  The host tensors must stay valid until that call returns.  The
+ *    buffer must not be the current policy's while work that reads it is queued; a buffer of a policy before that may
+ *    come back at once (once a call has read the current policy): the upload waits for the work queued before that call.
  * Errors: RL_EINVAL, RL_ENOSPACE, RL_EHIP. */
 int rollout_set_policy(rl_ctx* ctx, const rl_weights* policy);
 

@@ -203,8 +203,9 @@ struct rl_ctx {
     hipEvent_t ev_begin = nullptr, ev_glob_copied = nullptr, ev_glob_free = nullptr;
     hipEvent_t ev_copied[2] = {nullptr, nullptr}, ev_free[2] = {nullptr, nullptr};
     // a policy uploaded from host memory by rollout_set_policy: its copies (and the rebuild of the fp16 copy) run on
-    // copy_stream; the first call that reads the policy waits for ev_policy
-    hipEvent_t ev_policy = nullptr;
+    // copy_stream; the first call that reads the policy waits for ev_policy, and records ev_replaced on its stream first:
+    // what reads the policies before this one lies before it
+    hipEvent_t ev_policy = nullptr, ev_replaced = nullptr;
     bool policy_pending = false;
     // sequences
     int B = 0;                       // live sequences (0 = no prefill yet)
@@ -781,6 +782,7 @@ static int wait_policy(rl_ctx* c, hipStream_t s) {
         HIP_TRY(hipStreamWaitEvent(s, c->ev_policy, 0));
         return RL_OK;
     }
+    HIP_TRY(hipEventRecord(c->ev_replaced, s));
     HIP_TRY(hipEventSynchronize(c->ev_policy));
     c->policy_pending = false;
     return RL_OK;
@@ -872,7 +874,7 @@ void rollout_destroy(rl_ctx* c) {
         (void)hipStreamSynchronize(c->copy_stream);
         (void)hipStreamDestroy(c->copy_stream);
         for (hipEvent_t e : {c->ev_begin, c->ev_glob_copied, c->ev_glob_free, c->ev_copied[0], c->ev_copied[1],
-                             c->ev_free[0], c->ev_free[1], c->ev_policy})
+                             c->ev_free[0], c->ev_free[1], c->ev_policy, c->ev_replaced})
             if (e) (void)hipEventDestroy(e);
     }
     for (int k = 0; k < RL_K_COUNT; ++k)
@@ -909,7 +911,8 @@ int rollout_set_policy(rl_ctx* c, const rl_weights* policy) {
         const size_t nqkv = (size_t)(m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim;
         char* p = w.staging;
         hipStream_t cs = c->copy_stream;
-        hipError_t err = hipSuccess;
+        // the buffer may be that of a policy before the current one, whose last work is still queued
+        hipError_t err = hipStreamWaitEvent(cs, c->ev_replaced, 0);
         auto up = [&](const void*& ptr, size_t bytes) {
             if (err == hipSuccess) err = hipMemcpyAsync(p, ptr, bytes, hipMemcpyHostToDevice, cs);
             ptr = p;
@@ -1494,7 +1497,7 @@ static int ensure_copy_stream(rl_ctx* c) {
     if (c->copy_stream) return RL_OK;
     HIP_TRY(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
     for (hipEvent_t* e : {&c->ev_begin, &c->ev_glob_copied, &c->ev_glob_free, &c->ev_copied[0], &c->ev_copied[1],
-                          &c->ev_free[0], &c->ev_free[1], &c->ev_policy})
+                          &c->ev_free[0], &c->ev_free[1], &c->ev_policy, &c->ev_replaced})
         HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
     return RL_OK;
 }

@@ -62,10 +62,11 @@ def _pinned(w):
     return out
 
 
-@pytest.mark.parametrize("overwrite", [True], ids=["host-tensors-change"])
+@pytest.mark.parametrize("overwrite", [False, True], ids=["buffers-alternate", "host-tensors-change"])
 def test_policies_swapped_in_without_waits(overwrite):
-    """Policies uploaded in turn into two device buffers, each generating, with no wait anywhere.  With `overwrite`
-    every set's host tensors are overwritten (the last to be uploaded first) when the first call under it has returned."""
+    """Policies uploaded in turn into two device buffers, each generating, with no wait anywhere.  The third goes into the
+    first one's buffer while that one's long run is still queued.  With `overwrite` every set's host tensors are
+    overwritten (the last to be uploaded first) when the first call under it has returned."""
     shape = synth.ModelShape("swaps", 3, 1024, 8, 2, 128, 2048, 32768, 10000.0, "bf16", 0.02)
     B, P, runs = 8, 8, (400, 3, 5)
     cfg = R.make_cfg(shape, B, P + max(runs))
