@@ -130,7 +130,7 @@ def test_8b_long_ragged_four_layers():
 def test_8b_bench_configuration_full_length_row():
     """The configuration bench.py times (config 3: batch 128, prompts of 512, 512 sampled tokens, 32
     layers, chunks of 16384 tokens, decode replayed as a captured graph -- so the 256 x 256 GEMM tiles,
-    the ring decode GEMM at 128 rows and the paged attention at contexts up to 1023 are the kernels
+    the weight-streaming decode GEMM at 128 rows and the paged attention at contexts up to 1023 are the kernels
     that run), checked on one full row: the oracle is teacher-forced over the row's 1024 tokens under
     both models.  The bar is the contract's: every scored position of the row within 2e-2 of the
     oracle for the policy's and the reference's log-probs, the generation log-probs and the KL term;
@@ -286,7 +286,7 @@ def test_1b_bench_configuration_against_oracle():
 @pytest.mark.slow
 def test_8b_long_bench_configuration_against_oracle():
     """Config 4 as stated (8B shape at its full 32 layers, 32 ragged prompts of 1024-2048 tokens, 2048 sampled
-    tokens: decode at contexts from 1 k to 4 k with split-KV attention, rotary positions up to 4095, scoring over
+    tokens: decode at contexts from 1 k to 4 k, rotary positions up to 4095, scoring over
     rows of up to 4096 tokens), run whole on the GPU.  The row with the longest prompt (contexts pass 2048 and 4000)
     is checked over its full length under the policy: every log-prob within 2e-2, all 2048 sampled tokens inside the
     oracle's CDF bracket, generation log-probs within 2e-2.  The reference's log-probs and the KL term are checked

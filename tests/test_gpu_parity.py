@@ -247,7 +247,7 @@ def test_tuned_and_plain_kernels_agree(shape):
 @pytest.mark.parametrize("shape", [MINI64, MINI128], ids=lambda s: s.name)
 def test_big_tile_gemm_kernel_against_oracle(shape):
     """impl 2 sends every large-M GEMM (QKV with RoPE and cache write, output and down projections,
-    SwiGLU, scoring LM head with fused log-sum-exp) through the 256 x 256-tile kernel, which the
+    SwiGLU, scoring LM head with fused log-sum-exp) through the 256-column-tile kernel, which the
     benchmark shapes reach by size alone.  Here: ragged scoring over two row blocks with a partial
     second one, and a prefill whose cache the decode steps then read."""
     B, G = 6, 6
@@ -643,11 +643,12 @@ def test_policy_fp16_copy_gives_identical_rollouts():
 
 
 def test_long_context_decode_uses_split_kv():
-    """Contexts of 200-300 tokens: the decode attention runs with several KV splits per
-    (sequence, kv head) and merges them; ragged lengths leave partial and empty splits."""
+    """Contexts of 200-300 tokens in a context made for 1280: the decode attention runs with five KV splits per
+    (sequence, kv head) -- one per 16 pages of the longest sequence there could be -- and merges them; ragged lengths
+    leave partial and empty splits."""
     shape = MINI128
     B, G = 3, 6
-    ro, Wp, Wr, mp, mr = _setup(shape, B, 320)
+    ro, Wp, Wr, mp, mr = _setup(shape, B, 1280)
     ids, lens = synth.make_prompts(shape.vocab, B, 300, 180, 51)
     lens[0] = 17
     g_ids, _, g_lp = _generate(ro, ids, lens, G, 1.0, seed=13)
@@ -694,7 +695,7 @@ def test_precise_layers_shrink_the_error(shape, impl):
     the plain fp16 path's -- a wrong or missing lo term anywhere (GEMM k-wrap, q/k/v pairs, the three-term
     attention products, the lo planes of the cache, the pair-writing epilogues) would leave it where it
     was or make it worse.  Scoring (large-M kernels, ragged rows over several chunks) and generation
-    (decode kernels, paged lo planes, split-KV at contexts of 150-250 tokens) are both checked."""
+    (decode kernels, paged lo planes, contexts of 150-250 tokens) are both checked."""
     B, G = 4, 8
     ro, Wp, Wr, mp, mr = _setup(shape, B, 272, chunk=384)
     ro.rollout_set_impl(impl)
@@ -880,7 +881,7 @@ def test_end_of_sequence_on_the_tuned_path(fused):
 @pytest.mark.gpu
 def test_fp16_copies_in_the_large_m_gemms():
     """Scoring with fp16 copies of both weight sets (the policy's, kept by the context, and one the library builds for
-    the frozen reference) on the 256 x 256-tile kernel: bit-identical to scoring without copies, checked against the
+    the frozen reference) on the 256-column-tile kernel: bit-identical to scoring without copies, checked against the
     oracle, and the reference's copy is rebuilt after rollout_forget_fp16_copies when its values were changed in
     place."""
     shape, B = MINI128, 6
