@@ -897,8 +897,8 @@ int rollout_set_policy(rl_ctx* c, const rl_weights* policy) {
     if (w.location == 1) {
         // Host-resident set: every tensor is copied into the caller's device buffer on the library's copy stream
         // (so the upload overlaps with whatever the caller's streams are still running on the old policy, whose
-        // memory is not touched), and the context switches to the device copies.  Calls that read the policy make
-        // their stream wait for the upload.
+        // memory is not touched), and the context switches to the device copies.  The next call that reads the policy
+        // waits for the upload (wait_policy).
         const rl_model_cfg& m = c->cfg;
         if (!w.staging) return fail(RL_EINVAL, "host-resident policy needs a device buffer (rl_weights.staging)");
         if (((uintptr_t)w.staging & 255) != 0) return fail(RL_EINVAL, "policy buffer must be 256-byte aligned");
