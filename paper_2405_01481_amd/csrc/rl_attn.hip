@@ -38,12 +38,12 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // way, the workgroup sums the partials of its own G query heads and of its kv head's new key and value (in split
 // order), rotates q and k, keeps them in LDS as fp16, and -- split 0 only, after its loop -- appends k and v to the
 // cache page.
+// Queries are then read from LDS, and the wave that holds the page of the new token takes that token's key row and
+// value column from LDS instead of from the page, so nothing depends on when the appended values become visible.
 // A wave's page numbers are fetched once, one per lane (64 iterations' worth; without splits even before the position
 // is known), so that a page's loads wait for no index load; with up to 8 waves per workgroup short contexts need no
 // splits and no merge kernel.  32 rows, 8 kv heads, 200 keys, head_dim 64: 2 splits x 4 waves + merge 12.8 us, 8 waves
 // 7.0 us; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
-// Queries are then read from LDS, and the wave that holds the page of the new token takes that token's key row and
-// value column from LDS instead of from the page, so nothing depends on when the appended values become visible.
 template <int HD, int PT, bool SP, bool FU, int NW>
 __global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(DecodeAttnArgs a) {
     static_assert(!(SP && FU), "the pair layers keep the separate consumer kernel");
