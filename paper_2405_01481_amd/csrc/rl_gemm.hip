@@ -117,36 +117,10 @@ __device__ __forceinline__ float row32_sum(float v) {
 // Epilogue shared by the tile kernels, for one 32-row band of a wave's accumulators: acc[j][r] of the
 // wave in tile-column position wn is C(row, col) with
 //   row = m_base + 8*(r/4) + 4*(lane/32) + r%4,   col(tile-local) = wn*TN*32 + j*32 + lane%32
-// NR = 8 takes the band's first 16 rows only (registers 0 .. 7).
-// Row metadata of the MG_QKV epilogue held across a wave: lane l keeps position and cache page of rows row0 + l and
-// row0 + 64 + l (fetched before the main loop, so that the epilogue starts without a chain of dependent loads).
-struct QkvRowMeta {
-    int pos[2] = {-1, -1};    // < 0: padding row / past M
-    int page[2] = {0, 0};
-    int row0 = 0;
-};
-__device__ __forceinline__ QkvRowMeta qkv_row_meta(const GemmArgs& a, int row0, int lane) {
-    QkvRowMeta q;
-    q.row0 = row0;
-    int slot[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int m = row0 + h * 64 + lane;
-        const int p_ = a.tok_pos[min(m, a.M - 1)];
-        slot[h] = a.pool ? a.tok_slot[min(m, a.M - 1)] : 0;
-        q.pos[h] = m < a.M ? p_ : -1;
-    }
-    if (a.pool) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            q.page[h] = a.block_table[(int64_t)(q.pos[h] >= 0 ? slot[h] : 0) * a.mpps + max(q.pos[h], 0) / a.geo.PT];
-    }
-    return q;
-}
-
-template <int EPI, int BN, int TN, int WGN, int NR = 16>
+template <int EPI, int BN, int TN, int WGN>
 __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs& a, int m_base, int nb, int wn,
-                                            int ks, int lane, const QkvRowMeta* pre = nullptr) {
+                                            int ks, int lane) {
+    constexpr int NR = 16;
     const int lg = lane >> 5, lrow = lane & 31;
     if (EPI == MG_RESID) {
         // read-modify-write of the fp32 residual stream: all of the band's loads are issued before the
@@ -189,26 +163,13 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
         int pos[NR];                                           // < 0: padding row of the packed token list
         int page[NR];
         const bool to_pool = a.pool != nullptr && head_hi >= Hq;
-        if (pre) {
-            // the wave already holds these, one row per lane: pick them up with cross-lane reads
 #pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const int rel = m_base - pre->row0 + 8 * (r >> 2) + 4 * lg + (r & 3);   // 0 .. 127
-                const int src = rel & 63;
-                const int p0 = __shfl(pre->pos[0], src, RL_WAVE), p1 = __shfl(pre->pos[1], src, RL_WAVE);
-                const int g0 = __shfl(pre->page[0], src, RL_WAVE), g1 = __shfl(pre->page[1], src, RL_WAVE);
-                pos[r] = rel < 64 ? p0 : p1;
-                page[r] = rel < 64 ? g0 : g1;
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
-                const int p_ = a.tok_pos[min(m, a.M - 1)];
-                pos[r] = m < a.M ? p_ : -1;
-            }
+        for (int r = 0; r < NR; ++r) {
+            const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
+            const int p_ = a.tok_pos[min(m, a.M - 1)];
+            pos[r] = m < a.M ? p_ : -1;
         }
-        if (to_pool && !pre) {
+        if (to_pool) {
             int slot[NR];
 #pragma unroll
             for (int r = 0; r < NR; ++r) slot[r] = a.tok_slot[min(m_base + 8 * (r >> 2) + 4 * lg + (r & 3), a.M - 1)];
@@ -233,7 +194,7 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
                     if (m >= a.M) continue;
                     const bool pad = pos[r] < 0;               // padding rows get zeros: nothing non-finite is ever read back
                     const float x0 = pad ? 0.f : acc[j][r], x1 = pad ? 0.f : acc[j + 1][r];
-                    const float v0 = x0 * cs[r].x - x1 * cs[r].y, v1 = x1 * cs[r].x + x0 * cs[r].y;
+                    const float v0 = rope_lo(x0, x1, cs[r].x, cs[r].y), v1 = rope_hi(x0, x1, cs[r].x, cs[r].y);
                     f16_t h0, l0, h1, l1;
                     split_f16(v0, h0, l0);
                     split_f16(v1, h1, l1);
@@ -262,24 +223,6 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
                 continue;
             }
             const int g = head - Hq - Hkv;
-            if (a.v_out && a.vt_cap <= 0) {
-                // token-major V
-                {
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
-                        if (m >= a.M) continue;
-                        const bool pad = pos[r] < 0;
-                        f16_t h0, l0, h1, l1;
-                        split_f16(pad ? 0.f : acc[j][r], h0, l0);
-                        split_f16(pad ? 0.f : acc[j + 1][r], h1, l1);
-                        f16_t* o = a.v_out + ((int64_t)m * Hkv * S + g) * hd + jj;
-                        o[0] = h0; o[half] = h1;
-                        if (a.split_out) { o[Hkv * hd] = l0; o[Hkv * hd + half] = l1; }
-                    }
-                }
-            }
-            if (a.vt_cap <= 0 && !a.pool) continue;
             // V with dim-major destinations (vT[kv head][dim][token], and the V pages of the cache): the four
             // registers r = 4k .. 4k+3 of a lane are four consecutive tokens of one dimension, so they leave as one
             // 8-byte store instead of four 2-byte stores a cache line apart from their neighbours'.
@@ -296,11 +239,13 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         const float f0 = p[t] >= 0 ? acc[j][4 * rq + t] : 0.f, f1 = p[t] >= 0 ? acc[j + 1][4 * rq + t] : 0.f;
-                        const f16_t r0 = (f16_t)f0, r1 = (f16_t)f1;
-                        h0[t] = pl == 0 ? r0 : (f16_t)(f0 - (float)r0);
-                        h1[t] = pl == 0 ? r1 : (f16_t)(f1 - (float)r1);
+                        f16_t r0, r1, e0, e1;
+                        split_f16(f0, r0, e0);
+                        split_f16(f1, r1, e1);
+                        h0[t] = pl == 0 ? r0 : e0;
+                        h1[t] = pl == 0 ? r1 : e1;
                     }
-                    if (a.v_out && a.vt_cap > 0) {
+                    if (a.v_out) {
                         f16_t* o0 = a.v_out + ((int64_t)(pl * Hkv + g) * hd + jj) * a.vt_cap + m4;
                         f16_t* o1 = o0 + (int64_t)half * a.vt_cap;
                         if (m4 + 3 < a.M) {
@@ -605,10 +550,33 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a) {
 // WF16: W points at an fp16 copy of the weights and its fragments go from LDS straight into the MFMAs; otherwise W is
 // bf16 and each fragment is converted (exactly) next to the MFMAs of slice 1, which costs 5-10 % of the loop.  Both
 // forms feed the MFMAs the same values in the same order: their results are identical bit for bit.
-// The accumulators come out in the 16 x 16 layout (lane: column lane % 16, rows 4 * (lane / 16) + 0..3); before the
-// epilogues, which are written for the 32 x 32 layout, each wave passes them through its own 17 KB of the then idle
-// LDS, 64 rows at a time.
 // Requires K % 64 == 0, no split over K, 5 * 512 * 64 bytes of LDS.
+// Row metadata of the MG_QKV epilogue held across a wave: lane l keeps position and cache page of rows row0 + l and
+// row0 + 64 + l (fetched before the main loop, so that the epilogue starts without a chain of dependent loads).
+struct QkvRowMeta {
+    int pos[2] = {-1, -1};    // < 0: padding row / past M
+    int page[2] = {0, 0};
+    int row0 = 0;
+};
+__device__ __forceinline__ QkvRowMeta qkv_row_meta(const GemmArgs& a, int row0, int lane) {
+    QkvRowMeta q;
+    q.row0 = row0;
+    int slot[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int m = row0 + h * 64 + lane;
+        const int p_ = a.tok_pos[min(m, a.M - 1)];
+        slot[h] = a.pool ? a.tok_slot[min(m, a.M - 1)] : 0;
+        q.pos[h] = m < a.M ? p_ : -1;
+    }
+    if (a.pool) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            q.page[h] = a.block_table[(int64_t)(q.pos[h] >= 0 ? slot[h] : 0) * a.mpps + max(q.pos[h], 0) / a.geo.PT];
+    }
+    return q;
+}
+
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 template <int EPI, bool WF16, int MI>
 __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, int lda, const bf16_t* Wop, int m0, int nb, int wave,
@@ -668,7 +636,7 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
     _Pragma("unroll") for (int q = 0; q < 4 * ((AS) ? MI1 : MI0); ++q) {                                        \
         constexpr int NI_ = (AS) ? MI1 : MI0, NQ_ = 4 * NI_;                                                    \
         const int j_ = q / NI_, i_ = q % NI_;                                                                   \
-        acc[(AS) * MI0 + i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[AS][i_], __builtin_bit_cast(half8, wf[WS][j_]), acc[(AS) * MI0 + i_][j_], 0, 0, 0); \
+        acc[(AS) * MI0 + i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wf[WS][j_]), af[AS][i_], acc[(AS) * MI0 + i_][j_], 0, 0, 0); \
         if ((AS) == 0) {                                                                                        \
             _Pragma("unroll") for (int u_ = 0; u_ < MI1; ++u_)                                                  \
                 if (u_ * (NQ_ / 2) / MI1 == q) af[1][u_] = X8_LDA(NSO, MI0 + u_);                               \
@@ -737,9 +705,251 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
 #undef X8_SLICE
 }
 
+// ---- epilogues of the large-M kernel.  A wave's accumulators pass through its own LDS patch, 64 rows x 64 columns of
+// fp32 at a time, and come back with whole row pieces in each lane, so that everything that leaves is 16 bytes per lane
+// and stores and LDS accesses are few: with all 256 tiles of a round ending together, the matrix cores idle for as
+// long as an epilogue takes.  Row stride 68 floats: eight lanes on eight rows, or on two rows, meet no bank conflict.
+// W goes into the MFMAs as the first operand, so that a lane holds row lane % 16 of a 16 x 16 block and its
+// columns 4 * (lane / 16) .. + 3: 16-byte writes as well.  Against stores of one element per lane, 16384 rows of the 8B
+// shape: LM head 13.33 -> 12.21 ms, QKV 712 -> 647 us, residual and gate/up the same within 1 %: theirs wait for memory.
+static constexpr int PATCH_LD = 68;
+
+// Blocks FIRST .. FIRST + NB - 1 (16 rows each) of the wave's accumulators into the patch.
+template <int NB, int FIRST, int MI>
+__device__ __forceinline__ void patch_put(const floatx4_t (&acc)[MI][4], float* patch, int lane) {
+    float* const p = patch + (lane & 15) * PATCH_LD + 4 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<floatx4_t*>(p + i * 16 * PATCH_LD + j * 16) = acc[FIRST + i][j];
+    __builtin_amdgcn_wave_barrier();          // LDS accesses of a wave complete in order
+}
+template <int N>
+__device__ __forceinline__ void patch_get(float (&v)[N], const float* patch, int row, int col) {
+#pragma unroll
+    for (int x = 0; x < N / 4; ++x) {
+        const floatx4_t t = *reinterpret_cast<const floatx4_t*>(patch + row * PATCH_LD + col + 4 * x);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) v[4 * x + y] = t[y];
+    }
+}
+__device__ __forceinline__ float max_of(const float (&v)[16]) {
+    float m = v[0];
+#pragma unroll
+    for (int x = 1; x < 16; ++x) m = fmaxf(m, v[x]);
+    return m;
+}
+// over the four lanes of a quad, every lane with the same bits
+__device__ __forceinline__ float quad_max(float v) {
+    v = fmaxf(v, dpp_move<0xB1>(v));          // quad_perm [1,0,3,2]
+    return fmaxf(v, dpp_move<0x4E>(v));       // quad_perm [2,3,0,1]
+}
+__device__ __forceinline__ float quad_sum(float v) {
+    v += dpp_move<0xB1>(v);
+    return v + dpp_move<0x4E>(v);
+}
+// eight floats as fp16 pairs
+__device__ __forceinline__ void split8(const float (&v)[8], half8& hi, half8& lo) {
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        f16_t h, l;
+        split_f16(v[x], h, l);
+        hi[x] = h;
+        lo[x] = l;
+    }
+}
+
+// Rows HF * 64 .. of the wave (at most 64; m0 the first of them) of a tile in column block nb, wave column wn.
+template <int EPI, int MI, int HF>
+__device__ __forceinline__ void d8_half(const floatx4_t (&acc)[MI][4], float* patch, const GemmArgs& a, int m0, int nb,
+                                        int wn, int lane, const QkvRowMeta& meta) {
+    constexpr int NB = MI - HF * 4 < 4 ? MI - HF * 4 : 4;            // its 16-row blocks
+    if constexpr (EPI == MG_RESID || EPI == MG_STORE_F32) {
+        // four rows of 256 bytes per access.  The residual's loads all go out first (rows past M read row M - 1)
+        const int row = lane >> 4, c = nb * 256 + wn * 64 + (lane & 15) * 4;
+        floatx4_t old[NB * 4];
+        if constexpr (EPI == MG_RESID) {
+#pragma unroll
+            for (int it = 0; it < NB * 4; ++it)
+                old[it] = *reinterpret_cast<const floatx4_t*>(a.outF + (int64_t)min(m0 + it * 4 + row, a.M - 1) * a.ldc + c);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        patch_put<NB, HF * 4>(acc, patch, lane);
+#pragma unroll
+        for (int it = 0; it < NB * 4; ++it) {
+            const int m = m0 + it * 4 + row;
+            floatx4_t v = *reinterpret_cast<const floatx4_t*>(patch + (it * 4 + row) * PATCH_LD + (lane & 15) * 4);
+            if constexpr (EPI == MG_RESID) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x) v[x] = old[it][x] + v[x];
+            }
+            if (m < a.M) *reinterpret_cast<floatx4_t*>(a.outF + (int64_t)m * a.ldc + c) = v;
+        }
+    } else if constexpr (EPI == MG_SWIGLU) {
+        // columns 0 .. 31 of the wave are gates, 32 .. 63 the up projections of the same output columns; a quad of
+        // lanes holds a row
+        const int row = lane >> 2, c = (lane & 3) * 8;
+        f16_t* const o = a.outH + nb * 128 + wn * 32 + c;
+        patch_put<NB, HF * 4>(acc, patch, lane);
+#pragma unroll
+        for (int it = 0; it < NB; ++it) {
+            const int m = m0 + it * 16 + row;
+            float g[8], u[8], act[8];
+            patch_get(g, patch, it * 16 + row, c);
+            patch_get(u, patch, it * 16 + row, 32 + c);
+#pragma unroll
+            for (int x = 0; x < 8; ++x) act[x] = swiglu_act(g[x], u[x]);
+            half8 hi, lo;
+            split8(act, hi, lo);
+            if (m < a.M) {
+                *reinterpret_cast<half8*>(o + (int64_t)m * a.ldc) = hi;
+                if (a.split_out) *reinterpret_cast<half8*>(o + (int64_t)m * a.ldc + a.N) = lo;
+            }
+        }
+    } else if constexpr (EPI == MG_QKV) {
+        // The wave's columns belong to one head: columns w and w + 32 are the rotation pair (jb + w, jb + w + hd / 2)
+        const int hd = a.hd, half = hd >> 1, Hq = a.Hq, Hkv = a.Hkv;
+        const int head = hd == 128 ? nb * 2 + (wn >> 1) : nb * 4 + wn, jb = hd == 128 ? (wn & 1) * 32 : 0;
+        const int S = a.split_out ? 2 : 1;                     // fp16 pairs: rows of q and k are [hi heads | lo heads]
+        if (head < Hq + Hkv) {
+            // q and k: a quad of lanes per row rotates eight pairs each, rounds (and keeps what the rounding left over),
+            // stores token-major; k also to its page.  The rotation factors go out first
+            const int row = lane >> 2, c = (lane & 3) * 8;
+            int pos[NB], page[NB];
+            floatx4_t cs[NB][4];                               // (cos, sin) of two columns each
+#pragma unroll
+            for (int it = 0; it < NB; ++it) {
+                pos[it] = __shfl(meta.pos[HF], it * 16 + row, RL_WAVE);
+                page[it] = __shfl(meta.page[HF], it * 16 + row, RL_WAVE);
+                const float2* t = a.rope + (int64_t)max(pos[it], 0) * half + jb + c;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) cs[it][x] = *reinterpret_cast<const floatx4_t*>(t + 2 * x);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            patch_put<NB, HF * 4>(acc, patch, lane);
+#pragma unroll
+            for (int it = 0; it < NB; ++it) {
+                const int m = m0 + it * 16 + row;
+                const bool pad = pos[it] < 0;                  // padding rows get zeros: nothing non-finite is ever read back
+                float x0[8], x1[8], v0[8], v1[8];
+                patch_get(x0, patch, it * 16 + row, c);
+                patch_get(x1, patch, it * 16 + row, 32 + c);
+#pragma unroll
+                for (int x = 0; x < 8; ++x) {
+                    const float cx = cs[it][x >> 1][(x & 1) * 2], sx = cs[it][x >> 1][(x & 1) * 2 + 1];
+                    v0[x] = pad ? 0.f : rope_lo(x0[x], x1[x], cx, sx);
+                    v1[x] = pad ? 0.f : rope_hi(x0[x], x1[x], cx, sx);
+                }
+                if (m >= a.M) continue;
+                auto put = [](f16_t* p, int far, half8 h0, half8 h1) {
+                    *reinterpret_cast<half8*>(p) = h0;
+                    *reinterpret_cast<half8*>(p + far) = h1;
+                };
+                half8 h0, l0, h1, l1;
+                split8(v0, h0, l0);
+                split8(v1, h1, l1);
+                const int jj = jb + c;
+                if (head < Hq) {
+                    f16_t* o = a.q_out + (int64_t)m * Hq * hd * S + head * hd + jj;
+                    put(o, half, h0, h1);
+                    if (a.split_out) put(o + Hq * hd, half, l0, l1);
+                } else {
+                    const int g = head - Hq;
+                    if (a.k_out) {
+                        f16_t* o = a.k_out + ((int64_t)m * Hkv * S + g) * hd + jj;
+                        put(o, half, h0, h1);
+                        if (a.split_out) put(o + Hkv * hd, half, l0, l1);
+                    }
+                    if (a.pool && !pad) {
+                        const int st = pos[it] % a.geo.PT;
+                        put(a.pool + a.geo.k_off(a.layer, page[it], g, st, jj), half, h0, h1);
+                        if (a.split_out) put(a.pool + a.geo.k_off(a.layer_lo, page[it], g, st, jj), half, l0, l1);
+                    }
+                }
+            }
+        } else {
+            // V with dim-major destinations (vT[kv head][dim][token], and the V pages of the cache): a lane takes eight
+            // consecutive tokens of one dimension, 16 dimensions x 32 tokens per step
+            const int g = head - Hq - Hkv;
+            patch_put<NB, HF * 4>(acc, patch, lane);
+#pragma unroll
+            for (int rb = 0; rb < (NB + 1) / 2; ++rb) {
+                const int r0 = rb * 32 + (lane >> 4) * 8;      // first token; m0 + r0 is a multiple of 8
+                int pos[8], page[8];
+                bool run = r0 < NB * 16 && m0 + r0 + 7 < a.M;  // eight tokens of one sequence in one page
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    pos[t] = __shfl(meta.pos[HF], (r0 + t) & 63, RL_WAVE);
+                    page[t] = __shfl(meta.page[HF], (r0 + t) & 63, RL_WAVE);
+                    run = run && pos[t] == pos[0] + t;
+                }
+                run = run && pos[0] >= 0 && pos[0] % 8 == 0;
+                if (r0 >= NB * 16) continue;
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) {
+                    const int w = cb * 16 + (lane & 15);
+                    const int dim = w < 32 ? jb + w : half + jb + w - 32;
+                    float v[8];
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) v[t] = pos[t] < 0 ? 0.f : patch[(r0 + t) * PATCH_LD + w];
+                    half8 hi, lo;
+                    split8(v, hi, lo);
+                    for (int pl = 0; pl < S; ++pl) {           // plane 1: what the rounding left over
+                        const half8 h = pl == 0 ? hi : lo;
+                        if (a.v_out) {
+                            f16_t* o = a.v_out + ((int64_t)(pl * Hkv + g) * hd + dim) * a.vt_cap + m0 + r0;
+                            if (m0 + r0 + 7 < a.M) *reinterpret_cast<half8*>(o) = h;
+                            else {
+#pragma unroll
+                                for (int t = 0; t < 8; ++t)
+                                    if (m0 + r0 + t < a.M) o[t] = h[t];
+                            }
+                        }
+                        if (a.pool) {
+                            const int lay = pl == 0 ? a.layer : a.layer_lo;
+                            if (run) *reinterpret_cast<half8*>(a.pool + a.geo.v_off(lay, page[0], g, pos[0] % a.geo.PT, dim)) = h;
+                            else {
+#pragma unroll
+                                for (int t = 0; t < 8; ++t)
+                                    if (pos[t] >= 0) a.pool[a.geo.v_off(lay, page[t], g, pos[t] % a.geo.PT, dim)] = h[t];
+                            }
+                        }
+                    }
+                }
+            }
+        }
+    } else if constexpr (EPI == MG_LSE) {
+        // maximum and sum of exponentials of the wave's 64 columns: a quad of lanes per row, 16 columns each
+        const int row = lane >> 2, c = (lane & 3) * 16, n0 = nb * 256 + wn * 64;
+        int tg[NB];
+#pragma unroll
+        for (int it = 0; it < NB; ++it) tg[it] = a.tgt[min(m0 + it * 16 + row, a.M - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+        patch_put<NB, HF * 4>(acc, patch, lane);
+        const int nparts = a.N / 64;
+#pragma unroll
+        for (int it = 0; it < NB; ++it) {
+            const int m = m0 + it * 16 + row;
+            float z[16];
+            patch_get(z, patch, it * 16 + row, c);
+            const float mx = quad_max(max_of(z));
+            float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int x = 0; x < 16; ++x) s4[x & 3] += __expf(z[x] - mx);
+            const float se = quad_sum((s4[0] + s4[1]) + (s4[2] + s4[3]));
+            if ((lane & 3) == 0 && m < a.M) {
+                a.lse_part[(int64_t)m * nparts + nb * 4 + wn] = make_float2(mx, se);
+                const int d = tg[it] - n0;
+                if (d >= 0 && d < 64) a.z_tgt[m] = patch[(it * 16 + row) * PATCH_LD + d];
+            }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <int EPI, bool WF16, int MI>
 __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
-    constexpr int BM = 32 * MI, BN = 256, WGN = 4, TN = 2;
+    constexpr int BM = 32 * MI, WGN = 4;
     extern __shared__ __attribute__((aligned(1024))) char smem[];   // [5 stages][A BM x 64 B | W 256 x 64 B]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -751,76 +961,45 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     QkvRowMeta meta;
     dma8_loop<EPI, WF16, MI>(a, a.A, a.lda, a.W, m0, nb, wave, lane, smem, acc, meta);
     __syncthreads();                                   // every wave is done with the stages: LDS is free
-    // 16 x 16 layout -> 32 x 32 layout through this wave's own [64 rows][64 columns] fp32 patch; row stride 68 floats:
-    // four rows further on is 16 banks further on, so neither the writes (lanes 16 apart: 4 rows apart) nor the reads
-    // (lanes 32 apart: 4 rows apart, 32 consecutive columns per half-wave) collide
-    float* patch = reinterpret_cast<float*>(smem) + wave * (64 * 68);
-    const QkvRowMeta* pre = EPI == MG_QKV ? &meta : nullptr;
-    const int lg = lane >> 5, lrow = lane & 31;
-    // written out per half of 64 rows: with the largest epilogue the unroller gives up on a loop over the halves, and
-    // the accumulators must stay statically indexed.  A wave's last band has 16 rows where MI is odd.
-#define D8_READ(hf, b)                                                                                          \
-        floatx16 band##b[TN];                                                                                   \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                          \
-            _Pragma("unroll") for (int r = 0; r < 16; ++r)                                                      \
-                if ((hf) * 64 + (b) * 32 + 8 * (r >> 2) < MI * 16)                                              \
-                    band##b[j][r] = patch[((b) * 32 + 8 * (r >> 2) + 4 * lg + (r & 3)) * 68 + j * 32 + lrow];
-#define D8_BAND(hf, b)                                                                                          \
-        if constexpr ((hf) * 64 + (b) * 32 < MI * 16)                                                           \
-            mg_epilogue<EPI, BN, TN, WGN, (hf) * 64 + (b) * 32 + 32 <= MI * 16 ? 16 : 8>(                       \
-                band##b, a, m0 + wm * MI * 16 + (hf) * 64 + (b) * 32, nb, wn, 0, lane, pre);
-#define D8_HALF(hf)                                                                                             \
-    if constexpr ((hf) * 4 < MI) {                                                                              \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                           \
-            if ((hf) * 4 + i < MI)                                                                              \
-                _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                   \
-                    _Pragma("unroll") for (int t = 0; t < 4; ++t)                                               \
-                        patch[(i * 16 + 4 * (lane >> 4) + t) * 68 + j * 16 + (lane & 15)] = acc[(hf) * 4 + i < MI ? (hf) * 4 + i : 0][j][t]; \
-        __builtin_amdgcn_wave_barrier();      /* LDS accesses of a wave complete in order */                    \
-        D8_READ(hf, 0)                                                                                          \
-        D8_READ(hf, 1)                                                                                          \
-        __builtin_amdgcn_wave_barrier();                                                                        \
-        D8_BAND(hf, 0)                                                                                          \
-        D8_BAND(hf, 1)                                                                                          \
-    }
-    D8_HALF(0)
-    D8_HALF(1)
-#undef D8_READ
-#undef D8_BAND
-#undef D8_HALF
+    float* const patch = reinterpret_cast<float*>(smem) + wave * (64 * PATCH_LD);
+    const int m_w = m0 + wm * MI * 16;
+    d8_half<EPI, MI, 0>(acc, patch, a, m_w, nb, wn, lane, meta);
+    if constexpr (MI > 4) d8_half<EPI, MI, 1>(acc, patch, a, m_w + 64, nb, wn, lane, meta);
 }
 
-// Exact-KL epilogue for one 32-row band: zp / zr are the policy's and the reference's logits of the same
-// (row, column) entries.  Per row and per wave (64 columns) five numbers leave the kernel:
+// Exact-KL epilogue of a wave's 64 rows x 64 columns: per row five numbers leave the kernel,
 //   m_p = max z_p, S_p = sum exp(z_p - m_p), T = sum exp(z_p - m_p) (z_p - z_r), m_r = max z_r, S_r = sum exp(z_r - m_r)
-// from which  KL(pi_p || pi_r) = T/S_p - (m_p + log S_p) + (m_r + log S_r)  once all column groups are combined.  The 16
-// rows' reductions run level by level (independent chains).
-__device__ __forceinline__ void kl_epilogue(floatx16 (&zp)[2], floatx16 (&zr)[2], const GemmArgs& a, int m_base, int group,
-                                            int lane) {
-    const int lg = lane >> 5, lrow = lane & 31;
-    float mp[16], mr[16], sp[16], st[16], sr[16];
+// from which  KL(pi_p || pi_r) = T/S_p - (m_p + log S_p) + (m_r + log S_r)  once all column groups are combined.  Four
+// lanes share a row, 16 columns each; the reference's logits wait in registers while the policy's take the patch.
+__device__ __forceinline__ void kl_epilogue(const floatx4_t (&acc_p)[4][4], const floatx4_t (&acc_r)[4][4], float* patch,
+                                            const GemmArgs& a, int m0, int group, int lane) {
+    const int row = lane >> 2, c = (lane & 3) * 16;
+    float zr[4][16];
+    patch_put<4, 0>(acc_r, patch, lane);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { mp[r] = fmaxf(zp[0][r], zp[1][r]); mr[r] = fmaxf(zr[0][r], zr[1][r]); }
-    rows_max(mp);
-    rows_max(mr);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float e0 = __expf(zp[0][r] - mp[r]), e1 = __expf(zp[1][r] - mp[r]);
-        sp[r] = e0 + e1;
-        st[r] = e0 * (zp[0][r] - zr[0][r]) + e1 * (zp[1][r] - zr[1][r]);
-        sr[r] = __expf(zr[0][r] - mr[r]) + __expf(zr[1][r] - mr[r]);
-    }
-    rows_sum(sp);
-    rows_sum(st);
-    rows_sum(sr);
+    for (int it = 0; it < 4; ++it) patch_get(zr[it], patch, it * 16 + row, c);
+    __builtin_amdgcn_wave_barrier();
+    patch_put<4, 0>(acc_p, patch, lane);
     const int nparts = a.N / 64;
-    if (lrow != 0) return;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = m_base + 8 * (r >> 2) + 4 * lg + (r & 3);
-        if (m >= a.M) continue;
-        float* o = a.kl_part + ((int64_t)m * nparts + group) * 5;
-        o[0] = mp[r]; o[1] = sp[r]; o[2] = st[r]; o[3] = mr[r]; o[4] = sr[r];
+    for (int it = 0; it < 4; ++it) {
+        float zp[16];
+        patch_get(zp, patch, it * 16 + row, c);
+        const float mp = quad_max(max_of(zp)), mr = quad_max(max_of(zr[it]));
+        float sp = 0.f, st = 0.f, sr = 0.f;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+            const float e = __expf(zp[x] - mp);
+            sp += e;
+            st += e * (zp[x] - zr[it][x]);
+            sr += __expf(zr[it][x] - mr);
+        }
+        sp = quad_sum(sp); st = quad_sum(st); sr = quad_sum(sr);
+        const int m = m0 + it * 16 + row;
+        if ((lane & 3) == 0 && m < a.M) {
+            float* o = a.kl_part + ((int64_t)m * nparts + group) * 5;
+            o[0] = mp; o[1] = sp; o[2] = st; o[3] = mr; o[4] = sr;
+        }
     }
 }
 
@@ -830,7 +1009,7 @@ __device__ __forceinline__ void kl_epilogue(floatx16 (&zp)[2], floatx16 (&zr)[2]
 // this replaced, 8.4 ms.  N a multiple of 64: column groups past it are left out.
 template <bool WF16>
 __global__ __launch_bounds__(512, 1) void gemm_kl8_kernel(GemmArgs a) {
-    constexpr int MI = 4, BM = 32 * MI, WGN = 4, TN = 2;
+    constexpr int MI = 4, BM = 32 * MI, WGN = 4;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -844,31 +1023,10 @@ __global__ __launch_bounds__(512, 1) void gemm_kl8_kernel(GemmArgs a) {
     __syncthreads();                                   // the stages are filled again
     dma8_loop<MG_KLFULL, WF16, MI>(a, a.A, a.lda, a.W, m0, nb, wave, lane, smem, acc_p, meta);
     __syncthreads();
-    // 16 x 16 -> 32 x 32 layout through the wave's own LDS patch, as in the kernel above: 64 rows x 64 columns, one set
-    // after the other
-    float* patch = reinterpret_cast<float*>(smem) + wave * (64 * 68);
-    const int lg = lane >> 5, lrow = lane & 31;
-    floatx16 zr[2][TN], zp[2][TN];
-#define KL_RELAYOUT(acc, z)                                                                                     \
-    {                                                                                                           \
-        _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                          \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                       \
-                _Pragma("unroll") for (int t = 0; t < 4; ++t)                                                   \
-                    patch[(i * 16 + 4 * (lane >> 4) + t) * 68 + j * 16 + (lane & 15)] = acc[i][j][t];           \
-        __builtin_amdgcn_wave_barrier();      /* LDS accesses of a wave complete in order */                    \
-        _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                           \
-            _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                      \
-                _Pragma("unroll") for (int r = 0; r < 16; ++r)                                                  \
-                    z[b][j][r] = patch[(b * 32 + 8 * (r >> 2) + 4 * lg + (r & 3)) * 68 + j * 32 + lrow];        \
-        __builtin_amdgcn_wave_barrier();                                                                        \
-    }
-    KL_RELAYOUT(acc_r, zr)
-    KL_RELAYOUT(acc_p, zp)
-#undef KL_RELAYOUT
     const int group = nb * WGN + wn;
     if (group * 64 >= a.N) return;
-    kl_epilogue(zp[0], zr[0], a, m0 + wm * 64, group, lane);
-    kl_epilogue(zp[1], zr[1], a, m0 + wm * 64 + 32, group, lane);
+    float* const patch = reinterpret_cast<float*>(smem) + wave * (64 * PATCH_LD);
+    kl_epilogue(acc_p, acc_r, patch, a, m0 + wm * 64, group, lane);
 }
 
 template <int BM, int BN, int WGM, int WGN, int EPI, int BKT = 64, bool WF16 = false>
@@ -888,7 +1046,7 @@ static void launch(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s)
 
 template <bool WF16>
 static void launch_kl8(const GemmArgs& a, hipStream_t s) {
-    constexpr int BM = 128, stages = 5 * (BM + 256) * 64, patches = 8 * 64 * 68 * 4, lds = stages > patches ? stages : patches;
+    constexpr int BM = 128, stages = 5 * (BM + 256) * 64, patches = 8 * 64 * PATCH_LD * 4, lds = stages > patches ? stages : patches;
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void*)gemm_kl8_kernel<WF16>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -901,7 +1059,7 @@ static void launch_kl8(const GemmArgs& a, hipStream_t s) {
 }
 template <int EPI, bool WF16, int MI>
 static void launch_dma8_t(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
-    constexpr int BM = 32 * MI, stages = 5 * (BM + 256) * 64, patches = 8 * 64 * 68 * 4;
+    constexpr int BM = 32 * MI, stages = 5 * (BM + 256) * 64, patches = 8 * 64 * PATCH_LD * 4;
     constexpr int lds = stages > patches ? stages : patches;
     static bool attr_set = false;
     if (!attr_set) {

@@ -34,8 +34,19 @@ __device__ __forceinline__ float dpp_move(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 
+// The value as rounded to fp32, whatever is done with it next: a conversion to fp16 behind it may otherwise be fused with
+// the operation that produced it in one kernel and not in another.
+__device__ __forceinline__ float as_fp32(float v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
 // SiLU(g) * u.  The quotient is g times a reciprocal (1 ulp) instead of a division (ten instructions): the result is
 // rounded to fp16 right after.  Very negative g: exp overflows to +inf, its reciprocal is 0, the product -0.
 __device__ __forceinline__ float swiglu_act(float g, float u) {
-    return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+    return as_fp32(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
 }
+
+// Rotation of a (j, j + hd/2) pair by (cos, sin), the fused operations written out: every tile kernel rounds alike.
+__device__ __forceinline__ float rope_lo(float x0, float x1, float c, float s) { return as_fp32(fmaf(x0, c, -(x1 * s))); }
+__device__ __forceinline__ float rope_hi(float x0, float x1, float c, float s) { return as_fp32(fmaf(x1, c, x0 * s)); }
