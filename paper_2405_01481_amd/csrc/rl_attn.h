@@ -37,13 +37,15 @@ void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStr
 struct PrefillAttnArgs {
     const f16_t* q = nullptr;    // [rows, Hq, hd]
     const f16_t* k = nullptr;    // [rows, Hkv, hd]
-    const f16_t* vT = nullptr;   // [Hkv, hd, vt_cap]  (dim-major)
+    const f16_t* vT = nullptr;   // [Hkv][vt_cap / 32][hd][32 tokens]: dim-major tiles of 32 tokens
     f16_t* out = nullptr;        // [rows, Hq * hd]
-    const int4* blocks = nullptr;  // per workgroup: (first row of the sequence, its length, query block, 0)
+    const int4* blocks = nullptr;  // per workgroup: (first row of the sequence, its length, group of 32-query blocks, 0)
     int Hq = 0, Hkv = 0, hd = 0, vt_cap = 0;
     float scale = 0.f;
     // split = 1: fp16 pairs.  q, k and out rows are twice as wide, [hi heads | lo heads]; the lo plane of vT
-    // follows the hi plane ([2][Hkv, hd, vt_cap])
+    // follows the hi plane
     int split = 0;
 };
+// 32-query blocks that one entry of `blocks` stands for
+int k_attn_prefill_blocks(int Hq, int Hkv);
 void k_attn_prefill(const PrefillAttnArgs& a, int nblocks, hipStream_t s);

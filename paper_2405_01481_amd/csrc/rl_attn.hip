@@ -23,6 +23,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // 2^x as the hardware instruction alone.  The library's exp2f wraps it in a rescaling for results in the denormal
 // range (six instructions per value); softmax weights that small are zero for every purpose here.  2^-inf = 0.
+// s_waitcnt operand: at most vm vector loads outstanding
+constexpr int vm_only(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (15 << 8); }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // ------------------------------------------------------------------ decode: one new query per sequence
@@ -376,74 +378,101 @@ void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStr
 }
 
 // ------------------------------------------------------------------ prefill / scoring: causal attention over packed sequences
-// Workgroup = (32-query block of one sequence, kv head g); wave w handles query head g*G + w, so the
-// waves of a workgroup need the SAME keys and values.  Per 32-key block the K tile (32 keys x hd) and the
-// V^T tile (hd dims x 32 keys, from the dim-major value buffer) are staged ONCE per workgroup into LDS by
-// global -> LDS loads -- row-contiguous 16-byte pieces, whole rows per request; fetching the operands in
-// MFMA layout straight from memory instead makes every lane of a load touch a different row, and the
-// address path of the CU, not the MFMAs or the caches, then sets the pace -- and every wave reads its
-// operand fragments from there.  Two stages: the tile of block kb+1 is requested right after the barrier
-// that opens block kb.  16-byte chunks are XOR-swizzled on the source side of the loads (K: chunk ^ row%16
-// for 256-byte rows, chunk ^ (row/2)%8 for 128-byte rows; V^T: chunk ^ (row/4)%4) so that the fragment
-// reads spread over the banks.  The loads are issued from inline assembly and waited for by hand (the
-// compiler would otherwise make each of them complete at the next barrier).
+// Workgroup = (NQ consecutive 32-query blocks of one sequence, HW query heads of kv head g), four waves: wave w < HW x NQ
+// handles head h0 + w % HW of query block w / HW (a wave left over only helps staging), so the waves of a workgroup need the
+// SAME keys and values.  Keys are walked in steps of TS tiles of 32.  Per tile K (32 keys x hd) and V^T (hd dims x 32
+// keys, one contiguous piece of the value buffer) are staged ONCE per workgroup into LDS by global -> LDS loads of whole
+// lines (step ks + NS - 1 is requested right after the barrier that opens step ks), and every wave reads its operand
+// fragments from there.
+// What bounds it is a wave's own chain of scores -> maximum -> exponentials -> products, and for short sequences what a
+// workgroup costs before and after its loop.  Hence steps of 64 keys (two independent chains of score MFMAs; one maximum,
+// one cross-lane exchange, one rescaling per 64 keys), V^T fragments read before the softmax, two independent workgroups
+// per CU, one's start and end behind the other's loop, and an output that leaves as whole lines.  A kv head's
+// workgroups stay on one XCD (ids go round-robin to the eight, each with its own L2).
+// 16 x 1024 tokens of the 8B shape 257 -> 205 us (0.67 PFLOP/s; MFMAs busy a third of the time), 5 sequences of 1500 to 4096
+// tokens of the 70B shape 1065 -> 690 us (1.0 PFLOP/s), 8 of 70 to 512 of the 1B shape 21.9 -> 13.7, against steps of 32 keys
+// with a wait for the next tile in each and 16-byte output stores.  Eight waves per workgroup: 239, 747, 24.2; steps of 32
+// keys, three workgroups per CU: 218, 725, 16.8.
+// 16-byte chunks are XOR-swizzled on the source side of the loads (K: chunk ^ row%16 for 256-byte rows, chunk ^ (row/2)%8
+// for 128-byte rows; V^T: chunk ^ (row/4)%4) so that the fragment reads spread over the banks.  The loads are issued from
+// inline assembly and waited for by count (the compiler would otherwise make each of them complete at the next barrier).
 //   S^T (32 keys x 32 queries) by 32x32x16 MFMAs with K rows as A and Q^T as B; base-2 online softmax per
 //   query (a lane owns one query column); O^T += V^T P^T where the lane's own S^T registers, rounded to
 //   fp16, are the B operand.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+static constexpr int ap_tiles(bool SP) { return SP ? 1 : 2; }                      // 32-key tiles of a step
+static constexpr int AP_NW = 4;                                                    // waves of a workgroup
+static constexpr int ap_stages(int HD, bool SP) { return 2; }
+// query heads of a group of G that a workgroup takes (the group is cut in two where it has more than four)
+__host__ __device__ constexpr int ap_heads(int G) { return G <= AP_NW ? G : (G + 1) / 2; }
+static constexpr int ap_stage_bytes(int HD, bool SP) { return ap_tiles(SP) * (SP ? 4 : 2) * 32 * HD * 2; }
+
 // SP: q, k, v are fp16 pairs (value = hi + lo; rows of q, k and the output are [hi heads | lo heads], the lo plane
-// of V^T follows the hi plane).  A stage then holds four tiles (K hi, V^T hi, K lo, V^T lo), the scores take the
+// of V^T follows the hi plane).  A tile then has four parts (K hi, V^T hi, K lo, V^T lo), the scores take the
 // three leading terms k_hi q_hi + k_lo q_hi + k_hi q_lo, and the probabilities are split the same way for the
 // second contraction: three MFMAs where the plain kernel has one.
 template <int HD, bool SP>
-__global__ __launch_bounds__(512) void attn_prefill_kernel(PrefillAttnArgs a) {
-    constexpr int KSTEPS = HD / 16, DB = HD / 32;
+__global__ __launch_bounds__(AP_NW * 64, HD == 64 ? 3 : 2) void attn_prefill_kernel(PrefillAttnArgs a) {
+    constexpr int KSTEPS = HD / 16, DB = HD / 32, TS = ap_tiles(SP), NS = ap_stages(HD, SP);
     constexpr int KT = 32 * HD * 2;              // bytes of a K tile; a V^T tile is as large
-    constexpr int NT = SP ? 4 : 2;               // tiles of a stage: K, V^T (hi), then K, V^T (lo)
-    constexpr int STG = NT * KT;
-    constexpr int NIT = KT / 1024;               // 1 KB load instructions per tile
-    constexpr int NI = NT * NIT;
+    constexpr int NT = SP ? 4 : 2;               // parts of a tile: K, V^T (hi), then K, V^T (lo)
+    constexpr int STG = ap_stage_bytes(HD, SP);
+    constexpr int NIT = KT / 1024;               // 1 KB load instructions per part
+    constexpr int PER = TS * NT * NIT / AP_NW;       // of a step, per wave
     constexpr int KCH = HD / 8;                  // 16-byte chunks per K row
     constexpr int KRPI = 64 / KCH;               // K rows per load instruction
-    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [2 stages][STG]
+    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [NS stages][STG]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 31, g2 = lane >> 5;
-    const int4 blk = a.blocks[blockIdx.x];          // (row start, length, query block, -)
-    const int start = blk.x, len = blk.y, qb = blk.z;
-    const int g = blockIdx.y, G = a.Hq / a.Hkv, h = g * G + wave;
+    const int G = a.Hq / a.Hkv, HW = ap_heads(G), NQ = AP_NW / HW, parts = (G + HW - 1) / HW;
+    const int pg = blockIdx.x % (a.Hkv * parts), g = pg % a.Hkv, h0 = pg / a.Hkv * HW;   // kv head; first head of its group
+    const int4 blk = a.blocks[blockIdx.x / (a.Hkv * parts)];  // (row start, length, group of NQ query blocks, -)
+    const int start = blk.x, len = blk.y;
+    const int h = g * G + min(h0 + wave % HW, G - 1);
+    const int nqb = (len + 31) / 32;
+    const int qb = wave < HW * NQ && h0 + wave % HW < G ? blk.z * NQ + wave / HW : nqb;    // this wave's query block; nqb and later: none
+    const int last = min((blk.z + 1) * NQ, nqb) - 1;               // the workgroup's last key block
     const int qi = qb * 32 + col;                   // this lane's query (position in the sequence)
     const int qrow = start + min(qi, len - 1);
     const int kvw = (SP ? 2 : 1) * a.Hkv * HD;      // elements per K row
     const int qw = (SP ? 2 : 1) * a.Hq * HD;        // elements per query / output row
 
-    // staging: instruction i of the stage (i = wave, wave + G, ...) moves 1 KB
-    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-    const f16_t* kg = a.k + (int64_t)start * kvw + g * HD;               // K rows of this sequence, head g
-    const f16_t* vg = a.vT + (int64_t)g * HD * a.vt_cap + start;          // V^T rows (dims) of head g
-#define AP_STAGE(stage, kb)                                                                                      \
-    for (int i_ = wave; i_ < NI; i_ += G) {                                                                      \
-        const unsigned sa_ = lds_base + (stage) * STG + i_ * 1024;                                               \
-        const int t_ = i_ / NIT, ii_ = i_ % NIT;                                                                 \
-        unsigned off_;                                                                                           \
-        const f16_t* base_;                                                                                      \
-        if ((t_ & 1) == 0) {                     /* K: KRPI rows of KCH chunks */                                \
-            const int r_ = ii_ * KRPI + lane / KCH, pc_ = lane % KCH;                                            \
-            const int lc_ = pc_ ^ (HD == 128 ? (r_ & 15) : ((r_ >> 1) & 7));                                     \
-            /* tile row r_ holds key rho(r_): the middle two 4-row groups of every 16 are swapped, so that a */  \
-            /* lane's S^T registers 8kk .. 8kk+7 are eight CONSECUTIVE keys (one 16-byte V^T chunk)         */  \
-            const int key_ = (r_ & ~12) | ((r_ & 4) << 1) | ((r_ & 8) >> 1);                                     \
-            off_ = (unsigned)(((kb) * 32 + key_) * kvw + lc_ * 8) * 2u;                                          \
-            base_ = kg + (t_ >> 1) * a.Hkv * HD;                                                                 \
-        } else {                                 /* V^T: 16 dims of 4 chunks (32 keys) */                        \
-            const int r_ = ii_ * 16 + (lane >> 2), pc_ = lane & 3;                                               \
-            const int lc_ = pc_ ^ ((r_ >> 2) & 3);                                                               \
-            off_ = (unsigned)(r_ * a.vt_cap + (kb) * 32 + lc_ * 8) * 2u;                                         \
-            base_ = vg + (int64_t)(t_ >> 1) * a.Hkv * HD * a.vt_cap;                                             \
-        }                                                                                                        \
+    // Staging: load n of a wave moves 1 KB of part (wave + 4 n) / NIT of the step.
+    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+    const int64_t v_plane = (int64_t)a.vt_cap * HD;                       // V of one head: tiles of [HD dims][32 tokens]
+    unsigned s_off[PER];
+    const char* s_base[PER];
+    int s_blk[PER];                                                       // bytes from one key block to the next
+#pragma unroll
+    for (int n = 0; n < PER; ++n) {
+        const int t = (wave + AP_NW * n) / NIT % NT, ii = (wave + AP_NW * n) % NIT;
+        if ((t & 1) == 0) {                      // K: KRPI rows of KCH chunks
+            const int r = ii * KRPI + lane / KCH, pc = lane % KCH;
+            const int lc = pc ^ (HD == 128 ? (r & 15) : ((r >> 1) & 7));
+            // tile row r holds key rho(r): the middle two 4-row groups of every 16 are swapped, so that a lane's S^T
+            // registers 8kk .. 8kk+7 are eight CONSECUTIVE keys (one 16-byte V^T chunk)
+            const int key = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);
+            s_off[n] = (unsigned)(key * kvw + lc * 8) * 2u;
+            s_base[n] = reinterpret_cast<const char*>(a.k + (int64_t)start * kvw + (g + (t >> 1) * a.Hkv) * HD);
+            s_blk[n] = 32 * kvw * 2;
+        } else {                                 // V^T: 16 dims of 4 chunks (32 keys)
+            const int r = ii * 16 + (lane >> 2), pc = lane & 3;
+            const int lc = pc ^ ((r >> 2) & 3);
+            s_off[n] = (unsigned)(r * 32 + lc * 8) * 2u;
+            s_base[n] = reinterpret_cast<const char*>(a.vT + (g + (t >> 1) * a.Hkv) * v_plane + (int64_t)start * HD);
+            s_blk[n] = 32 * HD * 2;
+        }
+    }
+    // (blocks past the last one: that one again, its keys masked)
+#define AP_STAGE(stage, ks)                                                                                      \
+    _Pragma("unroll") for (int n_ = 0; n_ < PER; ++n_) {                                                         \
+        const int kb_ = min((ks) * TS + (wave + AP_NW * n_) / (NIT * NT), last);                                     \
+        const unsigned sa_ = lds_base + (stage) * STG + n_ * (AP_NW * 1024);                                               \
+        const char* g_ = s_base[n_] + (int64_t)kb_ * s_blk[n_];                                                  \
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                             \
-                     :: "s"(sa_), "v"(off_), "s"(base_) : "memory");                                             \
+                     :: "s"(sa_), "v"(s_off[n_]), "s"(g_) : "memory");                                           \
     }
 
     half8 qf[KSTEPS], ql[SP ? KSTEPS : 1];
@@ -460,125 +489,170 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(PrefillAttnArgs a) {
         for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
     const float scale = a.scale * LOG2E;
-    // this lane's fragment addresses inside a stage
+    // this lane's fragment addresses inside a tile
     const int ksw = HD == 128 ? (col & 15) : ((col >> 1) & 7);
     const int k_row = col * (HD * 2);                       // K row `col`
-    const int vsw = (col >> 2) & 3;                         // same for rows d*32 + col
+    const int v_row = col * 64, vsw = (col >> 2) & 3;       // V^T rows d*32 + col
 
-    AP_STAGE(0, 0)
-    for (int kb = 0; kb <= qb; ++kb) {
-        const int st = kb & 1;
-        // the tile of block kb has landed (this wave's part: its only loads in flight); after the barrier
-        // every wave's part has, and every wave is done with the other stage
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        AP_STAGE(1 - st, min(kb + 1, qb))                   // the last trip re-requests its own block, unused
-        const char* kt = smem + st * STG;
-        const char* vt = kt + KT;
-        // S^T = K Q^T
-        floatx16 stt;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) stt[r] = 0.f;
+    for (int t = 0; t < NS - 1; ++t) AP_STAGE(t, t)
+    int st = 0, fill = NS - 1;
+    for (int ks = 0; ks * TS <= last; ++ks) {
+        // the tiles of step ks have landed (this wave's part: the NS - 2 younger steps may be on their way); after the
+        // barrier every wave's part has, and every wave is done with the stage of step ks - 1
+        __builtin_amdgcn_s_waitcnt(vm_only((NS - 2) * PER));
+        __syncthreads();
+        AP_STAGE(fill, ks + NS - 1)                         // the last trips' are not used: the counts hold
+        const char* const kt = smem + st * STG;
+        st = st + 1 == NS ? 0 : st + 1;
+        fill = fill + 1 == NS ? 0 : fill + 1;
+        if (ks * TS > qb || qb >= nqb) continue;            // wave-uniform: behind its query block, or none
+        // S^T = K Q^T
+        floatx16 stt[TS];
+#pragma unroll
+        for (int t = 0; t < TS; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) stt[t][r] = 0.f;
         if (SP) {   // the two small terms first, the leading one last
 #pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) {
-                const int fo = k_row + (((s * 2 + g2) ^ ksw) * 16);
-                const half8 kl = *reinterpret_cast<const half8*>(kt + 2 * KT + fo);
-                const half8 kf = *reinterpret_cast<const half8*>(kt + fo);
-                stt = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qf[s], stt, 0, 0, 0);
-                stt = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[s], stt, 0, 0, 0);
-            }
+            for (int s = 0; s < KSTEPS; ++s)
+#pragma unroll
+                for (int t = 0; t < TS; ++t) {
+                    const char* kr = kt + t * NT * KT + k_row + (((s * 2 + g2) ^ ksw) * 16);
+                    const half8 kl = *reinterpret_cast<const half8*>(kr + 2 * KT);
+                    const half8 kf = *reinterpret_cast<const half8*>(kr);
+                    stt[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qf[s], stt[t], 0, 0, 0);
+                    stt[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[SP ? s : 0], stt[t], 0, 0, 0);
+                }
         }
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) {
-            const half8 kf = *reinterpret_cast<const half8*>(kt + k_row + (((s * 2 + g2) ^ ksw) * 16));
-            stt = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[s], stt, 0, 0, 0);
+        for (int s = 0; s < KSTEPS; ++s)
+#pragma unroll
+            for (int t = 0; t < TS; ++t) {
+                const half8 kf = *reinterpret_cast<const half8*>(kt + t * NT * KT + k_row + (((s * 2 + g2) ^ ksw) * 16));
+                stt[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[s], stt[t], 0, 0, 0);
+            }
+        // V^T fragments: the lane needs keys kk*16 + 8*g2 .. +8 of dim d*32 + col, one 16-byte chunk.  (Pairs: read when used)
+        half8 vf[SP ? 1 : TS][SP ? 1 : DB][2];
+        if constexpr (!SP) {
+#pragma unroll
+            for (int t = 0; t < TS; ++t)
+#pragma unroll
+                for (int d = 0; d < DB; ++d)
+#pragma unroll
+                    for (int kk = 0; kk < 2; ++kk)
+                        vf[t][d][kk] = *reinterpret_cast<const half8*>(kt + (t * NT + 1) * KT + d * 2048 + v_row + ((kk * 2 + g2) ^ vsw) * 16);
         }
         // register r of this lane is tile row 8*(r/4) + 4*g2 + r%4, which holds key kb*32 + 16*(r/8) + 8*g2 + r%8.
-        // Only the diagonal block needs the causal mask; the running maximum is kept in raw (unscaled) units,
+        // Only the diagonal step needs the causal mask; the running maximum is kept in raw (unscaled) units,
         // so that exp2(scale * (s - m)) is one fused multiply-add and one exp2 per element.
-        if (kb == qb) {
+        if ((ks + 1) * TS > qb) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = kb * 32 + 16 * (r >> 3) + 8 * g2 + (r & 7);
-                if (key > qi) stt[r] = -INFINITY;
-            }
+            for (int t = 0; t < TS; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int key = (ks * TS + t) * 32 + 16 * (r >> 3) + 8 * g2 + (r & 7);
+                    if (key > qi) stt[t][r] = -INFINITY;
+                }
         }
-        float mx = stt[0];
+        float mx = stt[0][0];
 #pragma unroll
-        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, stt[r]);
+        for (int t = 0; t < TS; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, stt[t][r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, RL_WAVE));
-        const float m_new = fmaxf(m_run, mx);        // finite: key kb*32 <= qi for every kb <= qb
+        const float m_new = fmaxf(m_run, mx);        // finite: key ks*TS*32 <= qi in every step taken
         const float alpha = fast_exp2((m_run - m_new) * scale);
         const float nms = -m_new * scale;
-        half8 pf[2], pl[SP ? 2 : 1];
-        float ps = 0.f;
+        half8 pf[TS][2], pl[SP ? TS : 1][2];
+        float ps[2] = {0.f, 0.f};
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float e = fast_exp2(fmaf(stt[r], scale, nms));
-            ps += e;
-            const f16_t eh = (f16_t)e;
-            pf[r >> 3][r & 7] = eh;
-            if (SP) pl[r >> 3][r & 7] = (f16_t)(e - (float)eh);
-        }
-        l_run = l_run * alpha + ps;
+        for (int t = 0; t < TS; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float e = fast_exp2(fmaf(stt[t][r], scale, nms));
+                ps[r & 1] += e;
+                const f16_t eh = (f16_t)e;
+                pf[t][r >> 3][r & 7] = eh;
+                if (SP) pl[SP ? t : 0][r >> 3][r & 7] = (f16_t)(e - (float)eh);
+            }
+        l_run = l_run * alpha + (ps[0] + ps[1]);
         m_run = m_new;
         // the accumulators are rescaled only when some query's maximum moved (rare after the first blocks)
-        const bool rescale = __any(alpha != 1.0f);
-        // O^T += V^T P^T: the lane needs keys kk*16 + 8*g2 .. +8 of dim d*32 + col: one 16-byte chunk
+        if (__any(alpha != 1.0f)) {
 #pragma unroll
-        for (int d = 0; d < DB; ++d) {
-            if (rescale) {
+            for (int d = 0; d < DB; ++d)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
-            }
-            const char* vr = vt + (d * 32 + col) * 64;
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                const int fo = ((kk * 2 + g2) ^ vsw) * 16;
-                const half8 vf = *reinterpret_cast<const half8*>(vr + fo);
-                if (SP) {
-                    const half8 vl = *reinterpret_cast<const half8*>(vr + 2 * KT + fo);
-                    o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl, pf[kk], o[d], 0, 0, 0);
-                    o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pl[SP ? kk : 0], o[d], 0, 0, 0);
-                }
-                o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[kk], o[d], 0, 0, 0);
-            }
         }
+        // O^T += V^T P^T
+#pragma unroll
+        for (int t = 0; t < TS; ++t)
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int d = 0; d < DB; ++d) {
+                    if constexpr (SP) {
+                        const char* vr = kt + (t * NT + 1) * KT + d * 2048 + v_row + ((kk * 2 + g2) ^ vsw) * 16;
+                        const half8 vh = *reinterpret_cast<const half8*>(vr), vl = *reinterpret_cast<const half8*>(vr + 2 * KT);
+                        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl, pf[t][kk], o[d], 0, 0, 0);
+                        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, pl[t][kk], o[d], 0, 0, 0);
+                        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, pf[t][kk], o[d], 0, 0, 0);
+                    } else {
+                        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[t][d][kk], pf[t][kk], o[d], 0, 0, 0);
+                    }
+                }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in LDS after the workgroup has ended
 #undef AP_STAGE
+    __syncthreads();                                   // every wave is done with the stages
+    // The output leaves as whole rows of a head: through this wave's own LDS patch ([32 queries][hd], rows padded by 16
+    // bytes), 16 bytes per lane.  (Straight from the registers it is 16 bytes of a row per store: eight times the requests.)
     l_run += __shfl_xor(l_run, 32, RL_WAVE);
-    if (qi < len) {
-        const float inv = 1.0f / l_run;
-        f16_t* op = a.out + (int64_t)(start + qi) * qw + h * HD;
+    const float inv = qb < nqb ? 1.0f / l_run : 0.f;
+    constexpr int LD = HD + 8, RPI = 512 / HD;         // rows per store instruction
+    static_assert(AP_NW * 32 * LD * 2 <= NS * STG, "the patches reuse the stages");
+    f16_t* const patch = reinterpret_cast<f16_t*>(smem) + wave * 32 * LD;
+#pragma unroll
+    for (int pl = 0; pl < (SP ? 2 : 1); ++pl) {        // plane 1: what the rounding left over
 #pragma unroll
         for (int d = 0; d < DB; ++d)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                half4 w4, l4;
+                half4 w4;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float r = o[d][4 * j + i] * inv;
-                    w4[i] = (f16_t)r;
-                    if (SP) l4[i] = (f16_t)(r - (float)w4[i]);
+                    const f16_t hi = (f16_t)r;
+                    w4[i] = pl == 0 ? hi : (f16_t)(r - (float)hi);
                 }
-                *reinterpret_cast<half4*>(op + d * 32 + 8 * j + 4 * g2) = w4;
-                if (SP) *reinterpret_cast<half4*>(op + a.Hq * HD + d * 32 + 8 * j + 4 * g2) = l4;
+                *reinterpret_cast<half4*>(patch + col * LD + d * 32 + 8 * j + 4 * g2) = w4;
             }
+        __builtin_amdgcn_wave_barrier();               // LDS accesses of a wave complete in order
+#pragma unroll
+        for (int it = 0; it < 32 / RPI; ++it) {
+            const int r = it * RPI + lane / (64 / RPI), c = lane % (64 / RPI) * 8;
+            const half8 v = *reinterpret_cast<const half8*>(patch + r * LD + c);
+            if (qb * 32 + r < len)
+                *reinterpret_cast<half8*>(a.out + (int64_t)(start + qb * 32 + r) * qw + (pl * a.Hq + h) * HD + c) = v;
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
+// 32-query blocks per workgroup: as many as give its eight waves work, one per query head of the group and query block.
+int k_attn_prefill_blocks(int Hq, int Hkv) { return AP_NW / ap_heads(Hq / Hkv); }
+
 template <int HD, bool SP>
 static void launch_prefill(const PrefillAttnArgs& a, int nblocks, hipStream_t s) {
-    constexpr int lds = 2 * (SP ? 4 : 2) * 32 * HD * 2;
+    constexpr int lds = ap_stages(HD, SP) * ap_stage_bytes(HD, SP);
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void*)attn_prefill_kernel<HD, SP>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         attr_set = true;
     }
-    dim3 grid(nblocks, a.Hkv);
-    attn_prefill_kernel<HD, SP><<<grid, 64 * (a.Hq / a.Hkv), lds, s>>>(a);
+    const int G = a.Hq / a.Hkv, HW = ap_heads(G);
+    attn_prefill_kernel<HD, SP><<<a.Hkv * ((G + HW - 1) / HW) * nblocks, AP_NW * 64, lds, s>>>(a);
 }
 
 void k_attn_prefill(const PrefillAttnArgs& a, int nblocks, hipStream_t s) {

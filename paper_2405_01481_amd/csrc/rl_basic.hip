@@ -93,12 +93,12 @@ void k_list_rows(const int* at, const int* first, const int* count, int n, int* 
 // same row, or -1 when there is none.
 // With align > 1 every row is padded to a multiple of align tokens; padding entries carry
 // token id 0, position -1 and no target.
-// blocks (optional): the prefill attention's work list, one entry (first row, length, query block) per 32-query block,
+// blocks (optional): the prefill attention's work list, one entry (first row, length, query block) per block of qrows queries,
 // late (long) blocks first so that the tail of the grid is short work, rows in order within a block index: an entry's
 // place is the number of entries with a later block, plus the earlier rows that have this one.
 __global__ void pack_tokens_kernel(const int* ids, int ld_ids, const int* seq_first, const int* row_slot,
                                    const int* row_start, const int* row_len, int align, int* tok_ids, int* tok_pos,
-                                   int* tok_slot, int* tok_tgt, int4* blocks) {
+                                   int* tok_slot, int* tok_tgt, int4* blocks, int qrows) {
     int r = blockIdx.x;
     int b = seq_first[r], st = row_start[r], len = row_len[r];
     const int slot = row_slot[r];
@@ -112,10 +112,10 @@ __global__ void pack_tokens_kernel(const int* ids, int ld_ids, const int* seq_fi
         if (tok_tgt) tok_tgt[st + t] = (real && t + 1 < len) ? src[t + 1] : -1;
     }
     if (!blocks) return;
-    for (int qb = threadIdx.x; qb < (len + 31) / 32; qb += blockDim.x) {
+    for (int qb = threadIdx.x; qb < (len + qrows - 1) / qrows; qb += blockDim.x) {
         int at = 0;
         for (int i = 0; i < (int)gridDim.x; ++i) {
-            const int nbi = (row_len[i] + 31) / 32;
+            const int nbi = (row_len[i] + qrows - 1) / qrows;
             at += max(0, nbi - (qb + 1)) + (i < r && nbi > qb ? 1 : 0);
         }
         blocks[at] = make_int4(st, len, qb, 0);
@@ -123,10 +123,10 @@ __global__ void pack_tokens_kernel(const int* ids, int ld_ids, const int* seq_fi
 }
 void k_pack_tokens(const int* ids, int ld_ids, const int* seq_first, const int* row_slot, const int* row_start,
                    const int* row_len, int align, int* tok_ids, int* tok_pos, int* tok_slot, int* tok_tgt, int4* blocks,
-                   int nrows, hipStream_t s) {
+                   int qrows, int nrows, hipStream_t s) {
     if (nrows <= 0) return;
     pack_tokens_kernel<<<nrows, 256, 0, s>>>(ids, ld_ids, seq_first, row_slot, row_start, row_len, align, tok_ids, tok_pos,
-                                             tok_slot, tok_tgt, blocks);
+                                             tok_slot, tok_tgt, blocks, qrows);
 }
 
 // After prefill of the first P-1 prompt tokens: remember the last prompt token, lengths, counters.

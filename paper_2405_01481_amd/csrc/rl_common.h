@@ -103,7 +103,7 @@ void k_put_rows(const int* seq_first_h, const int* row_slot_h, const int* row_st
                 int* seq_first, int* row_slot, int* row_start, int* row_len, hipStream_t s);
 void k_pack_tokens(const int* ids, int ld_ids, const int* seq_first, const int* row_slot, const int* row_start,
                    const int* row_len, int align, int* tok_ids, int* tok_pos, int* tok_slot, int* tok_tgt, int4* blocks,
-                   int nrows, hipStream_t s);
+                   int qrows, int nrows, hipStream_t s);
 void k_prefill_state(const int* ids, int ld_ids, const int* row_len, int* last_tok, int* seq_len, int* gen_count,
                      int* finished, int* step_count, int B, hipStream_t s);
 // State of n freshly prefilled slots: slot row_slot[i] starts sequence seq_first[i] (row of ids, also its output

@@ -57,7 +57,7 @@ struct GemmArgs {
     int lda2 = 0;
     const bf16_t* W2 = nullptr;
     float* kl_part = nullptr;
-    int vt_cap = 0;             // > 0: v_out is dim-major [Hkv][hd][vt_cap tokens]; 0: token-major [M][Hkv][hd]
+    int vt_cap = 0;             // tokens v_out has room for, a multiple of 32: [Hkv][vt_cap / 32][hd][32 tokens]
     KvGeom geo{};
     // tiles of up to 256 x 256 (splits == 1 only): 0 never, 1 when 128 x 128 tiles are more than one per CU,
     // 2 whenever the shape allows (N multiple of 256, K of 128)

@@ -114,6 +114,11 @@ __device__ __forceinline__ float row32_sum(float v) {
     return v + __shfl_xor(v, 16, RL_WAVE);
 }
 
+// Element of dimension d of token m in v_out, plane of one (lo / hi, kv head): [vt_cap / 32 tiles][hd][32 tokens].
+__device__ __forceinline__ int64_t v_tile_off(const GemmArgs& a, int plane, int m, int d) {
+    return (((int64_t)plane * (a.vt_cap >> 5) + (m >> 5)) * a.hd + d) * 32 + (m & 31);
+}
+
 // Epilogue shared by the tile kernels, for one 32-row band of a wave's accumulators: acc[j][r] of the
 // wave in tile-column position wn is C(row, col) with
 //   row = m_base + 8*(r/4) + 4*(lane/32) + r%4,   col(tile-local) = wn*TN*32 + j*32 + lane%32
@@ -223,7 +228,7 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
                 continue;
             }
             const int g = head - Hq - Hkv;
-            // V with dim-major destinations (vT[kv head][dim][token], and the V pages of the cache): the four
+            // V with dim-major destinations (tiles of 32 tokens of v_out, and the V pages of the cache): the four
             // registers r = 4k .. 4k+3 of a lane are four consecutive tokens of one dimension, so they leave as one
             // 8-byte store instead of four 2-byte stores a cache line apart from their neighbours'.
 #pragma unroll
@@ -246,8 +251,8 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
                         h1[t] = pl == 0 ? r1 : e1;
                     }
                     if (a.v_out) {
-                        f16_t* o0 = a.v_out + ((int64_t)(pl * Hkv + g) * hd + jj) * a.vt_cap + m4;
-                        f16_t* o1 = o0 + (int64_t)half * a.vt_cap;
+                        f16_t* o0 = a.v_out + v_tile_off(a, pl * Hkv + g, m4, jj);
+                        f16_t* o1 = o0 + half * 32;
                         if (m4 + 3 < a.M) {
                             *reinterpret_cast<half4*>(o0) = h0;
                             *reinterpret_cast<half4*>(o1) = h1;
@@ -869,7 +874,7 @@ __device__ __forceinline__ void d8_half(const floatx4_t (&acc)[MI][4], float* pa
                 }
             }
         } else {
-            // V with dim-major destinations (vT[kv head][dim][token], and the V pages of the cache): a lane takes eight
+            // V with dim-major destinations (tiles of 32 tokens of v_out, and the V pages of the cache): a lane takes eight
             // consecutive tokens of one dimension, 16 dimensions x 32 tokens per step
             const int g = head - Hq - Hkv;
             patch_put<NB, HF * 4>(acc, patch, lane);
@@ -898,7 +903,7 @@ __device__ __forceinline__ void d8_half(const floatx4_t (&acc)[MI][4], float* pa
                     for (int pl = 0; pl < S; ++pl) {           // plane 1: what the rounding left over
                         const half8 h = pl == 0 ? hi : lo;
                         if (a.v_out) {
-                            f16_t* o = a.v_out + ((int64_t)(pl * Hkv + g) * hd + dim) * a.vt_cap + m0 + r0;
+                            f16_t* o = a.v_out + v_tile_off(a, pl * Hkv + g, m0 + r0, dim);
                             if (m0 + r0 + 7 < a.M) *reinterpret_cast<half8*>(o) = h;
                             else {
 #pragma unroll

@@ -607,7 +607,7 @@ struct Chunk {
     std::vector<int> slots;   // cache slot of each row; empty = the row index itself
     int n = 0;          // rows in the list, padding included
     int max_ctx = 1;
-    int nblocks = 0;    // 32-query blocks (tuned path)
+    int nblocks = 0;    // entries of the attention's work list (tuned path)
 };
 static int pack_align(const rl_ctx* c) { return c->impl == 1 ? 32 : 1; }
 
@@ -633,16 +633,17 @@ static int chunk_take(const rl_ctx* c, const std::vector<int>& len_of, int b0, i
 static int pack_chunk(rl_ctx* c, const int* ids, int ld_ids, Chunk& ch, bool targets, hipStream_t s) {
     const Layout& L = c->L;
     const int nrows = (int)ch.rows_b.size();
+    const int qrows = 32 * k_attn_prefill_blocks(c->cfg.n_q_heads, c->cfg.n_kv_heads);
     if (c->impl == 1) {
         ch.nblocks = 0;
-        for (int len : ch.lens) ch.nblocks += (len + 31) / 32;
+        for (int len : ch.lens) ch.nblocks += (len + qrows - 1) / qrows;
         if (ch.nblocks > L.max_blocks) return fail(RL_EINVAL, "internal: attention block list overflow");
     }
     k_put_rows(ch.rows_b.data(), (ch.slots.empty() ? ch.rows_b : ch.slots).data(), ch.starts.data(), ch.lens.data(), nrows,
                c->at<int>(L.seq_first), c->at<int>(L.row_slot), c->at<int>(L.row_start), c->at<int>(L.row_len), s);
     k_pack_tokens(ids, ld_ids, c->at<int>(L.seq_first), c->at<int>(L.row_slot), c->at<int>(L.row_start),
                   c->at<int>(L.row_len), pack_align(c), c->at<int>(L.tok_ids), c->at<int>(L.tok_pos), c->at<int>(L.tok_slot),
-                  targets ? c->at<int>(L.tok_tgt) : nullptr, c->impl == 1 ? c->at<int4>(L.blocks) : nullptr, nrows, s);
+                  targets ? c->at<int>(L.tok_tgt) : nullptr, c->impl == 1 ? c->at<int4>(L.blocks) : nullptr, qrows, nrows, s);
     return RL_OK;
 }
 
