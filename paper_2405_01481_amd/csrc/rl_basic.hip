@@ -191,21 +191,22 @@ __device__ __forceinline__ floatx4 load4(const T* p) {
 
 // ---------------------------------------------------------------- embedding gather
 template <typename T>
-__global__ void embed_kernel(const int* ids, const T* E, int d, int V, float* x, int* errflag) {
+__global__ void embed_kernel(const int* ids, const T* E, int d, int V, float* x, int* errflag, const T* E2, int n1) {
     int n = blockIdx.x;
     int id = ids[n];
     if (id < 0 || id >= V) {
         if (threadIdx.x == 0) atomicOr(errflag, 1);
         id = id < 0 ? 0 : V - 1;
     }
-    const T* row = E + (int64_t)id * d;
+    const T* row = (E2 && n >= n1 ? E2 : E) + (int64_t)id * d;
     float* xo = x + (int64_t)n * d;
     for (int j = threadIdx.x; j < d; j += blockDim.x) xo[j] = to_f(row[j]);
 }
-void k_embed(int dtype, const int* ids, int n, const void* E, int d, int V, float* x, int* errflag, hipStream_t s) {
+void k_embed(int dtype, const int* ids, int n, const void* E, int d, int V, float* x, int* errflag, hipStream_t s,
+             const void* E2, int n1) {
     if (n <= 0) return;
-    if (dtype == 0) embed_kernel<float><<<n, 256, 0, s>>>(ids, (const float*)E, d, V, x, errflag);
-    else embed_kernel<bf16_t><<<n, 256, 0, s>>>(ids, (const bf16_t*)E, d, V, x, errflag);
+    if (dtype == 0) embed_kernel<float><<<n, 256, 0, s>>>(ids, (const float*)E, d, V, x, errflag, (const float*)E2, n1);
+    else embed_kernel<bf16_t><<<n, 256, 0, s>>>(ids, (const bf16_t*)E, d, V, x, errflag, (const bf16_t*)E2, n1);
 }
 
 // Store v as T at o[0]; with split also what the rounding left over, as T, at o[lo_off]: the pair hi + lo
@@ -260,12 +261,13 @@ __device__ __forceinline__ void put_pair4(T* o, int64_t lo_off, float4 v, float 
 
 // ---------------------------------------------------------------- RMSNorm: out = x * rsqrt(mean(x^2) + eps) * g
 // split: the output row is twice as wide, [d values rounded to T | d remainders] (fp16 pairs).
-// rows (optional): output row n is the norm of row rows[n].
+// rows (optional): output row n is the norm of row rows[n].  g2 (optional): the gains of rows n1 and later.
 template <typename T, typename TW>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const TW* g, T* out, int d, float eps, int split,
-                                                      const int* rows) {
+                                                      const int* rows, const TW* g2, int n1) {
     __shared__ float red[16];
     int n = blockIdx.x;
+    if (g2 && n >= n1) g = g2;
     const float* xr = x + (int64_t)(rows ? rows[n] : n) * d;
     T* o = out + (int64_t)n * d * (split ? 2 : 1);
     if (d % 4 == 0 && d <= 8192) {
@@ -296,10 +298,13 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* x, const TW* 
     for (int j = threadIdx.x; j < d; j += 256) put_pair(o + j, d, xr[j] * rs * to_f(g[j]), split);
 }
 void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split,
-               const int* rows) {
+               const int* rows, const void* g2, int n1) {
     if (n <= 0) return;
-    if (dtype == 0) rmsnorm_kernel<float, float><<<n, 256, 0, s>>>(x, (const float*)g, (float*)out, d, eps, 0, rows);
-    else rmsnorm_kernel<f16_t, bf16_t><<<n, 256, 0, s>>>(x, (const bf16_t*)g, (f16_t*)out, d, eps, split, rows);
+    if (dtype == 0)
+        rmsnorm_kernel<float, float><<<n, 256, 0, s>>>(x, (const float*)g, (float*)out, d, eps, 0, rows, (const float*)g2, n1);
+    else
+        rmsnorm_kernel<f16_t, bf16_t><<<n, 256, 0, s>>>(x, (const bf16_t*)g, (f16_t*)out, d, eps, split, rows,
+                                                        (const bf16_t*)g2, n1);
 }
 
 // ---------------------------------------------------------------- start of a decode step

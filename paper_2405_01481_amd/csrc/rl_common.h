@@ -111,11 +111,13 @@ void k_prefill_state(const int* ids, int ld_ids, const int* row_len, int* last_t
 void k_prefill_state_slots(const int* ids, int ld_ids, int n, const int* seq_first, const int* row_slot,
                            const int* row_len, const int* limit, int* last_tok, int* seq_len, int* gen_count,
                            int* finished, int* step_count, int* out_row, int* seq_id, int* gen_limit, hipStream_t s);
-void k_embed(int dtype, const int* ids, int n, const void* E, int d, int V, float* x, int* errflag, hipStream_t s);
+// E2: the table of rows n1 and later
+void k_embed(int dtype, const int* ids, int n, const void* E, int d, int V, float* x, int* errflag, hipStream_t s,
+             const void* E2 = nullptr, int n1 = 0);
 // split = 1 (bf16 configurations only): the output row is a row of fp16 pairs, [d hi | d lo], value = hi + lo
-// rows: output row i is the norm of row rows[i]
+// rows: output row i is the norm of row rows[i]; g2: the gains of output rows n1 and later
 void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split = 0,
-               const int* rows = nullptr);
+               const int* rows = nullptr, const void* g2 = nullptr, int n1 = 0);
 // rows[at[i] + j] = first[i] + j for j < count[i], i < n (all dev)
 void k_list_rows(const int* at, const int* first, const int* count, int n, int* rows, hipStream_t s);
 void k_gemm_simple(int dtype, int epi, const void* A, int lda, const void* W, const void* W2, int M, int N, int K,

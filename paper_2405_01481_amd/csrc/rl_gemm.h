@@ -20,6 +20,10 @@ struct GemmArgs {
     // dimensions are then twice as wide; the cache's lo planes live in layer `layer_lo`).
     int split_out = 0;
     int layer_lo = 0;
+    // Two models in one launch (tile kernels, splits == 1): rows [0, M1) of A multiply W, rows [M1, M) multiply Wb, the same
+    // matrix of another weight set.  Wb = nullptr: one weight set.
+    const bf16_t* Wb = nullptr;
+    int M1 = 0;
     int Wrows = 0;              // filled by the launcher
     int n_blocks_n = 0;         // filled by the launcher
     int k_per_split = 0;        // filled by the launcher

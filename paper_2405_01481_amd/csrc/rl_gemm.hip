@@ -58,6 +58,23 @@ __device__ __forceinline__ bool tile_of(int id, int MB, int NB, int& mb, int& nb
     return true;
 }
 
+// Row blocks of BM rows: a block's rows belong to one weight set.
+__host__ __device__ __forceinline__ int row_blocks(const GemmArgs& a, int BM) {
+    return a.Wb ? (a.M1 + BM - 1) / BM + (a.M - a.M1 + BM - 1) / BM : (a.M + BM - 1) / BM;
+}
+// First row of row block mb; with two weight sets a becomes the GEMM of the block's own (its weights, its end of rows).
+__device__ __forceinline__ int enter_row_block(GemmArgs& a, int BM, int mb) {
+    if (a.Wb) {
+        const int mb1 = (a.M1 + BM - 1) / BM;
+        if (mb >= mb1) {
+            a.W = a.Wb;
+            return a.M1 + (mb - mb1) * BM;
+        }
+        a.M = a.M1;
+    }
+    return mb * BM;
+}
+
 // Maximum / sum over the 32 lanes of a half-wave (the lanes that hold one row of a 32-column MFMA tile); every lane
 // ends with the same bits.  Four steps inside each row of 16 lanes are data-parallel-primitive moves (swap lanes 1
 // apart, 2 apart, mirror 8, mirror 16: each lane always meets a partner that holds the complementary set, and both
@@ -406,10 +423,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a) {
     f16_t* Ws = As + 2 * BM * LSTR;                         // [2][BN][LSTR]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WGN, wn = wave % WGN;
-    const int NB = a.n_blocks_n, MB = (a.M + BM - 1) / BM, ks = blockIdx.z;
+    const int NB = a.n_blocks_n, MB = row_blocks(a, BM), ks = blockIdx.z;
     int nb, mb;
     if (!tile_of(blockIdx.x, MB, NB, mb, nb)) return;
-    const int m0 = mb * BM;
+    const int m0 = enter_row_block(a, BM, mb);
     const int kbeg = ks * a.k_per_split, kend = min(a.K, kbeg + a.k_per_split);
     const int nk = (kend - kbeg + BKT - 1) / BKT;
 
@@ -925,8 +942,10 @@ __device__ __forceinline__ void d8_half(const floatx4_t (&acc)[MI][4], float* pa
             }
         }
     } else if constexpr (EPI == MG_LSE) {
-        // maximum and sum of exponentials of the wave's 64 columns: a quad of lanes per row, 16 columns each
-        const int row = lane >> 2, c = (lane & 3) * 16, n0 = nb * 256 + wn * 64;
+        // maximum and sum of exponentials of the wave's 64 columns: a quad of lanes per row, lane q taking columns 8 q ..
+        // 8 q + 7 and those 32 further on: the sums form the tree of the 128 x 128 kernel's reduction (columns 32 apart, then
+        // 1, 2, 4, 8, 16 apart), and its bits
+        const int row = lane >> 2, c = (lane & 3) * 8, n0 = nb * 256 + wn * 64;
         int tg[NB];
 #pragma unroll
         for (int it = 0; it < NB; ++it) tg[it] = a.tgt[min(m0 + it * 16 + row, a.M - 1)];
@@ -936,13 +955,16 @@ __device__ __forceinline__ void d8_half(const floatx4_t (&acc)[MI][4], float* pa
 #pragma unroll
         for (int it = 0; it < NB; ++it) {
             const int m = m0 + it * 16 + row;
-            float z[16];
-            patch_get(z, patch, it * 16 + row, c);
-            const float mx = quad_max(max_of(z));
-            float s4[4] = {0.f, 0.f, 0.f, 0.f};
+            float z0[8], z1[8], e[8];
+            patch_get(z0, patch, it * 16 + row, c);
+            patch_get(z1, patch, it * 16 + row, 32 + c);
+            float mx = z0[0];
 #pragma unroll
-            for (int x = 0; x < 16; ++x) s4[x & 3] += __expf(z[x] - mx);
-            const float se = quad_sum((s4[0] + s4[1]) + (s4[2] + s4[3]));
+            for (int x = 0; x < 8; ++x) mx = fmaxf(mx, fmaxf(z0[x], z1[x]));
+            mx = quad_max(mx);
+#pragma unroll
+            for (int x = 0; x < 8; ++x) e[x] = __expf(z0[x] - mx) + __expf(z1[x] - mx);
+            const float se = quad_sum(((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7])));
             if ((lane & 3) == 0 && m < a.M) {
                 a.lse_part[(int64_t)m * nparts + nb * 4 + wn] = make_float2(mx, se);
                 const int d = tg[it] - n0;
@@ -961,8 +983,8 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
     int nb, mb;
-    if (!tile_of(blockIdx.x, (a.M + BM - 1) / BM, a.n_blocks_n, mb, nb)) return;
-    const int m0 = mb * BM;
+    if (!tile_of(blockIdx.x, row_blocks(a, BM), a.n_blocks_n, mb, nb)) return;
+    const int m0 = enter_row_block(a, BM, mb);
     floatx4_t acc[MI][4];
     QkvRowMeta meta;
     dma8_loop<EPI, WF16, MI>(a, a.A, a.lda, a.W, m0, nb, wave, lane, smem, acc, meta);
@@ -1046,7 +1068,7 @@ static void launch(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s)
     }
     GemmArgs b = a;
     b.n_blocks_n = n_blocks_n;
-    dim3 grid(8 * ((n_blocks_n * ((a.M + BM - 1) / BM) + 7) / 8), 1, splits);
+    dim3 grid(8 * ((n_blocks_n * row_blocks(a, BM) + 7) / 8), 1, splits);
     gemm_mfma_kernel<BM, BN, WGM, WGN, EPI, BKT, WF16><<<grid, 256, lds, s>>>(b);
 }
 
@@ -1074,7 +1096,7 @@ static void launch_dma8_t(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
     }
     GemmArgs b = a;
     b.n_blocks_n = n_blocks_n;
-    dim3 grid(8 * ((n_blocks_n * ((a.M + BM - 1) / BM) + 7) / 8), 1, 1);
+    dim3 grid(8 * ((n_blocks_n * row_blocks(a, BM) + 7) / 8), 1, 1);
     gemm_dma8_kernel<EPI, WF16, MI><<<grid, 512, lds, s>>>(b);
 }
 template <int EPI, bool WF16>
@@ -1101,7 +1123,7 @@ static int big_row_blocks(int epi, const GemmArgs& a, int n_blocks_n) {
     int best = 8;
     float best_cost = 0.f;
     for (int mi = 8; mi >= 3; --mi) {
-        const int64_t tiles = (int64_t)((a.M + 32 * mi - 1) / (32 * mi)) * n_blocks_n;
+        const int64_t tiles = (int64_t)row_blocks(a, 32 * mi) * n_blocks_n;
         const float rem = (float)(tiles % 256) / 256.f;
         const float rounds = (float)(tiles / 256) + (rem > 0.f ? 0.7f + 0.3f * rem : 0.f);
         const float cost = rounds * (loop[mi] * (float)(a.K / 32) + (epi == MG_RESID ? 24.f : 8.f) * (float)mi / 8.f);
@@ -1135,7 +1157,7 @@ static bool use_big(int epi, const GemmArgs& a, int splits) {
     const int out_cols = epi == MG_SWIGLU ? 2 * a.N : a.N;   // tile columns
     if (out_cols % 256 != 0 || a.K % 128 != 0) return false;
     if ((uint64_t)a.M * a.lda * 2 >= (1ull << 32) || (uint64_t)a.Wrows * a.Kw * 2 >= (1ull << 32)) return false;
-    const int64_t tiles = (int64_t)((a.M + 127) / 128) * (out_cols / 128);
+    const int64_t tiles = (int64_t)row_blocks(a, 128) * (out_cols / 128);
     return a.big_mode >= 2 || tiles > 256;
 }
 

@@ -38,12 +38,13 @@ struct Layout {
     size_t out_row, seq_id, gen_limit;   // queue mode: per-slot output row, sequence id, token limit
     size_t splitk, attn_part, attn_ml, lse_part, z_tgt, blocks;
     size_t total;
-    int rows, logit_rows, mpps, nqkv, vt_cap, max_blocks;
+    int rows, pair_rows, logit_rows, mpps, nqkv, vt_cap, max_blocks;
 };
 
 static size_t esz_of(int dtype) { return dtype == RL_FP32 ? 4 : 2; }
 
 static const int kLogitRowsScore = 512;    // rows of logits materialised at a time by the plain scoring path
+static const int kTwoModelRows = 16384;     // rows up to which a workspace is made for two models' passes at once
 static const int kMaxSplitK = 16;
 static const int kMaxAttnSplits = 16;
 // bf16 configurations: the first layers can carry their activations (GEMM inputs, q, k, v, softmax
@@ -68,7 +69,9 @@ static Layout make_layout(const rl_model_cfg& c) {
     const size_t e = esz_of(c.dtype);
     const size_t pw = precise_cap(c) > 0 ? 2 : 1;   // activation rows hold fp16 pairs in the precise layers
     // token rows of one pass; sequences are packed at multiples of 32 rows on the tuned path
-    const int rows = (std::max(c.max_chunk_tokens, c.max_batch) + 31) / 32 * 32 + 32;
+    // (up to kTwoModelRows also those of two models' chunks at once: see both_fit)
+    L.pair_rows = c.dtype == RL_BF16 ? std::max(c.max_chunk_tokens, std::min(2 * ((c.max_chunk_tokens + 31) / 32 * 32), kTwoModelRows)) : 0;
+    const int rows = (std::max(std::max(c.max_chunk_tokens, L.pair_rows), c.max_batch) + 31) / 32 * 32 + 32;
     const int nqkv = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
     const int qd = c.n_q_heads * c.head_dim, kd = c.n_kv_heads * c.head_dim;
     L.rows = rows;
@@ -98,10 +101,11 @@ static Layout make_layout(const rl_model_cfg& c) {
     L.tok_pos = take((size_t)rows * 4);
     L.tok_slot = take((size_t)rows * 4);
     L.tok_tgt = take((size_t)rows * 4);
-    L.seq_first = take((size_t)c.max_batch * 4);
-    L.row_start = take((size_t)c.max_batch * 4);
-    L.row_len = take((size_t)c.max_batch * 4);
-    L.row_slot = take((size_t)c.max_batch * 4);
+    // (a chunk that carries two models lists its sequences twice)
+    L.seq_first = take((size_t)2 * c.max_batch * 4);
+    L.row_start = take((size_t)2 * c.max_batch * 4);
+    L.row_len = take((size_t)2 * c.max_batch * 4);
+    L.row_slot = take((size_t)2 * c.max_batch * 4);
     L.out_row = take((size_t)c.max_batch * 4);
     L.seq_id = take((size_t)c.max_batch * 4);
     L.gen_limit = take((size_t)c.max_batch * 4);
@@ -115,7 +119,7 @@ static Layout make_layout(const rl_model_cfg& c) {
     L.attn_ml = take((size_t)c.max_batch * c.n_q_heads * kMaxAttnSplits * 2 * 4);
     L.lse_part = take((size_t)rows * ((c.vocab + 63) / 64) * sizeof(float2));
     L.z_tgt = take((size_t)rows * 4);
-    L.max_blocks = rows / 32 + c.max_batch;
+    L.max_blocks = rows / 32 + 2 * c.max_batch;
     L.blocks = take((size_t)L.max_blocks * sizeof(int4));
     L.total = off;
     return L;
@@ -425,17 +429,20 @@ static const int kConvertRows = 4096;
 
 static bool g_large_gemm_copy = true;   // rollout_set_large_gemm_copy: off = as if no weight set had a copy
 
+// The fp16 copy of a weight tensor, if its set has one.
+static const void* fp16_copy_of(const rl_ctx* c, const void* w) {
+    auto it = c->shadow_of.find(w);
+    if (it != c->shadow_of.end()) return it->second;
+    it = c->other_shadow_of.find(w);
+    return it != c->other_shadow_of.end() ? it->second : nullptr;
+}
+
 // w_skip: elements of a0.W that lie before the rows this GEMM uses (a0.W itself is what a weight set's copy is found by).
 static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hipStream_t s, Scratch idle = {}, size_t w_skip = 0) {
     ProfScope ps(c, cls, s);
     GemmArgs a = a0;
     a.big_mode = c->big_mode;
-    auto copy_of = [&](const void* w) -> const void* {
-        auto it = c->shadow_of.find(w);
-        if (it != c->shadow_of.end()) return it->second;
-        it = c->other_shadow_of.find(w);
-        return it != c->other_shadow_of.end() ? it->second : nullptr;
-    };
+    auto copy_of = [&](const void* w) { return fp16_copy_of(c, w); };
     if (cls == RL_K_GEMM_DECODE && a.M <= 128 && (epi == MG_STORE_F32 || epi == MG_SWIGLU || epi == MG_SAMPLE) &&
         k_gemm_decode_supported(epi, a.N, a.K, a.Kw > 0 ? a.Kw : a.K)) {
         if (const void* h = copy_of((const void*)a.W)) { a.W = (const bf16_t*)h; a.w_f16 = 1; }
@@ -445,7 +452,21 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
             const int kw = a.Kw > 0 ? a.Kw : a.K;
             const size_t elems = (size_t)(epi == MG_SWIGLU ? a.up_offset + a.N : a.N) * kw;
             const void* const h = g_large_gemm_copy ? copy_of((const void*)a.W) : nullptr;
-            if (epi == MG_KLFULL) {                            // both models' copies or neither's
+            if (a.Wb) {                                        // two models: both weight sets as fp16 or neither
+                const void* hs[2] = {h, g_large_gemm_copy ? copy_of((const void*)a.Wb) : nullptr};
+                const size_t missing = (hs[0] ? 0 : 1) + (hs[1] ? 0 : 1);
+                if (missing == 0 || ((int64_t)a.M1 * (a.K / kw) >= kConvertRows && idle.bytes >= 2 * elems * missing)) {
+                    char* p = (char*)idle.p;
+                    const bf16_t* const ws[2] = {a.W, a.Wb};
+                    for (int i = 0; i < 2; ++i) {
+                        if (hs[i]) continue;
+                        k_bf16_to_f16(ws[i], p, (int64_t)elems, s);
+                        hs[i] = p;
+                        p += 2 * elems;
+                    }
+                    a.W = (const bf16_t*)hs[0]; a.Wb = (const bf16_t*)hs[1]; a.w_f16 = 1;
+                }
+            } else if (epi == MG_KLFULL) {                     // both models' copies or neither's
                 const void* const h2 = copy_of((const void*)a.W2);
                 if (h && h2) { a.W = (const bf16_t*)h; a.W2 = (const bf16_t*)h2; a.w_f16 = 1; }
             } else if (h) {
@@ -469,8 +490,9 @@ static int decode_splits(const rl_ctx* c, int n, int N, int K, int Kw) {
 }
 
 // bf16 weights / fp16 activations on the MFMA kernels.  paged: h holds the first layer's norm output (k_step_start).
+// W2 (not paged, nothing written to pages): the weight set of the second half of the rows.
 static void run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
-                            int nblocks, hipStream_t s, float* x, int l0, int l1) {
+                            int nblocks, hipStream_t s, float* x, int l0, int l1, const WeightsHost* W2) {
     const rl_model_cfg& m = c->cfg;
     const Layout& L = c->L;
     const int qd = m.n_q_heads * m.head_dim;
@@ -495,6 +517,8 @@ static void run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
         g.K = g.lda;
         g.Kw = width;
     };
+    const int n1 = W2 ? n / 2 : 0;
+    auto second = [&](std::vector<const void*> WeightsHost::*t, int l) { return W2 ? (const bf16_t*)(W2->*t)[l] : nullptr; };
     for (int l = l0; l < l1; ++l) {
         const int sp = l < c->precise, sp_next = l + 1 < c->precise && l + 1 < m.n_layers;
         GemmArgs g;
@@ -534,8 +558,9 @@ static void run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             const void* next = (l + 1 < m.n_layers) ? W.attn_norm[l + 1] : W.final_norm;
             k_resid_norm(x, part, ks, g.split_stride, next, h, n, m.d_model, m.rms_eps, s, sp_next);
         } else {
-            k_rmsnorm(1, x, W.attn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
+            k_rmsnorm(1, x, W.attn_norm[l], h, n, m.d_model, m.rms_eps, s, sp, nullptr, second(&WeightsHost::attn_norm, l), n1);
             g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.wqkv[l]; g.N = L.nqkv;
+            g.Wb = second(&WeightsHost::wqkv, l); g.M1 = n1;
             g.tok_pos = tpos; g.tok_slot = tslot; g.rope = rope; g.q_out = q; g.k_out = kb; g.v_out = vb;
             g.pool = write_pages ? (f16_t*)c->pool : nullptr; g.block_table = bt; g.mpps = L.mpps; g.layer = l;
             g.Hq = m.n_q_heads; g.Hkv = m.n_kv_heads; g.hd = m.head_dim; g.geo = c->geo; g.vt_cap = L.vt_cap;
@@ -551,27 +576,31 @@ static void run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
             attention(c, l, n, false, max_ctx, nblocks, s);
             g = GemmArgs();
             g.M = n; g.A = att; pair_in(g, qd, sp); g.W = (const bf16_t*)W.wo[l]; g.N = m.d_model;
+            g.Wb = second(&WeightsHost::wo, l); g.M1 = n1;
             g.outF = x; g.ldc = m.d_model;
             mfma(c, gcls, MG_RESID, g, 1, s, idle_ffn);
-            k_rmsnorm(1, x, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s, sp);
+            k_rmsnorm(1, x, W.ffn_norm[l], h, n, m.d_model, m.rms_eps, s, sp, nullptr, second(&WeightsHost::ffn_norm, l), n1);
             g = GemmArgs();
             g.M = n; g.A = h; pair_in(g, m.d_model, sp); g.W = (const bf16_t*)W.w_gate_up[l]; g.N = m.d_ffn;
+            g.Wb = second(&WeightsHost::w_gate_up, l); g.M1 = n1;
             g.up_offset = m.d_ffn; g.outH = ffn; g.ldc = sp ? 2 * m.d_ffn : m.d_ffn; g.split_out = sp;
             mfma(c, gcls, MG_SWIGLU, g, 1, s, idle_attn);
             g = GemmArgs();
             g.M = n; g.A = ffn; pair_in(g, m.d_ffn, sp); g.W = (const bf16_t*)W.w_down[l]; g.N = m.d_model;
+            g.Wb = second(&WeightsHost::w_down, l); g.M1 = n1;
             g.outF = x; g.ldc = m.d_model;
             mfma(c, gcls, MG_RESID, g, 1, s, idle_attn);
         }
     }
 }
 
+// W2: weight set of the second half of the rows (tuned path).
 // Layers [l0, l1) (default: all) on the n packed rows whose residual stream is x (default: the workspace's).
 static void run_layers(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
-                       int nblocks, hipStream_t s, float* x = nullptr, int l0 = 0, int l1 = -1) {
+                       int nblocks, hipStream_t s, float* x = nullptr, int l0 = 0, int l1 = -1, const WeightsHost* W2 = nullptr) {
     if (!x) x = c->at<float>(c->L.x);
     if (l1 < 0) l1 = c->cfg.n_layers;
-    if (c->impl == 1) run_layers_fast(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
+    if (c->impl == 1) run_layers_fast(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1, W2);
     else run_layers_plain(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
 }
 
@@ -1395,22 +1424,29 @@ int rollout_generate_queue(rl_ctx* c, const rl_sample_cfg* sample, const int32_t
     return RL_OK;
 }
 
-// Final norm, LM head and log-prob of every target token for the n packed rows whose residual stream is x.
-static void score_head(rl_ctx* c, const WeightsHost& W, float* x, int n, float* logp_out, int Lmax, hipStream_t s) {
+// Final norm, LM head and log-prob of every target token for the n packed rows whose residual stream is x.  W2: the
+// second half of the rows is that model's, its log-probs go to logp_out2 (tuned path).
+static void score_head(rl_ctx* c, const WeightsHost& W, float* x, int n, float* logp_out, int Lmax, hipStream_t s,
+                       const WeightsHost* W2 = nullptr, float* logp_out2 = nullptr) {
     const rl_model_cfg& m = c->cfg;
     const Layout& L = c->L;
     if (c->impl == 1) {
-        k_rmsnorm(m.dtype, x, W.final_norm, c->at<char>(L.h), n, m.d_model, m.rms_eps, s);
+        const int n1 = W2 ? n / 2 : n;
+        k_rmsnorm(m.dtype, x, W.final_norm, c->at<char>(L.h), n, m.d_model, m.rms_eps, s, 0, nullptr,
+                  W2 ? W2->final_norm : nullptr, n1);
         // LM head with the log-sum-exp and the target gather in its epilogue: no logits in memory
         GemmArgs g;
         g.M = n; g.A = c->at<f16_t>(L.h); g.lda = m.d_model; g.W = (const bf16_t*)W.lm_head; g.N = m.vocab;
         g.K = m.d_model; g.tgt = c->at<int>(L.tok_tgt); g.lse_part = c->at<float2>(L.lse_part);
         g.z_tgt = c->at<float>(L.z_tgt);
+        if (W2) { g.Wb = (const bf16_t*)W2->lm_head; g.M1 = n1; }
         // behind the last layer everything from the qkv to the FFN buffer is idle (they lie one behind the other)
         mfma(c, RL_K_LMHEAD_SCORE, MG_LSE, g, 1, s, {c->at<char>(L.qkv), L.ffn + L.ffn_bytes - L.qkv});
-        k_lse_reduce(c->at<float2>(L.lse_part), k_gemm_mfma_lse_parts(n, m.vocab, m.d_model, c->big_mode),
-                     c->at<float>(L.z_tgt), n, c->at<int>(L.tok_tgt), c->at<int>(L.tok_slot), c->at<int>(L.tok_pos),
-                     logp_out, Lmax, s);
+        const int nparts = k_gemm_mfma_lse_parts(n, m.vocab, m.d_model, c->big_mode);
+        for (int r0 = 0; r0 < n; r0 += n1)
+            k_lse_reduce(c->at<float2>(L.lse_part) + (size_t)r0 * nparts, nparts, c->at<float>(L.z_tgt) + r0, n1,
+                         c->at<int>(L.tok_tgt) + r0, c->at<int>(L.tok_slot) + r0, c->at<int>(L.tok_pos) + r0,
+                         r0 ? logp_out2 : logp_out, Lmax, s);
         return;
     }
     for (int r0 = 0; r0 < n; r0 += L.logit_rows) {
@@ -1448,6 +1484,62 @@ static int score_pass(rl_ctx* c, const WeightsHost& W, const int32_t* ids, const
                 c->at<int>(L.errflag), s);
         run_layers(c, W, ch.n, false, false, ch.max_ctx, ch.nblocks, s);
         apply_head(c, W, value_head, c->at<float>(L.x), ch.n, logp_out, Lmax, s);
+    }
+    return RL_OK;
+}
+
+// Two models' passes over a chunk of n rows as one pass over 2 n rows, the chunk's sequences listed twice: GEMMs of n rows
+// leave the last round of 256 tiles, or most CUs, idle, and short kernels wait for one another.  Each row is computed as it
+// is alone.  One pass against two: 1B shape 2240 rows (8 sequences of 70 to 512 tokens) 11.69 -> 9.83 ms, 8B shape (exact KL,
+// heads included) 5300 rows 27.4 -> 27.0; at 16384 rows there is nothing left to fill.  The rows for it cost a small
+// context up to twice the workspace (8B shape, 8 sequences of 1024: 1.5 GB more).  Taken where both fit -- unless the rows are enough for weights without an fp16 copy to be
+// converted ahead of their GEMMs, whose idle workspace has room for one model's at a time.
+static bool both_fit(const rl_ctx* c, const Chunk& ch, const WeightsHost& W1, const WeightsHost& W2) {
+    if (c->impl != 1 || 2 * ch.n > c->L.pair_rows) return false;
+    return ch.n < kConvertRows || (g_large_gemm_copy && fp16_copy_of(c, W1.wqkv[0]) && fp16_copy_of(c, W2.wqkv[0]));
+}
+
+// The chunk with its sequences listed once more behind it.
+static Chunk listed_twice(const Chunk& ch) {
+    Chunk t = ch;
+    for (size_t i = 0; i < ch.lens.size(); ++i) {
+        t.rows_b.push_back(ch.rows_b[i]);
+        t.starts.push_back(ch.n + ch.starts[i]);
+        t.lens.push_back(ch.lens[i]);
+    }
+    t.n = 2 * ch.n;
+    return t;
+}
+
+// score_pass of two device-resident weight sets.
+static int score_pass_both(rl_ctx* c, const WeightsHost& W1, const WeightsHost& W2, const int32_t* ids, const int32_t* seq_len,
+                           int B, int Lmax, float* out1, float* out2, hipStream_t s) {
+    const rl_model_cfg& m = c->cfg;
+    const Layout& L = c->L;
+    k_fill_f32(out1, 0.f, (int64_t)B * Lmax, s);
+    k_fill_f32(out2, 0.f, (int64_t)B * Lmax, s);
+    std::vector<int> len_of(seq_len, seq_len + B);
+    int b0 = 0;
+    while (b0 < B) {
+        Chunk ch;
+        b0 = chunk_take(c, len_of, b0, B, ch);
+        const bool both = both_fit(c, ch, W1, W2);
+        if (both) ch = listed_twice(ch);
+        int rc = pack_chunk(c, ids, Lmax, ch, true, s);
+        if (rc) return rc;
+        if (both) {
+            k_embed(m.dtype, c->at<int>(L.tok_ids), ch.n, W1.tok_embed, m.d_model, m.vocab, c->at<float>(L.x),
+                    c->at<int>(L.errflag), s, W2.tok_embed, ch.n / 2);
+            run_layers(c, W1, ch.n, false, false, ch.max_ctx, ch.nblocks, s, nullptr, 0, -1, &W2);
+            score_head(c, W1, c->at<float>(L.x), ch.n, out1, Lmax, s, &W2, out2);
+            continue;
+        }
+        for (const WeightsHost* W : {&W1, &W2}) {
+            k_embed(m.dtype, c->at<int>(L.tok_ids), ch.n, W->tok_embed, m.d_model, m.vocab, c->at<float>(L.x),
+                    c->at<int>(L.errflag), s);
+            run_layers(c, *W, ch.n, false, false, ch.max_ctx, ch.nblocks, s);
+            score_head(c, *W, c->at<float>(L.x), ch.n, W == &W1 ? out1 : out2, Lmax, s);
+        }
     }
     return RL_OK;
 }
@@ -1635,7 +1727,10 @@ int score_logprobs_kl(rl_ctx* c, const rl_weights* policy, const rl_weights* ref
         if (rc) return rc;
         if ((rc = ensure_other_shadow(c, wr, s))) return rc;
     }
-    if (logp_policy) {
+    if (logp_policy && reference && logp_ref && wp.location == 0 && wr.location == 0) {
+        if ((rc = score_pass_both(c, wp, wr, ids, seq_len, B, Lmax, logp_policy, logp_ref, s))) return rc;
+        reference = nullptr;                                   // both done
+    } else if (logp_policy) {
         rc = wp.location == 1 ? score_pass_streamed(c, wp, ids, seq_len, B, Lmax, logp_policy, s)
                               : score_pass(c, wp, ids, seq_len, B, Lmax, logp_policy, s);
         if (rc) return rc;
@@ -1691,7 +1786,9 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
         Chunk ch;
         b0 = chunk_take(c, len_of, b0, B, ch);
         const int n = ch.n;
-        if ((rc = pack_chunk(c, ids, Lmax, ch, true, s))) return rc;
+        const bool both = both_fit(c, ch, wp, wr);
+        Chunk run = both ? listed_twice(ch) : ch;
+        if ((rc = pack_chunk(c, ids, Lmax, run, true, s))) return rc;
         // The LM heads run on the rows that predict a response token and no others (prompt rows, last tokens and padding are
         // left out: half of the rows where prompts are half of the tokens).  Their list is kept where the log-sum-exp
         // path keeps its targets' logits.
@@ -1708,16 +1805,19 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
         k_put_rows(at.data(), ch.rows_b.data(), first.data(), count.data(), (int)at.size(), c->at<int>(L.seq_first),
                    c->at<int>(L.row_slot), c->at<int>(L.row_start), c->at<int>(L.row_len), s);
         k_list_rows(c->at<int>(L.seq_first), c->at<int>(L.row_start), c->at<int>(L.row_len), (int)at.size(), rows, s);
-        // policy body, final norm; keep its hidden states while the reference body runs on the same rows
-        k_embed(m.dtype, c->at<int>(L.tok_ids), n, wp.tok_embed, m.d_model, m.vocab, c->at<float>(L.x),
-                c->at<int>(L.errflag), s);
+        // both bodies and final norms; the policy's hidden states are kept while the reference body runs on the same rows
+        float* const x = c->at<float>(L.x);
+        k_embed(m.dtype, c->at<int>(L.tok_ids), run.n, wp.tok_embed, m.d_model, m.vocab, x, c->at<int>(L.errflag), s,
+                both ? wr.tok_embed : nullptr, n);
         if (nh == 0) continue;                                   // nothing to score; the ids have been looked at
-        run_layers(c, wp, n, false, false, ch.max_ctx, ch.nblocks, s);
-        k_rmsnorm(m.dtype, c->at<float>(L.x), wp.final_norm, c->at<char>(L.h_keep), nh, m.d_model, m.rms_eps, s, 0, rows);
-        k_embed(m.dtype, c->at<int>(L.tok_ids), n, wr.tok_embed, m.d_model, m.vocab, c->at<float>(L.x),
-                c->at<int>(L.errflag), s);
-        run_layers(c, wr, n, false, false, ch.max_ctx, ch.nblocks, s);
-        k_rmsnorm(m.dtype, c->at<float>(L.x), wr.final_norm, c->at<char>(L.h), nh, m.d_model, m.rms_eps, s, 0, rows);
+        run_layers(c, wp, run.n, false, false, run.max_ctx, run.nblocks, s, nullptr, 0, -1, both ? &wr : nullptr);
+        k_rmsnorm(m.dtype, x, wp.final_norm, c->at<char>(L.h_keep), nh, m.d_model, m.rms_eps, s, 0, rows);
+        if (!both) {
+            k_embed(m.dtype, c->at<int>(L.tok_ids), n, wr.tok_embed, m.d_model, m.vocab, x, c->at<int>(L.errflag), s);
+            run_layers(c, wr, n, false, false, run.max_ctx, run.nblocks, s);
+        }
+        k_rmsnorm(m.dtype, x + (both ? (size_t)n * m.d_model : 0), wr.final_norm, c->at<char>(L.h), nh, m.d_model, m.rms_eps, s,
+                  0, rows);
         for (int r0 = 0; r0 < nh; r0 += kl_rows) {
             const int nr = std::min(kl_rows, nh - r0);
             const char* hp = c->at<char>(L.h_keep) + (size_t)r0 * m.d_model * e;

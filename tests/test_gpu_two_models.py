@@ -1,0 +1,59 @@
+"""Scoring two models in one pass (sequences listed twice, each half of the rows on its own weight set): bit for bit what
+two passes give, whichever of the sets have an fp16 copy."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2405_01481_amd import rollout as R
+from paper_2405_01481_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+SHAPE = synth.ModelShape("two512", 2, 512, 8, 2, 128, 1024, 2048, 10000.0, "bf16", 0.05)
+
+
+def _ids(B, L):
+    return np.random.default_rng(7).integers(0, SHAPE.vocab, size=(B, L)).astype(np.int32)
+
+
+def _run(impl, copies, rows, lens, plens, L, wp, wr, alone):
+    """Log-probs of both models, their KL terms and the exact KL; with alone, the log-probs from one call per model."""
+    B = len(lens)
+    cfg = R.make_cfg(SHAPE, B, L, max_chunk_tokens=rows)
+    buf = [torch.empty(R.rollout_weight_shadow_bytes(cfg), dtype=torch.uint8, device=DEV) if on else None for on in copies]
+    Wp, Wr = R.Weights(wp, shadow=buf[0]), R.Weights(wr, shadow=buf[1])
+    ro = R.Rollout(cfg, Wp, DEV)
+    ro.rollout_set_impl(impl)
+    ids = torch.tensor(_ids(B, L), device=DEV)
+    outs = [torch.full((B, L), 9.0, device=DEV) for _ in range(5)]
+    if alone:
+        for w, o in zip((Wp, Wr), outs):
+            ro.score_logprobs_kl(w, None, ids, lens, plens, 0.0, o)
+    else:
+        ro.score_logprobs_kl(Wp, Wr, ids, lens, plens, 0.003, *outs[:4])
+    ro.score_kl_exact(Wp, Wr, ids, lens, plens, outs[4])
+    ro.rollout_check()
+    ro.close()
+    return [o.cpu().numpy() for o in outs]
+
+
+@pytest.mark.parametrize("copies", [(False, False), (True, False), (True, True)], ids=["none", "policy", "both"])
+@pytest.mark.parametrize("impl", [1, 2], ids=["by-size", "large-m"])
+def test_one_pass_gives_the_bits_of_two(impl, copies):
+    """One chunk of both models; several of them; and, for comparison, the same sequences at the head of a chunk of more than
+    8192 rows, which the workspace does not hold twice and which is run for one model after the other (with a last chunk
+    behind it that is again run for both together)."""
+    lens = np.array([1, 33, 64, 150, 200, 97, 31], np.int32)               # 672 rows with their padding
+    plens = np.array([1, 10, 64, 1, 100, 96, 1], np.int32)                 # one prompt without a response
+    more = np.concatenate([lens, np.random.default_rng(11).integers(150, 201, size=53).astype(np.int32)])
+    wp, wr = synth.make_weights(SHAPE, 1, DEV), synth.make_weights(SHAPE, 2, DEV)
+    B, L = len(lens), int(lens.max())
+    apart = _run(impl, copies, 10016, more, np.concatenate([plens, np.maximum(1, more[B:] // 2)]).astype(np.int32), L, wp, wr, True)
+    for rows in (1024, 416):
+        got = _run(impl, copies, rows, lens, plens, L, wp, wr, False)
+        for i in (0, 1, 4):
+            assert np.isfinite(got[i]).all() and np.array_equal(got[i], apart[i][:B]), (rows, i)
+        assert np.abs(got[0] - got[1]).max() > 0.1 and np.abs(got[4]).max() > 0
+    whole = _run(impl, copies, 10016, more, np.ones(len(more), np.int32), L, wp, wr, False)
+    assert all(np.array_equal(whole[i], apart[i]) for i in (0, 1))
