@@ -172,8 +172,9 @@ int rollout_generate(rl_ctx* ctx, const rl_sample_cfg* sample,
 /* Queue mode of rollout_generate (Section 3.2: response lengths vary widely, so generation work is handed
  * out dynamically rather than in fixed batches).  Q prompts, any number; at most max_batch are live at a
  * time.  Prompt q generates until it emits eos_id or has produced gen_limit[q] tokens; its cache pages
- * then go back to the pool and its slot takes the next prompt in line, which is prefilled while the other
- * slots wait.  The host looks at the finished flags every 8 decode steps; a finished sequence is parked
+ * then go back to the pool and its slot takes a waiting prompt, the one of the largest gen_limit first (in
+ * their order where the pool is smaller than max_batch of the longest rows need), which is prefilled while
+ * the other slots wait.  The host looks at the finished flags every 8 decode steps; a finished sequence is parked
  * meanwhile (no cache growth, no attention).  Row q's tokens and log-probs are exactly those
  * rollout_generate would give it in any batch: it draws U(seed, seq_id_base + q, n) for its n-th token and
  * no kernel mixes rows.
