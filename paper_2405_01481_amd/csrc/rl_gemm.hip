@@ -1140,6 +1140,21 @@ static void launch_big(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
     else launch_dma8<EPI, false>(b, n_blocks_n, mi, s);
 }
 
+// GEMMs below the large-M kernel: 128 x 128 tiles, or where these are at most half of the CUs' number tiles of 64 rows, for
+// the residual's also of 64 columns.  A workgroup's k-tile takes as long as its operands take to arrive (about 50 KB/us per
+// CU: 0.65 us for 32 KB), so a GEMM with idle CUs is as fast as its tiles are small.
+// 352 rows of the 8B shape: O and down projections 101 -> 78 us on average (96 tiles -> 192), QKV of the pair layer 40 us; at 144
+// tiles of 128 x 128 (QKV, 60 us) twice as many would double up on some CUs.
+// All of them sum a row over k in the same order: the bits do not depend on the choice.
+template <int EPI>
+static void launch_small(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
+    if (row_blocks(a, 128) * n_blocks_n > 128) { launch<128, 128, 2, 2, EPI>(a, n_blocks_n, 1, s); return; }
+    if constexpr (EPI == MG_RESID) {
+        if (row_blocks(a, 64) * n_blocks_n <= 128) { launch<64, 64, 2, 2, EPI>(a, 2 * n_blocks_n, 1, s); return; }
+    }
+    launch<64, 128, 2, 2, EPI>(a, n_blocks_n, 1, s);
+}
+
 bool k_gemm_mfma_supported(int epi, int N, int K, int hd) {
     if (epi == MG_KLFULL) return N % 128 == 0 && K % 128 == 0 && (uint64_t)N * K * 2 < (1ull << 32);
     if (K % BK != 0) return false;
@@ -1197,19 +1212,19 @@ void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s) {
             break;
         case MG_RESID:
             if (big) launch_big<MG_RESID>(a, a.N / 256, s);
-            else launch<128, 128, 2, 2, MG_RESID>(a, a.N / 128, 1, s);
+            else launch_small<MG_RESID>(a, a.N / 128, s);
             break;
         case MG_SWIGLU:
             if (big) launch_big<MG_SWIGLU>(a, a.N / 128, s);
-            else launch<128, 128, 2, 2, MG_SWIGLU>(a, a.N / 64, 1, s);
+            else launch_small<MG_SWIGLU>(a, a.N / 64, s);
             break;
         case MG_LSE:
             if (big) launch_big<MG_LSE>(a, a.N / 256, s);
-            else launch<128, 128, 2, 2, MG_LSE>(a, a.N / 128, 1, s);
+            else launch_small<MG_LSE>(a, a.N / 128, s);
             break;
         case MG_QKV:
             if (big) launch_big<MG_QKV>(a, a.N / 256, s);
-            else launch<128, 128, 2, 2, MG_QKV>(a, a.N / 128, 1, s);
+            else launch_small<MG_QKV>(a, a.N / 128, s);
             break;
         case MG_KLFULL:
             if (a.w_f16) launch_kl8<true>(a, s);
