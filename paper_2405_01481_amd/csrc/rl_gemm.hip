@@ -3,16 +3,17 @@
 // Weights stay bf16 in HBM and are converted to fp16 on their way to the MFMA operand registers
 // (exact for every weight of normal fp16 magnitude) -- or are read from an fp16 copy where a weight set
 // has one; the contraction runs on fp16 MFMAs (v_mfma_f32_16x16x32_f16 in the large-M kernel,
-// v_mfma_f32_32x32x16_f16 in the others) with fp32 accumulation.  Three kernels share one set of epilogues (the decode
-// step's weight-streaming GEMMs are in rl_gemm_stream.hip):
-//   * gemm_mfma_kernel: 128 x 128 tiles staged through registers -- small M, and split-K for decode
+// v_mfma_f32_32x32x16_f16 in the others) with fp32 accumulation.  Three kernels (the decode step's
+// weight-streaming GEMMs are in rl_gemm_stream.hip):
+//   * gemm_mfma_kernel: 128 x 128, 64 x 128 and 64 x 64 tiles staged through registers -- small M, and split-K for decode
 //     batches above 128 rows;
 //   * gemm_dma8_kernel: tiles of 96 to 256 rows x 256 columns, eight waves, operands staged by global ->
 //     LDS loads -- the large-M GEMMs of prefill and scoring;
 //   * gemm_kl8_kernel:  the same loop run twice on tiles of 128 rows -- the exact full-vocabulary KL, which needs the
 //     policy's and the reference's logits of a tile together.
 // Epilogues: fp32 store / split-K partial, residual add, SwiGLU, RoPE + q/k/v split for
-// the QKV projection, log-sum-exp + target gather for the scoring LM head.
+// the QKV projection, log-sum-exp + target gather for the scoring LM head; mg_epilogue for the first kernel, d8_half for
+// the second.  Both round alike: a row's results do not depend on which of them its GEMM's size picks.
 #include "rl_common.h"
 #include "rl_gemm.h"
 #include "rl_gemm_dev.h"
@@ -136,7 +137,7 @@ __device__ __forceinline__ int64_t v_tile_off(const GemmArgs& a, int plane, int 
     return (((int64_t)plane * (a.vt_cap >> 5) + (m >> 5)) * a.hd + d) * 32 + (m & 31);
 }
 
-// Epilogue shared by the tile kernels, for one 32-row band of a wave's accumulators: acc[j][r] of the
+// Epilogue of gemm_mfma_kernel for one 32-row band of a wave's accumulators: acc[j][r] of the
 // wave in tile-column position wn is C(row, col) with
 //   row = m_base + 8*(r/4) + 4*(lane/32) + r%4,   col(tile-local) = wn*TN*32 + j*32 + lane%32
 template <int EPI, int BN, int TN, int WGN>
