@@ -87,6 +87,21 @@ __global__ void list_rows_kernel(const int* at, const int* first, const int* cou
 void k_list_rows(const int* at, const int* first, const int* count, int n, int* rows, hipStream_t s) {
     if (n > 0) list_rows_kernel<<<n, 256, 0, s>>>(at, first, count, rows);
 }
+// One block per row, 16 bytes per access.
+__global__ __launch_bounds__(256) void gather_rows_kernel(const f16_t* src_a, f16_t* dst_a, int wa, const float* src_x, float* dst_x,
+                                                          int d, const int* rows) {
+    const int64_t i = blockIdx.x, r = rows[i];
+    const float4* sa = reinterpret_cast<const float4*>(src_a + r * wa);
+    const float4* sx = reinterpret_cast<const float4*>(src_x + r * d);
+    float4* da = reinterpret_cast<float4*>(dst_a + i * wa);
+    float4* dx = reinterpret_cast<float4*>(dst_x + i * d);
+    for (int j = threadIdx.x; j < wa / 8; j += 256) da[j] = sa[j];
+    for (int j = threadIdx.x; j < d / 4; j += 256) dx[j] = sx[j];
+}
+void k_gather_rows(const f16_t* src_a, f16_t* dst_a, int wa, const float* src_x, float* dst_x, int d, const int* rows, int n,
+                   hipStream_t s) {
+    if (n > 0) gather_rows_kernel<<<n, 256, 0, s>>>(src_a, dst_a, wa, src_x, dst_x, d, rows);
+}
 // Pack rows of a padded [*, ld_ids] id matrix into a flat token list.
 // Row r of the chunk is batch row seq_first[r]; its row_len[r] tokens go to
 // [row_start[r], row_start[r] + row_len[r]).  tok_tgt (optional) = next token id of the

@@ -118,6 +118,9 @@ void k_embed(int dtype, const int* ids, int n, const void* E, int d, int V, floa
 // rows: output row i is the norm of row rows[i]; g2: the gains of output rows n1 and later
 void k_rmsnorm(int dtype, const float* x, const void* g, void* out, int n, int d, float eps, hipStream_t s, int split = 0,
                const int* rows = nullptr, const void* g2 = nullptr, int n1 = 0);
+// Row i of dst_a (wa halfs) and dst_x (d floats) = row rows[i] of src_a and src_x; wa a multiple of 8, d of 4.
+void k_gather_rows(const f16_t* src_a, f16_t* dst_a, int wa, const float* src_x, float* dst_x, int d, const int* rows, int n,
+                   hipStream_t s);
 // rows[at[i] + j] = first[i] + j for j < count[i], i < n (all dev)
 void k_list_rows(const int* at, const int* first, const int* count, int n, int* rows, hipStream_t s);
 void k_gemm_simple(int dtype, int epi, const void* A, int lda, const void* W, const void* W2, int M, int N, int K,
