@@ -403,7 +403,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 static constexpr int ap_tiles(bool SP) { return SP ? 1 : 2; }                      // 32-key tiles of a step
 static constexpr int AP_NW = 4;                                                    // waves of a workgroup
-static constexpr int ap_stages(int HD, bool SP) { return 2; }
+static constexpr int AP_NS = 2;                                                    // stages
 // query heads of a group of G that a workgroup takes (the group is cut in two where it has more than four)
 __host__ __device__ constexpr int ap_heads(int G) { return G <= AP_NW ? G : (G + 1) / 2; }
 static constexpr int ap_stage_bytes(int HD, bool SP) { return ap_tiles(SP) * (SP ? 4 : 2) * 32 * HD * 2; }
@@ -414,7 +414,7 @@ static constexpr int ap_stage_bytes(int HD, bool SP) { return ap_tiles(SP) * (SP
 // second contraction: three MFMAs where the plain kernel has one.
 template <int HD, bool SP>
 __global__ __launch_bounds__(AP_NW * 64, HD == 64 ? 3 : 2) void attn_prefill_kernel(PrefillAttnArgs a) {
-    constexpr int KSTEPS = HD / 16, DB = HD / 32, TS = ap_tiles(SP), NS = ap_stages(HD, SP);
+    constexpr int KSTEPS = HD / 16, DB = HD / 32, TS = ap_tiles(SP), NS = AP_NS;
     constexpr int KT = 32 * HD * 2;              // bytes of a K tile; a V^T tile is as large
     constexpr int NT = SP ? 4 : 2;               // parts of a tile: K, V^T (hi), then K, V^T (lo)
     constexpr int STG = ap_stage_bytes(HD, SP);
@@ -645,7 +645,7 @@ int k_attn_prefill_blocks(int Hq, int Hkv) { return AP_NW / ap_heads(Hq / Hkv); 
 
 template <int HD, bool SP>
 static void launch_prefill(const PrefillAttnArgs& a, int nblocks, hipStream_t s) {
-    constexpr int lds = ap_stages(HD, SP) * ap_stage_bytes(HD, SP);
+    constexpr int lds = AP_NS * ap_stage_bytes(HD, SP);
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void*)attn_prefill_kernel<HD, SP>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

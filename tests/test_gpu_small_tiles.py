@@ -13,7 +13,7 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("hd", [64, 128])
 def test_tile_sizes_give_the_same_bits(hd):
-    """d = 512: four column blocks of 128 for the two residual GEMMs, so 256, 1216 and 5056 rows in a chunk put them on
+    """d = 512: four column blocks of 128 for the two residual GEMMs, so chunks of 256 and 1216 rows put them on
     64 x 64 tiles (16 and 76 of 64 rows), 64 x 128 at 2720 (172) and 128 x 128 at 5056 (160 of 128 rows); the QKV projection
     and the LM head take 64 x 128 tiles up to 1216 rows.  Scores of the same sequences, each chunked differently."""
     s = synth.ModelShape(f"small{hd}", 2, 512, 512 // hd, 512 // hd // 2, hd, 1024, 1024, 10000.0, "bf16", 0.05)
