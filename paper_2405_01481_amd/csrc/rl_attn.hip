@@ -554,6 +554,15 @@ __global__ __launch_bounds__(AP_NW * 64, HD == 64 ? 3 : 2) void attn_prefill_ker
                     const int key = (ks * TS + t) * 32 + 16 * (r >> 3) + 8 * g2 + (r & 7);
                     if (key > qi) stt[t][r] = -INFINITY;
                 }
+            // A tile wholly behind the query block has no weight, whatever its values are: 0 times an infinity is not 0
+            if constexpr (!SP) {
+#pragma unroll
+                for (int t = 1; t < TS; ++t)
+                    if (ks * TS + t > qb) {
+#pragma unroll
+                        for (int d = 0; d < DB; ++d) vf[t][d][0] = vf[t][d][1] = half8{};
+                    }
+            }
         }
         float mx = stt[0][0];
 #pragma unroll
