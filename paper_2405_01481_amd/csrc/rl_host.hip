@@ -1526,12 +1526,18 @@ static int score_pass(rl_ctx* c, const WeightsHost& W, const int32_t* ids, const
 // leave the last round of 256 tiles, or most CUs, idle, and short kernels wait for one another.  Each row is computed as it
 // is alone.  One pass against two: 1B shape 2240 rows (8 sequences of 70 to 512 tokens) 11.69 -> 9.83 ms, 8B shape (exact KL,
 // heads included) 5300 rows 27.4 -> 27.0; at 16384 rows there is nothing left to fill.  The rows for it cost a small
-// context up to twice the workspace (8B shape, 8 sequences of 1024: 1.5 GB more).  Taken where both fit -- unless the rows
-// are enough for weights without an fp16 copy to be converted ahead of their GEMMs, whose idle workspace has room for one
-// model's at a time.
+// context up to twice the workspace (8B shape, 8 sequences of 1024: 1.5 GB more).  Taken where both fit, and
+//   * with copies of both models always;
+//   * with none unless the rows are enough for weights to be converted ahead of their GEMMs, whose idle workspace has room
+//     for one model's at a time;
+//   * with one copy, which a joint GEMM does not read, as long as one model's residual GEMM is at most half a round of 256 x 256
+//     tiles, so that the other half pays for it.  One pass against two, one copy: 8B width 1536 rows 0.97, 2048 0.97,
+//     3072 1.02, 4064 1.01; 70B width 512 rows 0.93, 1024 0.98, 1536 1.06, 3072 1.02; 1B width 3072 rows 0.95, 4064 0.89.
 static bool both_fit(const rl_ctx* c, const Chunk& ch, const WeightsHost& W1, const WeightsHost& W2) {
     if (c->impl != 1 || 2 * ch.n > c->L.pair_rows) return false;
-    return ch.n < kConvertRows || (g_large_gemm_copy && fp16_copy_of(c, W1.wqkv[0]) && fp16_copy_of(c, W2.wqkv[0]));
+    const bool copy1 = g_large_gemm_copy && fp16_copy_of(c, W1.wqkv[0]), copy2 = g_large_gemm_copy && fp16_copy_of(c, W2.wqkv[0]);
+    if (copy1 && copy2) return true;
+    return ch.n < kConvertRows && (copy1 == copy2 || (int64_t)ch.n * c->cfg.d_model <= 128 * 256 * 256);
 }
 
 // The chunk with its sequences listed once more behind it.

@@ -57,3 +57,30 @@ def test_one_pass_gives_the_bits_of_two(impl, copies):
         assert np.abs(got[0] - got[1]).max() > 0.1 and np.abs(got[4]).max() > 0
     whole = _run(impl, copies, 10016, more, np.ones(len(more), np.int32), L, wp, wr, False)
     assert all(np.array_equal(whole[i], apart[i]) for i in (0, 1))
+
+
+@pytest.mark.parametrize("copies,rows,passes", [((True, False), 2048, 1), ((True, False), 2176, 2), ((False, True), 2176, 2),
+                                               ((False, False), 2176, 1), ((True, True), 2176, 1)])
+def test_one_copy_joins_only_small_passes(copies, rows, passes):
+    """Width 4096: with a copy of one model of two, 2048 rows are the most that run as one pass (its GEMMs read no copy).
+    Counted in GEMM launches, four per layer and pass; the results are those of the models alone."""
+    s = synth.ModelShape("wide", 1, 4096, 2, 1, 64, 256, 256, 10000.0, "bf16", 0.02)
+    L = rows // 4
+    cfg = R.make_cfg(s, 4, L)
+    W = [R.Weights(synth.make_weights(s, i + 1, DEV),
+                   shadow=torch.empty(R.rollout_weight_shadow_bytes(cfg), dtype=torch.uint8, device=DEV) if on else None)
+         for i, on in enumerate(copies)]
+    ro = R.Rollout(cfg, W[0], DEV)
+    ids = torch.tensor(np.random.default_rng(1).integers(0, s.vocab, size=(4, L)).astype(np.int32), device=DEV)
+    lens, plens = np.full(4, L, np.int32), np.ones(4, np.int32)
+    alone = [torch.zeros(4, L, device=DEV) for _ in W]
+    for w, o in zip(W, alone):
+        ro.score_logprobs_kl(w, None, ids, lens, plens, 0.0, o)
+    both = [torch.zeros(4, L, device=DEV) for _ in W]
+    ro.rollout_profile_enable(R.RL_K_GEMM_PREFILL, 1)
+    ro.score_logprobs_kl(*W, ids, lens, plens, 0.0, *both)
+    launches = ro.rollout_profile_read(R.RL_K_GEMM_PREFILL)[1]
+    ro.rollout_check()
+    ro.close()
+    assert launches == 4 * passes
+    assert all(torch.equal(a, b) for a, b in zip(alone, both))
