@@ -757,11 +757,18 @@ __device__ __forceinline__ void patch_get(float (&v)[N], const float* patch, int
         for (int y = 0; y < 4; ++y) v[4 * x + y] = t[y];
     }
 }
-__device__ __forceinline__ float max_of(const float (&v)[16]) {
-    float m = v[0];
+// Maximum and sum of a lane's 16 values, columns c .. c + 7 and c + 32 .. c + 39 of a wave's 64 where its quad holds the
+// others (c = 0, 8, 16, 24).  The sum pairs the columns 32 apart, then 1, 2 and 4 apart (quad_sum goes on with 8 and 16): a
+// term is rounded at six additions, one after the other it would be at up to 17, and the exact KL is a small difference of
+// such sums (error against 64 bits 0.5 to 16 % larger, V = 131072 to 256).
+__device__ __forceinline__ float max_of(const float (&v0)[8], const float (&v1)[8]) {
+    float m = v0[0];
 #pragma unroll
-    for (int x = 1; x < 16; ++x) m = fmaxf(m, v[x]);
+    for (int x = 0; x < 8; ++x) m = fmaxf(m, fmaxf(v0[x], v1[x]));
     return m;
+}
+__device__ __forceinline__ float sum_of(const float (&v)[8]) {
+    return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
 }
 // over the four lanes of a quad, every lane with the same bits
 __device__ __forceinline__ float quad_max(float v) {
@@ -959,13 +966,10 @@ __device__ __forceinline__ void d8_half(const floatx4_t (&acc)[MI][4], float* pa
             float z0[8], z1[8], e[8];
             patch_get(z0, patch, it * 16 + row, c);
             patch_get(z1, patch, it * 16 + row, 32 + c);
-            float mx = z0[0];
-#pragma unroll
-            for (int x = 0; x < 8; ++x) mx = fmaxf(mx, fmaxf(z0[x], z1[x]));
-            mx = quad_max(mx);
+            const float mx = quad_max(max_of(z0, z1));
 #pragma unroll
             for (int x = 0; x < 8; ++x) e[x] = __expf(z0[x] - mx) + __expf(z1[x] - mx);
-            const float se = quad_sum(((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7])));
+            const float se = quad_sum(sum_of(e));
             if ((lane & 3) == 0 && m < a.M) {
                 a.lse_part[(int64_t)m * nparts + nb * 4 + wn] = make_float2(mx, se);
                 const int d = tg[it] - n0;
@@ -999,35 +1003,39 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
 // Exact-KL epilogue of a wave's 64 rows x 64 columns: per row five numbers leave the kernel,
 //   m_p = max z_p, S_p = sum exp(z_p - m_p), T = sum exp(z_p - m_p) (z_p - z_r), m_r = max z_r, S_r = sum exp(z_r - m_r)
 // from which  KL(pi_p || pi_r) = T/S_p - (m_p + log S_p) + (m_r + log S_r)  once all column groups are combined.  Four
-// lanes share a row, 16 columns each; the reference's logits wait in registers while the policy's take the patch.
+// lanes share a row as in the log-sum-exp epilogue; the reference's logits wait in registers while the policy's take the
+// patch.
 __device__ __forceinline__ void kl_epilogue(const floatx4_t (&acc_p)[4][4], const floatx4_t (&acc_r)[4][4], float* patch,
                                             const GemmArgs& a, int m0, int group, int lane) {
-    const int row = lane >> 2, c = (lane & 3) * 16;
-    float zr[4][16];
+    const int row = lane >> 2, c = (lane & 3) * 8;
+    float r0[4][8], r1[4][8];
     patch_put<4, 0>(acc_r, patch, lane);
 #pragma unroll
-    for (int it = 0; it < 4; ++it) patch_get(zr[it], patch, it * 16 + row, c);
+    for (int it = 0; it < 4; ++it) {
+        patch_get(r0[it], patch, it * 16 + row, c);
+        patch_get(r1[it], patch, it * 16 + row, 32 + c);
+    }
     __builtin_amdgcn_wave_barrier();
     patch_put<4, 0>(acc_p, patch, lane);
     const int nparts = a.N / 64;
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-        float zp[16];
-        patch_get(zp, patch, it * 16 + row, c);
-        const float mp = quad_max(max_of(zp)), mr = quad_max(max_of(zr[it]));
-        float sp = 0.f, st = 0.f, sr = 0.f;
+        float p0[8], p1[8], sp[8], st[8], sr[8];
+        patch_get(p0, patch, it * 16 + row, c);
+        patch_get(p1, patch, it * 16 + row, 32 + c);
+        const float mp = quad_max(max_of(p0, p1)), mr = quad_max(max_of(r0[it], r1[it]));
 #pragma unroll
-        for (int x = 0; x < 16; ++x) {
-            const float e = __expf(zp[x] - mp);
-            sp += e;
-            st += e * (zp[x] - zr[it][x]);
-            sr += __expf(zr[it][x] - mr);
+        for (int x = 0; x < 8; ++x) {
+            const float e0 = __expf(p0[x] - mp), e1 = __expf(p1[x] - mp);
+            sp[x] = e0 + e1;
+            st[x] = e0 * (p0[x] - r0[it][x]) + e1 * (p1[x] - r1[it][x]);
+            sr[x] = __expf(r0[it][x] - mr) + __expf(r1[it][x] - mr);
         }
-        sp = quad_sum(sp); st = quad_sum(st); sr = quad_sum(sr);
+        const float s_p = quad_sum(sum_of(sp)), t = quad_sum(sum_of(st)), s_r = quad_sum(sum_of(sr));
         const int m = m0 + it * 16 + row;
         if ((lane & 3) == 0 && m < a.M) {
             float* o = a.kl_part + ((int64_t)m * nparts + group) * 5;
-            o[0] = mp; o[1] = sp; o[2] = st; o[3] = mr; o[4] = sr;
+            o[0] = mp; o[1] = s_p; o[2] = t; o[3] = mr; o[4] = s_r;
         }
     }
 }

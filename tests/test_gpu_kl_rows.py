@@ -50,3 +50,30 @@ def test_exact_kl_rows(shape, copies, tol):
     with pytest.raises(R.RolloutError):
         ro.rollout_check()
     ro.close()
+
+
+def test_exact_kl_sums_keep_their_small_terms():
+    """Every 64 columns: one logit of 0, the others -16.75 (policy) or -40 (reference), all exact (unit hidden state, weights on
+    a grid).  The 63 small terms of e^-16.75 = 0.89 x 2^-24 vanish one by one in a sum that starts from the large one, 15 of
+    them in a lane that adds its 16 columns in turn: 8e-7 of the KL of 7.4e-5.  Added pairwise, the large term is rounded
+    at six levels, 2^-24 each; the two logarithms round once each (of about 0.7), and the reduction over two groups adds two
+    roundings: 6e-7 in all."""
+    s = synth.ModelShape("klsum", 1, 256, 4, 2, 64, 256, 128, 10000.0, "bf16", 0.02, rms_eps=0.0)
+    W = []
+    for k, small in enumerate((-16.75, -40.0)):
+        w = synth.make_weights(s, k + 1, DEV)
+        w["tok_embed"].fill_(1.0)
+        w["final_norm"].fill_(1.0)
+        for l in ("wo", "w_down"):
+            w["layers"][0][l].zero_()
+        w["lm_head"].fill_(small / 256)
+        w["lm_head"][::64] = 0.0
+        W.append(R.Weights(w))
+    ro = R.Rollout(R.make_cfg(s, 1, 8), W[0], DEV)
+    kl = torch.zeros(1, 8, device=DEV)
+    ro.score_kl_exact(*W, torch.zeros(1, 8, dtype=torch.int32, device=DEV), np.array([8], np.int32), np.array([1], np.int32), kl)
+    ro.rollout_check()
+    ro.close()
+    a, b = 63 * np.exp(-16.75), 63 * np.exp(-40.0)
+    want = (a * (40.0 - 16.75)) / (1 + a) - np.log1p(a) + np.log1p(b)
+    assert np.abs(kl[0, 1:].cpu().numpy() - want).max() < 6e-7
