@@ -118,6 +118,11 @@ typedef struct rl_sample_cfg {
 /* Bytes the caller must provide as `workspace` / `kv_pool` for this configuration
  * (0 if cfg is NULL or invalid). */
 size_t rollout_workspace_bytes(const rl_model_cfg* cfg);
+/* Bytes of a `workspace` in which score_logprobs_kl and score_kl_exact run policy and reference, both device-resident, as
+ * one pass (chunks of up to 8192 tokens; same results bit for bit, 1 to 40 % faster): holds twice max_chunk_tokens rows
+ * where those are at most 16384 (with a longer max_chunk_tokens, as many as it is).  Between the two sizes the smaller one
+ * counts. */
+size_t rollout_scoring_workspace_bytes(const rl_model_cfg* cfg);
 size_t rollout_kv_pool_bytes(const rl_model_cfg* cfg);
 /* Bytes of the optional fp16 copy of a device-resident bf16 policy (rl_weights.fp16_copy of the policy): the
  * per-layer matrices and the LM head, i.e. about the size of the policy; 0 for fp32 configurations. */
@@ -131,7 +136,7 @@ size_t rollout_weight_staging_bytes(const rl_model_cfg* cfg);
 
 /* Create a context that generates with `policy` (Section 3.2: the engine keeps
  * weights, KV cache and activations resident).  workspace and kv_pool are dev
- * buffers of at least the sizes above, 256-byte aligned; their contents are
+ * buffers of at least rollout_workspace_bytes and rollout_kv_pool_bytes, 256-byte aligned; their contents are
  * scratch owned by the context until rollout_destroy.  Blocks until the
  * context's tables are initialised.  Errors: RL_EINVAL (NULL, n_q_heads %
  * n_kv_heads != 0, head_dim not 64/128, d_model or d_ffn not a multiple of 64,

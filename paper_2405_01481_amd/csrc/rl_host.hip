@@ -39,13 +39,13 @@ struct Layout {
     size_t out_row, seq_id, gen_limit;   // queue mode: per-slot output row, sequence id, token limit
     size_t splitk, attn_part, attn_ml, lse_part, z_tgt, blocks;
     size_t total;
-    int rows, pair_rows, logit_rows, mpps, nqkv, vt_cap, max_blocks;
+    int rows, pair_rows, max_seqs, logit_rows, mpps, nqkv, vt_cap, max_blocks;
 };
 
 static size_t esz_of(int dtype) { return dtype == RL_FP32 ? 4 : 2; }
 
 static const int kLogitRowsScore = 512;    // rows of logits materialised at a time by the plain scoring path
-static const int kTwoModelRows = 16384;     // rows up to which a workspace is made for two models' passes at once
+static const int kTwoModelRows = 16384;     // rows up to which a scoring workspace is made for two models' passes at once
 static const int kMaxSplitK = 16;
 static const int kMaxAttnSplits = 16;
 // bf16 configurations: the first layers can carry their activations (GEMM inputs, q, k, v, softmax
@@ -59,7 +59,12 @@ static const int kMaxPreciseLayers = 2;
 static const int kDefaultPreciseLayers = 1;
 static int precise_cap(const rl_model_cfg& c) { return c.dtype == RL_BF16 ? std::min(kMaxPreciseLayers, c.n_layers) : 0; }
 
-static Layout make_layout(const rl_model_cfg& c) {
+static bool fast_path_supported(const rl_model_cfg& m);
+
+// two_models: with room for passes over two models' chunks at once (see both_fit), up to kTwoModelRows rows; the same where
+// the tuned path does not run.
+static Layout make_layout(const rl_model_cfg& c, bool two_models = false) {
+    two_models = two_models && fast_path_supported(c);
     Layout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -70,9 +75,10 @@ static Layout make_layout(const rl_model_cfg& c) {
     const size_t e = esz_of(c.dtype);
     const size_t pw = precise_cap(c) > 0 ? 2 : 1;   // activation rows hold fp16 pairs in the precise layers
     // token rows of one pass; sequences are packed at multiples of 32 rows on the tuned path
-    // (up to kTwoModelRows also those of two models' chunks at once: see both_fit)
-    L.pair_rows = c.dtype == RL_BF16 ? std::max(c.max_chunk_tokens, std::min(2 * ((c.max_chunk_tokens + 31) / 32 * 32), kTwoModelRows)) : 0;
-    const int rows = (std::max(std::max(c.max_chunk_tokens, L.pair_rows), c.max_batch) + 31) / 32 * 32 + 32;
+    L.pair_rows = c.max_chunk_tokens;
+    if (two_models) L.pair_rows = std::max(L.pair_rows, std::min(2 * ((c.max_chunk_tokens + 31) / 32 * 32), kTwoModelRows));
+    L.max_seqs = two_models ? 2 * c.max_batch : c.max_batch;     // a chunk that carries two models lists its sequences twice
+    const int rows = (std::max(L.pair_rows, c.max_batch) + 31) / 32 * 32 + 32;
     const int nqkv = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
     const int qd = c.n_q_heads * c.head_dim, kd = c.n_kv_heads * c.head_dim;
     L.rows = rows;
@@ -102,11 +108,10 @@ static Layout make_layout(const rl_model_cfg& c) {
     L.tok_pos = take((size_t)rows * 4);
     L.tok_slot = take((size_t)rows * 4);
     L.tok_tgt = take((size_t)rows * 4);
-    // (a chunk that carries two models lists its sequences twice)
-    L.seq_first = take((size_t)2 * c.max_batch * 4);
-    L.row_start = take((size_t)2 * c.max_batch * 4);
-    L.row_len = take((size_t)2 * c.max_batch * 4);
-    L.row_slot = take((size_t)2 * c.max_batch * 4);
+    L.seq_first = take((size_t)L.max_seqs * 4);
+    L.row_start = take((size_t)L.max_seqs * 4);
+    L.row_len = take((size_t)L.max_seqs * 4);
+    L.row_slot = take((size_t)L.max_seqs * 4);
     L.out_row = take((size_t)c.max_batch * 4);
     L.seq_id = take((size_t)c.max_batch * 4);
     L.gen_limit = take((size_t)c.max_batch * 4);
@@ -120,7 +125,7 @@ static Layout make_layout(const rl_model_cfg& c) {
     L.attn_ml = take((size_t)c.max_batch * c.n_q_heads * kMaxAttnSplits * 2 * 4);
     L.lse_part = take((size_t)rows * ((c.vocab + 63) / 64) * sizeof(float2));
     L.z_tgt = take((size_t)rows * 4);
-    L.max_blocks = rows / 32 + 2 * c.max_batch;
+    L.max_blocks = rows / 32 + L.max_seqs;
     L.blocks = take((size_t)L.max_blocks * sizeof(int4));
     L.total = off;
     return L;
@@ -841,6 +846,11 @@ size_t rollout_workspace_bytes(const rl_model_cfg* cfg) {
     return make_layout(*cfg).total;
 }
 
+size_t rollout_scoring_workspace_bytes(const rl_model_cfg* cfg) {
+    if (validate_cfg(cfg) != RL_OK) return 0;
+    return std::max(make_layout(*cfg).total, make_layout(*cfg, true).total);
+}
+
 size_t rollout_weight_shadow_bytes(const rl_model_cfg* cfg) {
     if (validate_cfg(cfg) != RL_OK) return 0;
     return shadow_bytes_of(*cfg);
@@ -867,7 +877,8 @@ int rollout_init(const rl_model_cfg* cfg, const rl_weights* policy, void* worksp
     if (!workspace || !kv_pool) return fail(RL_EINVAL, "workspace / kv_pool is NULL");
     if (((uintptr_t)workspace & 255) || ((uintptr_t)kv_pool & 255))
         return fail(RL_EINVAL, "workspace / kv_pool must be 256-byte aligned");
-    Layout L = make_layout(*cfg);
+    Layout L = make_layout(*cfg, true);
+    if (workspace_bytes < L.total) L = make_layout(*cfg);
     if (workspace_bytes < L.total)
         return fail(RL_ENOSPACE, "workspace too small: %zu < %zu bytes", workspace_bytes, L.total);
     if (kv_pool_bytes < rollout_kv_pool_bytes(cfg))
@@ -1525,8 +1536,9 @@ static int score_pass(rl_ctx* c, const WeightsHost& W, const int32_t* ids, const
 // Two models' passes over a chunk of n rows as one pass over 2 n rows, the chunk's sequences listed twice: GEMMs of n rows
 // leave the last round of 256 tiles, or most CUs, idle, and short kernels wait for one another.  Each row is computed as it
 // is alone.  One pass against two: 1B shape 2240 rows (8 sequences of 70 to 512 tokens) 11.69 -> 9.83 ms, 8B shape (exact KL,
-// heads included) 5300 rows 27.4 -> 27.0; at 16384 rows there is nothing left to fill.  The rows for it cost a small
-// context up to twice the workspace (8B shape, 8 sequences of 1024: 1.5 GB more).  Taken where both fit, and
+// heads included) 5300 rows 27.4 -> 27.0; at 16384 rows there is nothing left to fill.  The rows for it are in the workspace if
+// the caller gave rollout_scoring_workspace_bytes (up to twice the smaller size; 8B shape, 8 sequences of 1000: 1.4 GB
+// more).  Taken where both fit, and
 //   * with copies of both models always;
 //   * with none unless the rows are enough for weights to be converted ahead of their GEMMs, whose idle workspace has room
 //     for one model's at a time;
@@ -1534,7 +1546,7 @@ static int score_pass(rl_ctx* c, const WeightsHost& W, const int32_t* ids, const
 //     tiles, so that the other half pays for it.  One pass against two, one copy: 8B width 1536 rows 0.97, 2048 0.97,
 //     3072 1.02, 4064 1.01; 70B width 512 rows 0.93, 1024 0.98, 1536 1.06, 3072 1.02; 1B width 3072 rows 0.95, 4064 0.89.
 static bool both_fit(const rl_ctx* c, const Chunk& ch, const WeightsHost& W1, const WeightsHost& W2) {
-    if (c->impl != 1 || 2 * ch.n > c->L.pair_rows) return false;
+    if (c->impl != 1 || 2 * ch.n > c->L.pair_rows || 2 * (int)ch.lens.size() > c->L.max_seqs) return false;
     const bool copy1 = g_large_gemm_copy && fp16_copy_of(c, W1.wqkv[0]), copy2 = g_large_gemm_copy && fp16_copy_of(c, W2.wqkv[0]);
     if (copy1 && copy2) return true;
     return ch.n < kConvertRows && (copy1 == copy2 || (int64_t)ch.n * c->cfg.d_model <= 128 * 256 * 256);

@@ -50,6 +50,21 @@ def test_sizes_and_cfg_validation():
     assert R.lib().rollout_weight_staging_bytes(None) == 0
 
 
+@pytest.mark.parametrize("shape,batch,max_seq,need,scoring", [
+    (synth.TINY, 4, 64, 15380992, 15380992), (synth.L1B, 8, 512, 463590656, 832380416),
+    (synth.L8B, 8, 1000, 1760545280, 3199685376), (synth.L8B, 128, 1024, 3300761344, 3300765440),
+    (synth.L70B, 2, 4096, 3041837312, 5723476224)])
+def test_workspace_sizes(shape, batch, max_seq, need, scoring):
+    """What a context needs holds max_chunk_tokens rows; a caller's buffer of that size stays large enough.  Room for two
+    models' rows is a size of its own."""
+    cfg = R.make_cfg(shape, batch, max_seq)
+    assert (R.rollout_workspace_bytes(cfg), R.rollout_scoring_workspace_bytes(cfg)) == (need, scoring)
+    # a shape that the tuned path does not run has nothing to gain
+    odd = R.make_cfg(synth.ModelShape("odd", 2, 192, 3, 1, 64, 320, 333, 1e4, "bf16", 0.02), batch, max_seq)
+    assert R.rollout_scoring_workspace_bytes(odd) == R.rollout_workspace_bytes(odd) > 0
+    assert R.lib().rollout_scoring_workspace_bytes(None) == 0
+
+
 def test_null_and_state_errors_without_gpu():
     lib = R.lib()
     h = C.c_void_p()

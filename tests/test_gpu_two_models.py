@@ -84,3 +84,35 @@ def test_one_copy_joins_only_small_passes(copies, rows, passes):
     ro.close()
     assert launches == 4 * passes
     assert all(torch.equal(a, b) for a, b in zip(alone, both))
+
+
+@pytest.mark.parametrize("two_models,max_batch,passes", [(True, 7, 1), (False, 7, 2), (False, 14, 1)])
+def test_workspace_of_either_size(two_models, max_batch, passes):
+    """The smaller workspace serves every call: two models run one after the other in it, or as one pass where the chunk is
+    small enough and half of max_batch lists its sequences (704 rows of 1408, 7 sequences).  One byte less is refused."""
+    lens = np.array([1, 33, 64, 150, 200, 97, 31], np.int32)
+    plens = np.array([1, 10, 64, 1, 100, 96, 1], np.int32)
+    B, L = len(lens), int(lens.max())
+    cfg = R.make_cfg(SHAPE, max_batch, L, max_chunk_tokens=704 if max_batch == 7 else 1408)
+    need, scoring = R.rollout_workspace_bytes(cfg), R.rollout_scoring_workspace_bytes(cfg)
+    assert need < scoring
+    wp, wr = synth.make_weights(SHAPE, 1, DEV), synth.make_weights(SHAPE, 2, DEV)
+    Wp, Wr = R.Weights(wp), R.Weights(wr)
+    h = R.C.c_void_p()
+    kv = torch.empty(R.rollout_kv_pool_bytes(cfg), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    assert R.lib().rollout_init(R.C.byref(cfg), R.C.byref(Wp.struct), R._ptr(ws), need - 1, R._ptr(kv), kv.numel(),
+                                R.C.byref(h)) == R.RL_ENOSPACE
+    ro = R.Rollout(cfg, Wp, DEV, two_models=two_models)
+    assert ro.workspace.numel() == (scoring if two_models else need)
+    ids = torch.tensor(_ids(B, L), device=DEV)
+    outs = [torch.full((B, L), 9.0, device=DEV) for _ in range(5)]
+    ro.rollout_profile_enable(R.RL_K_GEMM_PREFILL, 1)
+    ro.score_logprobs_kl(Wp, Wr, ids, lens, plens, 0.003, *outs[:4])
+    assert ro.rollout_profile_read(R.RL_K_GEMM_PREFILL)[1] == 4 * SHAPE.n_layers * passes
+    ro.score_kl_exact(Wp, Wr, ids, lens, plens, outs[4])
+    ro.rollout_check()
+    ro.close()
+    want = _run(1, (False, False), 1024, lens, plens, L, wp, wr, True)
+    for i in (0, 1, 4):
+        assert np.array_equal(outs[i].cpu().numpy(), want[i])
