@@ -44,7 +44,7 @@ def test_one_pass_gives_the_bits_of_two(impl, copies):
     """One chunk of both models; several of them; and, for comparison, the same sequences at the head of a chunk of more than
     8192 rows, which the workspace does not hold twice and which is run for one model after the other (with a last chunk
     behind it that is again run for both together)."""
-    lens = np.array([1, 33, 64, 150, 200, 97, 31], np.int32)               # 672 rows with their padding
+    lens = np.array([1, 33, 64, 150, 200, 97, 31], np.int32)               # 704 rows with their padding
     plens = np.array([1, 10, 64, 1, 100, 96, 1], np.int32)                 # one prompt without a response
     more = np.concatenate([lens, np.random.default_rng(11).integers(150, 201, size=53).astype(np.int32)])
     wp, wr = synth.make_weights(SHAPE, 1, DEV), synth.make_weights(SHAPE, 2, DEV)
@@ -57,6 +57,24 @@ def test_one_pass_gives_the_bits_of_two(impl, copies):
         assert np.abs(got[0] - got[1]).max() > 0.1 and np.abs(got[4]).max() > 0
     whole = _run(impl, copies, 10016, more, np.ones(len(more), np.int32), L, wp, wr, False)
     assert all(np.array_equal(whole[i], apart[i]) for i in (0, 1))
+
+
+@pytest.mark.parametrize("copies", [(False, False), (True, False), (False, True), (True, True)], ids=["none", "policy", "reference", "both"])
+@pytest.mark.parametrize("impl", [1, 2], ids=["by-size", "large-m"])
+def test_weights_converted_for_both_models(impl, copies):
+    """Chunks of 2048 to 4095 rows per model: the pair layer's GEMMs count twice as long and have the weight sets that bring no
+    copy converted into idle workspace, both or one of them, behind one another.  Against one model at a time."""
+    r = np.random.default_rng(17)
+    lens = r.integers(150, 201, size=50).astype(np.int32)
+    plens = np.maximum(1, lens // 2).astype(np.int32)
+    rows = (lens + 31) // 32 * 32
+    assert 4096 < rows.sum() < 16384 and rows.max() <= 224          # chunks of 3500: two full ones and more than 2048 rows behind
+    L = int(lens.max())
+    wp, wr = synth.make_weights(SHAPE, 1, DEV), synth.make_weights(SHAPE, 2, DEV)
+    alone = _run(impl, copies, 10016, lens, plens, L, wp, wr, True)
+    both = _run(impl, copies, 3500, lens, plens, L, wp, wr, False)
+    for i in (0, 1, 4):
+        assert np.isfinite(both[i]).all() and np.array_equal(both[i], alone[i]), i
 
 
 @pytest.mark.parametrize("copies,rows,passes", [((True, False), 2048, 1), ((True, False), 2176, 2), ((False, True), 2176, 2),
