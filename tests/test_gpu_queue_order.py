@@ -40,3 +40,23 @@ def test_rows_do_not_depend_on_the_order(shape, limits):
             assert np.array_equal(l, got[0][1])
         else:
             assert np.abs(l - got[0][1]).max() < 1e-5
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
+@pytest.mark.parametrize("pages,steps", [(8, 64), (6, 96)], ids=["longest-first", "as-they-come"])
+def test_decode_steps_of_either_order(shape, pages, steps):
+    """Limits 40, six times 3, 40 on two slots, steps in bursts of eight, counted in attention launches.  Longest first: both
+    long rows (five bursts), then the short ones two at a time as soon as a slot is free (three bursts).  As they come, refilled
+    when both slots are free: 40 steps for rows 0 and 1, 8 for 2 and 3, 8 for 4 and 5, 40 for 6 and 7."""
+    lim = np.array([40, 3, 3, 3, 3, 3, 3, 40], np.int32)
+    Q, P = len(lim), 17
+    ro = R.Rollout(R.make_cfg(shape, 2, 64, n_pages=pages), R.Weights(synth.make_weights(shape, 1, DEV)), DEV)
+    ids = torch.tensor(np.random.default_rng(5).integers(0, shape.vocab, size=(Q, P)).astype(np.int32), device=DEV)
+    out, n = torch.zeros(Q, 40, dtype=torch.int32, device=DEV), torch.zeros(Q, dtype=torch.int32, device=DEV)
+    ro.rollout_profile_enable(R.RL_K_ATTN_DECODE, 1)
+    ro.rollout_generate_queue(R.sample_cfg(3, 1.0), ids, np.full(Q, P, np.int32), lim, 40, out, n)
+    launches = ro.rollout_profile_read(R.RL_K_ATTN_DECODE)[1]
+    ro.rollout_check()
+    ro.close()
+    assert np.array_equal(n.cpu().numpy(), lim)
+    assert launches == steps * shape.n_layers
