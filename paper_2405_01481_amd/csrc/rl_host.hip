@@ -1870,13 +1870,11 @@ int score_kl_exact(rl_ctx* c, const rl_weights* policy, const rl_weights* refere
                 both ? wr.tok_embed : nullptr, n);
         if (nh == 0) continue;                                   // nothing to score; the ids have been looked at
         // The same rows are all that is asked of the last layer behind its attention (half of the rows: 8B shape, 4 layers,
-        // 8 sequences of 300 to 1024 tokens 26.6 -> 25.1 ms).  They go where the heads' results will be, if that is large enough.
+        // 8 sequences of 300 to 1024 tokens 26.6 -> 25.1 ms).  They go into the logits' buffer, if it is large enough.
         KeepRows keep{rows, both ? 2 * nh : nh, nullptr};
-        const size_t kb = (size_t)keep.n * m.d_model * 4;
-        if (c->impl == 1 && (int64_t)keep.n * 10 <= (int64_t)run.n * 9) {
-            if (kb <= (size_t)L.logit_rows * m.vocab * 4) keep.x = c->at<float>(L.logits);
-            else if (kb <= (size_t)L.rows * ((m.vocab + 63) / 64) * sizeof(float2)) keep.x = c->at<float>(L.lse_part);
-        }
+        if (c->impl == 1 && (int64_t)keep.n * 10 <= (int64_t)run.n * 9 &&
+            (size_t)keep.n * m.d_model <= (size_t)L.logit_rows * m.vocab)
+            keep.x = c->at<float>(L.logits);
         const KeepRows* const kp = keep.x ? &keep : nullptr;
         float* const xr = kp ? keep.x : x;                       // final norms: of compacted rows, or of listed ones
         const int* const xrows = kp ? nullptr : rows;
