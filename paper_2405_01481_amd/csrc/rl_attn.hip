@@ -21,10 +21,10 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 #define LOG2E 1.4426950408889634f
 
-// 2^x as the hardware instruction alone.  The library's exp2f wraps it in a rescaling for results in the denormal
-// range (six instructions per value); softmax weights that small are zero for every purpose here.  2^-inf = 0.
 // s_waitcnt operand: at most vm vector loads outstanding
 constexpr int vm_only(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (15 << 8); }
+// 2^x as the hardware instruction alone.  The library's exp2f wraps it in a rescaling for results in the denormal
+// range (six instructions per value); softmax weights that small are zero for every purpose here.  2^-inf = 0.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // ------------------------------------------------------------------ decode: one new query per sequence
@@ -387,8 +387,9 @@ void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStr
 // What bounds it is a wave's own chain of scores -> maximum -> exponentials -> products, and for short sequences what a
 // workgroup costs before and after its loop.  Hence steps of 64 keys (two independent chains of score MFMAs; one maximum,
 // one cross-lane exchange, one rescaling per 64 keys), V^T fragments read before the softmax, two independent workgroups
-// per CU, one's start and end behind the other's loop, and an output that leaves as whole lines.  A kv head's
-// workgroups stay on one XCD (ids go round-robin to the eight, each with its own L2).
+// per CU, one's start and end behind the other's loop, and an output that leaves as whole lines.  Where
+// kv heads (times two for groups of more than four) are a multiple of eight, a kv head's workgroups stay on one XCD (ids go
+// round-robin to the eight, each with its own L2).
 // 16 x 1024 tokens of the 8B shape 257 -> 205 us (0.67 PFLOP/s; MFMAs busy a third of the time), 5 sequences of 1500 to 4096
 // tokens of the 70B shape 1065 -> 690 us (1.0 PFLOP/s), 8 of 70 to 512 of the 1B shape 21.9 -> 13.7, against steps of 32 keys
 // with a wait for the next tile in each and 16-byte output stores.  Eight waves per workgroup: 239, 747, 24.2; steps of 32
@@ -617,6 +618,7 @@ __global__ __launch_bounds__(AP_NW * 64, HD == 64 ? 3 : 2) void attn_prefill_ker
     __syncthreads();                                   // every wave is done with the stages
     // The output leaves as whole rows of a head: through this wave's own LDS patch ([32 queries][hd], rows padded by 16
     // bytes), 16 bytes per lane.  (Straight from the registers it is 16 bytes of a row per store: eight times the requests.)
+    // The writes into the patch are the kernel's only LDS bank conflicts: counted 96 cycles per wave, at any length.
     l_run += __shfl_xor(l_run, 32, RL_WAVE);
     const float inv = qb < nqb ? 1.0f / l_run : 0.f;
     constexpr int LD = HD + 8, RPI = 512 / HD;         // rows per store instruction
@@ -649,7 +651,7 @@ __global__ __launch_bounds__(AP_NW * 64, HD == 64 ? 3 : 2) void attn_prefill_ker
     }
 }
 
-// 32-query blocks per workgroup: as many as give its eight waves work, one per query head of the group and query block.
+// 32-query blocks per workgroup: as many as give its four waves work, one per query head and query block.
 int k_attn_prefill_blocks(int Hq, int Hkv) { return AP_NW / ap_heads(Hq / Hkv); }
 
 template <int HD, bool SP>

@@ -304,8 +304,7 @@ __device__ __forceinline__ void mg_epilogue(floatx16 (&acc)[TN], const GemmArgs&
         return;
     }
     if constexpr (EPI == MG_SWIGLU) {
-        // A band that lies wholly inside the matrix (the rule on the large-M path) and leaves as plain fp16: no
-        // per-element bounds checks or branches, one row pointer per register row.  Same values as the general path.
+        // A band that lies wholly inside the matrix and leaves as plain fp16: no per-element bounds checks or branches, one row pointer per register row.  Same values as the general path.
         const int n_first = nb * (BN / 2) + wn * TN * 16;      // of this wave's TN * 16 output columns
         if (m_base + 2 * NR <= a.M && n_first + TN * 16 <= a.N && !a.split_out) {   // wave-uniform
             f16_t* o = a.outH + (int64_t)(m_base + 4 * lg) * a.ldc + n_first + lrow;
@@ -548,6 +547,30 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a) {
     if (TM > 1) mg_epilogue<EPI, BN, TN, WGN>(acc[TM > 1 ? 1 : 0], a, m0 + wm * TM * 32 + 32, nb, wn, ks, lane);
 }
 
+// Row metadata of the MG_QKV epilogue held across a wave: lane l keeps position and cache page of rows row0 + l and
+// row0 + 64 + l (fetched before the main loop, so that the epilogue starts without a chain of dependent loads).
+struct QkvRowMeta {
+    int pos[2] = {-1, -1};    // < 0: padding row / past M
+    int page[2] = {0, 0};
+};
+__device__ __forceinline__ QkvRowMeta qkv_row_meta(const GemmArgs& a, int row0, int lane) {
+    QkvRowMeta q;
+    int slot[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int m = row0 + h * 64 + lane;
+        const int p_ = a.tok_pos[min(m, a.M - 1)];
+        slot[h] = a.pool ? a.tok_slot[min(m, a.M - 1)] : 0;
+        q.pos[h] = m < a.M ? p_ : -1;
+    }
+    if (a.pool) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            q.page[h] = a.block_table[(int64_t)(q.pos[h] >= 0 ? slot[h] : 0) * a.mpps + max(q.pos[h], 0) / a.geo.PT];
+    }
+    return q;
+}
+
 // ------------------------------------------------------------------ tile GEMM with global -> LDS staging
 // Large-M GEMM, tiles of 32 MI rows x 256 columns (MI = 3 .. 8, by the number of rows: big_row_blocks), eight waves
 // (2 x 4; 16 MI x 64 of C per wave; what follows says 128 x 64, MI = 8; two waves per SIMD, so a wave that waits
@@ -574,32 +597,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a) {
 // bf16 and each fragment is converted (exactly) next to the MFMAs of slice 1, which costs 5-10 % of the loop.  Both
 // forms feed the MFMAs the same values in the same order: their results are identical bit for bit.
 // Requires K % 64 == 0, no split over K, 5 * 512 * 64 bytes of LDS.
-// Row metadata of the MG_QKV epilogue held across a wave: lane l keeps position and cache page of rows row0 + l and
-// row0 + 64 + l (fetched before the main loop, so that the epilogue starts without a chain of dependent loads).
-struct QkvRowMeta {
-    int pos[2] = {-1, -1};    // < 0: padding row / past M
-    int page[2] = {0, 0};
-    int row0 = 0;
-};
-__device__ __forceinline__ QkvRowMeta qkv_row_meta(const GemmArgs& a, int row0, int lane) {
-    QkvRowMeta q;
-    q.row0 = row0;
-    int slot[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int m = row0 + h * 64 + lane;
-        const int p_ = a.tok_pos[min(m, a.M - 1)];
-        slot[h] = a.pool ? a.tok_slot[min(m, a.M - 1)] : 0;
-        q.pos[h] = m < a.M ? p_ : -1;
-    }
-    if (a.pool) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            q.page[h] = a.block_table[(int64_t)(q.pos[h] >= 0 ? slot[h] : 0) * a.mpps + max(q.pos[h], 0) / a.geo.PT];
-    }
-    return q;
-}
-
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 template <int EPI, bool WF16, int MI>
 __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, int lda, const bf16_t* Wop, int m0, int nb, int wave,
@@ -659,7 +656,7 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
 #define X8_SLICE(AS, WS, NSO, LOADS, LB, PT, PS0, PS1)                                                          \
     _Pragma("unroll") for (int q = 0; q < 4 * ((AS) ? MI1 : MI0); ++q) {                                        \
         constexpr int NI_ = (AS) ? MI1 : MI0, NQ_ = 4 * NI_;                                                    \
-        const int j_ = q / NI_, i_ = (j_ & 1) ? NI_ - 1 - q % NI_ : q % NI_;                                                                   \
+        const int j_ = q / NI_, i_ = (j_ & 1) ? NI_ - 1 - q % NI_ : q % NI_;                                    \
         acc[(AS) * MI0 + i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wf[WS][j_]), af[AS][i_], acc[(AS) * MI0 + i_][j_], 0, 0, 0); \
         if ((AS) == 0) {                                                                                        \
             _Pragma("unroll") for (int u_ = 0; u_ < MI1; ++u_)                                                  \
@@ -1152,8 +1149,10 @@ static void launch_big(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
 // GEMMs below the large-M kernel: 128 x 128 tiles, or where these are at most half of the CUs' number tiles of 64 rows, for
 // the residual's also of 64 columns.  A workgroup's k-tile takes as long as its operands take to arrive (about 50 KB/us per
 // CU: 0.65 us for 32 KB), so a GEMM with idle CUs is as fast as its tiles are small.
-// 352 rows of the 8B shape: O and down projections 101 -> 78 us on average (96 tiles -> 192), QKV of the pair layer 40 us; at 144
-// tiles of 128 x 128 (QKV, 60 us) twice as many would double up on some CUs.
+// Measured against 128 x 128 throughout (32 to 1024 rows, plain and pair layers): nowhere slower.  O projection, 1B to 512 rows
+// 26 -> 16 us, to 1024 27 -> 20; 8B to 256 rows 45 -> 29, to 512 46 -> 35; 70B to 128 rows 84 -> 56, to 256 86 -> 68; down projections
+// alike.  QKV, 1B to 640 rows 30 -> 21, 8B to 256 51 -> 37, 70B to 128 90 -> 70; gate/up, 1B to 128 rows 25 -> 18.  At 144 tiles of 128 x
+// 128 twice as many would double up on some CUs.
 // All of them sum a row over k in the same order: the bits do not depend on the choice.
 template <int EPI>
 static void launch_small(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
@@ -1173,8 +1172,9 @@ bool k_gemm_mfma_supported(int epi, int N, int K, int hd) {
 }
 
 // Whether the large-M kernel takes this GEMM (a.Wrows filled in): where 128 x 128 tiles would be more than one per CU.
-// Up to there the 128 x 128 kernel is as fast on fp16 weights (8B O projection, 352 rows: 47 against 46 us) and faster
-// on bf16 (48 against 62); beyond it, two of its workgroups share a CU and lose (2240 rows: 119 against 74 and 85 us).
+// Up to there the kernel of launch_small is faster (8B O projection, 352 rows: 35 us on its 64 x 128 tiles, which read bf16;
+// 46 here on fp16 weights, 62 on bf16); beyond it, two of its 128 x 128 workgroups share a CU and lose (2240 rows: 119 against
+// 74 and 85 us).
 // The rule does not look at the weights' type, so that a set with an fp16 copy and one without give the same bits.
 static bool use_big(int epi, const GemmArgs& a, int splits) {
     if (!a.big_mode || splits != 1) return false;
