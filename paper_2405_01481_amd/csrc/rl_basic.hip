@@ -372,6 +372,36 @@ void k_step_start(int dtype, const int* tok_in, const int* last_tok, const int* 
                                                            (f16_t*)h, eps, split);
 }
 
+// ---------------------------------------------------------------- sums and maxima over lanes by data-parallel-primitive moves
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+// sum over 16 lanes, sum and maximum over the wave, every lane with the result
+__device__ __forceinline__ float sum16(float v) {
+    v = dpp_add<0xB1>(v);        // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);        // quad_perm [2,3,0,1]
+    v = dpp_add<0x141>(v);       // row_half_mirror
+    return dpp_add<0x140>(v);    // row_mirror
+}
+__device__ __forceinline__ float sum64(float v) {
+    v = sum16(v);
+    v += __shfl_xor(v, 16, RL_WAVE);
+    return v + __shfl_xor(v, 32, RL_WAVE);
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_int(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false); }
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float v) { return fmaxf(v, __int_as_float(dpp_int<CTRL>(__float_as_int(v)))); }
+__device__ __forceinline__ float max64(float v) {
+    v = dpp_max<0xB1>(v);
+    v = dpp_max<0x4E>(v);
+    v = dpp_max<0x141>(v);
+    v = dpp_max<0x140>(v);
+    v = fmaxf(v, __shfl_xor(v, 16, RL_WAVE));
+    return fmaxf(v, __shfl_xor(v, 32, RL_WAVE));
+}
+
 // ---------------------------------------------------------------- plain GEMM  C = A[M,K] * W[N,K]^T
 // fp32 multiply-adds on the matrix cores (v_mfma_f32_16x16x4_f32), whatever the operand types.  A workgroup owns
 // MT x NT tiles of 16 x 16 outputs; its eight waves split K between them -- wave w takes the 16-wide k chunks
@@ -398,7 +428,7 @@ struct PlainGemmArgs {
 template <typename T, typename TW, int EPI, int MT, int NT, bool NORM>
 __global__ __launch_bounds__(512) void gemm_plain_kernel(PlainGemmArgs a) {
     constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;        // weight matrices
-    constexpr int U = MT * NT * NW <= 2 ? 4 : 1;         // chunks requested at a time
+    constexpr int U = MT * NT * NW == 1 ? 8 : MT * NT * NW == 2 ? 4 : 1;   // chunks requested at a time
     __shared__ float red[8][NW * NT * 256];
     __shared__ float ssq[8][MT * 16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, q4 = lane >> 4;
@@ -422,6 +452,12 @@ __global__ __launch_bounds__(512) void gemm_plain_kernel(PlainGemmArgs a) {
         for (int w = 0; w < NW; ++w)
 #pragma unroll
             for (int j = 0; j < NT; ++j) acc[w][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    // the element this thread adds to, requested with the operands (one tile: a thread has at most one)
+    float old = 0.f;
+    if (EPI == EPI_RESID && MT * NT == 1 && threadIdx.x < 256) {
+        const int l = threadIdx.x >> 2, m = m0 + 4 * (l >> 4) + (threadIdx.x & 3), n = n0 + (l & 15);
+        old = a.outF[(int64_t)min(m, a.M - 1) * a.ldc + min(n, a.N - 1)];
     }
     const int nc = a.K / 16;                              // K is a multiple of 64
     for (int c0 = wave; c0 < nc; c0 += 8 * U) {
@@ -493,7 +529,7 @@ __global__ __launch_bounds__(512) void gemm_plain_kernel(PlainGemmArgs a) {
             }
             const int64_t o = (int64_t)m * a.ldc + n;
             if (EPI == EPI_STORE_F32) a.outF[o] = v;
-            else if (EPI == EPI_RESID) a.outF[o] += v;
+            else if (EPI == EPI_RESID) a.outF[o] = (MT * NT == 1 ? old : a.outF[o]) + v;
             else ((T*)a.outT)[o] = from_f<T>(v / (1.0f + __expf(-v)) * u);
         }
     }
@@ -528,6 +564,62 @@ void k_gemm_norm_f32(int epi, const float* x, const float* gain, float eps, cons
     const PlainGemmArgs a{x, W, W2, K, M, N, K, out, out, ldc, gain, eps};
     if (epi == EPI_SWIGLU) gemm_plain_t<float, float, EPI_SWIGLU, true>(a, s);
     else gemm_plain_t<float, float, EPI_STORE_F32, true>(a, s);
+}
+
+// outF += A W^T for at most 8 rows, fp32 (the down projection of a decode step of few rows).  The tiles above give it one
+// workgroup per 16 columns, whose eight waves share four SIMDs and multiply padding rows; here four columns have a workgroup
+// and its four waves share K, so that every operand is requested at once from four times as many CUs.  16 lanes per column,
+// lane l taking k = 64 j + 4 l .. + 3.  Rows are independent: the rows of a call do not change a row's sums.
+// 256 columns, K = 1024, in a graph of such launches: 4 rows 4.3 -> 2.7 us, 8 rows 4.7 -> 3.5.
+template <int NM>
+__global__ __launch_bounds__(256) void gemm_rows_kernel(PlainGemmArgs a) {
+    constexpr int U = NM == 4 ? 4 : 2;                               // chunks of 64 k at a time
+    __shared__ float red[4][NM][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, q4 = lane >> 4;
+    const int n = min((int)blockIdx.x * 4 + q4, a.N - 1);            // N is a multiple of 4
+    const float* const A = (const float*)a.A + l16 * 4;
+    const float* const W = (const float*)a.W + (int64_t)n * a.K + l16 * 4;
+    // lane l16 = row m of the first wave puts out column n; what it adds to is requested with the operands
+    float* const o = a.outF + (int64_t)min(l16, a.M - 1) * a.ldc + n;
+    const float old = *o;
+    float acc[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) acc[m] = 0.f;
+    const int nc = a.K / 64, per = (nc + 3) / 4, cend = min(nc, (wave + 1) * per);         // K is a multiple of 64
+    for (int c0 = wave * per; c0 < cend; c0 += U) {
+        floatx4 xf[U][NM], wf[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = min(c0 + u, cend - 1) * 64;                // past the end: the last chunk again, not used
+            wf[u] = load4(W + k);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) xf[u][m] = load4(A + (int64_t)min(m, a.M - 1) * a.lda + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + u >= cend) break;                               // wave-uniform
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+                acc[m] += xf[u][m][0] * wf[u][0] + xf[u][m][1] * wf[u][1] + xf[u][m][2] * wf[u][2] + xf[u][m][3] * wf[u][3];
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        const float t = sum16(acc[m]);
+        if (l16 == m) red[wave][m][q4] = t;
+    }
+    __syncthreads();
+    if (wave == 0 && l16 < a.M) *o = old + (((red[0][l16][q4] + red[1][l16][q4]) + red[2][l16][q4]) + red[3][l16][q4]);
+}
+// From the context's limit of rows, never from the rows of a call.  One round of loads (K up to 256) is as fast on the tiles; on
+// wide matrices the rows, read again by every four columns, weigh more than the weights.  8 rows, K = N = 512 / 1024 / 2048 /
+// 4096: tiles 3.3 / 4.8 / 8.8 / 16 us, this 2.9 / 3.8 / 6.5 / 21; 4 rows 3.1 / 4.3 / 8.7 / 16 and 2.4 / 2.9 / 4.5 / 12.
+bool k_gemm_rows_supported(int N, int K, int max_batch) { return max_batch <= 8 && K > 256 && N <= 2048 && N % 4 == 0; }
+void k_gemm_rows_f32(const float* A, int lda, const float* W, int M, int N, int K, float* out, int ldc, hipStream_t s) {
+    if (M <= 0 || M > 8 || N <= 0) return;                           // callers check first
+    const PlainGemmArgs a{A, W, nullptr, lda, M, N, K, out, nullptr, ldc, nullptr, 0.f};
+    if (M <= 4) gemm_rows_kernel<4><<<N / 4, 256, 0, s>>>(a);
+    else gemm_rows_kernel<8><<<N / 4, 256, 0, s>>>(a);
 }
 
 // ---------------------------------------------------------------- RoPE + split + KV append
@@ -693,10 +785,6 @@ void k_rope_append_split(int dtype, const float* part, int nsplit, int64_t split
 // without branches (a split past the last re-reads the last), and 16 lanes reduce by data-parallel-primitive moves.  Behind
 // a GEMM it adds 3.4 us to a step (32 rows of 2048, 4 or 8 splits).  Against 1024 threads for every row and a branch per
 // split: 200 steps of the 1B shape, 32 rows, 197.6 -> 196.1 ms.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
 template <typename T, typename TW, int NSP, int PER>
 __global__ __launch_bounds__(1024) void resid_norm_kernel(float* x, const float* part, int nsplit, int64_t split_stride,
                                                           const TW* g, T* out, int d, float eps, int split) {
@@ -726,12 +814,7 @@ __global__ __launch_bounds__(1024) void resid_norm_kernel(float* x, const float*
             ss += v[it].x * v[it].x + v[it].y * v[it].y + v[it].z * v[it].z + v[it].w * v[it].w;
         }
     }
-    ss = dpp_add<0xB1>(ss);      // quad_perm [1,0,3,2]
-    ss = dpp_add<0x4E>(ss);      // quad_perm [2,3,0,1]
-    ss = dpp_add<0x141>(ss);     // row_half_mirror
-    ss = dpp_add<0x140>(ss);     // row_mirror
-    ss += __shfl_xor(ss, 16, RL_WAVE);
-    ss += __shfl_xor(ss, 32, RL_WAVE);
+    ss = sum64(ss);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
     __syncthreads();
     float t = 0.f;
@@ -890,6 +973,218 @@ void k_attn_simple_decode(int dtype, const float* qkv, const float2* rope, void*
                                                                block_table, mpps, tok_pos, tok_slot, (f16_t*)out, Hq);
 }
 
+// Everything of a plain fp32 decode layer up to the attention's output in one launch: RMSNorm, the QKV projection of this row
+// and kv head, rotation, append and attention; in the first layer also the start of the step (position, embedding).  One block
+// of 16 waves per (row, kv head).  At the sizes this path serves a launch costs as much as what it does (an empty one takes
+// 1.6 us behind another), so the projection is repeated per row, a dot product of 16-byte pieces per wave and column, and the
+// pages' first keys and values are requested before it: they wait for the position and a page number, not for the query.
+// 4 rows, 48 keys, d 256, in a step's trace: 3.8 + 7.4 us for the two kernels before (and 2.2 for the step's start), 7.4 now.
+// A row's sums depend on the shape and its own length only.
+struct PlainFrontArgs {
+    const float *x, *gain, *W;
+    float eps;
+    int d;
+    const float2* rope;
+    float* pool;
+    int layer;
+    KvGeom geo;
+    const int *bt, *tok_pos;
+    int mpps, Hq, ctx_cap;
+    float* out;
+    PlainStart start;             // .E: first layer
+};
+template <int HD, int G>
+__global__ __launch_bounds__(1024) void plain_front_kernel(PlainFrontArgs a) {
+    constexpr int HALF = HD / 2, NC = (G + 2) * HD;
+    constexpr int CG = NC / 64, CB = CG % 3 == 0 ? 3 : 2;              // groups of four columns per wave: of all, at a time
+    constexpr int TPK = HD / 4, KPP = 1024 / TPK, PARTS = 1024 / HD;   // threads per key, keys per pass; groups of 4 tokens per pass
+    static_assert(KPP == PARTS * 4 && CG % CB == 0, "keys and values advance together");
+    extern __shared__ __attribute__((aligned(16))) float sm[];
+    float* const qkv = sm;                          // [G + 2][HD]: queries, key, value
+    float* const part = qkv + NC;                   // [G][PARTS][HD]
+    float* const sm_l = part + G * 1024;            // [4]
+    float* const sc = sm_l + 4;                     // [G][ctx_cap]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.x, g = blockIdx.y, Hkv = a.geo.Hkv, d = a.d;
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int km = tid / TPK, sub = tid % TPK, dd = tid % HD, pt = tid / HD;
+    const int* const bt = a.bt + (int64_t)b * a.mpps;
+    // entries past the last page are never used
+    const int page_k = bt[min(km / 16, a.mpps - 1)], page_v = bt[min(pt / 4, a.mpps - 1)];
+    // Projection: 16 lanes per column, lane l16 taking k = 64 j + 4 l16 .. + 3; four columns per wave and step, 256 k at a
+    // time.  The first weights are requested before anything that is waited for.
+    const float* wrow[CG];
+#pragma unroll
+    for (int i = 0; i < CG; ++i) {
+        const int c = (wave * CG + i) * 4 + q4, hh = c / HD;
+        wrow[i] = a.W + (int64_t)((hh < G ? g * G + hh : hh == G ? a.Hq + g : a.Hq + Hkv + g) * HD + c % HD) * d + l16 * 4;
+    }
+    floatx4 w[CB][4];
+    auto request = [&](int k0, int c0) {
+#pragma unroll
+        for (int i = 0; i < CB; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[i][j] = load4(wrow[c0 + i] + min(k0 + j * 64, d - 64));
+    };
+    request(0, 0);
+    int pos;
+    const float* x;
+    if (a.start.E) {
+        pos = a.start.finished[b] ? -1 : a.start.seq_len[b];
+        const int id = a.start.tok_in ? a.start.tok_in[b] : a.start.last_tok[b];
+        x = a.start.E + (int64_t)min(max(id, 0), a.start.V - 1) * d;
+        if (g == 0) {
+            if (tid == 0) {
+                a.start.pos_out[b] = pos;
+                a.start.slot_out[b] = b;
+                if (id < 0 || id >= a.start.V) atomicOr(a.start.errflag, 1);
+            }
+            for (int j = tid; j < d; j += 1024) a.start.x_out[(int64_t)b * d + j] = x[j];
+        }
+    } else {
+        pos = a.tok_pos[b];
+        x = a.x + (int64_t)b * d;
+    }
+    floatx4 xv[4], gv[4];
+    auto request_x = [&](int kb) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = min(kb + j * 64, d - 64) + l16 * 4;
+            xv[j] = load4(x + k);
+            gv[j] = load4(a.gain + k);
+        }
+    };
+    request_x(0);
+    const int ctx = pos + 1;
+    float* const out = a.out + ((int64_t)b * a.Hq + g * G) * HD;
+    if (ctx <= 0) {                                 // parked row: no keys, zeros
+        if (tid < G * HD) out[tid] = 0.f;
+        return;
+    }
+    floatx4 k0 = {0.f, 0.f, 0.f, 0.f}, v0 = {0.f, 0.f, 0.f, 0.f};
+    if (km < pos) k0 = load4(a.pool + a.geo.k_off(a.layer, page_k, g, km % 16, sub * 4));
+    if (pt * 4 < pos) v0 = load4(a.pool + a.geo.v_off(a.layer, page_v, g, pt * 4 % 16, dd));
+    const float2 cs = a.rope[(int64_t)pos * HALF + tid % HALF];
+    const int page_new = bt[pos / 16];
+    float acc[CG], ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < CG; ++i) acc[i] = 0.f;
+    for (int kb = 0; kb < d; kb += 256) {
+        if (kb > 0) request_x(kb);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (kb + j * 64 >= d) xv[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            ss += xv[j][0] * xv[j][0] + xv[j][1] * xv[j][1] + xv[j][2] * xv[j][2] + xv[j][3] * xv[j][3];
+            xv[j] *= gv[j];
+        }
+#pragma unroll
+        for (int c0 = 0; c0 < CG; c0 += CB) {
+            if (kb > 0 || c0 > 0) request(kb, c0);
+#pragma unroll
+            for (int i = 0; i < CB; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[c0 + i] += xv[j][0] * w[i][j][0] + xv[j][1] * w[i][j][1] + xv[j][2] * w[i][j][2] + xv[j][3] * w[i][j][3];
+        }
+    }
+    const float rs = 1.0f / sqrtf(sum16(ss) / (float)d + a.eps);
+#pragma unroll
+    for (int i = 0; i < CG; ++i) {
+        const float v = sum16(acc[i]) * rs;
+        if (l16 == 0) qkv[(wave * CG + i) * 4 + q4] = v;
+    }
+    __syncthreads();
+    if (tid < (G + 1) * HALF) {                     // queries and the key
+        float* const p = qkv + tid / HALF * HD + tid % HALF;
+        const float p0 = p[0], p1 = p[HALF];
+        p[0] = p0 * cs.x - p1 * cs.y;
+        p[HALF] = p1 * cs.x + p0 * cs.y;
+    }
+    __syncthreads();
+    const float* const k_new = qkv + G * HD;
+    const float* const v_new = qkv + (G + 1) * HD;
+    if (tid < HD) {
+        a.pool[a.geo.k_off(a.layer, page_new, g, pos % 16, tid)] = k_new[tid];
+        a.pool[a.geo.v_off(a.layer, page_new, g, pos % 16, tid)] = v_new[tid];
+    }
+    const float scale = 1.0f / sqrtf((float)HD);
+    for (int m0 = 0; m0 < ctx; m0 += KPP) {
+        const int m = m0 + km;
+        floatx4 kv = k0;
+        if (m0 > 0 && m < pos) kv = load4(a.pool + a.geo.k_off(a.layer, bt[m / 16], g, m % 16, sub * 4));
+        if (m == pos) kv = *reinterpret_cast<const floatx4*>(k_new + sub * 4);
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+            const floatx4 q = *reinterpret_cast<const floatx4*>(qkv + h * HD + sub * 4);
+            float s = sum16(q[0] * kv[0] + q[1] * kv[1] + q[2] * kv[2] + q[3] * kv[3]);
+            if (TPK == 32) s += __shfl_xor(s, 16, RL_WAVE);
+            if (sub == 0 && m < ctx) sc[h * a.ctx_cap + m] = s * scale;
+        }
+    }
+    __syncthreads();
+    float mx[G];                                    // every wave forms the maximum and the sum itself
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+        mx[h] = -INFINITY;
+        float l = 0.f;
+        for (int m = lane; m < ctx; m += 64) mx[h] = fmaxf(mx[h], sc[h * a.ctx_cap + m]);
+        mx[h] = max64(mx[h]);
+        if (wave == h) {
+            for (int m = lane; m < ctx; m += 64) l += __expf(sc[h * a.ctx_cap + m] - mx[h]);
+            l = sum64(l);
+            if (lane == 0) sm_l[h] = l;
+        }
+    }
+    float o[G];
+#pragma unroll
+    for (int h = 0; h < G; ++h) o[h] = pt == 0 ? __expf(sc[h * a.ctx_cap + pos] - mx[h]) * v_new[dd] : 0.f;
+    for (int m0 = 0; m0 < pos; m0 += KPP) {
+        const int m = m0 + pt * 4;
+        if (m >= pos) continue;
+        floatx4 v = v0;
+        if (m0 > 0) v = load4(a.pool + a.geo.v_off(a.layer, bt[m / 16], g, m % 16, dd));
+#pragma unroll
+        for (int h = 0; h < G; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)             // slots past the last key hold anything
+                if (m + i < pos) o[h] += __expf(sc[h * a.ctx_cap + m + i] - mx[h]) * v[i];
+    }
+#pragma unroll
+    for (int h = 0; h < G; ++h) part[(h * PARTS + pt) * HD + dd] = o[h];
+    __syncthreads();
+    if (tid < G * HD) {
+        const int h = tid / HD;
+        float r = 0.f;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) r += part[(h * PARTS + i) * HD + dd];
+        out[tid] = r / sm_l[h];
+    }
+}
+static size_t plain_front_lds(int G, int hd, int ctx) { return (size_t)((G + 2) * hd + G * 1024 + 4 + G * ctx) * sizeof(float); }
+// A block reads its columns' weights by itself: up to 512 KB it takes less than the launch it saves (196 KB: 2 us).  Blocks
+// beyond one per CU would wait for a second round.
+bool k_plain_front_supported(int Hq, int Hkv, int hd, int d, int max_batch, int max_seq) {
+    const int G = Hq / Hkv;
+    if (!(G == 1 || G == 2 || (G == 4 && hd == 64))) return false;
+    return (int64_t)(G + 2) * hd * d * 4 <= 512 * 1024 && (int64_t)max_batch * Hkv <= 256 && plain_front_lds(G, hd, max_seq) <= 65536;
+}
+void k_plain_front(const float* x, const float* gain, float eps, const float* W, int d, const float2* rope, float* pool, int layer,
+                   KvGeom geo, const int* block_table, int mpps, const int* tok_pos, float* out, int n, int Hq, int max_ctx,
+                   const PlainStart& start, hipStream_t s) {
+    if (n <= 0) return;
+    const PlainFrontArgs a{x, gain, W, eps, d, rope, pool, layer, geo, block_table, tok_pos, mpps, Hq, max_ctx, out, start};
+    const int G = Hq / geo.Hkv;
+    const dim3 grid(n, geo.Hkv);
+    const size_t lds = plain_front_lds(G, geo.hd, max_ctx);
+    if (geo.hd == 64) {
+        if (G == 1) plain_front_kernel<64, 1><<<grid, 1024, lds, s>>>(a);
+        else if (G == 2) plain_front_kernel<64, 2><<<grid, 1024, lds, s>>>(a);
+        else plain_front_kernel<64, 4><<<grid, 1024, lds, s>>>(a);
+    } else {
+        if (G == 1) plain_front_kernel<128, 1><<<grid, 1024, lds, s>>>(a);
+        else plain_front_kernel<128, 2><<<grid, 1024, lds, s>>>(a);
+    }
+}
+
 // ---------------------------------------------------------------- sampling
 // Counter-based uniform: two rounds of the splitmix64 output function over
 // (seed, sequence id, step); top 24 bits -> [0,1).  Integer-only, so the CPU
@@ -912,42 +1207,31 @@ __device__ __forceinline__ ArgMax argmax_combine(ArgMax a, ArgMax b) {
     if (b.v > a.v || (b.v == a.v && b.i < a.i)) return b;
     return a;
 }
-__device__ ArgMax block_argmax(const float* z, int V, ArgMax* red) {
-    ArgMax a{-INFINITY, 0x7fffffff};
-    if ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0) {
-        // 16-byte loads; a thread meets its candidates in increasing index order, so "first strictly greater"
-        // keeps the lowest index among equals
-        const float4* z4 = reinterpret_cast<const float4*>(z);
-        for (int i = threadIdx.x; i < V / 4; i += blockDim.x) {
-            const float4 q = z4[i];
-            if (q.x > a.v) { a.v = q.x; a.i = 4 * i; }
-            if (q.y > a.v) { a.v = q.y; a.i = 4 * i + 1; }
-            if (q.z > a.v) { a.v = q.z; a.i = 4 * i + 2; }
-            if (q.w > a.v) { a.v = q.w; a.i = 4 * i + 3; }
-        }
-    } else {
-        for (int i = threadIdx.x; i < V; i += blockDim.x) {
-            float v = z[i];
-            if (v > a.v) { a.v = v; a.i = i; }
-        }
-    }
+template <int CTRL>
+__device__ __forceinline__ ArgMax argmax_dpp(ArgMax a) {
+    return argmax_combine(a, ArgMax{__int_as_float(dpp_int<CTRL>(__float_as_int(a.v))), dpp_int<CTRL>(a.i)});
+}
+// over a block, every thread with the result; red holds one element per wave and is used for nothing else
+__device__ __forceinline__ ArgMax block_argmax(ArgMax a, ArgMax* red) {
+    a = argmax_dpp<0xB1>(a);     // quad_perm [1,0,3,2]
+    a = argmax_dpp<0x4E>(a);     // quad_perm [2,3,0,1]
+    a = argmax_dpp<0x141>(a);    // row_half_mirror
+    a = argmax_dpp<0x140>(a);    // row_mirror
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        ArgMax b{__shfl_xor(a.v, o, RL_WAVE), __shfl_xor(a.i, o, RL_WAVE)};
-        a = argmax_combine(a, b);
-    }
+    for (int o = 16; o < 64; o <<= 1) a = argmax_combine(a, ArgMax{__shfl_xor(a.v, o, RL_WAVE), __shfl_xor(a.i, o, RL_WAVE)});
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     if ((threadIdx.x & 63) == 0) red[w] = a;
     __syncthreads();
     ArgMax r = red[0];
     for (int i = 1; i < nw; ++i) r = argmax_combine(r, red[i]);
-    __syncthreads();
     return r;
 }
 
 // One block of 1024 threads per sequence.  Wave w owns the contiguous vocabulary
 // segment [w*seg, (w+1)*seg); sums are formed lane-column-wise then reduced, in a
-// fixed order, so results are reproducible run to run.
+// fixed order, so results are reproducible run to run.  A chain of loads, reductions and barriers: everything the row needs is
+// requested first, lanes reduce by data-parallel-primitive moves, greedy leaves out the tempered sums (4 rows of 4096, in a
+// graph of such launches: 4.7 -> 4.0 us).
 // out_ids / out_logp (optional) are [B, out_stride]; the column is the sequence's decode-step
 // counter, kept on the device so that a captured step can be replayed unchanged.
 __global__ __launch_bounds__(1024) void sample_kernel(const float* logits, int ldz, int V, SampleArgs a, int* last_tok,
@@ -957,15 +1241,27 @@ __global__ __launch_bounds__(1024) void sample_kernel(const float* logits, int l
     __shared__ ArgMax ared[16];
     __shared__ float ws1[16], wsT[16];
     __shared__ int s_tok;
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const float* z = logits + (int64_t)b * ldz;
+    const bool greedy = !(a.temperature > 0.f);
+    const float invT = greedy ? 1.0f : 1.0f / a.temperature;
+    int seg = (V + 15) / 16;
+    seg = (seg + 255) / 256 * 256;
+    const int s0 = w * seg, s1 = min(V, s0 + seg);
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0;
+    const float4* const z4 = reinterpret_cast<const float4*>(z);
+    // the first 16 bytes of every lane (all of a vocabulary of 4096) stay in registers; the row's counters travel with them
+    float4 first = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (vec && s0 / 4 + lane < s1 / 4) first = z4[s0 / 4 + lane];
     const int64_t orow = a.out_row ? a.out_row[b] : b;
+    const int n_gen = gen_count[b], st = step_count[b], len = seq_len[b], limit = a.gen_limit ? a.gen_limit[b] : 0;
+    const int64_t seq = a.seq_base + (a.seq_id ? a.seq_id[b] : b);
     if (finished[b] != 0) {
         // a finished sequence keeps emitting eos_id with log-prob 0 and no longer advances
         if (threadIdx.x == 0) {
             last_tok[b] = a.eos_id >= 0 ? a.eos_id : 0;   // a parked row still feeds a valid id through the GEMMs
             if (tok_out) tok_out[b] = a.eos_id;
             if (logp_out) logp_out[b] = 0.f;
-            const int st = step_count[b];
             step_count[b] = st + 1;
             if (st < out_stride) {
                 if (out_ids) out_ids[orow * out_stride + st] = a.eos_id;
@@ -974,41 +1270,47 @@ __global__ __launch_bounds__(1024) void sample_kernel(const float* logits, int l
         }
         return;
     }
-    const float* z = logits + (int64_t)b * ldz;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    ArgMax am = block_argmax(z, V, ared);
-    const float mx = am.v;
-    const bool greedy = !(a.temperature > 0.f);
-    const float invT = greedy ? 1.0f : 1.0f / a.temperature;
-    int seg = (V + 15) / 16;
-    seg = (seg + 255) / 256 * 256;
-    const int s0 = w * seg, s1 = min(V, s0 + seg);
-    float c1 = 0.f, cT = 0.f;
-    if ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0) {
-        const float4* z4 = reinterpret_cast<const float4*>(z);
+    ArgMax am{-INFINITY, 0x7fffffff};
+    if (vec) {
         for (int i = s0 / 4 + lane; i < s1 / 4; i += 64) {
-            const float4 q = z4[i];
+            const float4 q = i == s0 / 4 + lane ? first : z4[i];   // increasing index: "first greater" keeps the lowest of equals
+            if (q.x > am.v) { am.v = q.x; am.i = 4 * i; }
+            if (q.y > am.v) { am.v = q.y; am.i = 4 * i + 1; }
+            if (q.z > am.v) { am.v = q.z; am.i = 4 * i + 2; }
+            if (q.w > am.v) { am.v = q.w; am.i = 4 * i + 3; }
+        }
+    } else {
+        for (int i = s0 + lane; i < s1; i += 64)
+            if (z[i] > am.v) { am.v = z[i]; am.i = i; }
+    }
+    am = block_argmax(am, ared);
+    const float mx = am.v;
+    float c1 = 0.f, cT = 0.f;
+    if (vec) {
+        for (int i = s0 / 4 + lane; i < s1 / 4; i += 64) {
+            const float4 q = i == s0 / 4 + lane ? first : z4[i];
             const float d0 = q.x - mx, d1 = q.y - mx, d2 = q.z - mx, d3 = q.w - mx;
             c1 += (__expf(d0) + __expf(d1)) + (__expf(d2) + __expf(d3));
-            cT += (__expf(d0 * invT) + __expf(d1 * invT)) + (__expf(d2 * invT) + __expf(d3 * invT));
+            if (!greedy) cT += (__expf(d0 * invT) + __expf(d1 * invT)) + (__expf(d2 * invT) + __expf(d3 * invT));
         }
     } else {
         for (int i = s0 + lane; i < s1; i += 64) {
             float dz = z[i] - mx;
             c1 += __expf(dz);
-            cT += __expf(dz * invT);
+            if (!greedy) cT += __expf(dz * invT);
         }
     }
-    c1 = wave_sum(c1);
-    cT = wave_sum(cT);
+    c1 = sum64(c1);
+    if (!greedy) cT = sum64(cT);
     if (lane == 0) { ws1[w] = c1; wsT[w] = cT; }
-    if (threadIdx.x == 0) s_tok = greedy ? am.i : V - 1;
+    if (threadIdx.x == 0) s_tok = V - 1;
     __syncthreads();
     float tot1 = 0.f, totT = 0.f;
+#pragma unroll
     for (int i = 0; i < 16; ++i) { tot1 += ws1[i]; totT += wsT[i]; }
-    const int n_gen = gen_count[b];
+    int tok = am.i;
     if (!greedy) {
-        float u = hash_uniform(a.seed, (uint64_t)(a.seq_base + (a.seq_id ? a.seq_id[b] : b)), (uint64_t)n_gen);
+        float u = hash_uniform(a.seed, (uint64_t)seq, (uint64_t)n_gen);
         float target = u * totT;
         float cum = 0.f;
         int wsel = -1;
@@ -1042,21 +1344,20 @@ __global__ __launch_bounds__(1024) void sample_kernel(const float* logits, int l
             if (found < 0) found = s1 - 1;   // crossing falls on the segment end within rounding
             if (lane == 0) s_tok = found;
         }
+        __syncthreads();
+        tok = s_tok;
     }
-    __syncthreads();
     if (threadIdx.x == 0) {
-        const int tok = s_tok;
-        const float lp = z[tok] - mx - logf(tot1);
+        const float lp = (greedy ? mx : z[tok]) - mx - logf(tot1);
         gen_count[b] = n_gen + 1;
-        if ((a.eos_id >= 0 && tok == a.eos_id) || (a.gen_limit && n_gen + 1 >= a.gen_limit[b])) {
+        if ((a.eos_id >= 0 && tok == a.eos_id) || (a.gen_limit && n_gen + 1 >= limit)) {
             finished[b] = 1;
             if (a.out_len) a.out_len[orow] = n_gen + 1;
         }
         last_tok[b] = tok;
-        seq_len[b] = seq_len[b] + 1;
+        seq_len[b] = len + 1;
         if (tok_out) tok_out[b] = tok;
         if (logp_out) logp_out[b] = lp;
-        const int st = step_count[b];
         step_count[b] = st + 1;
         if (st < out_stride) {
             if (out_ids) out_ids[orow * out_stride + st] = tok;

@@ -97,6 +97,14 @@ void k_set_pages(int* block_table, int mpps, const int* triples_host, int n_trip
 void k_step_start(int dtype, const int* tok_in, const int* last_tok, const int* seq_len, const int* finished, int* tok_pos,
                   int* tok_slot, const void* E, int d, int V, float* x, int* errflag, const void* norm_gain, void* h,
                   float eps, int split, int B, hipStream_t s);
+// What the first layer's k_plain_front does of k_step_start (E == nullptr: nothing).
+struct PlainStart {
+    const float* E = nullptr;
+    const int *tok_in = nullptr, *last_tok = nullptr, *seq_len = nullptr, *finished = nullptr;
+    int V = 0;
+    float* x_out = nullptr;
+    int *pos_out = nullptr, *slot_out = nullptr, *errflag = nullptr;
+};
 // n row descriptors of a chunk from host arrays through kernel arguments (nothing is copied by the runtime, the host
 // arrays are free when the call returns)
 void k_put_rows(const int* seq_first_h, const int* row_slot_h, const int* row_start_h, const int* row_len_h, int n,
@@ -128,6 +136,9 @@ void k_gemm_simple(int dtype, int epi, const void* A, int lda, const void* W, co
 // C = RMSNorm(x; gain) * W^T (EPI_STORE_F32) or SwiGLU of it (W gate, W2 up), all fp32: the norm is part of the GEMM.
 void k_gemm_norm_f32(int epi, const float* x, const float* gain, float eps, const float* W, const float* W2, int M, int N,
                      int K, float* out, int ldc, hipStream_t s);
+// out[M, N] += A W^T, fp32, at most 8 rows; which contexts it suits follows from their limits
+bool k_gemm_rows_supported(int N, int K, int max_batch);
+void k_gemm_rows_f32(const float* A, int lda, const float* W, int M, int N, int K, float* out, int ldc, hipStream_t s);
 void k_rope_append(int dtype, const float* qkv, int n, const int* tok_pos, const int* tok_slot, const float2* rope,
                    void* q_out, void* k_out, void* v_out, void* pool, int layer, KvGeom geo, const int* block_table,
                    int mpps, int Hq, hipStream_t s);
@@ -145,6 +156,12 @@ void k_attn_simple(int dtype, const void* q, const void* kc, const void* vc, con
 void k_attn_simple_decode(int dtype, const float* qkv, const float2* rope, void* pool, int layer, KvGeom geo,
                           const int* block_table, int mpps, const int* tok_pos, const int* tok_slot, void* out, int n,
                           int Hq, int max_ctx, hipStream_t s);
+// fp32 decode, one row per cache slot: RMSNorm, QKV projection, rotation, append and attention of a layer, x [n, d] -> out
+// [n, Hq hd].  Which contexts it suits follows from their limits, never from the rows of a call.
+bool k_plain_front_supported(int Hq, int Hkv, int hd, int d, int max_batch, int max_seq);
+void k_plain_front(const float* x, const float* gain, float eps, const float* W, int d, const float2* rope, float* pool, int layer,
+                   KvGeom geo, const int* block_table, int mpps, const int* tok_pos, float* out, int n, int Hq, int max_ctx,
+                   const PlainStart& start, hipStream_t s);
 void k_sample(const float* logits, int ldz, int V, int B, SampleArgs a, int* last_tok, int* seq_len, int* gen_count,
               int* finished, int* step_count, int* tok_out, float* logp_out, int* out_ids, float* out_logp,
               int out_stride, hipStream_t s);

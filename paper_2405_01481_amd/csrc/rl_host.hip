@@ -392,8 +392,16 @@ static void norm_gemm(rl_ctx* c, int cls, int epi, const float* x, const void* g
     gemm(c, cls, epi, h, m.d_model, W, W2, n, N, m.d_model, outF, outT, N, s);
 }
 
+// The plain decode layers' front as one kernel (fp32, sizes that suit it): whether this context takes it.
+static bool plain_front(const rl_ctx* c) {
+    const rl_model_cfg& m = c->cfg;
+    return c->impl == 0 && m.dtype == RL_FP32 && c->fused_qkv &&
+           k_plain_front_supported(m.n_q_heads, m.n_kv_heads, m.head_dim, m.d_model, m.max_batch, m.max_seq);
+}
+
+// start (decode, plain_front): the first layer also starts the step.
 static void run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
-                             int nblocks, hipStream_t s, float* x, int l0, int l1) {
+                             int nblocks, hipStream_t s, float* x, int l0, int l1, const PlainStart* start) {
     const rl_model_cfg& m = c->cfg;
     const Layout& L = c->L;
     const int dt = m.dtype;
@@ -410,17 +418,31 @@ static void run_layers_plain(rl_ctx* c, const WeightsHost& W, int n, bool paged,
     const int* bt = c->at<int>(L.block_table);
     const float2* rope = c->at<float2>(L.rope);
     const int gcls = paged ? RL_K_GEMM_DECODE : RL_K_GEMM_PREFILL;
+    auto resid_gemm = [&](const void* A, int K, const void* w) {      // x += A w^T
+        if (paged && dt == RL_FP32 && k_gemm_rows_supported(m.d_model, K, m.max_batch)) {
+            ProfScope ps(c, gcls, s);
+            k_gemm_rows_f32((const float*)A, K, (const float*)w, n, m.d_model, K, x, m.d_model, s);
+        } else {
+            gemm(c, gcls, EPI_RESID, A, K, w, nullptr, n, m.d_model, K, x, nullptr, m.d_model, s);
+        }
+    };
     for (int l = l0; l < l1; ++l) {
-        norm_gemm(c, gcls, EPI_STORE_F32, x, W.attn_norm[l], W.wqkv[l], nullptr, n, L.nqkv, qkv, nullptr, s);
+        if (start) {
+            ProfScope ps(c, RL_K_ATTN_DECODE, s);
+            k_plain_front(x, (const float*)W.attn_norm[l], m.rms_eps, (const float*)W.wqkv[l], m.d_model, rope, (float*)c->pool, l,
+                          c->geo, bt, L.mpps, tpos, (float*)att, n, m.n_q_heads, max_ctx, l == 0 ? *start : PlainStart{}, s);
+        } else {
+            norm_gemm(c, gcls, EPI_STORE_F32, x, W.attn_norm[l], W.wqkv[l], nullptr, n, L.nqkv, qkv, nullptr, s);
+        }
         if (!paged)
             k_rope_append(dt, qkv, n, tpos, tslot, rope, q, kb, vb, write_pages ? c->pool : nullptr, l, c->geo, bt, L.mpps,
                           m.n_q_heads, s);
         if (!paged && write_pages && l + 1 == m.n_layers) break;   // prefill: nothing reads what lies behind the last keys and values
-        attention(c, l, n, paged, max_ctx, nblocks, s);
-        gemm(c, gcls, EPI_RESID, att, qd, W.wo[l], nullptr, n, m.d_model, qd, x, nullptr, m.d_model, s);
+        if (!start) attention(c, l, n, paged, max_ctx, nblocks, s);
+        resid_gemm(att, qd, W.wo[l]);
         const char* wg = (const char*)W.w_gate_up[l];
         norm_gemm(c, gcls, EPI_SWIGLU, x, W.ffn_norm[l], wg, wg + (size_t)m.d_ffn * m.d_model * e, n, m.d_ffn, nullptr, ffn, s);
-        gemm(c, gcls, EPI_RESID, ffn, m.d_ffn, W.w_down[l], nullptr, n, m.d_model, m.d_ffn, x, nullptr, m.d_model, s);
+        resid_gemm(ffn, m.d_ffn, W.w_down[l]);
     }
 }
 
@@ -615,11 +637,11 @@ static void run_layers_fast(rl_ctx* c, const WeightsHost& W, int n, bool paged, 
 // Layers [l0, l1) (default: all) on the n packed rows whose residual stream is x (default: the workspace's).
 static void run_layers(rl_ctx* c, const WeightsHost& W, int n, bool paged, bool write_pages, int max_ctx,
                        int nblocks, hipStream_t s, float* x = nullptr, int l0 = 0, int l1 = -1, const WeightsHost* W2 = nullptr,
-                       const KeepRows* keep = nullptr) {
+                       const KeepRows* keep = nullptr, const PlainStart* start = nullptr) {
     if (!x) x = c->at<float>(c->L.x);
     if (l1 < 0) l1 = c->cfg.n_layers;
     if (c->impl == 1) run_layers_fast(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1, W2, keep);
-    else run_layers_plain(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1);
+    else run_layers_plain(c, W, n, paged, write_pages, max_ctx, nblocks, s, x, l0, l1, start);
 }
 
 // Logits fp32 [nr, V] of nr rows.  Tuned path: of the workspace's h, which holds the final norm's output; plain path: of
@@ -1147,10 +1169,17 @@ static int decode_step_impl(rl_ctx* c, const rl_sample_cfg* sample, const int32_
     int rc = ensure_pages(c, need, s);
     if (rc) return rc;
     const bool fast = c->impl == 1;
-    k_step_start(m.dtype, tok_in, c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.finished), c->at<int>(L.tok_pos),
-                 c->at<int>(L.tok_slot), c->policy.tok_embed, m.d_model, m.vocab, c->at<float>(L.x), c->at<int>(L.errflag),
-                 fast ? c->policy.attn_norm[0] : nullptr, c->at<char>(L.h), m.rms_eps, c->precise > 0, B, s);
-    run_layers(c, c->policy, B, true, true, max_ctx, 0, s);
+    if (plain_front(c)) {
+        const PlainStart st{(const float*)c->policy.tok_embed, tok_in, c->at<int>(L.last_tok), c->at<int>(L.seq_len),
+                            c->at<int>(L.finished), m.vocab, c->at<float>(L.x), c->at<int>(L.tok_pos), c->at<int>(L.tok_slot),
+                            c->at<int>(L.errflag)};
+        run_layers(c, c->policy, B, true, true, max_ctx, 0, s, nullptr, 0, -1, nullptr, nullptr, &st);
+    } else {
+        k_step_start(m.dtype, tok_in, c->at<int>(L.last_tok), c->at<int>(L.seq_len), c->at<int>(L.finished), c->at<int>(L.tok_pos),
+                     c->at<int>(L.tok_slot), c->policy.tok_embed, m.d_model, m.vocab, c->at<float>(L.x), c->at<int>(L.errflag),
+                     fast ? c->policy.attn_norm[0] : nullptr, c->at<char>(L.h), m.rms_eps, c->precise > 0, B, s);
+        run_layers(c, c->policy, B, true, true, max_ctx, 0, s);
+    }
     SampleArgs a{sample->seed, sample->seq_id_base, sample->temperature, sample->eos_id};
     if (queue_out_len) {
         a.out_row = c->at<int>(L.out_row);
