@@ -234,10 +234,11 @@ struct rl_ctx {
         hipStream_t s;
         const void* out_len = nullptr;   // non-null: queue mode (per-slot output rows, ids, limits)
         int ctx_cap = 0;                 // plain kernels: longest context the captured attention launches have LDS for
+        int steps = 1;                   // decode steps in the captured graph
         bool operator==(const GraphKey& o) const {
             return B == o.B && G == o.G && impl == o.impl && eos == o.eos && out_ids == o.out_ids &&
                    out_logp == o.out_logp && seed == o.seed && base == o.base && temp == o.temp && s == o.s &&
-                   out_len == o.out_len && ctx_cap == o.ctx_cap;
+                   out_len == o.out_len && ctx_cap == o.ctx_cap && steps == o.steps;
         }
     } gkey{};
     hipGraphExec_t gexec = nullptr;
@@ -1222,6 +1223,15 @@ static bool graph_usable(const rl_ctx* c, hipStream_t s, int ctx_cap) {
     return s != nullptr && c->use_graph;
 }
 
+// Decode steps per captured graph of a run of G tokens.  Between two replays the device is idle for about 7.5 us, a launch
+// inside a graph costs 1.6, and every node about 1.4 us of host time when it is captured: more steps pay where a step is a
+// handful of launches (the fp32 configuration's 10: its whole pass 1760 -> 1640 us with 8), and not for the 112 or more of a
+// tuned step.  A quarter of G at most: a run whose buffers are new, and which captures, gains as well.
+static int graph_steps(const rl_ctx* c, int G) {
+    if (!plain_front(c)) return 1;
+    return std::max(1, std::min(std::min(8, 96 / (4 * c->cfg.n_layers + 2)), G / 4));
+}
+
 // The decode step is identical from one token to the next (positions, step counters and page tables live on the
 // device), so it is captured once and replayed.  Makes c->gexec the step of `key`; one that it replaces is put aside.
 static int capture_step(rl_ctx* c, const rl_ctx::GraphKey& key, const rl_sample_cfg* sample, int32_t* out_ids, float* out_logp,
@@ -1237,7 +1247,8 @@ static int capture_step(rl_ctx* c, const rl_ctx::GraphKey& key, const rl_sample_
     const char* what = "hipStreamBeginCapture";
     if (e == hipSuccess) {
         const std::vector<int> saved = c->cached;
-        rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, key.G, key.s, queue_out_len, ctx_cap);
+        for (int i = 0; i < key.steps && rc == RL_OK; ++i)
+            rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, key.G, key.s, queue_out_len, ctx_cap);
         c->cached = saved;
         e = hipStreamEndCapture(key.s, &graph);
         what = "hipStreamEndCapture";
@@ -1306,17 +1317,18 @@ int rollout_generate(rl_ctx* c, const rl_sample_cfg* sample, const int32_t* prom
     rc = ensure_pages(c, need, s);
     if (rc) return rc;
     const int ctx_cap = *std::max_element(need.begin(), need.end());
+    int done = 0;                                              // steps that the captured graph covers
     if (graph_usable(c, s, ctx_cap)) {
         const rl_ctx::GraphKey key{B, G, c->impl, sample->eos_id, out_ids, out_logp, sample->seed, sample->seq_id_base,
-                                   sample->temperature, s, nullptr, c->impl == 1 ? 0 : ctx_cap};
+                                   sample->temperature, s, nullptr, c->impl == 1 ? 0 : ctx_cap, graph_steps(c, G)};
         if ((rc = capture_step(c, key, sample, out_ids, out_logp, nullptr, ctx_cap))) return rc;
-        if ((rc = replay_step(c, G))) return rc;
-        for (int b = 0; b < B; ++b) c->cached[b] += G;
-    } else {
-        for (int n = 0; n < G; ++n) {
-            rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, G, s);
-            if (rc) return rc;
-        }
+        if ((rc = replay_step(c, G / key.steps))) return rc;
+        done = G / key.steps * key.steps;
+        for (int b = 0; b < B; ++b) c->cached[b] += done;
+    }
+    for (int n = done; n < G; ++n) {
+        rc = decode_step_impl(c, sample, nullptr, nullptr, nullptr, out_ids, out_logp, G, s);
+        if (rc) return rc;
     }
     if (out_len) k_out_len(c->at<int>(c->L.gen_count), out_len, B, s);
     HIP_TRY(hipGetLastError());

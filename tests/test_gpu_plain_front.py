@@ -59,3 +59,23 @@ def test_front_against_oracle(G, hd, d, F, B):
         assert (ended[b, stop:] == eos).all() and (ended_lp[b, stop:] == 0).all()
     ro.close()
 
+
+def test_steps_per_graph_and_the_ones_left_over():
+    """Runs of 1 to 37 tokens on one context, captured (several steps a graph, a remainder of eager ones) and eager: the same
+    tokens and log-probs; a run as long as max_seq allows."""
+    shape, B, P, most = _shape(1, 64, 128, 128), 3, 9, 37
+    ro = R.Rollout(R.make_cfg(shape, B, P - 1 + most), R.Weights(synth.make_weights(shape, 1, DEV)), DEV)
+    ids, lens = synth.make_prompts(shape.vocab, B, P, P, 3)
+    prompts, side, want = torch.tensor(ids, device=DEV), torch.cuda.Stream(), None
+    for stream, G in [(torch.cuda.default_stream(), most)] + [(side, g) for g in (1, 4, 7, 8, 15, 33, most, most)]:
+        out = torch.zeros(B, G, dtype=torch.int32, device=DEV)
+        lp = torch.zeros(B, G, device=DEV)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            ro.rollout_generate(R.sample_cfg(4, 0.7), prompts, lens, G, out, None, lp)
+        torch.cuda.synchronize()
+        ro.rollout_check()
+        got = out.cpu().numpy(), lp.cpu().numpy()
+        want = want or got
+        assert np.array_equal(got[0], want[0][:, :G]) and np.array_equal(got[1], want[1][:, :G]), G
+    ro.close()
