@@ -9,7 +9,7 @@ struct GemmArgs {
     int lda = 0;
     const bf16_t* W = nullptr;  // [Wrows, K] row-major
     int w_f16 = 0;              // W points at an fp16 copy made by k_bf16_to_f16 (no conversion in the kernel): decode GEMMs,
-                                // and large-M GEMMs for which k_gemm_mfma_reads_f16_copy() says yes
+                                // and the GEMMs for which k_gemm_mfma_reads_f16_copy() says yes
     int M = 0, N = 0, K = 0;    // N = output columns (MG_SWIGLU: d_ffn)
     // Activations carried as fp16 pairs (value = hi + lo, about 22 significant bits): A is [M, 2 Kw] with the hi
     // halves of a row in columns [0, Kw) and the lo halves in [Kw, 2 Kw), K = 2 Kw, and the k index into W wraps

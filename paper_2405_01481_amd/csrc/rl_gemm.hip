@@ -2,18 +2,19 @@
 //
 // Weights stay bf16 in HBM and are converted to fp16 on their way to the MFMA operand registers
 // (exact for every weight of normal fp16 magnitude) -- or are read from an fp16 copy where a weight set
-// has one; the contraction runs on fp16 MFMAs (v_mfma_f32_16x16x32_f16 in the large-M kernel,
-// v_mfma_f32_32x32x16_f16 in the others) with fp32 accumulation.  Three kernels (the decode step's
+// has one; the contraction runs on fp16 MFMAs (v_mfma_f32_32x32x16_f16 in the first kernel,
+// v_mfma_f32_16x16x32_f16 in the others) with fp32 accumulation.  Four kernels (the decode step's
 // weight-streaming GEMMs are in rl_gemm_stream.hip):
-//   * gemm_mfma_kernel: 128 x 128, 64 x 128 and 64 x 64 tiles staged through registers -- small M, and split-K for decode
-//     batches above 128 rows;
+//   * gemm_mfma_kernel: 128 x 128, 64 x 128 and 64 x 64 tiles staged through registers -- small M on bf16 weights, and split-K
+//     for decode batches above 128 rows;
+//   * gemm_ring_kernel: the same tiles staged by global -> LDS loads -- small M where a weight set has its fp16 copy;
 //   * gemm_dma8_kernel: tiles of 96 to 256 rows x 256 columns, eight waves, operands staged by global ->
 //     LDS loads -- the large-M GEMMs of prefill and scoring;
 //   * gemm_kl8_kernel:  the same loop run twice on tiles of 128 rows -- the exact full-vocabulary KL, which needs the
 //     policy's and the reference's logits of a tile together.
 // Epilogues: fp32 store / split-K partial, residual add, SwiGLU, RoPE + q/k/v split for
 // the QKV projection, log-sum-exp + target gather for the scoring LM head; mg_epilogue for the first kernel, d8_half for
-// the second.  Both round alike: a row's results do not depend on which of them its GEMM's size picks.
+// the second and third.  Both round alike: a row's results do not depend on which of them its GEMM's size picks.
 #include "rl_common.h"
 #include "rl_gemm.h"
 #include "rl_gemm_dev.h"
@@ -572,6 +573,12 @@ __device__ __forceinline__ QkvRowMeta qkv_row_meta(const GemmArgs& a, int row0, 
 }
 
 // ------------------------------------------------------------------ tile GEMM with global -> LDS staging
+// Stages of gemm_ring_kernel: what fits in 160 KB of LDS, at most eight.
+static constexpr int ring_stages(int MI, int WGM, int WGN) {
+    const int fit = 160 * 1024 / ((16 * MI * WGM + 64 * WGN) * 128);
+    return fit < 8 ? fit : 8;
+}
+
 // Large-M GEMM, tiles of 32 MI rows x 256 columns (MI = 3 .. 8, by the number of rows: big_row_blocks), eight waves
 // (2 x 4; 16 MI x 64 of C per wave; what follows says 128 x 64, MI = 8; two waves per SIMD, so a wave that waits
 // -- at a barrier, for its fragment reads, behind a queued staging load -- leaves the SIMD's matrix core to the other
@@ -997,6 +1004,108 @@ __global__ __launch_bounds__(512, 1) void gemm_dma8_kernel(GemmArgs a) {
     if constexpr (MI > 4) d8_half<EPI, MI, 1>(acc, patch, a, m_w + 64, nb, wn, lane, meta);
 }
 
+// GEMMs below the large-M kernel whose weights are there as fp16: tiles of 16 MI WGM rows x 64 WGN columns, WGM x WGN waves of
+// 16 MI x 64 each, operands global -> LDS in k-tiles of 64 through as many stages as fit.  Such a GEMM has at most one workgroup
+// per CU and is bound by what that workgroup draws: measured, a CU has about 64 KB on its way at once, which is 115 - 145
+// KB/us from L2, 95 behind it and 62 - 65 from memory, whatever the row stride and however many stages wait.  So all of them are
+// kept on their way and nothing else may show: one barrier per k-tile, in its middle; the fragments of the second 32 k are read
+// under the MFMAs of the first, those of the next k-tile under the second's, and the k-tile that fills the freed stage is
+// requested among the same MFMAs.  0.53 us per k-tile of 128 x 128 tiles (0.37 with its operands in L2; the MFMAs alone 0.25)
+// against 0.66 staged through registers.  bf16 weights stay with that kernel: it converts them once on their way to LDS, here
+// every wave would on its own.
+// 16-byte chunks of a 128-byte row are XOR-swizzled with (row / 2) % 8 on the source side of the loads (fragment reads: 16 rows,
+// one 16-byte read per lane).  MFMAs, their order along k and the epilogues are the large-M kernel's: a row's bits do not depend
+// on which of the kernels runs.  The tile's columns are half or a quarter of a 256-column tile there.  Offsets count from the
+// tile's first row of A and of W.
+template <int EPI, int MI, int WGM, int WGN>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_ring_kernel(GemmArgs a) {
+    constexpr int BM = 16 * MI * WGM, BN = 64 * WGN, NWV = WGM * WGN, RB = 128, QC = 256 / BN;   // QC: tiles per 256 columns
+    constexpr int S = ring_stages(MI, WGM, WGN), ST = (BM + BN) * RB, NI = (BM + BN) / 8 / NWV;
+    static_assert((BM + BN) / 8 % NWV == 0, "every wave counts the same loads");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];   // [S][A BM x 128 B | W BN x 128 B]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    int nt, mb;
+    if (!tile_of(blockIdx.x, row_blocks(a, BM), a.n_blocks_n, mb, nt)) return;
+    const int m0 = enter_row_block(a, BM, mb);
+    const int nb = nt / QC, c0 = nt % QC * BN;                       // 256-column tile, first column in it
+    const int nk = a.K / 64, nkw = a.Kw / 64;
+    const int w_first = w_row_of<EPI, 256>(c0, nb, a);
+    const char* const Ag = reinterpret_cast<const char*>(a.A + (int64_t)m0 * a.lda);
+    const char* const Wg = reinterpret_cast<const char*>(a.W + (int64_t)min(w_first, a.Wrows - 1) * a.Kw);
+    // request t of a wave: the 1 KB block t * NWV + wave = 8 rows of a stage; lane -> row + lane / 8, chunk lane % 8
+    unsigned off[NI];
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+        const int row = (t * NWV + wave) * 8 + (lane >> 3);
+        const unsigned ch = (unsigned)((lane & 7) ^ ((row >> 1) & 7)) * 16u;
+        if ((t * NWV + wave) * 8 < BM) off[t] = (unsigned)min(row, a.M - 1 - m0) * (unsigned)a.lda * 2u + ch;   // rows >= M: clamped, never stored
+        else off[t] = (unsigned)(min(w_row_of<EPI, 256>(c0 + row - BM, nb, a), a.Wrows - 1) - min(w_first, a.Wrows - 1)) * (unsigned)a.Kw * 2u + ch;
+    }
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+    // request t of k-tile kt (the last trips ask for the final k-tile again, so that the counts hold)
+#define RG_ISSUE1(stage, kt, t)                                                                                 \
+    {                                                                                                           \
+        const int k_ = min((kt), nk - 1);                                                                       \
+        const unsigned l_ = lds0 + (stage) * ST + (t) * (NWV * 1024);                                           \
+        const char* g_ = ((t) * NWV + wave) * 8 < BM ? Ag + (size_t)k_ * RB : Wg + (size_t)wrap_k(k_, nkw) * RB; \
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(l_), "v"(off[t]), "s"(g_) : "memory"); \
+    }
+    floatx4_t acc[MI][4];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    const int fr = lane & 15, q = lane >> 4, sw = (fr >> 1) & 7;
+    const int fa = (wm * MI * 16 + fr) * RB, fw = (BM + wn * 64 + fr) * RB;
+    const int ch0 = (q ^ sw) * 16, ch1 = ((4 + q) ^ sw) * 16;        // this lane's chunk of the first and of the second 32 k
+    half8 af[2][MI];
+    half8 wf[2][4];
+#define RG_READ(set, u, so, ch)                                                                                 \
+    if ((u) < 4) wf[set][(u) & 3] = *reinterpret_cast<const half8*>((so) + fw + (u) * 16 * RB + (ch));        \
+    else if ((u) < 4 + MI) af[set][(u) < 4 + MI && (u) >= 4 ? (u) - 4 : 0] = *reinterpret_cast<const half8*>((so) + fa + ((u) - 4) * 16 * RB + (ch));
+    // 4 MI MFMAs on fragment set `set`; behind them the reads of the other set, and LOADS: the requests of k-tile PT
+#define RG_SLICE(set, so, ch, LOADS, stage, PT)                                                                 \
+    _Pragma("unroll") for (int n = 0; n < 4 * MI; ++n) {                                                        \
+        const int j_ = n / MI, i_ = (j_ & 1) ? MI - 1 - n % MI : n % MI;                                        \
+        acc[i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[set][j_], af[set][i_], acc[i_][j_], 0, 0, 0);   \
+        _Pragma("unroll") for (int u = 0; u < 4 + MI; ++u)                                                      \
+            if (u * 4 * MI / (4 + MI) == n) { RG_READ(1 - (set), u, so, ch) }                                   \
+        _Pragma("unroll") for (int t = 0; t < NI; ++t)                                                          \
+            if ((LOADS) && (t * 4 * MI + 2 * MI) / NI == n) { RG_ISSUE1(stage, PT, t) }                         \
+        __builtin_amdgcn_sched_barrier(0);                                                                      \
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int t = 0; t < NI; ++t) RG_ISSUE1(s, s, t)
+    QkvRowMeta meta;
+    if constexpr (EPI == MG_QKV) meta = qkv_row_meta(a, m0 + wm * MI * 16, lane);
+    __builtin_amdgcn_s_waitcnt(dma_waitcnt(EPI == MG_QKV ? 0 : NI * (S - 1), 15));
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4 + MI; ++u) { RG_READ(0, u, smem, ch0) }
+    int st = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        const int nx = st + 1 == S ? 0 : st + 1;
+        RG_SLICE(0, smem + st * ST, ch1, false, 0, 0)
+        // k-tile kt + 1 landed; every wave has read its fragments of k-tile kt, whose stage is filled again
+        __builtin_amdgcn_s_waitcnt(dma_waitcnt(NI * (S - 2), 0));
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        RG_SLICE(1, smem + nx * ST, ch0, true, st, kt + S)
+        st = nx;
+    }
+#undef RG_READ
+#undef RG_SLICE
+    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));      // nothing may land in LDS after this point
+#undef RG_ISSUE1
+    __syncthreads();
+    float* const patch = reinterpret_cast<float*>(smem) + wave * (16 * MI * PATCH_LD);
+    d8_half<EPI, MI, 0>(acc, patch, a, m0 + wm * MI * 16, nb, c0 / 64 + wn, lane, meta);
+}
+
 // Exact-KL epilogue of a wave's 64 rows x 64 columns: per row five numbers leave the kernel,
 //   m_p = max z_p, S_p = sum exp(z_p - m_p), T = sum exp(z_p - m_p) (z_p - z_r), m_r = max z_r, S_r = sum exp(z_r - m_r)
 // from which  KL(pi_p || pi_r) = T/S_p - (m_p + log S_p) + (m_r + log S_r)  once all column groups are combined.  Four
@@ -1078,6 +1187,29 @@ static void launch(const GemmArgs& a, int n_blocks_n, int splits, hipStream_t s)
     gemm_mfma_kernel<BM, BN, WGM, WGN, EPI, BKT, WF16><<<grid, 256, lds, s>>>(b);
 }
 
+template <int EPI, int MI, int WGM, int WGN>
+static void launch_ring_t(const GemmArgs& a, int cols, hipStream_t s) {
+    constexpr int BM = 16 * MI * WGM, BN = 64 * WGN, lds = ring_stages(MI, WGM, WGN) * (BM + BN) * 128;
+    static_assert(lds >= WGM * WGN * 16 * MI * PATCH_LD * 4, "the epilogue's patches reuse the stages");
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void*)gemm_ring_kernel<EPI, MI, WGM, WGN>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_set = true;
+    }
+    GemmArgs b = a;
+    b.n_blocks_n = cols / BN;
+    gemm_ring_kernel<EPI, MI, WGM, WGN><<<8 * ((b.n_blocks_n * row_blocks(a, BM) + 7) / 8), 64 * WGM * WGN, lds, s>>>(b);
+}
+// The smallest tile of which the 256 CUs have at most one each (128 x 128 are, see use_ring).  Against the register-staged kernel on
+// bf16 weights, us: 1B O projection at 512 / 1024 / 2048 rows 13.2 / 19.7 / 30.9 -> 12.5 / 15.6 / 22.4, down 50 / 60 / 90 -> 36 / 49 / 67,
+// gate/up at 96 / 256 rows 21.0 / 25.6 -> 19.1 / 21.1; 8B O at 256 / 512 / 1024 rows 27.6 / 34.6 / 48.8 -> 21 / 30 / 40, down 92 / 112 /
+// 148 -> 69 / 101 / 138.  The other tiles at these sizes: 128 x 128 at 512 rows of 1B down 63, 64 x 128 at 2048 101, 64 x 64 137.
+template <int EPI>
+static void launch_ring(const GemmArgs& a, int cols, hipStream_t s) {
+    if (row_blocks(a, 64) * (cols / 64) <= 256) launch_ring_t<EPI, 1, 4, 1>(a, cols, s);            // 64 x 64
+    else if (row_blocks(a, 64) * (cols / 128) <= 256) launch_ring_t<EPI, 1, 4, 2>(a, cols, s);      // 64 x 128
+    else launch_ring_t<EPI, 2, 4, 2>(a, cols, s);                                                   // 128 x 128
+}
 template <bool WF16>
 static void launch_kl8(const GemmArgs& a, hipStream_t s) {
     constexpr int BM = 128, stages = 5 * (BM + 256) * 64, patches = 8 * 64 * PATCH_LD * 4, lds = stages > patches ? stages : patches;
@@ -1146,7 +1278,7 @@ static void launch_big(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
     else launch_dma8<EPI, false>(b, n_blocks_n, mi, s);
 }
 
-// GEMMs below the large-M kernel: 128 x 128 tiles, or where these are at most half of the CUs' number tiles of 64 rows, for
+// GEMMs below the large-M kernel on bf16 weights: 128 x 128 tiles, or where these are at most half of the CUs' number tiles of 64 rows, for
 // the residual's also of 64 columns.  A workgroup's k-tile takes as long as its operands take to arrive (about 50 KB/us per
 // CU: 0.65 us for 32 KB), so a GEMM with idle CUs is as fast as its tiles are small.
 // Measured against 128 x 128 throughout (32 to 1024 rows, plain and pair layers): nowhere slower.  O projection, 1B to 512 rows
@@ -1156,6 +1288,7 @@ static void launch_big(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
 // All of them sum a row over k in the same order: the bits do not depend on the choice.
 template <int EPI>
 static void launch_small(const GemmArgs& a, int n_blocks_n, hipStream_t s) {
+    if (a.w_f16) { launch_ring<EPI>(a, n_blocks_n * 128, s); return; }
     if (row_blocks(a, 128) * n_blocks_n > 128) { launch<128, 128, 2, 2, EPI>(a, n_blocks_n, 1, s); return; }
     if constexpr (EPI == MG_RESID) {
         if (row_blocks(a, 64) * n_blocks_n <= 128) { launch<64, 64, 2, 2, EPI>(a, 2 * n_blocks_n, 1, s); return; }
@@ -1185,13 +1318,20 @@ static bool use_big(int epi, const GemmArgs& a, int splits) {
     return a.big_mode >= 2 || tiles > 256;
 }
 
+// Below it: fp16 weights and at most one 128 x 128 tile per CU.
+static bool use_ring(int epi, const GemmArgs& a, int splits) {
+    if (splits != 1 || (epi != MG_RESID && epi != MG_SWIGLU && epi != MG_QKV && epi != MG_LSE) || use_big(epi, a, splits)) return false;
+    if (a.K % 64 != 0 || a.Kw % 64 != 0 || (uint64_t)a.Wrows * a.Kw * 2 >= (1ull << 32) || (uint64_t)a.lda * 256 >= (1ull << 31)) return false;
+    return row_blocks(a, 128) * ((epi == MG_SWIGLU ? 2 * a.N : a.N) / 128) <= 256;
+}
+
 int k_gemm_mfma_lse_parts(int M, int N, int K, int big_mode) {
     // column groups are as wide as a wave's share of the tile: 64 columns on the 256-column and on the 128 x 128 kernel
     (void)M; (void)K; (void)big_mode;
     return N / 64;
 }
 
-// Whether k_gemm_mfma will run this GEMM on the kernel that can read an fp16 copy of W (GemmArgs.w_f16).
+// Whether k_gemm_mfma will run this GEMM on a kernel that can read an fp16 copy of W (GemmArgs.w_f16).
 bool k_gemm_mfma_reads_f16_copy(int epi, GemmArgs a, int splits) {
     if (a.M <= 0 || a.N <= 0) return false;
     if (epi == MG_KLFULL) return true;
@@ -1200,7 +1340,7 @@ bool k_gemm_mfma_reads_f16_copy(int epi, GemmArgs a, int splits) {
     const int kt = a.K / BK, per = (kt + splits - 1) / splits;
     splits = (kt + per - 1) / per;
     a.Wrows = epi == MG_SWIGLU ? a.up_offset + a.N : a.N;
-    return use_big(epi, a, splits);
+    return use_big(epi, a, splits) || use_ring(epi, a, splits);
 }
 
 void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s) {
@@ -1213,7 +1353,7 @@ void k_gemm_mfma(int epi, GemmArgs a, int splits, hipStream_t s) {
     splits = (kt + per - 1) / per;
     a.Wrows = epi == MG_SWIGLU ? a.up_offset + a.N : a.N;
     const bool big = use_big(epi, a, splits);
-    if (a.w_f16 && !big && epi != MG_KLFULL) return;     // callers check k_gemm_mfma_reads_f16_copy first
+    if (a.w_f16 && !big && epi != MG_KLFULL && !use_ring(epi, a, splits)) return;     // callers check k_gemm_mfma_reads_f16_copy first
     switch (epi) {
         case MG_STORE_F32:
             if (big) launch_big<MG_STORE_F32>(a, a.N / 256, s);
