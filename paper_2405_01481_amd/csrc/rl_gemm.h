@@ -28,6 +28,7 @@ struct GemmArgs {
     int n_blocks_n = 0;         // filled by the launcher
     int k_per_split = 0;        // filled by the launcher
     int rotate_k = 0;           // filled by the launcher (k_gemm_decode)
+    int pair = 0;               // filled by the launcher (k_gemm_decode): A holds pairs, K = 2 Kw
     int up_offset = 0;          // MG_SWIGLU: row of W where the up projection starts
     float* outF = nullptr;      // MG_STORE_F32 (+ split * split_stride) / MG_RESID
     f16_t* outH = nullptr;      // MG_SWIGLU
@@ -80,7 +81,7 @@ int k_gemm_mfma_lse_parts(int M, int N, int K, int big_mode);
 // 4 GiB.  max_rows: the most rows the context will ever pass; tiles and k_gemm_decode_splits, the number of splits that suits an
 // MG_STORE_F32 GEMM, follow from it and the shape, never from the rows of a call.
 bool k_gemm_decode_supported(int epi, int N, int K, int Kw);
-int k_gemm_decode_splits(int N, int K, int max_rows);
+int k_gemm_decode_splits(int N, int K, int Kw, int max_rows);
 void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s);
 // The same GEMM (MG_STORE_F32, MG_SWIGLU) on the 128 x 128 tile kernel, a.k_per_split and a.Wrows filled in.
 void k_gemm_tile_decode(int epi, const GemmArgs& a, int splits, hipStream_t s);

@@ -56,8 +56,10 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, q = lane >> 4, wk = wave % GS_WK, wn = wave / GS_WK;
     const int t0 = blockIdx.x * CT;                            // first 16-row tile of W
-    const int kbeg = blockIdx.z * a.k_per_split, kend = min(a.K, kbeg + a.k_per_split);
-    const int nk = (kend - kbeg) / GS_KT, kt0 = kbeg / GS_KT, nkw = a.Kw / GS_KT;
+    const int kbeg = blockIdx.z * a.k_per_split, kend = min(a.Kw, kbeg + a.k_per_split);
+    const int nk = (kend - kbeg) / GS_KT, kt0 = kbeg / GS_KT;
+    // activations as fp16 pairs: every k-tile of W meets the hi tile of A, then the lo tile, in two trips; W is requested on the first
+    const int pair = a.pair, nv = nk << pair;
     const int rot = a.rotate_k ? (int)(blockIdx.x % (unsigned)nk) : 0;
     // Staging: request t of a wave fills the 1 KB block t*8 + wave = 4 rows of a W stage, or (counted from wave 4 on if W's
     // tiles are odd) of an A stage; lane -> row + lane/16, physical chunk lane%16, which holds the row's logical chunk
@@ -85,13 +87,14 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(off), "s"(g) : "memory")
 #define GS_ISSUE_W(stage, kt)                                                                                   \
     {                                                                                                           \
-        const char* g_ = Wg + (size_t)wrap_k(GS_TILE(kt), nkw) * GS_RB;                                         \
+        const char* g_ = Wg + (size_t)GS_TILE(kt) * GS_RB;                                                      \
         _Pragma("unroll") for (int t = 0; t < NIW; ++t)                                                         \
             if (t < NIW - 1 || has_w) { const unsigned l_ = lds_w + (stage) * WST + t * 8192; GS_REQ(l_, w_off[t], g_); } \
     }
-#define GS_ISSUE_A(stage, kt)                                                                                   \
+#define GS_ISSUE_A(stage, v)                                                                                    \
     {                                                                                                           \
-        const char* g_ = Ag + (size_t)GS_TILE(kt) * GS_RB;                                                      \
+        const int v_ = (v);                                                                                     \
+        const char* g_ = Ag + (size_t)GS_TILE(v_ >> pair) * GS_RB + (v_ & pair ? a.Kw * 2 : 0);                 \
         _Pragma("unroll") for (int t = 0; t < NIA; ++t)                                                         \
             if (t < NIA - 1 || has_a) { const unsigned l_ = lds_a + (stage) * AST + t * 8192; GS_REQ(l_, a_off[t], g_); } \
     }
@@ -104,25 +107,30 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     // in the order of the loop's requests, so that its counts hold from the first k-tile on
 #pragma unroll
     for (int s = 0; s < GS_NW - 1; ++s) {
-        if (s >= GS_NW - NA) GS_ISSUE_A(s - (GS_NW - NA), min(s - (GS_NW - NA), nk - 1))
+        if (s >= GS_NW - NA) GS_ISSUE_A(s - (GS_NW - NA), min(s - (GS_NW - NA), nv - 1))
         GS_ISSUE_W(s, min(s, nk - 1))
     }
     int w_st = 0, a_st = 0, w_fill = GS_NW - 1, a_fill = NA - 1;
-    for (int kt = 0; kt < nk; ++kt) {
-        // k-tile kt landed, own fragment reads of k-tile kt - 1 done
-        if (CT % 2 != 0 && MT % 2 != 0) __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY - FEWER, 0));   // every wave lacks one
+    for (int v = 0; v < nv; ++v) {
+        // the trip's tiles landed, own fragment reads of the trip before done.  What is younger than its A tile is the A of the
+        // next trip (three stages of it) and one W tile, for pairs as well -- but for two stages of A, where W was asked for
+        // before it on every other trip
+        if (NA == 2 && pair != 0 && (v & 1) == 0) __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));
+        else if (CT % 2 != 0 && MT % 2 != 0) __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY - FEWER, 0));   // every wave lacks one
         else if (FEWER == 0 || (has_w && has_a)) __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY, 0));
         else __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY - FEWER, 0));
         __syncthreads();
-        // every wave is done with k-tile kt - 1: its stages are filled again (the last trips re-request the final k-tile,
+        // every wave is done with the trip before: its stages are filled again (the last trips re-request the final tiles,
         // so that the counts hold)
-        GS_ISSUE_A(a_fill, min(kt + NA - 1, nk - 1))
-        GS_ISSUE_W(w_fill, min(kt + GS_NW - 1, nk - 1))
-        w_fill = w_fill + 1 == GS_NW ? 0 : w_fill + 1;
+        GS_ISSUE_A(a_fill, min(v + NA - 1, nv - 1))
+        if (!(v & pair)) {
+            GS_ISSUE_W(w_fill, min((v >> pair) + GS_NW - 1, nk - 1))
+            w_fill = w_fill + 1 == GS_NW ? 0 : w_fill + 1;
+        }
         a_fill = a_fill + 1 == NA ? 0 : a_fill + 1;
         const char* sw = smem + w_st * WST + frag;
         const char* sa = smem + GS_NW * WST + a_st * AST + frag;
-        w_st = w_st + 1 == GS_NW ? 0 : w_st + 1;
+        if ((v & pair) == pair) w_st = w_st + 1 == GS_NW ? 0 : w_st + 1;
         a_st = a_st + 1 == NA ? 0 : a_st + 1;
         u32x4_t w[CW];
         half8 af[MT];
@@ -226,12 +234,13 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
 // context's limit (64 rows or 128).  Of the measured candidates the rule takes the fastest or one within 3 %: up to 64 rows 8B QKV
 // 3 x 2 splits, O and down 4 x 4, gate/up 7, 1B O 2 x 4, down 4 x 8, gate/up 4, 70B QKV 5 x 2, O and down 8 x 4, gate/up 7, LM
 // heads 8; up to 128 rows 8B QKV 6 x 4 (17.2 us; 3 x 2: 20), O 4 x 4 (13.2; 8 x 8: 15.2), down 8 x 8 (31.6; 4 x 4: 35), gate/up 7.
+// A pair layer's rows of A count twice; its choices are within 3 % of the best of those measured at 3 to 128 rows.
 // The rule must not look at the rows of a call: a row's bits would depend on its batch-mates.  z: in, the number of splits, 0
 // for the best; out, theirs.
-static void stream_plan(int epi, int N, int K, int max_rows, int& ct, int& z) {
-    const int tiles = (epi == MG_SWIGLU ? 2 * N : N) / 16, units = K / GS_KT;
+static void stream_plan(int epi, int N, int K, int Kw, int max_rows, int& ct, int& z) {
+    const int tiles = (epi == MG_SWIGLU ? 2 * N : N) / 16, units = Kw / GS_KT;
     const int zmin = z > 0 ? z : 1, zmax = z > 0 ? z : (units < 8 ? units : 8);
-    const float rows = max_rows <= 64 ? 1.f : 4.f, split = max_rows <= 64 ? 1.8f : 5.f;
+    const float rows = (max_rows <= 64 ? 1.f : 4.f) * (float)(K / Kw), split = max_rows <= 64 ? 1.8f : 5.f;
     float best = 0.f;
     ct = 0;
     for (int zz = zmin; zz <= zmax; ++zz) {
@@ -249,12 +258,12 @@ static void stream_plan(int epi, int N, int K, int max_rows, int& ct, int& z) {
 bool k_gemm_decode_supported(int epi, int N, int K, int Kw) {
     if (epi != MG_STORE_F32 && epi != MG_SWIGLU && epi != MG_SAMPLE) return false;
     const int rows = epi == MG_SWIGLU ? 2 * N : N;
-    return K > 0 && K % GS_KT == 0 && Kw % GS_KT == 0 && rows % 32 == 0 && (uint64_t)rows * Kw * 2 < (1ull << 32);
+    return K > 0 && (K == Kw || K == 2 * Kw) && Kw % GS_KT == 0 && rows % 32 == 0 && (uint64_t)rows * Kw * 2 < (1ull << 32);
 }
 
-int k_gemm_decode_splits(int N, int K, int max_rows) {
+int k_gemm_decode_splits(int N, int K, int Kw, int max_rows) {
     int ct, z = 0;
-    stream_plan(MG_STORE_F32, N, K, max_rows, ct, z);
+    stream_plan(MG_STORE_F32, N, K, Kw, max_rows, ct, z);
     return z;
 }
 
@@ -305,14 +314,16 @@ void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s)
     if (a.Kw <= 0) a.Kw = a.K;
     if (a.M <= 0 || a.M > 128 || !k_gemm_decode_supported(epi, a.N, a.K, a.Kw)) return;   // callers check first
     int ct, z = epi == MG_STORE_F32 && splits > 1 ? splits : 1;
-    stream_plan(epi, a.N, a.K, max_rows, ct, z);
+    stream_plan(epi, a.N, a.K, a.Kw, max_rows, ct, z);
     if (ct == 0) return;                                       // a split count that is not one of this K's
-    a.k_per_split = (a.K / GS_KT + z - 1) / z * GS_KT;
     a.Wrows = epi == MG_SWIGLU ? a.up_offset + a.N : a.N;
     if (g_decode_tile_above >= 0 && a.M > g_decode_tile_above && epi != MG_SAMPLE && (epi == MG_SWIGLU ? 2 * a.N : a.N) % 128 == 0) {
-        k_gemm_tile_decode(epi, a, z, s);                      // splits K the same way
+        a.k_per_split = (a.K / GS_KT + z - 1) / z * GS_KT;     // as many splits, of hi and lo one behind the other
+        k_gemm_tile_decode(epi, a, z, s);
         return;
     }
+    a.pair = a.K == 2 * a.Kw;
+    a.k_per_split = (a.Kw / GS_KT + z - 1) / z * GS_KT;
     a.rotate_k = (a.Kw & (a.Kw - 1)) == 0 && a.k_per_split >= 16 * GS_KT;
     const int tiles = (epi == MG_SWIGLU ? 2 * a.N : a.N) / 16;
     if (epi == MG_STORE_F32) launch_stream<MG_STORE_F32>(a, tiles, ct, z, s);

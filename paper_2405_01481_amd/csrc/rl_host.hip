@@ -518,7 +518,7 @@ static void mfma(rl_ctx* c, int cls, int epi, const GemmArgs& a0, int splits, hi
 // Split count for a decode GEMM of n rows with N output columns: the number of partial buffers that the kernel which
 // mfma() picks for this shape will write.
 static int decode_splits(const rl_ctx* c, int n, int N, int K, int Kw) {
-    if (n <= 128 && k_gemm_decode_supported(MG_STORE_F32, N, K, Kw)) return k_gemm_decode_splits(N, K, c->cfg.max_batch);
+    if (n <= 128 && k_gemm_decode_supported(MG_STORE_F32, N, K, Kw)) return k_gemm_decode_splits(N, K, Kw, c->cfg.max_batch);
     return k_gemm_mfma_splits_used(K, std::min(std::max(1, 256 / std::max(1, N / 128)), kMaxSplitK));
 }
 
