@@ -46,7 +46,13 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // is known), so that a page's loads wait for no index load; with up to 8 waves per workgroup short contexts need no
 // splits and no merge kernel.  32 rows, 8 kv heads, 200 keys, head_dim 64: 2 splits x 4 waves + merge 12.8 us, 8 waves
 // 7.0 us; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
-template <int HD, int PT, bool SP, bool FU, int NW>
+// ST: the cache is read as non-temporal (k_attn_decode).
+template <typename V, bool ST>
+__device__ __forceinline__ V kv_load(const f16_t* p) {
+    if constexpr (ST) return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+    else return *reinterpret_cast<const V*>(p);
+}
+template <int HD, int PT, bool SP, bool FU, int NW, bool ST>
 __global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(DecodeAttnArgs a) {
     static_assert(!(SP && FU), "the pair layers keep the separate consumer kernel");
     static_assert(PT == 16, "page tile is one 16-row MFMA block");
@@ -137,12 +143,12 @@ __global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(Decode
 #define AD_FETCH(pg)                                                                                             \
     {                                                                                                            \
         _Pragma("unroll") for (int s = 0; s < KS; ++s) {                                                         \
-            kn[s] = *reinterpret_cast<const half8*>(kbase + (pg) * page_stride + s * 32);                        \
-            if (SP) knl[s] = *reinterpret_cast<const half8*>(kbase + lo_off + (pg) * page_stride + s * 32);      \
+            kn[s] = kv_load<half8, ST>(kbase + (pg) * page_stride + s * 32);                                     \
+            if (SP) knl[s] = kv_load<half8, ST>(kbase + lo_off + (pg) * page_stride + s * 32);                   \
         }                                                                                                        \
         _Pragma("unroll") for (int d = 0; d < DB; ++d) {                                                         \
-            vn[d] = *reinterpret_cast<const half4*>(vbase + (pg) * page_stride + d * 16 * PT);                   \
-            if (SP) vnl[d] = *reinterpret_cast<const half4*>(vbase + lo_off + (pg) * page_stride + d * 16 * PT); \
+            vn[d] = kv_load<half4, ST>(vbase + (pg) * page_stride + d * 16 * PT);                                \
+            if (SP) vnl[d] = kv_load<half4, ST>(vbase + lo_off + (pg) * page_stride + d * 16 * PT);              \
         }                                                                                                        \
     }
     if (p < pend) {
@@ -355,17 +361,17 @@ void k_attn_decode_plan(int max_batch, int Hkv, int mpps, int max_splits, int* w
     *nsplit = std::max(1, std::min(std::min((256 + wgs - 1) / wgs, mpps / 16), max_splits));
 }
 
-template <int HD, bool SP, bool FU>
+template <int HD, bool SP, bool FU, bool ST>
 static void launch_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s) {
     const dim3 grid(B, a.Hkv, nsplit);
-    if (waves == 8) attn_decode_kernel<HD, 16, SP, FU, 8><<<grid, 512, 0, s>>>(a);
-    else attn_decode_kernel<HD, 16, SP, FU, 4><<<grid, 256, 0, s>>>(a);
+    if (waves == 8) attn_decode_kernel<HD, 16, SP, FU, 8, ST><<<grid, 512, 0, s>>>(a);
+    else attn_decode_kernel<HD, 16, SP, FU, 4, ST><<<grid, 256, 0, s>>>(a);
 }
-template <int HD>
+template <int HD, bool ST>
 static void launch_attn_decode_hd(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s) {
-    if (a.split) launch_attn_decode<HD, true, false>(a, B, waves, nsplit, s);
-    else if (a.qkv_part) launch_attn_decode<HD, false, true>(a, B, waves, nsplit, s);
-    else launch_attn_decode<HD, false, false>(a, B, waves, nsplit, s);
+    if (a.split) launch_attn_decode<HD, true, false, ST>(a, B, waves, nsplit, s);
+    else if (a.qkv_part) launch_attn_decode<HD, false, true, ST>(a, B, waves, nsplit, s);
+    else launch_attn_decode<HD, false, false, ST>(a, B, waves, nsplit, s);
     if (nsplit > 1)
         attn_merge_kernel<HD><<<B * a.Hq, HD, 0, s>>>(a.part_o, a.part_ml, a.out, nsplit, a.Hq, a.split);
 }
@@ -373,8 +379,17 @@ static void launch_attn_decode_hd(const DecodeAttnArgs& a, int B, int waves, int
 void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s) {
     if (B <= 0) return;
     if (a.qkv_part && (a.split || !k_attn_decode_consumes_qkv(a.Hq, a.Hkv, a.geo.hd))) return;   // callers check first
-    if (a.geo.hd == 128) launch_attn_decode_hd<128>(a, B, waves, nsplit, s);
-    else launch_attn_decode_hd<64>(a, B, waves, nsplit, s);
+    // Non-temporal where a layer's keys and values of these rows' longest contexts are far more than the L2s hold.  8B width, per
+    // launch: 128 rows, 592 keys (300 MB; the limit 350) 61.6 -> 59.2 us, pair layer 120 -> 105; 32 rows, 1600 keys (200; 280) 44.2 ->
+    // 43.2 and 83.8 -> 80.6.  Shorter ones lose: 70B width, 64 rows, 230 keys (60; 90) 17.1 -> 17.4, 1B 32 rows 7.0 -> 7.6, 3 rows 8.4 -> 9.0.
+    const bool far = (int64_t)B * a.mpps * a.geo.page_elems() * 4 > ((int64_t)128 << 20);
+    if (a.geo.hd == 128) {
+        if (far) launch_attn_decode_hd<128, true>(a, B, waves, nsplit, s);
+        else launch_attn_decode_hd<128, false>(a, B, waves, nsplit, s);
+    } else {
+        if (far) launch_attn_decode_hd<64, true>(a, B, waves, nsplit, s);
+        else launch_attn_decode_hd<64, false>(a, B, waves, nsplit, s);
+    }
 }
 
 // ------------------------------------------------------------------ prefill / scoring: causal attention over packed sequences

@@ -28,6 +28,7 @@ struct GemmArgs {
     int n_blocks_n = 0;         // filled by the launcher
     int k_per_split = 0;        // filled by the launcher
     int rotate_k = 0;           // filled by the launcher (k_gemm_decode)
+    int stream_w = 0;           // filled by the launcher (k_gemm_decode): W is read as non-temporal
     int pair = 0;               // filled by the launcher (k_gemm_decode): A holds pairs, K = 2 Kw
     int up_offset = 0;          // MG_SWIGLU: row of W where the up projection starts
     float* outF = nullptr;      // MG_STORE_F32 (+ split * split_stride) / MG_RESID

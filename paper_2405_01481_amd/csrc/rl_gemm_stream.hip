@@ -85,11 +85,18 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
 #define GS_TILE(kt) (kt0 + ((kt) + rot >= nk ? (kt) + rot - nk : (kt) + rot))
 #define GS_REQ(lds, off, g)                                                                                     \
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(off), "s"(g) : "memory")
+#define GS_REQ_NT(lds, off, g)                                                                                  \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" :: "s"(lds), "v"(off), "s"(g) : "memory")
 #define GS_ISSUE_W(stage, kt)                                                                                   \
     {                                                                                                           \
         const char* g_ = Wg + (size_t)GS_TILE(kt) * GS_RB;                                                      \
-        _Pragma("unroll") for (int t = 0; t < NIW; ++t)                                                         \
-            if (t < NIW - 1 || has_w) { const unsigned l_ = lds_w + (stage) * WST + t * 8192; GS_REQ(l_, w_off[t], g_); } \
+        if (a.stream_w) {                                                                                       \
+            _Pragma("unroll") for (int t = 0; t < NIW; ++t)                                                     \
+                if (t < NIW - 1 || has_w) { const unsigned l_ = lds_w + (stage) * WST + t * 8192; GS_REQ_NT(l_, w_off[t], g_); } \
+        } else {                                                                                                \
+            _Pragma("unroll") for (int t = 0; t < NIW; ++t)                                                     \
+                if (t < NIW - 1 || has_w) { const unsigned l_ = lds_w + (stage) * WST + t * 8192; GS_REQ(l_, w_off[t], g_); } \
+        }                                                                                                       \
     }
 #define GS_ISSUE_A(stage, v)                                                                                    \
     {                                                                                                           \
@@ -152,6 +159,7 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
 #undef GS_ISSUE_A
 #undef GS_ISSUE_W
 #undef GS_REQ
+#undef GS_REQ_NT
 #undef GS_TILE
     // the four waves along k meet in LDS, IB row tiles at a time; tile (i, j) of lane (r, q): column r, rows 4 q .. 4 q + 3
     floatx4* const red = reinterpret_cast<floatx4*>(smem);
@@ -323,6 +331,11 @@ void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s)
         return;
     }
     a.pair = a.K == 2 * a.Kw;
+    // Weights pass through the caches once; those that are well beyond the eight L2s together (32 MB) are read as non-temporal: 8B
+    // gate/up 42.4 -> 38.9 us at 32 rows, down 22.5 -> 20.9, LM head 192 -> 186 (180 -> 166 at 3 rows), 70B gate/up 168 -> 152, down 89
+    // -> 78, QKV 33.4 -> 31.2 at 64 rows, 1B gate/up (67 MB) 14.3 -> 13.8 at 32.  Below that they are slower: 8B QKV (50 MB) at 128 rows
+    // in a step 18.8 -> 21.2, O (34 MB) 13.3 -> 14.0.
+    a.stream_w = (int64_t)a.Wrows * a.Kw * 2 > ((int64_t)60 << 20);
     a.k_per_split = (a.Kw / GS_KT + z - 1) / z * GS_KT;
     a.rotate_k = (a.Kw & (a.Kw - 1)) == 0 && a.k_per_split >= 16 * GS_KT;
     const int tiles = (epi == MG_SWIGLU ? 2 * a.N : a.N) / 16;
