@@ -15,6 +15,8 @@
 // Epilogues: fp32 store / split-K partial, residual add, SwiGLU, RoPE + q/k/v split for
 // the QKV projection, log-sum-exp + target gather for the scoring LM head; mg_epilogue for the first kernel, d8_half for
 // the second and third.  Both round alike: a row's results do not depend on which of them its GEMM's size picks.
+#include <type_traits>
+
 #include "rl_common.h"
 #include "rl_gemm.h"
 #include "rl_gemm_dev.h"
@@ -634,7 +636,7 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
 #define X8_LOAD(st, kt, l)                                                                                      \
     {                                                                                                           \
-        const int kt_ = min((kt), nk - 1);                                                                      \
+        const int kt_ = (kt);                                                                                   \
         const unsigned sa_ = lds_base + (st) * STAGE + ((l) >= LPA ? BM * 64 : 0) + X8_BLOCK(l) * 1024;         \
         const char* g_ = (l) < LPA ? Ag + (size_t)kt_ * 64 : Wg + (size_t)wrap_k(kt_, nkw) * 64;                \
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                            \
@@ -660,12 +662,14 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
     // of staging loads behind the last quarter.  With MI = 8: reads behind MFMAs 0, 2, 4, 6 / 0 - 3 and 4, 6, 8, 10,
     // conversions behind 8 - 15, loads behind 12, 14.  The MFMAs walk the row blocks back and forth, so that each shares an
     // operand with the one before it: 0.3 - 0.7 % on whole passes (8B width, 4000 to 16384 rows), where power sets the pace.
-#define X8_SLICE(AS, WS, NSO, LOADS, LB, PT, PS0, PS1)                                                          \
+#define X8_SLICE(AS, WS, NSO, LOADS, LB, PT, PS0, PS1) X8_SLICE_(AS, WS, true, NSO, LOADS, LB, PT, PS0, PS1)
+#define X8_SLICE_(AS, WS, READS, NSO, LOADS, LB, PT, PS0, PS1)                                                  \
     _Pragma("unroll") for (int q = 0; q < 4 * ((AS) ? MI1 : MI0); ++q) {                                        \
         constexpr int NI_ = (AS) ? MI1 : MI0, NQ_ = 4 * NI_;                                                    \
         const int j_ = q / NI_, i_ = (j_ & 1) ? NI_ - 1 - q % NI_ : q % NI_;                                    \
         acc[(AS) * MI0 + i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, wf[WS][j_]), af[AS][i_], acc[(AS) * MI0 + i_][j_], 0, 0, 0); \
-        if ((AS) == 0) {                                                                                        \
+        if (!(READS)) {                                                                                         \
+        } else if ((AS) == 0) {                                                                                 \
             _Pragma("unroll") for (int u_ = 0; u_ < MI1; ++u_)                                                  \
                 if (u_ * (NQ_ / 2) / MI1 == q) af[1][u_] = X8_LDA(NSO, MI0 + u_);                               \
         } else {                                                                                                \
@@ -706,16 +710,16 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
 #pragma unroll
         for (int c = 0; c < 4; ++c) wf[0][j][c] = WF16 ? w_[c] : X8_CVT2(w_[c]);
     }
-    for (int kt = 0; kt < nk; kt += 2) {
+    // Even k-tile kt (W set 0): slice 0, barrier (tile kt+1 complete, stage of tile kt released after this slice's reads), slice 1
+    // with the first loads of pair (kt+4, kt+5); odd k-tile kt+1 (W set 1) alike, its barrier completing tile kt+2.
+    int kt = 0;
+    for (; kt < nk - 4; kt += 2) {
         const int o0 = s0 * STAGE, o1 = s1 * STAGE, o2 = s2 * STAGE;
-        // even k-tile kt (W set 0): slice 0, barrier (tile kt+1 complete, stage of tile kt released after this
-        // slice's reads), slice 1 with the first loads of pair (kt+4, kt+5)
         X8_SLICE(0, 0, o0, 0, 0, 0, 0, 0)
         __builtin_amdgcn_s_waitcnt(dma_waitcnt(2 * LPT, 0));
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
         X8_SLICE(1, 0, o1, LPT - 2, 0, kt + 4, s4, s0)
-        // odd k-tile kt+1 (W set 1)
         X8_SLICE(0, 1, o1, 1, LPT - 2, kt + 4, s4, s0)
         __builtin_amdgcn_s_waitcnt(dma_waitcnt(2 * (LPT - 1) + 1, 0));
         __syncthreads();
@@ -724,13 +728,36 @@ __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, i
         const int t0 = s0, t1 = s1;
         s0 = s2; s1 = s3; s2 = s4; s3 = t0; s4 = t1;
     }
-    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 15));   // nothing may land in LDS after this point
+    // The last four k-tiles, nothing left to ask for (asking for the final tile again, to keep one form of the trip, leaves a
+    // memory latency between the last MFMAs and the epilogue).  Behind tile nk - 2 only its pair's last load is younger.
+    {
+        const int o0 = s0 * STAGE, o1 = s1 * STAGE, o2 = s2 * STAGE, o3 = s3 * STAGE;
+        X8_SLICE(0, 0, o0, 0, 0, 0, 0, 0)
+        __builtin_amdgcn_s_waitcnt(dma_waitcnt(2 * LPT, 0));
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        X8_SLICE(1, 0, o1, 0, 0, 0, 0, 0)
+        X8_SLICE(0, 1, o1, 0, 0, 0, 0, 0)
+        __builtin_amdgcn_s_waitcnt(dma_waitcnt(1, 0));
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        X8_SLICE(1, 1, o2, 0, 0, 0, 0, 0)
+        X8_SLICE(0, 0, o2, 0, 0, 0, 0, 0)
+        __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        X8_SLICE(1, 0, o3, 0, 0, 0, 0, 0)
+        X8_SLICE(0, 1, o3, 0, 0, 0, 0, 0)
+        X8_SLICE_(1, 1, false, 0, 0, 0, 0, 0, 0)
+    }
+    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));    // nothing is on its way to LDS
 #undef X8_LOAD
 #undef X8_BLOCK
 #undef X8_CVT2
 #undef X8_LDA
 #undef X8_LDW
 #undef X8_SLICE
+#undef X8_SLICE_
 }
 
 // ---- epilogues of the large-M kernel.  A wave's accumulators pass through its own LDS patch, 64 rows x 64 columns of
@@ -1044,10 +1071,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_ring_kernel(GemmArgs a) {
         else off[t] = (unsigned)(min(w_row_of<EPI, 256>(c0 + row - BM, nb, a), a.Wrows - 1) - min(w_first, a.Wrows - 1)) * (unsigned)a.Kw * 2u + ch;
     }
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
-    // request t of k-tile kt (the last trips ask for the final k-tile again, so that the counts hold)
+    // request t of k-tile kt
 #define RG_ISSUE1(stage, kt, t)                                                                                 \
     {                                                                                                           \
-        const int k_ = min((kt), nk - 1);                                                                       \
+        const int k_ = (kt);                                                                                    \
         const unsigned l_ = lds0 + (stage) * ST + (t) * (NWV * 1024);                                           \
         const char* g_ = ((t) * NWV + wave) * 8 < BM ? Ag + (size_t)k_ * RB : Wg + (size_t)wrap_k(k_, nkw) * RB; \
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(l_), "v"(off[t]), "s"(g_) : "memory"); \
@@ -1066,40 +1093,63 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_ring_kernel(GemmArgs a) {
     if ((u) < 4) wf[set][(u) & 3] = *reinterpret_cast<const half8*>((so) + fw + (u) * 16 * RB + (ch));        \
     else if ((u) < 4 + MI) af[set][(u) < 4 + MI && (u) >= 4 ? (u) - 4 : 0] = *reinterpret_cast<const half8*>((so) + fa + ((u) - 4) * 16 * RB + (ch));
     // 4 MI MFMAs on fragment set `set`; behind them the reads of the other set, and LOADS: the requests of k-tile PT
-#define RG_SLICE(set, so, ch, LOADS, stage, PT)                                                                 \
+#define RG_SLICE(set, READS, so, ch, LOADS, stage, PT)                                                          \
     _Pragma("unroll") for (int n = 0; n < 4 * MI; ++n) {                                                        \
         const int j_ = n / MI, i_ = (j_ & 1) ? MI - 1 - n % MI : n % MI;                                        \
         acc[i_][j_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[set][j_], af[set][i_], acc[i_][j_], 0, 0, 0);   \
         _Pragma("unroll") for (int u = 0; u < 4 + MI; ++u)                                                      \
-            if (u * 4 * MI / (4 + MI) == n) { RG_READ(1 - (set), u, so, ch) }                                   \
+            if ((READS) && u * 4 * MI / (4 + MI) == n) { RG_READ(1 - (set), u, so, ch) }                        \
         _Pragma("unroll") for (int t = 0; t < NI; ++t)                                                          \
             if ((LOADS) && (t * 4 * MI + 2 * MI) / NI == n) { RG_ISSUE1(stage, PT, t) }                         \
         __builtin_amdgcn_sched_barrier(0);                                                                      \
     }
 #pragma unroll
     for (int s = 0; s < S; ++s)
+        if (s < nk) {
 #pragma unroll
-        for (int t = 0; t < NI; ++t) RG_ISSUE1(s, s, t)
+            for (int t = 0; t < NI; ++t) RG_ISSUE1(s, s, t)
+        }
     QkvRowMeta meta;
     if constexpr (EPI == MG_QKV) meta = qkv_row_meta(a, m0 + wm * MI * 16, lane);
-    __builtin_amdgcn_s_waitcnt(dma_waitcnt(EPI == MG_QKV ? 0 : NI * (S - 1), 15));
+    if (EPI == MG_QKV || nk < S) __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 15));
+    else __builtin_amdgcn_s_waitcnt(dma_waitcnt(NI * (S - 1), 15));
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 4 + MI; ++u) { RG_READ(0, u, smem, ch0) }
-    int st = 0;
-    for (int kt = 0; kt < nk; ++kt) {
+    int st = 0, kt = 0;
+    // k-tile kt: its first 32 k, barrier (k-tile kt + 1 landed; every wave has read its fragments of k-tile kt, whose stage is
+    // free), its second 32 k
+    for (; kt < nk - S; ++kt) {
         const int nx = st + 1 == S ? 0 : st + 1;
-        RG_SLICE(0, smem + st * ST, ch1, false, 0, 0)
-        // k-tile kt + 1 landed; every wave has read its fragments of k-tile kt, whose stage is filled again
+        RG_SLICE(0, true, smem + st * ST, ch1, false, 0, 0)
         __builtin_amdgcn_s_waitcnt(dma_waitcnt(NI * (S - 2), 0));
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
-        RG_SLICE(1, smem + nx * ST, ch0, true, st, kt + S)
+        RG_SLICE(1, true, smem + nx * ST, ch0, true, st, kt + S)
         st = nx;
     }
+    // the last S, all requested: r k-tiles behind this one.  With fewer than S in all everything has landed
+    auto tail = [&](auto rc) __attribute__((always_inline)) {
+        constexpr int r = decltype(rc)::value;
+        if (r >= S || nk <= r) return;
+        const int nx = st + 1 == S ? 0 : st + 1;
+        RG_SLICE(0, true, smem + st * ST, ch1, false, 0, 0)
+        if (r > 0) {
+            __builtin_amdgcn_s_waitcnt(dma_waitcnt(r > 0 ? NI * (r - 1) : 0, 0));
+            __syncthreads();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        RG_SLICE(1, r > 0, smem + nx * ST, ch0, false, 0, 0)
+        st = nx;
+    };
+    static_assert(S <= 8, "tails written out below");
+    tail(std::integral_constant<int, 7>{}); tail(std::integral_constant<int, 6>{});
+    tail(std::integral_constant<int, 5>{}); tail(std::integral_constant<int, 4>{});
+    tail(std::integral_constant<int, 3>{}); tail(std::integral_constant<int, 2>{});
+    tail(std::integral_constant<int, 1>{}); tail(std::integral_constant<int, 0>{});
 #undef RG_READ
 #undef RG_SLICE
-    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));      // nothing may land in LDS after this point
+    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));      // nothing is on its way to LDS
 #undef RG_ISSUE1
     __syncthreads();
     float* const patch = reinterpret_cast<float*>(smem) + wave * (16 * MI * PATCH_LD);

@@ -23,6 +23,8 @@
 // Against a kernel on 128 x 128 tiles with k-tiles of 64 (which it replaced), per launch: 8B at 3 rows QKV 12.8 -> 10.4 us, O 9.8
 // -> 8, gate/up 52 -> 40, down 23 -> 21, LM head 222 -> 177; at 128 rows 18.1 -> 17.3, 15.3 -> 14, 58 -> 54.5, 33.5 -> 33.5, 227 ->
 // 230; 1B at 32 rows 8.2 -> 5.3, 7.0 -> 4.2, 21.7 -> 13.9, 11.3 -> 9.3; 70B (bf16) at 64 rows 38 -> 33, 38 -> 29.5, 171 -> 170, 84 -> 82.
+#include <type_traits>
+
 #include "rl_common.h"
 #include "rl_gemm.h"
 #include "rl_gemm_dev.h"
@@ -46,12 +48,9 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     constexpr int WST = CT * 16 * GS_RB, AST = MT * 16 * GS_RB;               // bytes of a stage
     constexpr int NBW = CT * 4, NBA = MT * 4;                                 // its 1 KB requests: 4 rows x 256 B each
     constexpr int NIW = (NBW + 7) / 8, NIA = (NBA + 7) / 8;                   // per wave; odd tile counts: half of the waves one fewer
-    // what may be in flight when a k-tile is read: its younger siblings, W of GS_NW - 2 k-tiles and A of NA - 2
-    constexpr int FLY_W = GS_NW - 2, FLY_A = NA - 2, FLY = NIW * FLY_W + NIA * FLY_A;
-    constexpr int FEWER = (CT % 2 != 0 && MT % 2 != 0) ? FLY_W : CT % 2 != 0 ? FLY_W : MT % 2 != 0 ? FLY_A : 0;
     constexpr int IB = MT * CT * GS_WK * 1024 <= gs_lds(MT, CT) ? MT : MT / 2;   // row tiles per exchange at the end
     static_assert(IB * CT * GS_WK * 1024 <= gs_lds(MT, CT), "the exchange reuses the stages");
-    static_assert(MT % 2 == 0 || (MT == 1 && FLY_A == FLY_W), "one odd A tile, in flight as long as W's");
+    static_assert(MT % 2 == 0 || MT == 1, "one odd A tile");
     extern __shared__ __attribute__((aligned(1024))) char smem[];            // [GS_NW][W tiles] [NA][A tiles]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, q = lane >> 4, wk = wave % GS_WK, wn = wave / GS_WK;
@@ -114,24 +113,32 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     // in the order of the loop's requests, so that its counts hold from the first k-tile on
 #pragma unroll
     for (int s = 0; s < GS_NW - 1; ++s) {
-        if (s >= GS_NW - NA) GS_ISSUE_A(s - (GS_NW - NA), min(s - (GS_NW - NA), nv - 1))
-        GS_ISSUE_W(s, min(s, nk - 1))
+        if (s >= GS_NW - NA && s - (GS_NW - NA) < nv) GS_ISSUE_A(s - (GS_NW - NA), s - (GS_NW - NA))
+        if (s < nk) GS_ISSUE_W(s, s)
     }
     int w_st = 0, a_st = 0, w_fill = GS_NW - 1, a_fill = NA - 1;
+    // at most w tiles of W and at most `as` of A on their way; waves with one request fewer than others count theirs
+    auto wait = [&](auto wc, auto ac) {
+        constexpr int w = decltype(wc)::value, as = decltype(ac)::value, all = NIW * w + NIA * as;
+        if (CT % 2 != 0 && MT % 2 != 0) __builtin_amdgcn_s_waitcnt(dma_waitcnt(all - (w > as ? w : as), 0));   // every wave lacks one of either
+        else if ((w == 0 || CT % 2 == 0 || has_w) && (as == 0 || MT % 2 == 0 || has_a)) __builtin_amdgcn_s_waitcnt(dma_waitcnt(all, 0));
+        else __builtin_amdgcn_s_waitcnt(dma_waitcnt(all - (CT % 2 != 0 ? w : 0) - (MT % 2 != 0 ? as : 0), 0));
+    };
+    constexpr std::integral_constant<int, 0> none{};
+    constexpr std::integral_constant<int, GS_NW - 2> fly_w{};
+    constexpr std::integral_constant<int, NA - 2> fly_a{};
     for (int v = 0; v < nv; ++v) {
-        // the trip's tiles landed, own fragment reads of the trip before done.  What is younger than its A tile is the A of the
-        // next trip (three stages of it) and one W tile, for pairs as well -- but for two stages of A, where W was asked for
-        // before it on every other trip
-        if (NA == 2 && pair != 0 && (v & 1) == 0) __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));
-        else if (CT % 2 != 0 && MT % 2 != 0) __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY - FEWER, 0));   // every wave lacks one
-        else if (FEWER == 0 || (has_w && has_a)) __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY, 0));
-        else __builtin_amdgcn_s_waitcnt(dma_waitcnt(FLY - FEWER, 0));
+        // the trip's tiles landed, own fragment reads of the trip before done.  What may still be on its way is younger than the
+        // trip's A tile: the A of the next trip (with three stages of it) and one tile of W; nothing behind the last ones.  Pairs ask
+        // for W on every other trip: none is young two trips before the end, nor with two stages of A on even trips
+        if (v + 1 == nv) wait(none, none);
+        else if (pair && (v + 3 >= nv || (NA == 2 && (v & 1) == 0))) wait(none, fly_a);
+        else wait(fly_w, fly_a);
         __syncthreads();
-        // every wave is done with the trip before: its stages are filled again (the last trips re-request the final tiles,
-        // so that the counts hold)
-        GS_ISSUE_A(a_fill, min(v + NA - 1, nv - 1))
+        // every wave is done with the trip before: its stages are filled again
+        if (v + NA - 1 < nv) GS_ISSUE_A(a_fill, v + NA - 1)
         if (!(v & pair)) {
-            GS_ISSUE_W(w_fill, min((v >> pair) + GS_NW - 1, nk - 1))
+            if ((v >> pair) + GS_NW - 1 < nk) GS_ISSUE_W(w_fill, (v >> pair) + GS_NW - 1)
             w_fill = w_fill + 1 == GS_NW ? 0 : w_fill + 1;
         }
         a_fill = a_fill + 1 == NA ? 0 : a_fill + 1;
@@ -155,7 +162,7 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
             }
         }
     }
-    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));             // nothing may land in LDS from here on
+    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));             // fragment reads done; nothing is on its way to LDS
 #undef GS_ISSUE_A
 #undef GS_ISSUE_W
 #undef GS_REQ
