@@ -17,7 +17,7 @@
 //     split over Z workgroups whose partial sums the consumer reduces (stream_plan).
 // Eight waves: four along the k-tile (32 k each), two along the columns, so that every W fragment is read, and on bf16
 // weights converted, by one wave only; each wave holds all MT x 16 rows.  The four partial accumulators meet in LDS after
-// the loop, in wave order.  Three stages (above 64 rows two of A: LDS is full), one barrier per k-tile; the loads are issued
+// the loop, in wave order.  Three stages (above 64 rows two of A: LDS is full; four of small tiles, gs_nw), one barrier per k-tile; the loads are issued
 // from inline assembly (the compiler would wait for them at every barrier) and counted by hand: two k-tiles of W are in
 // flight while one is consumed.
 // Against a kernel on 128 x 128 tiles with k-tiles of 64 (which it replaced), per launch: 8B at 3 rows QKV 12.8 -> 10.4 us, O 9.8
@@ -31,9 +31,12 @@
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-static constexpr int GS_KT = 128, GS_RB = 256, GS_WK = 4, GS_NW = 3;      // k-tile, its bytes per row, waves along k, stages of W
-static constexpr int gs_na(int MT) { return MT == 8 ? 2 : 3; }             // stages of A
-static constexpr int gs_lds(int MT, int CT) { return (GS_NW * CT + gs_na(MT) * MT) * 16 * GS_RB; }
+static constexpr int GS_KT = 128, GS_RB = 256, GS_WK = 4;                 // k-tile, its bytes per row, waves along k
+// Stages of W and of A.  Tiles of up to 6 x 16 rows of A and W together ask for three k-tiles at a time: a split of the 1B shape has
+// four in all (O at 32 rows 4.5 -> 4.4 us, down 8.7 -> 8.5; 8B O 8.3 -> 8.0; QKV 5.3 -> 5.4).  More in flight is nothing to larger tiles.
+static constexpr int gs_nw(int MT, int CT) { return MT < 8 && MT + CT <= 6 ? 4 : 3; }
+static constexpr int gs_na(int MT, int CT) { return MT == 8 ? 2 : gs_nw(MT, CT); }
+static constexpr int gs_lds(int MT, int CT) { return (gs_nw(MT, CT) * CT + gs_na(MT, CT) * MT) * 16 * GS_RB; }
 
 // Row of W behind row rr of the 16-row tile t.  MG_SWIGLU: 8 gate rows and the 8 up rows of the same columns.
 template <int EPI>
@@ -44,14 +47,14 @@ __device__ __forceinline__ int stream_w_row(int t, int rr, const GemmArgs& a) {
 
 template <int EPI, int MT, int CT, bool WF16>
 __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm_stream_kernel(GemmArgs a) {
-    constexpr int WN = 8 / GS_WK, CW = (CT + WN - 1) / WN, NA = gs_na(MT);
+    constexpr int WN = 8 / GS_WK, CW = (CT + WN - 1) / WN, NW = gs_nw(MT, CT), NA = gs_na(MT, CT);
     constexpr int WST = CT * 16 * GS_RB, AST = MT * 16 * GS_RB;               // bytes of a stage
     constexpr int NBW = CT * 4, NBA = MT * 4;                                 // its 1 KB requests: 4 rows x 256 B each
     constexpr int NIW = (NBW + 7) / 8, NIA = (NBA + 7) / 8;                   // per wave; odd tile counts: half of the waves one fewer
     constexpr int IB = MT * CT * GS_WK * 1024 <= gs_lds(MT, CT) ? MT : MT / 2;   // row tiles per exchange at the end
     static_assert(IB * CT * GS_WK * 1024 <= gs_lds(MT, CT), "the exchange reuses the stages");
     static_assert(MT % 2 == 0 || MT == 1, "one odd A tile");
-    extern __shared__ __attribute__((aligned(1024))) char smem[];            // [GS_NW][W tiles] [NA][A tiles]
+    extern __shared__ __attribute__((aligned(1024))) char smem[];            // [NW][W tiles] [NA][A tiles]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, q = lane >> 4, wk = wave % GS_WK, wn = wave / GS_WK;
     const int t0 = blockIdx.x * CT;                            // first 16-row tile of W
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
         a_off[t] = (unsigned)min(row, a.M - 1) * (unsigned)a.lda * 2u + (unsigned)((lane & 15) ^ (row & 15)) * 16u;
     }
     const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
-    const unsigned lds_a = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + GS_NW * WST + wa * 1024;
+    const unsigned lds_a = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + NW * WST + wa * 1024;
     const char* const Ag = reinterpret_cast<const char*>(a.A);
     const char* const Wg = reinterpret_cast<const char*>(a.W);
 #define GS_TILE(kt) (kt0 + ((kt) + rot >= nk ? (kt) + rot - nk : (kt) + rot))
@@ -112,11 +115,11 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     const int frag = r * GS_RB + (((wk * 4 + q) ^ r) * 16);    // this lane's 16 bytes of a 16-row tile
     // in the order of the loop's requests, so that its counts hold from the first k-tile on
 #pragma unroll
-    for (int s = 0; s < GS_NW - 1; ++s) {
-        if (s >= GS_NW - NA && s - (GS_NW - NA) < nv) GS_ISSUE_A(s - (GS_NW - NA), s - (GS_NW - NA))
+    for (int s = 0; s < NW - 1; ++s) {
+        if (s >= NW - NA && s - (NW - NA) < nv) GS_ISSUE_A(s - (NW - NA), s - (NW - NA))
         if (s < nk) GS_ISSUE_W(s, s)
     }
-    int w_st = 0, a_st = 0, w_fill = GS_NW - 1, a_fill = NA - 1;
+    int w_st = 0, a_st = 0, w_fill = NW - 1, a_fill = NA - 1;
     // at most w tiles of W and at most `as` of A on their way; waves with one request fewer than others count theirs
     auto wait = [&](auto wc, auto ac) {
         constexpr int w = decltype(wc)::value, as = decltype(ac)::value, all = NIW * w + NIA * as;
@@ -125,26 +128,35 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
         else __builtin_amdgcn_s_waitcnt(dma_waitcnt(all - (CT % 2 != 0 ? w : 0) - (MT % 2 != 0 ? as : 0), 0));
     };
     constexpr std::integral_constant<int, 0> none{};
-    constexpr std::integral_constant<int, GS_NW - 2> fly_w{};
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, NW - 2> fly_w{};
     constexpr std::integral_constant<int, NA - 2> fly_a{};
     for (int v = 0; v < nv; ++v) {
         // the trip's tiles landed, own fragment reads of the trip before done.  What may still be on its way is younger than the
-        // trip's A tile: the A of the next trip (with three stages of it) and one tile of W; nothing behind the last ones.  Pairs ask
-        // for W on every other trip: none is young two trips before the end, nor with two stages of A on even trips
+        // trip's A tile: A of the next NA - 2 trips and as many tiles of W (one with two stages of A); nothing behind the last ones.
+        // Pairs ask for W on every other trip, so that one is young at most (fewer are waited for than could be on some trips),
+        // none near the end, nor with two stages of A on even trips
         if (v + 1 == nv) wait(none, none);
-        else if (pair && (v + 3 >= nv || (NA == 2 && (v & 1) == 0))) wait(none, fly_a);
-        else wait(fly_w, fly_a);
+        else if (!pair) {
+            if (NW == 4 && v + 2 == nv) wait(one, one);
+            else wait(fly_w, fly_a);
+        } else if (NA == 4) {
+            if (v + 2 == nv) wait(none, one);
+            else if (v + 6 > nv) wait(none, fly_a);
+            else wait(one, fly_a);
+        } else if (v + 3 >= nv || (NA == 2 && (v & 1) == 0)) wait(none, fly_a);
+        else wait(one, fly_a);
         __syncthreads();
         // every wave is done with the trip before: its stages are filled again
         if (v + NA - 1 < nv) GS_ISSUE_A(a_fill, v + NA - 1)
         if (!(v & pair)) {
-            if ((v >> pair) + GS_NW - 1 < nk) GS_ISSUE_W(w_fill, (v >> pair) + GS_NW - 1)
-            w_fill = w_fill + 1 == GS_NW ? 0 : w_fill + 1;
+            if ((v >> pair) + NW - 1 < nk) GS_ISSUE_W(w_fill, (v >> pair) + NW - 1)
+            w_fill = w_fill + 1 == NW ? 0 : w_fill + 1;
         }
         a_fill = a_fill + 1 == NA ? 0 : a_fill + 1;
         const char* sw = smem + w_st * WST + frag;
-        const char* sa = smem + GS_NW * WST + a_st * AST + frag;
-        if ((v & pair) == pair) w_st = w_st + 1 == GS_NW ? 0 : w_st + 1;
+        const char* sa = smem + NW * WST + a_st * AST + frag;
+        if ((v & pair) == pair) w_st = w_st + 1 == NW ? 0 : w_st + 1;
         a_st = a_st + 1 == NA ? 0 : a_st + 1;
         u32x4_t w[CW];
         half8 af[MT];
