@@ -30,6 +30,7 @@
 #include "rl_gemm_dev.h"
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef f16_t half4 __attribute__((ext_vector_type(4)));
 
 static constexpr int GS_KT = 128, GS_RB = 256, GS_WK = 4;                 // k-tile, its bytes per row, waves along k
 // Stages of W and of A.  Tiles of up to 6 x 16 rows of A and W together ask for three k-tiles at a time: a split of the 1B shape has
@@ -177,8 +178,6 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));             // fragment reads done; nothing is on its way to LDS
 #undef GS_ISSUE_A
 #undef GS_ISSUE_W
-#undef GS_REQ
-#undef GS_REQ_NT
 #undef GS_TILE
     // the four waves along k meet in LDS, IB row tiles at a time; tile (i, j) of lane (r, q): column r, rows 4 q .. 4 q + 3
     floatx4* const red = reinterpret_cast<floatx4*>(smem);
@@ -256,6 +255,201 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
     }
 }
 
+// GEMMs whose weights are more than one round of workgroups (LM heads, gate/up of the 70B width), on tiles of up to 128 rows x 256
+// columns, the whole K each.  What a CU has on its way at once is about 64 KB, of W and A together, so A's bytes cost what W's
+// do: 256 columns read A half as often as 128.  One round of wide tiles also pays once for what a workgroup does alone,
+// its first loads and its epilogue.  Eight waves: two along the k-step of 64 (32 k each), four along the columns, each wave
+// all rows; every W fragment is read, and on bf16 weights converted, by one wave.  As many stages as LDS holds, of which all but
+// one are on their way; no request past the last k-step.  A pair layer's stage holds A's hi and lo rows: W is read once.  Chunks
+// of the 128-byte rows are XOR-swizzled on the source side as above.  At the end the two waves along k each finish half of the
+// row tiles and hand the other half over.  The MFMAs take W first: a lane holds four consecutive columns of a row.
+// Against gemm_stream_kernel (fp16 weights; bf16 within 3 % of it), 3, 32, 64, 128 rows: LM head of the 8B shape 161, 170, 179, 218
+// -> 161, 159, 164, 176 us; of 65536 x 4096 84, 88, 93, 109 -> 85, 84, 85, 87; 70B gate/up 148, 151, 152, 183 -> 144, 143,
+// 145, 153; in a pair layer 147, 160, 186, 282 -> 145, 145, 151, 225.  Where stream_kernel's tiles are one round already it has the same or
+// better times (8B gate/up 128 rows 50.6, on these tiles 69; a 56 x 128 form 51): wide_tiles.
+static constexpr int GW_KT = 64, GW_RB = 128, GW_CT = 16;                // k-step, its bytes per row, column tiles
+static constexpr int gw_stage(int MT, bool PAIR) { return (GW_CT + MT * (PAIR ? 2 : 1)) * 16 * GW_RB; }
+static constexpr int gw_stages(int MT, bool PAIR) { return 160 * 1024 / gw_stage(MT, PAIR); }     // 2 .. 4
+
+template <int EPI, int MT, bool WF16, bool PAIR>
+__global__ __launch_bounds__(512, 2) void gemm_wide_kernel(GemmArgs a) {
+    constexpr int CT = GW_CT, CW = CT / 4, S = gw_stages(MT, PAIR), ST = gw_stage(MT, PAIR);
+    constexpr int NB = ST / 1024, NI = (NB + 7) / 8;           // 1 KB requests of a stage, 8 rows each; per wave
+    constexpr int KEEP = MT > 1 ? MT / 2 : 1;                  // row tiles a wave finishes
+    static_assert(8 * KEEP * CW * 1024 <= S * ST, "the exchange reuses the stages");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];            // [S][W tiles | A tiles | A tiles, lo]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, q = lane >> 4, kh = wave & 1, wn = wave >> 1;
+    const int t0 = blockIdx.x * CT;                            // first 16-row tile of W
+    const int nk = a.Kw / GW_KT;
+    const int rot = a.rotate_k ? (int)((blockIdx.x * 2) % (unsigned)nk) : 0;
+    // request t of a wave fills the 1 KB block t * 8 + wave of a stage; lane -> row + lane / 8, physical chunk lane % 8, which holds
+    // the row's logical chunk (lane % 8) ^ (row / 2 % 8)
+    const bool has_last = NB % 8 == 0 || wave < NB % 8;
+    unsigned off[NI];
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+        const int row = (t * 8 + wave) * 8 + (lane >> 3);      // rows past the end: clamped, never stored
+        const unsigned ch = (unsigned)((lane & 7) ^ ((row >> 1) & 7)) * 16u;
+        if (t * 8 + wave < CT * 2) off[t] = (unsigned)min(stream_w_row<EPI>(t0 + (row >> 4), row & 15, a), a.Wrows - 1) * (unsigned)a.Kw * 2u + ch;
+        else {
+            const int ra = row - CT * 16, m = ra < MT * 16 ? ra : ra - MT * 16;
+            off[t] = (unsigned)min(m, a.M - 1) * (unsigned)a.lda * 2u + (ra < MT * 16 ? 0u : (unsigned)a.Kw * 2u) + ch;
+        }
+    }
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem + wave * 1024;
+    const char* const Ag = reinterpret_cast<const char*>(a.A);
+    const char* const Wg = reinterpret_cast<const char*>(a.W);
+#define GW_ISSUE(stage, k)                                                                                      \
+    {                                                                                                           \
+        const int k_ = (k) + rot;                                                                               \
+        const size_t o_ = (size_t)(k_ >= nk ? k_ - nk : k_) * GW_RB;                                    \
+        _Pragma("unroll") for (int t = 0; t < NI; ++t) {                                                        \
+            const unsigned l_ = lds0 + (stage) * ST + t * 8192;                                                 \
+            if (t < NI - 1 || has_last) {                                                                       \
+                if (t * 8 + wave < CT * 2) {                                                                    \
+                    const char* g_ = Wg + o_;                                                                   \
+                    if (a.stream_w) GS_REQ_NT(l_, off[t], g_);                                                  \
+                    else GS_REQ(l_, off[t], g_);                                                                \
+                } else {                                                                                        \
+                    const char* g_ = Ag + o_;                                                                   \
+                    GS_REQ(l_, off[t], g_);                                                                     \
+                }                                                                                               \
+            }                                                                                                   \
+        }                                                                                                       \
+    }
+    floatx4 acc[MT][CW];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < CW; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s)
+        if (s < nk) GW_ISSUE(s, s)
+    const int frag = r * GW_RB + (((kh * 4 + q) ^ ((r >> 1) & 7)) * 16);     // this lane's 16 bytes of a 16-row tile
+    int st = 0, fill = S - 1;
+    static_assert(S >= 2 && S <= 4, "waits written out below");
+    auto landed = [&](int left, auto uc) __attribute__((always_inline)) {
+        constexpr int u = decltype(uc)::value;
+        if (u > S - 2 || (u == S - 2 ? left < u : left != u)) return;
+        if (has_last) __builtin_amdgcn_s_waitcnt(dma_waitcnt(NI * u, 0));
+        else __builtin_amdgcn_s_waitcnt(dma_waitcnt((NI - 1) * u, 0));
+    };
+    for (int j = 0; j < nk; ++j) {
+        // stage j landed, own fragment reads of the step before done; the steps requested behind it, at most S - 2, may be on their way
+        const int left = nk - 1 - j;
+        landed(left, std::integral_constant<int, 2>{});
+        landed(left, std::integral_constant<int, 1>{});
+        landed(left, std::integral_constant<int, 0>{});
+        __syncthreads();
+        // every wave is done with the step before: its stage is filled again
+        if (left >= S - 1) GW_ISSUE(fill, j + S - 1)
+        fill = fill + 1 == S ? 0 : fill + 1;
+        const char* sw = smem + st * ST + frag;
+        const char* sa = sw + CT * 16 * GW_RB;
+        st = st + 1 == S ? 0 : st + 1;
+        u32x4_t w[CW];
+        half8 af[MT];
+#pragma unroll
+        for (int c = 0; c < CW; ++c)
+            w[c] = *reinterpret_cast<const u32x4_t*>(sw + (wn * CW + c) * 16 * GW_RB);
+#pragma unroll
+        for (int p = 0; p < (PAIR ? 2 : 1); ++p) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) af[i] = *reinterpret_cast<const half8*>(sa + (p * MT + i) * 16 * GW_RB);
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const half8 wf = WF16 ? __builtin_bit_cast(half8, w[c]) : bf16x8_to_half8(w[c]);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf, af[i], acc[i][c], 0, 0, 0);
+            }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(dma_waitcnt(0, 0));             // fragment reads done; nothing is on its way to LDS
+#undef GW_ISSUE
+    // The two waves along k: each finishes half of the row tiles and hands the other half over
+    floatx4* const red = reinterpret_cast<floatx4*>(smem);
+    __syncthreads();
+    if (MT > 1 || kh == 1) {
+#pragma unroll
+        for (int i = 0; i < KEEP; ++i)
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const floatx4 first = acc[i][c], second = acc[MT > 1 ? KEEP + i : 0][c];
+                red[((wave * KEEP + i) * CW + c) * 64 + lane] = MT == 1 || kh ? first : second;
+            }
+    }
+    __syncthreads();
+    if (MT == 1 && kh == 1) return;
+    const int m0 = kh * KEEP * 16;
+    floatx4 v[KEEP][CW];
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+            const floatx4 first = acc[i][c], second = acc[MT > 1 ? KEEP + i : 0][c], own = MT > 1 && kh ? second : first;
+            const floatx4 o = red[(((wave ^ 1) * KEEP + i) * CW + c) * 64 + lane];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[i][c][x] = own[x] + o[x];
+        }
+    // lane (r, q): row r of a row tile, columns 4 q .. 4 q + 3 of a column tile
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+        const int m = m0 + i * 16 + r;
+        if constexpr (EPI == MG_SAMPLE) {
+            // statistics of 32-column blocks = two tiles; ties of the maximum go to the lowest column
+            const int nblk = a.N / 32;
+#pragma unroll
+            for (int c = 0; c < CW; c += 2) {
+                const int blk = (t0 + wn * CW + c) / 2;
+                const floatx4 v0 = v[i][c], v1 = v[i][c + 1];
+                float mx = fmaxf(fmaxf(fmaxf(v0[0], v0[1]), fmaxf(v0[2], v0[3])), fmaxf(fmaxf(v1[0], v1[1]), fmaxf(v1[2], v1[3])));
+                mx = fmaxf(mx, __shfl_xor(mx, 16, RL_WAVE));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, RL_WAVE));
+                int mi = 32;
+                float e1 = 0.f, eT = 0.f;
+#pragma unroll
+                for (int x = 3; x >= 0; --x) mi = v1[x] == mx ? 16 + q * 4 + x : mi;
+#pragma unroll
+                for (int x = 3; x >= 0; --x) mi = v0[x] == mx ? q * 4 + x : mi;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    e1 += __expf(v0[x] - mx) + __expf(v1[x] - mx);
+                    eT += __expf((v0[x] - mx) * a.inv_temp) + __expf((v1[x] - mx) * a.inv_temp);
+                }
+                mi = min(mi, __shfl_xor(mi, 16, RL_WAVE));
+                e1 += __shfl_xor(e1, 16, RL_WAVE);
+                eT += __shfl_xor(eT, 16, RL_WAVE);
+                mi = min(mi, __shfl_xor(mi, 32, RL_WAVE));
+                e1 += __shfl_xor(e1, 32, RL_WAVE);
+                eT += __shfl_xor(eT, 32, RL_WAVE);
+                if (q == 0 && m < a.M && blk < nblk)
+                    a.samp_part[(int64_t)m * nblk + blk] = make_float4(mx, eT, e1, __int_as_float(mi < 32 ? mi : -1));
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                half4 hi, lo;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const float up = __shfl_xor(v[i][c][x], 32, RL_WAVE);           // lanes q < 2 hold the gate, q + 2 the up columns
+                    f16_t h, l;
+                    split_f16(swiglu_act(v[i][c][x], up), h, l);
+                    hi[x] = h; lo[x] = l;
+                }
+                const int n = (t0 + wn * CW + c) * 8 + q * 4;
+                if (q < 2 && m < a.M && n < a.N) {
+                    f16_t* o = a.outH + (int64_t)m * a.ldc + n;
+                    *reinterpret_cast<half4*>(o) = hi;
+                    if (a.split_out) *reinterpret_cast<half4*>(o + a.N) = lo;
+                }
+            }
+        }
+    }
+}
+#undef GS_REQ
+#undef GS_REQ_NT
+
 // Tiles per workgroup and splits over K.  A workgroup's time goes with its k-tiles x (CT + what its rows of A cost), times
 // the rounds of 256 workgroups; each split costs its consumer a pass over the partial sums.  Both costs are those of the
 // context's limit (64 rows or 128).  Of the measured candidates the rule takes the fastest or one within 3 %: up to 64 rows 8B QKV
@@ -280,6 +474,16 @@ static void stream_plan(int epi, int N, int K, int Kw, int max_rows, int& ct, in
             if (ct == 0 || cost < best) { best = cost; ct = c; z = zz; }
         }
     }
+}
+
+// Whether a GEMM without splits takes gemm_wide_kernel: rounds of 256 workgroups times what one draws per k-step (its columns and
+// rows in 16s; A of a context of more than 64 rows counts 4, as above) and 2 for what it does alone.  Measured at 3 to
+// 128 rows on 4 LM heads and 4 gate/up widths, plain and pair, fp16 and bf16 (tiles of 16 columns: 1024 to 9496): the faster one, or within
+// 2 % at 3 rows and 5 % above.  As the plan, it must not look at the rows of a call.
+static bool wide_tiles(int tiles, int ct, int pair, int max_rows) {
+    const int rows = (max_rows <= 64 ? 1 : 4) << pair;
+    auto rounds = [&](int c) { return ((tiles + c - 1) / c + 255) / 256; };
+    return rounds(GW_CT) * (GW_CT + 2 + rows) <= rounds(ct) * (ct + 2 + rows);
 }
 
 bool k_gemm_decode_supported(int epi, int N, int K, int Kw) {
@@ -320,6 +524,33 @@ static void launch_stream_ct(const GemmArgs& a, int tiles, int z, hipStream_t s)
         }
     }
 }
+template <int EPI, int MT, bool WF16, bool PAIR>
+static void launch_wide_t(const GemmArgs& a, int tiles, hipStream_t s) {
+    constexpr int lds = gw_stages(MT, PAIR) * gw_stage(MT, PAIR);
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute((const void*)gemm_wide_kernel<EPI, MT, WF16, PAIR>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        attr_set = true;
+    }
+    gemm_wide_kernel<EPI, MT, WF16, PAIR><<<(tiles + GW_CT - 1) / GW_CT, 512, lds, s>>>(a);
+}
+template <int EPI, bool WF16, bool PAIR>
+static void launch_wide_m(const GemmArgs& a, int tiles, hipStream_t s) {
+    if (a.M <= 16) launch_wide_t<EPI, 1, WF16, PAIR>(a, tiles, s);
+    else if (a.M <= 32) launch_wide_t<EPI, 2, WF16, PAIR>(a, tiles, s);
+    else if (a.M <= 64) launch_wide_t<EPI, 4, WF16, PAIR>(a, tiles, s);
+    else launch_wide_t<EPI, 8, WF16, PAIR>(a, tiles, s);
+}
+template <int EPI>
+static void launch_wide(const GemmArgs& a, int tiles, hipStream_t s) {
+    if (a.w_f16) {
+        if (a.pair) launch_wide_m<EPI, true, true>(a, tiles, s);
+        else launch_wide_m<EPI, true, false>(a, tiles, s);
+    } else {
+        if (a.pair) launch_wide_m<EPI, false, true>(a, tiles, s);
+        else launch_wide_m<EPI, false, false>(a, tiles, s);
+    }
+}
 template <int EPI>
 static void launch_stream(const GemmArgs& a, int tiles, int ct, int z, hipStream_t s) {
     switch (ct) {
@@ -358,6 +589,11 @@ void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s)
     a.k_per_split = (a.Kw / GS_KT + z - 1) / z * GS_KT;
     a.rotate_k = (a.Kw & (a.Kw - 1)) == 0 && a.k_per_split >= 16 * GS_KT;
     const int tiles = (epi == MG_SWIGLU ? 2 * a.N : a.N) / 16;
+    if (epi != MG_STORE_F32 && wide_tiles(tiles, ct, a.pair, max_rows)) {
+        if (epi == MG_SWIGLU) launch_wide<MG_SWIGLU>(a, tiles, s);
+        else launch_wide<MG_SAMPLE>(a, tiles, s);
+        return;
+    }
     if (epi == MG_STORE_F32) launch_stream<MG_STORE_F32>(a, tiles, ct, z, s);
     else if (epi == MG_SWIGLU) launch_stream<MG_SWIGLU>(a, tiles, ct, z, s);
     else launch_stream<MG_SAMPLE>(a, tiles, ct, z, s);
