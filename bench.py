@@ -511,7 +511,7 @@ def main():
         "attn_prefill": ("mfma", 4.0 * shape.n_q_heads * shape.head_dim * attn_pairs / 1e12, "TFLOP",
                          "causal prefill attention (attn_prefill_kernel)"),
         "gemm_decode": ("hbm", G * gemm_decode_bytes_per_step(shape, B) / 1e9, "GB",
-                        "weight-streaming decode GEMMs (gemm_stream_kernel)"),
+                        "weight-streaming decode GEMMs (gemm_stream_kernel, gemm_wide_kernel)"),
         "attn_decode": ("hbm", attn_decode_bytes(shape, plen, G) / 1e9, "GB",
                         "paged GQA decode attention (attn_decode_kernel)"),
     }

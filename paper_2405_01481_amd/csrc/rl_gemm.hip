@@ -600,12 +600,13 @@ static constexpr int ring_stages(int MI, int WGM, int WGN) {
 // tile 2, 1, 1 go out in the three slices that may issue them.  Loads complete in issue order, so the waits are
 // counts: inside an even k-tile p everything but the youngest 8 loads (pair p+2, p+3) has landed, i.e. tile p+1;
 // inside an odd tile p+1 everything but the youngest 7 (tile p+3's last load and the 6 of pair p+4, p+5 issued so
-// far), i.e. tile p+2.  The loop issues the same number of loads on every trip (the last trips re-request the final
-// tile), so the counts hold to the end; vmcnt(0) after the loop keeps loads from landing in LDS later.
+// far), i.e. tile p+2.  The last four k-tiles, behind which nothing is left to ask for, are written out with counts of their
+// own (re-requesting the final tile instead, for one form of the trip, kept the epilogue waiting for a memory latency: whole
+// passes 0.1 - 0.4 % longer).
 // WF16: W points at an fp16 copy of the weights and its fragments go from LDS straight into the MFMAs; otherwise W is
 // bf16 and each fragment is converted (exactly) next to the MFMAs of slice 1, which costs 5-10 % of the loop.  Both
 // forms feed the MFMAs the same values in the same order: their results are identical bit for bit.
-// Requires K % 64 == 0, no split over K, 5 * 512 * 64 bytes of LDS.
+// Requires K % 64 == 0 and K >= 128, no split over K, 5 * 512 * 64 bytes of LDS.
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 template <int EPI, bool WF16, int MI>
 __device__ __forceinline__ void dma8_loop(const GemmArgs& a, const f16_t* Aop, int lda, const bf16_t* Wop, int m0, int nb, int wave,

@@ -1,9 +1,9 @@
 // Weight-streaming GEMMs of a decode step of at most 128 rows:  C[M,N] = A[M,K] (fp16) * W[N,K]^T (bf16 or fp16 copy).
 //
 // Bound by reading W once.  What a plain read of these matrices reaches here, launch included, sets the floor: 12.6 MB
-// in 3.8 us, 33.5 MB in 6.5, 117 MB in 20, 235 MB in 38 (3.3, 5.2, 5.8, 6.2 TB/s).  A comes on top, from L2 and at about
-// 17 TB/s over all workgroups, each of which reads its rows once (gate/up of the 8B shape: 39.3, 40.7, 43.7, 54 us at 3, 32,
-// 64, 128 rows).  Three things decide how close a GEMM comes, all measured:
+// in 3.8 us, 33.5 MB in 6.5, 117 MB in 20, 235 MB in 38 (3.3, 5.2, 5.8, 6.2 TB/s).  A comes on top, from L2: every workgroup
+// reads its rows once, and they take their part of the about 64 KB that a CU has on its way at once (gate/up of the 8B shape:
+// 38.3, 38.4, 39.8, 50 us at 3, 32, 64, 128 rows).  Three things decide how close a GEMM comes, all measured:
 //   * how rows are read.  64-byte pieces of 16 rows (operands straight into MFMA layout) reach 60 - 80 % of the plain
 //     read on the short matrices, 256-byte pieces 95 %.  So operands go global -> LDS in k-tiles of 128 (a 1 KB
 //     request = 4 rows x 256 B), 16-byte chunks XOR-swizzled with the row on the source side, so that the fragment
@@ -17,9 +17,9 @@
 //     split over Z workgroups whose partial sums the consumer reduces (stream_plan).
 // Eight waves: four along the k-tile (32 k each), two along the columns, so that every W fragment is read, and on bf16
 // weights converted, by one wave only; each wave holds all MT x 16 rows.  The four partial accumulators meet in LDS after
-// the loop, in wave order.  Three stages (above 64 rows two of A: LDS is full; four of small tiles, gs_nw), one barrier per k-tile; the loads are issued
-// from inline assembly (the compiler would wait for them at every barrier) and counted by hand: two k-tiles of W are in
-// flight while one is consumed.
+// the loop, in wave order.  Three stages (above 64 rows two of A: LDS is full; four of small tiles, gs_nw), one barrier per
+// k-tile; the loads are issued from inline assembly (the compiler would wait for them at every barrier) and counted by hand: two
+// k-tiles of W are in flight while one is consumed.
 // Against a kernel on 128 x 128 tiles with k-tiles of 64 (which it replaced), per launch: 8B at 3 rows QKV 12.8 -> 10.4 us, O 9.8
 // -> 8, gate/up 52 -> 40, down 23 -> 21, LM head 222 -> 177; at 128 rows 18.1 -> 17.3, 15.3 -> 14, 58 -> 54.5, 33.5 -> 33.5, 227 ->
 // 230; 1B at 32 rows 8.2 -> 5.3, 7.0 -> 4.2, 21.7 -> 13.9, 11.3 -> 9.3; 70B (bf16) at 64 rows 38 -> 33, 38 -> 29.5, 171 -> 170, 84 -> 82.

@@ -24,7 +24,7 @@ import subprocess
 import sys
 
 # kernel name pattern -> class of bench.py's roofline entries (the LM-head GEMM is the tile kernel with epilogue 5)
-CLASSES = {r"gemm_stream_kernel": "gemm_decode", r"attn_decode_kernel": "attn_decode",
+CLASSES = {r"gemm_stream_kernel": "gemm_decode", r"gemm_wide_kernel": "gemm_decode", r"attn_decode_kernel": "attn_decode",
            r"gemm_dma8_kernel<[0-4][,>]": "gemm_prefill", r"gemm_dma8_kernel<5[,>]": "lmhead_score",
            r"attn_prefill_kernel": "attn_prefill"}
 
@@ -78,10 +78,11 @@ def traffic(fetch_csv, write_csv, workload, out_json):
     except Exception:
         commit = ""
     res = {}
-    for pattern, cls in CLASSES.items():
-        names = sorted(k for k in fetch if re.match(pattern, k))
-        f = [x for k, v in fetch.items() if re.match(pattern, k) for x in v]
-        w = [x for k, v in write.items() if re.match(pattern, k) for x in v]
+    for cls in dict.fromkeys(CLASSES.values()):
+        of_cls = lambda k: any(c == cls and re.match(pat, k) for pat, c in CLASSES.items())
+        names = sorted(k for k in fetch if of_cls(k))
+        f = [x for k, v in fetch.items() if of_cls(k) for x in v]
+        w = [x for k, v in write.items() if of_cls(k) for x in v]
         if not f or not w:
             continue
         res[cls] = {"kernels": names, "commit": commit,
