@@ -48,7 +48,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // 7.0 us; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
 // ST: the cache is read as non-temporal (k_attn_decode).
 template <typename V, bool ST>
-__device__ __forceinline__ V kv_load(const f16_t* p) {
+__device__ __forceinline__ V kv_load(const char* p) {
     if constexpr (ST) return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
     else return *reinterpret_cast<const V*>(p);
 }
@@ -109,8 +109,8 @@ __global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(Decode
     if (gridDim.z != 1) pages = bt[min(pbeg + wave + NW * lane, a.mpps - 1)];
     const int p_new = (ctx - 1) / PT, st_new = (ctx - 1) % PT;   // page and slot of the new token
     const int64_t page_new = FU && ctx > 0 ? bt[p_new] : 0;
-    const f16_t* kbase = a.pool + a.geo.k_off(a.layer, 0, g, 0, 0) + col * HD + g4 * 8;
-    const f16_t* vbase = a.pool + a.geo.v_off(a.layer, 0, g, 0, 0) + col * PT + g4 * 4;
+    const f16_t* const kbase = a.pool + a.geo.k_off(a.layer, 0, g, 0, 0);
+    const f16_t* const vbase = a.pool + a.geo.v_off(a.layer, 0, g, 0, 0);
     const int64_t page_stride = a.geo.page_elems();
     const int64_t lo_off = SP ? (int64_t)(a.layer_lo - a.layer) * a.geo.layer_elems() : 0;   // hi plane -> lo plane
     const int qrow = (SP ? 2 : 1) * a.Hq * HD;       // elements per query / output row
@@ -140,21 +140,26 @@ __global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(Decode
     half8 kf[KS], kn[KS], kfl[SP ? KS : 1], knl[SP ? KS : 1];
     half4 vf[DB], vn[DB], vfl[SP ? DB : 1], vnl[SP ? DB : 1];
     int p = pbeg + wave;
-#define AD_FETCH(pg)                                                                                             \
-    {                                                                                                            \
-        _Pragma("unroll") for (int s = 0; s < KS; ++s) {                                                         \
-            kn[s] = kv_load<half8, ST>(kbase + (pg) * page_stride + s * 32);                                     \
-            if (SP) knl[s] = kv_load<half8, ST>(kbase + lo_off + (pg) * page_stride + s * 32);                   \
-        }                                                                                                        \
-        _Pragma("unroll") for (int d = 0; d < DB; ++d) {                                                         \
-            vn[d] = kv_load<half4, ST>(vbase + (pg) * page_stride + d * 16 * PT);                                \
-            if (SP) vnl[d] = kv_load<half4, ST>(vbase + lo_off + (pg) * page_stride + d * 16 * PT);              \
-        }                                                                                                        \
-    }
-    if (p < pend) {
-        const int64_t pg = __builtin_amdgcn_readlane(pages, 0);
-        AD_FETCH(pg)
-    }
+    // A page's address is the wave's, a lane adds 32 bits.  The lanes' parts count as changed with every page (nothing is executed
+    // for that): as constants they are added to the 64-bit bases ahead of the loop, and at head_dim 128 the registers
+    // these take, with the two pages live across the branch below, were 8 to 12 bytes of scratch per lane.
+    unsigned k_lane = (col * HD + g4 * 8) * 2, v_lane = (col * PT + g4 * 4) * 2;
+    auto fetch = [&](int64_t pg) __attribute__((always_inline)) {
+        const char* const kp = (const char*)(kbase + pg * page_stride);
+        const char* const vp = (const char*)(vbase + pg * page_stride);
+        asm("" : "+v"(k_lane), "+v"(v_lane) : "s"(pg));
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            kn[s] = kv_load<half8, ST>(kp + k_lane + s * 64);
+            if (SP) knl[s] = kv_load<half8, ST>(kp + lo_off * 2 + k_lane + s * 64);
+        }
+#pragma unroll
+        for (int d = 0; d < DB; ++d) {
+            vn[d] = kv_load<half4, ST>(vp + v_lane + d * 32 * PT);
+            if (SP) vnl[d] = kv_load<half4, ST>(vp + lo_off * 2 + v_lane + d * 32 * PT);
+        }
+    };
+    if (p < pend) fetch(__builtin_amdgcn_readlane(pages, 0));
     if (FU) {
         if (ctx > 0) {   // uniform over the workgroup; a parked row has no keys and no query
 #pragma unroll
@@ -217,11 +222,12 @@ __global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(Decode
         }
         if (p + NW < pend) {
             // a wave's last page asks for nothing: a re-read of that page, unused, was still waited for at the end and
-            // read twice by waves of few pages (8 rows at 200 tokens 8.1 -> 7.5 us, 128 at 592 61.3 -> 57.9)
+            // read twice by waves of few pages (8 rows at 200 tokens 8.4 -> 7.5 us, 128 at 592 62 -> 59.5).  The pair kernel takes
+            // 208 VGPRs for it, two waves per SIMD: with the re-read three (156), 128 rows 103 instead of 105.5, 32 at 1600
+            // 80.6 and 80.9, head_dim 64, 64 at 280, 16.7 and 16.4
             ++it;
             if ((it & 63) == 0) pages = bt[min(p + NW + NW * lane, a.mpps - 1)];
-            const int64_t pg = __builtin_amdgcn_readlane(pages, it & 63);
-            AD_FETCH(pg)
+            fetch(__builtin_amdgcn_readlane(pages, it & 63));
         }
         floatx4 s0 = {0.f, 0.f, 0.f, 0.f};
         if (SP) {   // the two small terms first, the leading one last
@@ -265,7 +271,6 @@ __global__ __launch_bounds__(NW * 64, SP ? 2 : 4) void attn_decode_kernel(Decode
             acc[d] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf[d], pf0, acc[d], 0, 0, 0);
         }
     }
-#undef AD_FETCH
     // FU: the new token's key and value go to the cache only now -- stores count towards the same in-order
     // completion counter as loads, so stores issued before the loop would hold back every page load behind them
     if (FU && split == 0 && ctx > 0) {
