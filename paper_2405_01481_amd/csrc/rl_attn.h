@@ -16,6 +16,7 @@ struct DecodeAttnArgs {
     // split = 1: q and out rows are fp16 pairs, [Hq * hd hi | Hq * hd lo]; the cache's lo planes of K and V are
     // in layer `layer_lo` of the pool
     int split = 0, layer_lo = 0;
+    int stream = 0;                  // the cache is read as non-temporal (k_attn_decode_streams)
     // qkv_part != nullptr (plain layers only, Hq / Hkv <= 8): q is not read; the kernel itself sums the QKV
     // projection's split-K partial rows [qkv_nsplit][B, (Hq + 2 Hkv) hd] (split stride in floats), rotates q and k
     // with rope[pos][hd/2] = (cos, sin), and appends k and v of the new token to the cache through pool_w
@@ -30,6 +31,9 @@ struct DecodeAttnArgs {
 bool k_attn_decode_consumes_qkv(int Hq, int Hkv, int hd);
 // waves per workgroup (4 or 8) and splits of a sequence's keys that suit a context's limits
 void k_attn_decode_plan(int max_batch, int Hkv, int mpps, int max_splits, int* waves, int* nsplit);
+// Whether a decode launch of B rows whose longest context is max_ctx reads the cache as non-temporal (pair: a pair layer).  The
+// results are the same bits either way.
+bool k_attn_decode_streams(int B, int max_ctx, int Hkv, int hd, int pair);
 void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s);
 
 // Causal attention over a packed token list.  Sequences start at rows that are multiples of 32

@@ -46,7 +46,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // is known), so that a page's loads wait for no index load; with up to 8 waves per workgroup short contexts need no
 // splits and no merge kernel.  32 rows, 8 kv heads, 200 keys, head_dim 64: 2 splits x 4 waves + merge 12.8 us, 8 waves
 // 7.0 us; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
-// ST: the cache is read as non-temporal (k_attn_decode).
+// ST: the cache is read as non-temporal (k_attn_decode_streams).
 template <typename V, bool ST>
 __device__ __forceinline__ V kv_load(const char* p) {
     if constexpr (ST) return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
@@ -381,18 +381,24 @@ static void launch_attn_decode_hd(const DecodeAttnArgs& a, int B, int waves, int
         attn_merge_kernel<HD><<<B * a.Hq, HD, 0, s>>>(a.part_o, a.part_ml, a.out, nsplit, a.Hq, a.split);
 }
 
+// Non-temporal where the keys and values of one layer would be far more than the L2s hold if all rows had the longest context: that
+// of the run, never the context's limit, which may be many times longer.  Whole generations of 64 tokens, per launch: 8B
+// width 139 MB (128 rows, 264 keys) 2.4 us shorter, 113 MB (32, 864) 1.5, 109 (64, 414) 1.0, 1B 139 (64, 1064) 1.4, 87 (64, 664) 0.5; 70B 95
+// MB, rows of 100 to 300 keys 1.2 us longer, of 300 2.3 shorter; 61 and 64 MB 0.5 shorter; small ones are longer: 1B 44 MB 0.3, 17
+// MB 0.4, 8B 9 MB (8, 264) 0.9 of 8.
+static const int64_t kStreamBytes = (int64_t)100 << 20;
+bool k_attn_decode_streams(int B, int max_ctx, int Hkv, int hd, int pair) {
+    return (int64_t)B * max_ctx * Hkv * hd * (pair ? 8 : 4) > kStreamBytes;
+}
+
 void k_attn_decode(const DecodeAttnArgs& a, int B, int waves, int nsplit, hipStream_t s) {
     if (B <= 0) return;
     if (a.qkv_part && (a.split || !k_attn_decode_consumes_qkv(a.Hq, a.Hkv, a.geo.hd))) return;   // callers check first
-    // Non-temporal where a layer's keys and values of these rows' longest contexts are far more than the L2s hold.  8B width, per
-    // launch: 128 rows, 592 keys (300 MB; the limit 350) 61.6 -> 59.2 us, pair layer 120 -> 105; 32 rows, 1600 keys (200; 280) 44.2 ->
-    // 43.2 and 83.8 -> 80.6.  Shorter ones lose: 70B width, 64 rows, 230 keys (60; 90) 17.1 -> 17.4, 1B 32 rows 7.0 -> 7.6, 3 rows 8.4 -> 9.0.
-    const bool far = (int64_t)B * a.mpps * a.geo.page_elems() * 4 > ((int64_t)128 << 20);
     if (a.geo.hd == 128) {
-        if (far) launch_attn_decode_hd<128, true>(a, B, waves, nsplit, s);
+        if (a.stream) launch_attn_decode_hd<128, true>(a, B, waves, nsplit, s);
         else launch_attn_decode_hd<128, false>(a, B, waves, nsplit, s);
     } else {
-        if (far) launch_attn_decode_hd<64, true>(a, B, waves, nsplit, s);
+        if (a.stream) launch_attn_decode_hd<64, true>(a, B, waves, nsplit, s);
         else launch_attn_decode_hd<64, false>(a, B, waves, nsplit, s);
     }
 }

@@ -235,10 +235,11 @@ struct rl_ctx {
         const void* out_len = nullptr;   // non-null: queue mode (per-slot output rows, ids, limits)
         int ctx_cap = 0;                 // plain kernels: longest context the captured attention launches have LDS for
         int steps = 1;                   // decode steps in the captured graph
+        int stream_kv = 0;               // tuned kernels: which of the captured attention launches read the cache as non-temporal
         bool operator==(const GraphKey& o) const {
             return B == o.B && G == o.G && impl == o.impl && eos == o.eos && out_ids == o.out_ids &&
                    out_logp == o.out_logp && seed == o.seed && base == o.base && temp == o.temp && s == o.s &&
-                   out_len == o.out_len && ctx_cap == o.ctx_cap && steps == o.steps;
+                   out_len == o.out_len && ctx_cap == o.ctx_cap && steps == o.steps && stream_kv == o.stream_kv;
         }
     } gkey{};
     hipGraphExec_t gexec = nullptr;
@@ -348,6 +349,7 @@ static void attention(rl_ctx* c, int l, int n, bool paged, int max_ctx, int nblo
         a.part_ml = c->at<float>(L.attn_ml); a.mpps = L.mpps; a.layer = l; a.Hq = m.n_q_heads; a.Hkv = m.n_kv_heads;
         a.scale = 1.0f / sqrtf((float)m.head_dim); a.geo = c->geo;
         a.split = sp; a.layer_lo = m.n_layers + l;
+        a.stream = k_attn_decode_streams(n, max_ctx, m.n_kv_heads, m.head_dim, sp);
         if (qkv_part) {
             a.qkv_part = qkv_part; a.qkv_nsplit = qkv_nsplit; a.qkv_split_stride = qkv_split_stride;
             a.rope = c->at<float2>(L.rope); a.pool_w = (f16_t*)c->pool;
@@ -1232,6 +1234,15 @@ static int graph_steps(const rl_ctx* c, int G) {
     return std::max(1, std::min(std::min(8, 96 / (4 * c->cfg.n_layers + 2)), G / 4));
 }
 
+// Which attention launches of a run with these rows and this longest context read the cache as non-temporal: 1 the plain layers',
+// 2 the pair layers'.
+static int stream_kv(const rl_ctx* c, int B, int ctx_cap) {
+    const rl_model_cfg& m = c->cfg;
+    if (c->impl != 1) return 0;
+    return (k_attn_decode_streams(B, ctx_cap, m.n_kv_heads, m.head_dim, 0) ? 1 : 0) |
+           (k_attn_decode_streams(B, ctx_cap, m.n_kv_heads, m.head_dim, 1) ? 2 : 0);
+}
+
 // The decode step is identical from one token to the next (positions, step counters and page tables live on the
 // device), so it is captured once and replayed.  Makes c->gexec the step of `key`; one that it replaces is put aside.
 static int capture_step(rl_ctx* c, const rl_ctx::GraphKey& key, const rl_sample_cfg* sample, int32_t* out_ids, float* out_logp,
@@ -1320,7 +1331,7 @@ int rollout_generate(rl_ctx* c, const rl_sample_cfg* sample, const int32_t* prom
     int done = 0;                                              // steps that the captured graph covers
     if (graph_usable(c, s, ctx_cap)) {
         const rl_ctx::GraphKey key{B, G, c->impl, sample->eos_id, out_ids, out_logp, sample->seed, sample->seq_id_base,
-                                   sample->temperature, s, nullptr, c->impl == 1 ? 0 : ctx_cap, graph_steps(c, G)};
+                                   sample->temperature, s, nullptr, c->impl == 1 ? 0 : ctx_cap, graph_steps(c, G), stream_kv(c, B, ctx_cap)};
         if ((rc = capture_step(c, key, sample, out_ids, out_logp, nullptr, ctx_cap))) return rc;
         if ((rc = replay_step(c, G / key.steps))) return rc;
         done = G / key.steps * key.steps;
@@ -1462,7 +1473,8 @@ int rollout_generate_queue(rl_ctx* c, const rl_sample_cfg* sample, const int32_t
         if ((rc = ensure_pages(c, need, s))) { rollout_reset(c); return rc; }
         if (graph) {
             const rl_ctx::GraphKey key{nslots, Gmax, c->impl, sample->eos_id, out_ids, out_logp, sample->seed,
-                                       sample->seq_id_base, sample->temperature, s, out_len, c->impl == 1 ? 0 : ctx_cap};
+                                       sample->seq_id_base, sample->temperature, s, out_len, c->impl == 1 ? 0 : ctx_cap, 1,
+                                       stream_kv(c, nslots, ctx_cap)};
             rc = capture_step(c, key, sample, out_ids, out_logp, out_len, ctx_cap);
             if (rc == RL_OK) rc = replay_step(c, kQueueBurst);
             if (rc) { rollout_reset(c); return rc; }

@@ -123,3 +123,16 @@ def check_row(model, seq, P, seed, row, gpu_logp_row, gen_ids_row=None, gen_logp
         stats["gen_max"] = float(ge.max(initial=0.0))
         assert ge.max(initial=0.0) <= tol, f"row {row}: generation log-prob error {ge.max():.3e}"
     return want, stats
+
+
+def kernels_run(fn):
+    """Names of the GPU kernels that fn() launches, those of replayed graphs included."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    names = {e.key for e in p.key_averages()}
+    assert any("kernel" in n for n in names), names
+    return names
