@@ -1160,12 +1160,16 @@ __global__ __launch_bounds__(1024) void plain_front_kernel(PlainFrontArgs a) {
     }
 }
 static size_t plain_front_lds(int G, int hd, int ctx) { return (size_t)((G + 2) * hd + G * 1024 + 4 + G * ctx) * sizeof(float); }
-// A block reads its columns' weights by itself: up to 512 KB it takes less than the launch it saves (196 KB: 2 us).  Blocks
-// beyond one per CU would wait for a second round.
+// A block reads its columns' weights by itself, 256 k of them at a time, each a memory latency.  Whole generations of 48 tokens, 6 layers,
+// 4 to 256 blocks, contexts of 12 to 60 keys, time of this over the two kernels': one query head per kv head, head_dim 64, d 640 (480 KB a
+// block) 0.94 - 0.95; 128, d 320 (480 KB) 0.97 - 1.00; two heads, 64, d 384 and 512 (384, 512 KB) 0.94 - 0.97; 128, d 64 to 256 (128
+// to 512 KB) 0.91 - 1.00; four heads, 64, d 64 (96 KB) 0.92 - 1.02, 192 0.92 - 0.99, 256 (384 KB) 0.92 - 1.03, 320 (480 KB) 1.00 - 1.09.  Longer
+// contexts gain more: alone, 400 to 14000 keys, 0.55 - 0.95.  Blocks beyond one per CU would wait for a second round.
 bool k_plain_front_supported(int Hq, int Hkv, int hd, int d, int max_batch, int max_seq) {
     const int G = Hq / Hkv;
     if (!(G == 1 || G == 2 || (G == 4 && hd == 64))) return false;
-    return (int64_t)(G + 2) * hd * d * 4 <= 512 * 1024 && (int64_t)max_batch * Hkv <= 256 && plain_front_lds(G, hd, max_seq) <= 65536;
+    return (int64_t)(G + 2) * hd * d * 4 <= (G == 4 ? 384 : 512) * 1024 && (int64_t)max_batch * Hkv <= 256 &&
+           plain_front_lds(G, hd, max_seq) <= 65536;
 }
 void k_plain_front(const float* x, const float* gain, float eps, const float* W, int d, const float2* rope, float* pool, int layer,
                    KvGeom geo, const int* block_table, int mpps, const int* tok_pos, float* out, int n, int Hq, int max_ctx,

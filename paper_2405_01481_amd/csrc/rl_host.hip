@@ -1226,12 +1226,13 @@ static bool graph_usable(const rl_ctx* c, hipStream_t s, int ctx_cap) {
 }
 
 // Decode steps per captured graph of a run of G tokens.  Between two replays the device is idle for about 7.5 us, a launch
-// inside a graph costs 1.6, and every node about 1.4 us of host time when it is captured: more steps pay where a step is a
+// inside a graph costs 1.6, and every node about 1.4 us of host time when it is captured: more steps pay where an fp32 step is a
 // handful of launches (the fp32 configuration's 10: its whole pass 1760 -> 1640 us with 8), and not for the 112 or more of a
 // tuned step.  A quarter of G at most: a run whose buffers are new, and which captures, gains as well.
 static int graph_steps(const rl_ctx* c, int G) {
-    if (!plain_front(c)) return 1;
-    return std::max(1, std::min(std::min(8, 96 / (4 * c->cfg.n_layers + 2)), G / 4));
+    if (c->impl != 0 || c->cfg.dtype != RL_FP32) return 1;
+    const int nodes = plain_front(c) ? 4 * c->cfg.n_layers + 2 : 5 * c->cfg.n_layers + 3;
+    return std::max(1, std::min(std::min(8, 96 / nodes), G / 4));
 }
 
 // Which attention launches of a run with these rows and this longest context read the cache as non-temporal: 1 the plain layers',

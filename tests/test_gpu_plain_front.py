@@ -1,6 +1,7 @@
 """The fp32 decode step's fused front (norm, QKV projection, rotation, append and attention in one kernel) and its products for
-few rows, against the oracle: every head group the kernel is built for, widths that are no multiple of its 256-wide steps,
-contexts across its passes of 64 (head_dim 128: 32) keys, rows on both sides of the limit of 8."""
+few rows, against the oracle: every head group the kernel is built for, up to the widest it takes, widths that are no multiple of its
+256-wide steps, as many blocks as it takes, contexts across its passes of 64 (head_dim 128: 32) keys, rows on both sides of the limit
+of 8; and shapes just past it, which the separate kernels run."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +9,7 @@ import torch
 from oracle import rollout_oracle as O
 from paper_2405_01481_amd import rollout as R
 from paper_2405_01481_amd import synth
-from tests.helpers import verify_rollout
+from tests.helpers import kernels_run, verify_rollout
 
 pytestmark = pytest.mark.gpu
 
@@ -19,11 +20,20 @@ def _shape(G, hd, d, F):
     return synth.ModelShape(f"front_{G}_{hd}", 2, d, 2 * G, 2, hd, F, 515, 10000.0, "fp32", 0.08)
 
 
-@pytest.mark.parametrize("G,hd,d,F,B", [(1, 64, 64, 64, 1), (2, 64, 320, 320, 4), (4, 64, 256, 576, 5), (1, 128, 192, 448, 8),
-                                        (2, 128, 128, 320, 9), (4, 128, 128, 64, 3)])
-def test_front_against_oracle(G, hd, d, F, B):
+def _ran(names):
+    """Whether the fused front ran, and whether the product for few rows did."""
+    return any("plain_front_kernel" in n for n in names), any("gemm_rows_kernel" in n for n in names)
+
+
+@pytest.mark.parametrize("G,hd,d,F,B,front", [
+    (1, 64, 64, 64, 1, True), (2, 64, 320, 320, 4, True), (4, 64, 256, 576, 5, True), (1, 128, 192, 448, 8, True),
+    (2, 128, 128, 320, 9, True), (1, 64, 640, 320, 2, True), (2, 64, 512, 64, 4, True), (1, 128, 320, 64, 6, True),
+    (2, 128, 256, 320, 8, True), (1, 64, 64, 64, 128, True), (1, 64, 64, 64, 129, False), (1, 64, 704, 64, 2, False),
+    (2, 64, 576, 64, 2, False), (4, 64, 320, 64, 3, False), (1, 128, 384, 64, 2, False), (2, 128, 320, 64, 2, False),
+    (4, 128, 128, 64, 3, False)])
+def test_front_against_oracle(G, hd, d, F, B, front):
     """Prompts of 1 to 70 tokens, so that the contexts cross 16-token pages and the passes of 32 and 64 keys; a row of the batch
-    gives the same bits alone; an early end of sequence parks a row.  (4, 128) is past what the kernel takes."""
+    gives the same bits alone; an early end of sequence parks a row.  `front`: what the shape takes."""
     shape, Gen = _shape(G, hd, d, F), 11
     w = synth.make_weights(shape, 1, DEV)
     ro = R.Rollout(R.make_cfg(shape, B, 70 + Gen), R.Weights(w), DEV)
@@ -45,9 +55,12 @@ def test_front_against_oracle(G, hd, d, F, B):
         ro.rollout_check()
         return out.cpu().numpy(), lp.cpu().numpy(), n.cpu().numpy()
 
+    names = kernels_run(lambda: generate(list(range(B))))
+    # K > 256 takes the product for few rows, as long as the context holds at most 8
+    assert _ran(names) == (front, B <= 8 and (F > 256 or 2 * G * hd > 256)), sorted(names)
     out, lp, _ = generate(list(range(B)))
     m = O.Model(shape, synth.weights_for_oracle(w))
-    verify_rollout(m, [ids[b, :plen[b]] for b in range(B)], out, lp, 0.7, 4, 0, 1e-5, 1e-4)
+    verify_rollout(m, [ids[b, :plen[b]] for b in range(B)], out, lp, 0.7, 4, 0, 1e-5, 1e-4, rows=None if B < 16 else [0, 1, 63, B - 1])
     one, one_lp, _ = generate([B - 1], base=B - 1)
     assert np.array_equal(one[0], out[-1]) and np.array_equal(one_lp[0], lp[-1])
     eos = int(out[0, 4])
