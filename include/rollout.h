@@ -329,13 +329,17 @@ int rollout_set_precise_layers(rl_ctx* ctx, int32_t n);
  * with the next decode step; live sequences are kept.  Errors: RL_EINVAL. */
 int rollout_set_fused_sampling(rl_ctx* ctx, int32_t on);
 
-/* Tuned bf16 path only.  on != 0 (default): in a decode step (Section 3.2's generation stage) the attention kernel of
+/* on != 0 (default), tuned bf16 path: in a decode step (Section 3.2's generation stage) the attention kernel of
  * a plain layer is itself the consumer of the QKV projection's split-K partial sums: each workgroup adds up the
  * partial rows of its own query heads and of its kv head's new key and value (in split order), applies the rotary
  * embedding, appends key and value to the cache page and attends with them.  on = 0: a separate kernel does that
  * first and attention reads its results.  The arithmetic is the same either way; fp16-pair layers
  * (rollout_set_precise_layers) and models with more than 6 query heads per kv head at head_dim 128 always use the
- * separate kernel.  The caller must have waited for work on the context.
+ * separate kernel.
+ * fp32 contexts whose shape suits it (few query heads per kv head, at most 512 KB of QKV weights per kv head, at most 256 pairs of
+ * row and kv head): one kernel does a layer's norm, QKV projection, rotation, append and attention, the first layer's also
+ * the start of the step.  on = 0: the separate kernels, with the sums in another order (log-probs agree to fp32 rounding).
+ * The caller must have waited for work on the context.
  * Takes effect with the next decode step; live sequences are kept.  Errors: RL_EINVAL. */
 int rollout_set_fused_qkv_consumer(rl_ctx* ctx, int32_t on);
 
@@ -346,15 +350,16 @@ int rollout_forget_fp16_copies(rl_ctx* ctx);
 /* Measurement switch (process-wide): decode-step GEMMs of more than `rows` (and at most 128) rows run on the 128 x 128
  * tile kernel instead of the weight-streaming kernel (default: a negative value = never). */
 int rollout_set_decode_tile_rows(int32_t rows);
-/* Measurement switch, process-wide: on = 0 makes the large-M GEMMs leave the fp16 copies (rl_weights.fp16_copy) alone and
- * treat every weight set as one that has none (converted on the fly, or ahead of a GEMM of many rows into workspace that
- * is idle then); on != 0 (default) lets them read the copy.  Results are the same bit for bit. */
+/* Measurement switch, process-wide: on = 0 makes the GEMMs of prefill, scoring and values leave the fp16 copies
+ * (rl_weights.fp16_copy) alone and treat every weight set as one that has none (converted on the fly, or ahead of a GEMM of
+ * many rows into workspace that is idle then; small-M GEMMs then run on the register-staged tile kernel, which reads bf16);
+ * on != 0 (default) lets them read the copy.  Results are the same bit for bit. */
 int rollout_set_large_gemm_copy(int32_t on);
 
 /* Kernel classes for timing. */
 enum {
     RL_K_GEMM_DECODE = 0,   /* weight-streaming GEMMs of a decode step */
-    RL_K_ATTN_DECODE = 1,   /* paged GQA decode attention */
+    RL_K_ATTN_DECODE = 1,   /* paged GQA decode attention (fp32, fused front: with the layer's norm and QKV projection) */
     RL_K_GEMM_PREFILL = 2,  /* large-M GEMMs of prefill / scoring */
     RL_K_ATTN_PREFILL = 3,  /* causal prefill attention */
     RL_K_LMHEAD_SCORE = 4,  /* fused LM head + log-sum-exp + gather */

@@ -455,7 +455,9 @@ struct Scratch { char* p = nullptr; size_t bytes = 0; };
 // Rows from which a GEMM on bf16 weights without an fp16 copy is worth one, made just before it in idle workspace: the
 // copy moves 4 bytes per weight, the kernel then runs without conversions beside its MFMAs, which saves a tenth of its
 // time and therefore grows with the rows (a pair layer's count twice: it multiplies every weight twice).  Same bits.  Measured on whole passes: 70B width, 12544 rows 245.0 -> 233.4 ms;
-// 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.
+// 8B width, 4928 rows 19.0 -> 18.2 ms; by the 4 bytes at a copy's rate the two are even at about 3500 rows.  Narrow GEMMs of so many rows,
+// which the large-M kernel leaves to gemm_ring_kernel, gain as well: 8 layers of d 1024, 4096 rows 1.64 -> 1.58 ms, of d 512
+// 0.82 -> 0.78, 8192 rows 1.17 -> 1.12.
 static const int kConvertRows = 4096;
 
 static bool g_large_gemm_copy = true;   // rollout_set_large_gemm_copy: off = as if no weight set had a copy
