@@ -1,11 +1,14 @@
 """Small-M GEMMs on a weight set's fp16 copy (tiles of 64 x 64, 64 x 128 and 128 x 128 fed by global -> LDS loads) against the same
 GEMMs on bf16 weights (staged through registers): the same products in the same order, so the same bits."""
+import re
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2405_01481_amd import rollout as R
 from paper_2405_01481_amd import synth
+from tests.helpers import kernels_run
 
 pytestmark = pytest.mark.gpu
 
@@ -27,7 +30,7 @@ def _tile(rows, cols):
 @pytest.mark.parametrize("name", SHAPES)
 def test_fp16_copy_gives_the_bits_of_bf16_weights(name, chunk):
     """Scores of policy and reference (chunks of one model, and of both models' rows with two weight sets) and a prefill into the
-    cache followed by decode, with and without the copies."""
+    cache followed by decode, with and without the copies: the kernel runs with them and only with them."""
     s = SHAPES[name]
     if chunk == 2016 and name == "hd128":
         assert {_tile(chunk, 2 * s.d_ffn), _tile(chunk, s.d_model), _tile(chunk // 2, 2 * s.d_ffn)} == {(128, 128), (64, 64), (64, 128)}
@@ -44,13 +47,20 @@ def test_fp16_copy_gives_the_bits_of_bf16_weights(name, chunk):
         Wp, Wr = R.Weights(wp, shadow=shadow[0]), R.Weights(wr, shadow=shadow[1])
         ro = R.Rollout(cfg, Wp, DEV)
         outs = [torch.zeros(B, L, device=DEV) for _ in range(4)]
-        ro.score_logprobs_kl(Wp, Wr, ids, lens, np.ones(B, np.int32), 0.003, *outs)
         one = torch.zeros(B, L, device=DEV)
-        ro.score_logprobs_kl(Wp, None, ids, lens, np.ones(B, np.int32), 0.003, one)
         out = torch.zeros(B, 4, dtype=torch.int32, device=DEV)
         lp = torch.zeros(B, 4, device=DEV)
-        ro.rollout_generate(R.sample_cfg(4, 0.7), ids, lens, 4, out, None, lp)
-        ro.rollout_check()
+
+        def passes():
+            ro.score_logprobs_kl(Wp, Wr, ids, lens, np.ones(B, np.int32), 0.003, *outs)
+            ro.score_logprobs_kl(Wp, None, ids, lens, np.ones(B, np.int32), 0.003, one)
+            ro.rollout_generate(R.sample_cfg(4, 0.7), ids, lens, 4, out, None, lp)
+            ro.rollout_check()
+        names = kernels_run(passes)
+        ring = {(int(m[1]) * 64, int(m[2]) * 64) for n in names if (m := re.search(r"gemm_ring_kernel<\d, (\d), 4, (\d)>", n))}
+        assert ring if copies else not ring, (copies, names)
+        if copies and chunk == 2016 and name == "hd128":
+            assert ring == {(64, 64), (64, 128), (128, 128)}
         got.append([t.cpu().numpy() for t in outs + [one, out, lp]])
         ro.close()
     for a, b in zip(*got):

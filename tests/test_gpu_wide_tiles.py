@@ -8,13 +8,13 @@ import torch
 from oracle import rollout_oracle as O
 from paper_2405_01481_amd import rollout as R
 from paper_2405_01481_amd import synth
-from tests.helpers import verify_rollout
+from tests.helpers import kernels_run, verify_rollout
 
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 # the second layer (or the first) carries its activations as fp16 pairs; 16-column tiles of gate/up and LM head and which of them go wide
-SHAPES = {"short": (synth.ModelShape("wide_short", 2, 384, 6, 3, 64, 27456, 65504, 10000.0, "bf16", 0.03), (True, True)),
+SHAPES = {"short": (synth.ModelShape("wide_short", 2, 384, 6, 3, 64, 27456, 65408, 10000.0, "bf16", 0.03), (True, True)),
           "apart": (synth.ModelShape("wide_apart", 2, 2048, 8, 2, 128, 28672, 4096, 10000.0, "bf16", 0.015), (True, False)),
           "two": (synth.ModelShape("wide_two", 2, 256, 4, 2, 64, 2048, 128256, 10000.0, "bf16", 0.06), (False, True))}
 
@@ -47,8 +47,15 @@ def test_wide_tiles_rows_and_widths(name, copy, most):
     for n in few + (most,):
         out = torch.full((n, G), -1, dtype=torch.int32, device=DEV)
         lp = torch.full((n, G), 9.0, dtype=torch.float32, device=DEV)
-        ro.rollout_generate(R.sample_cfg(4, 0.8), torch.tensor(ids[:n], device=DEV), lens[:n], G, out, None, lp)
-        ro.rollout_check()
+
+        def generate():
+            ro.rollout_generate(R.sample_cfg(4, 0.8), torch.tensor(ids[:n], device=DEV), lens[:n], G, out, None, lp)
+            ro.rollout_check()
+        if n == most:                                  # gate/up is epilogue 3, the LM head 7
+            ran = kernels_run(generate)
+            assert tuple(any(f"gemm_wide_kernel<{epi}," in k for k in ran) for epi in (3, 7)) == wide, ran
+        else:
+            generate()
         res[n] = (out.cpu().numpy(), lp.cpu().numpy())
     for n in few:                                      # a row's bits do not depend on its batch-mates
         assert np.array_equal(res[n][0], res[most][0][:n]) and np.array_equal(res[n][1], res[most][1][:n]), n
