@@ -1484,6 +1484,7 @@ __global__ __launch_bounds__(1024) void sample_blocks_kernel(const float4* stats
         __syncthreads();
         // the 32 logits of the chosen block: column t / 32, 32 threads per column over 16-byte pieces of k
         const int blk = s_blk;
+        const float4 top = st4[blk];
         const int col = t >> 5, part = t & 31;
         const bf16_t* wrow = W + ((int64_t)blk * 32 + col) * d;
         const f16_t* hrow = h + (int64_t)b * ldh;
@@ -1512,7 +1513,9 @@ __global__ __launch_bounds__(1024) void sample_blocks_kernel(const float4* stats
             if (t == 0) {
                 const int c = hit ? __ffsll((long long)hit) - 1 : 31;
                 s_tok = blk * 32 + c;
-                s_ztok = zs[c];
+                // the block's largest logit as the LM head has it: of the row's largest, which most draws take, nothing but the
+                // sum of exponentials is left then, and not the rounding of two sums over d in different order
+                s_ztok = c == __float_as_int(top.w) ? top.x : zs[c];
             }
         }
     } else if (t == 0) {
