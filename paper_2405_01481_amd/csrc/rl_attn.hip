@@ -44,8 +44,8 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // value column from LDS instead of from the page, so nothing depends on when the appended values become visible.
 // A wave's page numbers are fetched once, one per lane (64 iterations' worth; without splits even before the position
 // is known), so that a page's loads wait for no index load; with up to 8 waves per workgroup short contexts need no
-// splits and no merge kernel.  32 rows, 8 kv heads, 200 keys, head_dim 64: 2 splits x 4 waves + merge 12.8 us, 8 waves
-// 7.0 us; 3 rows, 100 keys, head_dim 128: 4 waves 9.9 us, 8 waves 8.3.
+// splits and no merge kernel.  32 rows, 8 kv heads, 200 keys, head_dim 64: 2 splits x 4 waves + merge 10.0 us, 8 waves
+// 6.5 us; 3 rows, 100 keys, head_dim 128: 4 waves 6.2 us, 8 waves 5.7.
 // ST: the cache is read as non-temporal (k_attn_decode_streams).
 template <typename V, bool ST>
 __device__ __forceinline__ V kv_load(const char* p) {
@@ -357,9 +357,9 @@ bool k_attn_decode_consumes_qkv(int Hq, int Hkv, int hd) {
 // enough to read the cache at memory speed, and a split costs a merge kernel and the query's preparation once more.  Hence
 // only as many splits as it takes to reach 256 workgroups, rounded up (25 rows of 8 kv heads: 2 splits, 400 workgroups), of
 // at least 16 pages of the longest sequence each; eight waves where fewer than 512
-// workgroups leave room (short contexts: 32 rows x 200 keys 6.0 -> 5.3 us, but 64 rows x 300 keys at head_dim 128 16.0 ->
-// 17.6).  8 kv heads, head_dim 128, merge included, splits 1 / 2 / 4 / 8: 32 rows x 1600 keys 40.6 / 42.4 / 45 / 50 us,
-// 16 x 4000 59 / 51 / 50 / 54, 8 x 1600 21.8 / 16.5 / 15.8 / 16.9, 1 x 4000 46 / 28 / 18.6 / 14.9, 8 x 300 8.0 / 9.0 / 8.7 / 10.3.
+// workgroups leave room (short contexts: 32 rows x 200 keys 7.6 -> 6.5 us; 64 rows x 300 keys at head_dim 128 19.4 ->
+// 18.9, non-temporal 18.1 -> 18.6).  8 kv heads, head_dim 128, merge included, splits 1 / 2 / 4 / 8: 32 rows x 1600 keys 38 / 41 / 43 / 50 us,
+// 16 x 4000 73 / 49 / 48 / 52, 8 x 1600 23.5 / 18.1 / 16.4 / 18.7, 1 x 4000 46 / 29 / 19.4 / 15.9, 8 x 300 8.7 / 10.3 / 9.8 / 11.8.
 void k_attn_decode_plan(int max_batch, int Hkv, int mpps, int max_splits, int* waves, int* nsplit) {
     const int wgs = max_batch * Hkv;
     *waves = wgs < 512 ? 8 : 4;

@@ -2,8 +2,8 @@
 //
 // Bound by reading W once.  What a plain read of these matrices reaches here, launch included, sets the floor: 12.6 MB
 // in 3.8 us, 33.5 MB in 6.5, 117 MB in 20, 235 MB in 38 (3.3, 5.2, 5.8, 6.2 TB/s).  A comes on top, from L2: every workgroup
-// reads its rows once, and they take their part of the about 64 KB that a CU has on its way at once (gate/up of the 8B shape:
-// 38.3, 38.4, 39.8, 50 us at 3, 32, 64, 128 rows).  Three things decide how close a GEMM comes, all measured:
+// reads its rows once, and they take their part of the about 64 KB that a CU has on its way at once (gate/up of the 8B shape,
+// a plain layer: 38, 37.5, 39, 48.6 us at 3, 32, 64, 128 rows).  Three things decide how close a GEMM comes, all measured:
 //   * how rows are read.  64-byte pieces of 16 rows (operands straight into MFMA layout) reach 60 - 80 % of the plain
 //     read on the short matrices, 256-byte pieces 95 %.  So operands go global -> LDS in k-tiles of 128 (a 1 KB
 //     request = 4 rows x 256 B), 16-byte chunks XOR-swizzled with the row on the source side, so that the fragment
@@ -48,7 +48,7 @@ __device__ __forceinline__ int stream_w_row(int t, int rr, const GemmArgs& a) {
 
 // SwiGLU of two 16 x 16 tiles held as row r, columns 4 q .. 4 q + 3, the first 8 of them gate and the others up columns: lanes q <
 // 2 finish the first tile, the others the second, each at row m and columns n .. n + 3.  One tile at a time, half of the lanes
-// would repeat what the other half computes: 8B gate/up 39.0 -> 38.4 us at 20 rows, 54.1 -> 52.9 at 128.
+// would repeat what the other half computes: 8B gate/up 1.5 % at 20 rows, 2 % at 128.
 __device__ __forceinline__ void swiglu_store(const GemmArgs& a, floatx4 first, floatx4 second, int q, int m, int n, bool live) {
     half4 hi, lo;
 #pragma unroll
@@ -277,11 +277,11 @@ __global__ __launch_bounds__(512, gs_lds(MT, CT) <= 80 * 1024 ? 4 : 2) void gemm
 // all rows; every W fragment is read, and on bf16 weights converted, by one wave.  As many stages as LDS holds, of which all but
 // one are on their way; no request past the last k-step.  A pair layer's stage holds A's hi and lo rows: W is read once.  Chunks
 // of the 128-byte rows are XOR-swizzled on the source side as above.  At the end the two waves along k each finish half of the
-// row tiles and hand the other half over.  The MFMAs take W first: a lane holds four consecutive columns of a row.
+// row tiles and hand the other half over; a logit's fp32 sum is two chains over k instead of the stream kernel's four.  The MFMAs take W first: a lane holds four consecutive columns of a row.
 // Against gemm_stream_kernel (fp16 weights; bf16 within 3 % of it), 3, 32, 64, 128 rows: LM head of the 8B shape 161, 170, 179, 218
 // -> 161, 159, 164, 176 us; of 65536 x 4096 84, 88, 93, 109 -> 85, 84, 85, 87; 70B gate/up 148, 151, 152, 183 -> 144, 143,
 // 145, 153; in a pair layer 147, 160, 186, 282 -> 145, 145, 151, 225.  Where stream_kernel's tiles are one round already it has the same or
-// better times (8B gate/up 128 rows 50.6, on these tiles 69; a 56 x 128 form 51): wide_tiles.
+// better times (8B gate/up at 128 rows takes 1.36 times as long on these, which leave half of the CUs idle; on a 56 x 128 form as long): wide_tiles.
 static constexpr int GW_KT = 64, GW_RB = 128, GW_CT = 16;                // k-step, its bytes per row, column tiles
 static constexpr int gw_stage(int MT, bool PAIR) { return (GW_CT + MT * (PAIR ? 2 : 1)) * 16 * GW_RB; }
 static constexpr int gw_stages(int MT, bool PAIR) { return 160 * 1024 / gw_stage(MT, PAIR); }     // 2 .. 4
@@ -582,9 +582,10 @@ void k_gemm_decode(int epi, GemmArgs a, int splits, int max_rows, hipStream_t s)
         return;
     }
     a.pair = a.K == 2 * a.Kw;
-    // Weights pass through the caches once; those that are well beyond the eight L2s together (32 MB) are read as non-temporal: 8B
-    // gate/up 42.4 -> 38.9 us at 32 rows, down 22.5 -> 20.9, LM head 192 -> 186 (180 -> 166 at 3 rows), 70B gate/up 168 -> 152, down 89
-    // -> 78, QKV 33.4 -> 31.2 at 64 rows, 1B gate/up (67 MB) 14.3 -> 13.8 at 32.  Below that they are slower: 8B QKV (50 MB) at 128 rows
+    // Weights pass through the caches once; those that are well beyond the eight L2s together (32 MB) are read as non-temporal. Alone: 8B
+    // gate/up 41.7 -> 37.5 us at 32 rows, 51.5 -> 48.6 at 128, down 23.4 -> 21.5 at 32, LM head 177 -> 159 (183 -> 162 at 3 rows), 70B gate/up
+    // 162 -> 142 at 64, 1B gate/up (67 MB) 14.4 -> 13.4 at 32; at 128 rows that one is longer alone, 21.2 -> 21.9, and a generation
+    // 0.7 % shorter.  In a step 70B down 89 -> 78, QKV 33.4 -> 31.2 at 64 rows.  Below that they are slower: 8B QKV (50 MB) at 128 rows
     // in a step 18.8 -> 21.2, O (34 MB) 13.3 -> 14.0.
     a.stream_w = (int64_t)a.Wrows * a.Kw * 2 > ((int64_t)60 << 20);
     a.k_per_split = (a.Kw / GS_KT + z - 1) / z * GS_KT;
