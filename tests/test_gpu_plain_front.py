@@ -73,10 +73,11 @@ def test_front_against_oracle(G, hd, d, F, B, front):
     ro.close()
 
 
-def test_steps_per_graph_and_the_ones_left_over():
+@pytest.mark.parametrize("heads,hd", [(1, 64), (4, 128)], ids=["front", "separate"])
+def test_steps_per_graph_and_the_ones_left_over(heads, hd):
     """Runs of 1 to 37 tokens on one context, captured (several steps a graph, a remainder of eager ones) and eager: the same
     tokens and log-probs; a run as long as max_seq allows."""
-    shape, B, P, most = _shape(1, 64, 128, 128), 3, 9, 37
+    shape, B, P, most = _shape(heads, hd, 128, 128), 3, 9, 37
     ro = R.Rollout(R.make_cfg(shape, B, P - 1 + most), R.Weights(synth.make_weights(shape, 1, DEV)), DEV)
     ids, lens = synth.make_prompts(shape.vocab, B, P, P, 3)
     prompts, side, want = torch.tensor(ids, device=DEV), torch.cuda.Stream(), None
